@@ -17,8 +17,10 @@
  * the calls return without synchronising (mcsd_build_mask excepted).  Functions return MCSD_OK (0) or a
  * negative status; they never abort, throw or print.  Arguments are validated on the host before any
  * launch; on error nothing has been enqueued and no output has been touched.  The calls read no environment
- * variable and keep no mutable state besides the mask handles and the one-shot arming of mcsd_profile_next, so
- * calls on distinct streams (with distinct workspaces) may be made from several host threads at once.
+ * variable and keep no mutable state that a result depends on besides the mask handles and the one-shot arming of
+ * mcsd_profile_next (workgroups that share a verification walk exchange partial sums through device memory of the
+ * library, in messages tagged so that launches cannot take each other's), so calls on distinct streams (with distinct
+ * workspaces) may be made from several host threads at once.
  *
  * Tree convention.  A tree is the tuple of per-level branching factors (b_1 .. b_G), e.g. (4,2,2,1) or the
  * target-initialised (2,4,3,1,1) of Sec. 4.1.  Level l has N_l = b_1*...*b_l nodes; nodes are numbered
@@ -314,6 +316,23 @@ int mcsd_verify_tree_sampling(const mcsd_mask_view_t *mask, mcsd_mode_t mode, mc
                               int64_t p_batch_stride, int64_t q_batch_stride, const float *u_accept,
                               const float *u_sample, int32_t n_new, int32_t *out_path, int32_t *out_accept_len,
                               int32_t *out_new_tokens, void *workspace, size_t workspace_bytes, void *hip_stream);
+
+/* The same walk with the launch in the caller's hands, for measurement and tests; results do not depend on it.
+ * team : 0: the library chooses; 1..16: at most this many workgroups share a walk where the vocabulary allows it (a
+ *        workgroup holds 2048 to 16384 entries, so large vocabularies need several in any case)
+ * polls: how often a workgroup of a team looks for another one's partial sum before it computes that sum itself;
+ *        0: the library chooses; -1: it never looks
+ * MCSD_EINVAL for values outside these ranges.  tuning == NULL means all zeros. */
+typedef struct {
+    int32_t team;
+    int32_t polls;
+} mcsd_verify_tuning_t;
+
+int mcsd_verify_tree_tuned(const mcsd_verify_tuning_t *tuning, const mcsd_mask_view_t *mask, mcsd_mode_t mode,
+                           mcsd_sampling_t sampling, int32_t B, int32_t V, const int32_t *tokens, const float *p_target,
+                           const float *q_draft, int64_t p_batch_stride, int64_t q_batch_stride, const float *u_accept,
+                           const float *u_sample, int32_t n_new, int32_t *out_path, int32_t *out_accept_len,
+                           int32_t *out_new_tokens, void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /* ---------------------------------------------------------------------------------------------------
  * Update after acceptance (Fig. 1 step 6): the accepted path becomes part of the prefix.

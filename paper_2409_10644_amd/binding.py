@@ -20,7 +20,7 @@ EXPORTS = ["mcsd_strerror", "mcsd_build_mask", "mcsd_slice_mask", "mcsd_free_mas
            "mcsd_tree_attention_rows_workspace", "mcsd_tree_attention_rows",
            "mcsd_tree_attention_gqa_workspace", "mcsd_tree_attention_gqa",
            "mcsd_tree_attention_fp8kv_workspace", "mcsd_tree_attention_fp8kv",
-           "mcsd_verify_tree_workspace", "mcsd_verify_tree", "mcsd_verify_tree_sampling", "mcsd_commit_path", "mcsd_early_stop_distribution",
+           "mcsd_verify_tree_workspace", "mcsd_verify_tree", "mcsd_verify_tree_sampling", "mcsd_verify_tree_tuned", "mcsd_commit_path", "mcsd_early_stop_distribution",
            "mcsd_early_stop_hidden", "mcsd_profile_next", "mcsd_stream_read", "mcsd_issue_probe", "mcsd_placement_probe", "mcsd_workspace_init",
            "mcsd_tree_attention_tuned_workspace", "mcsd_tree_attention_tuned", "mcsd_tree_attention_static",
            "mcsd_tree_attention_plan"]
@@ -55,6 +55,11 @@ class AttentionPlan(C.Structure):
     _fields_ = [("mfma_path", C.c_int32), ("query_blocks", C.c_int32), ("key_splits", C.c_int32),
                 ("workgroups", C.c_int32), ("stages", C.c_int32), ("fold_in_kernel", C.c_int32),
                 ("ordered_by_length", C.c_int32)]
+
+
+class VerifyTuning(C.Structure):
+    """mcsd_verify_tuning_t"""
+    _fields_ = [("team", C.c_int32), ("polls", C.c_int32)]
 
 
 class McsdError(RuntimeError):
@@ -95,6 +100,8 @@ def _load() -> C.CDLL:
     lib.mcsd_verify_tree_sampling.restype = C.c_int
     lib.mcsd_verify_tree_sampling.argtypes = [C.POINTER(MaskView), C.c_int, C.c_int, i32, i32, vp, vp, vp, i64, i64, vp,
                                               vp, i32, vp, vp, vp, vp, sz, vp]
+    lib.mcsd_verify_tree_tuned.restype = C.c_int
+    lib.mcsd_verify_tree_tuned.argtypes = [C.POINTER(VerifyTuning)] + lib.mcsd_verify_tree_sampling.argtypes
     lib.mcsd_profile_next.restype = C.c_int
     lib.mcsd_tree_attention_rows_workspace.restype = C.c_size_t
     lib.mcsd_tree_attention_rows_workspace.argtypes = [i32, i32, i32, i32, i32, i32]
@@ -221,7 +228,7 @@ def new_workspace(nbytes: int, stream=None) -> torch.Tensor:
     return ws
 
 
-def _tuning_ref(tuning: Optional[AttentionTuning]):
+def _tuning_ref(tuning):
     return None if tuning is None else C.byref(tuning)
 
 
@@ -360,6 +367,19 @@ def verify_tree_sampling(view: MaskView, mode: int, sampling: int, B: int, V: in
                                        _ptr(out_path), _ptr(out_accept_len), _ptr(out_new_tokens), _ptr(workspace),
                                        ws_bytes, _stream(stream))
     _check(st, "mcsd_verify_tree_sampling")
+
+
+def verify_tree_tuned(tuning: Optional[VerifyTuning], view: MaskView, mode: int, sampling: int, B: int, V: int,
+                      tokens: torch.Tensor, p_target: torch.Tensor, q_draft: Optional[torch.Tensor], p_batch_stride: int,
+                      q_batch_stride: int, u_accept: torch.Tensor, u_sample: Optional[torch.Tensor], n_new: int,
+                      out_path: torch.Tensor, out_accept_len: torch.Tensor, out_new_tokens: Optional[torch.Tensor],
+                      workspace: Optional[torch.Tensor], stream=None) -> None:
+    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    st = lib.mcsd_verify_tree_tuned(_tuning_ref(tuning), C.byref(view), mode, sampling, B, V, _ptr(tokens), _ptr(p_target),
+                                    _ptr(q_draft), p_batch_stride, q_batch_stride, _ptr(u_accept), _ptr(u_sample), n_new,
+                                    _ptr(out_path), _ptr(out_accept_len), _ptr(out_new_tokens), _ptr(workspace), ws_bytes,
+                                    _stream(stream))
+    _check(st, "mcsd_verify_tree_tuned")
 
 
 def _ptr_array(tensors: Sequence[torch.Tensor]):

@@ -2,12 +2,19 @@
 // recursive rejection sampling down the candidate tree, longest-path selection for target-initialised
 // trees, and sampling of the new token(s).
 //
-// One workgroup of 1024 lanes walks one tree (draft-initialised) or one level-1 subtree (target-initialised).
-// Sums over the vocabulary follow the balanced binary tree over the zero-padded index space that the header
-// specifies; all arithmetic is binary64 with explicit fma, so results equal the oracle's recursion bit for bit.
+// A walk (one tree, or one level-1 subtree of a target-initialised one) is latency: a chain of row fetches, vocabulary sums
+// and accept tests.  Sums over the vocabulary follow the balanced binary tree over the zero-padded index space that the
+// header specifies; all arithmetic is binary64 with explicit fma, so results equal the oracle's recursion bit for bit.
 //
-// Vocabularies up to 32768 (verify_walk_fast_kernel): a context's two rows are read once, on its first rejection.
-// Lane t of the workgroup owns the 32 CONSECUTIVE elements 32 t .. 32 t + 31: an aligned subtree of the sum tree, so
+// verify_walk_team_kernel: several workgroups share a walk, each holding an aligned power-of-two chunk of the vocabulary
+// (4096 to 16384 entries) in registers, so the rows arrive through as many compute units as share the walk and no row is
+// read twice; they exchange one partial sum per rejection round.  A context visited after its first rejection costs a row
+// fetch (0.5-1 us) and 1.5-2 us a round.  Measured, rows in the last-level cache, us per call before (one workgroup per
+// walk; vocabularies above 32768 streamed from memory every round) and after: 1 walk of 32000 entries 11.5 -> 7.1, 128 of
+// 32000 25 -> 21, 64 (8 sequences, target-initialised) 19.8 -> 16, 16 of 131072 171 -> 17, 1 of 34347 66 -> 8.8.
+//
+// verify_walk_fast_kernel: one workgroup per walk, for vocabularies up to 32768 when there are more walks than the chip
+// has room for teams.  Lane t owns the 32 CONSECUTIVE elements 32 t .. 32 t + 31: an aligned subtree of the sum tree, so
 // a sum is 31 in-lane additions, one 6-level butterfly over the wavefront's 64 lanes and a 4-level tree over the 16
 // wavefront sums (one barrier per rejection round).  The residual r <- max(r - S q, 0) lives in registers as
 // binary64 and is updated in place; the draft row is parked in LDS.  Rows are fetched with coalesced 16-byte loads
@@ -17,71 +24,71 @@
 // sums, then the heap of the chosen wavefront's lane sums (kept in LDS from the butterfly's levels), then the 32
 // elements of the chosen lane, recomputed from the rows and the history of sums.
 //
-// Larger vocabularies (verify_walk_kernel): the residual is never stored; after j rejections an element is recomputed
-// from p, q and the j previous sums (a chain of j fused multiply-adds), a round is one coalesced sweep over the two
-// rows, 256-element blocks are reduced by butterflies and a tree over the block sums that every wavefront adds for
-// itself; a heap over the blocks is built in LDS only for the inverse-CDF descent.
-//
 // Compiled with -ffp-contract=off.
+#include <atomic>
+#include <chrono>
+
 #include "mcsd_internal.h"
 
 namespace {
 
 constexpr int VT = 1024;                 // threads per workgroup
-constexpr int BLK = 256;                 // vocabulary elements per wavefront load
-constexpr int MAX_NB = MCSD_MAX_VOCAB / BLK;
 
 struct VerifyParams {
     McsdTreeDesc t;
     int32_t mode, B, V, n_nodes, n_new, R;
-    int32_t NB;                          // power of two >= ceil(V / BLK)
     const int32_t *tokens;
     const float *p, *q;
     int64_t pbs, qbs;
     const float *ua, *us;
+    const int32_t *parent;               // of every tree node, -1 on level 1
     int32_t *cand_path;                  // [B][R][gamma]
     int32_t *cand_len;                   // [B][R]
     int32_t *cand_new;                   // [B][R][n_new]
+    // target-initialised trees: where the longest walk goes, and with what the walks of a sequence find out who is last
+    int32_t *out_path, *out_len, *out_new;
+    unsigned long long *done;            // [B][R * workgroups per walk]
+    unsigned long long launch_id;        // of this launch alone; never 0
 };
 
-template <int NBMAX>
-struct SharedT {
-    double leaf[2][NBMAX];               // sums of the 256-element blocks, double-buffered over rejection rounds
-    double heapB[2 * NBMAX];             // heap over the blocks: leaves at [NB, 2NB), root at 1 (built for the descent only)
-    double heapA[2 * BLK];               // heap inside one block, rebuilt for each descent
-    double s_hist[MCSD_MAX_BRANCH + 1];  // S before each rejection round of the current context
-    double sq_hist[MCSD_MAX_BRANCH + 1]; // candidates without replacement: sum of the shrunken draft row before each round
-    int x_hist[MCSD_MAX_BRANCH + 1];     // ... and the token rejected in that round (its draft mass is zero afterwards)
-    int lo_idx, hi_idx;
-};
+// A result that workgroups on other dies read in the same launch: written through to where they see it.
+__device__ inline void put(int32_t *at, int32_t v) { __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline int32_t get(const int32_t *at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // max(d, 0) as one instruction.  d is never NaN here, and the sign of a zero result never reaches a decision
 // (zeros only enter sums, products and comparisons with 0), so this equals "d > 0 ? d : 0" for every use below.
 __device__ inline double pos_part(double d) { return __builtin_fmax(d, 0.0); }
 
+// The rejections at a context: S before each round; for candidates without replacement also the sum of the shrunken
+// draft row before each round and the token rejected in it (its draft mass is zero afterwards).
+struct History {
+    double s[MCSD_MAX_BRANCH + 1], sq[MCSD_MAX_BRANCH + 1];
+    int x[MCSD_MAX_BRANCH + 1];
+};
+
 // One element of the distribution after `rounds` rejections, from its target value r and draft value qd.
 // With replacement: r <- max(r - S q, 0) per round.  NOREP (candidates drawn without replacement): the draft row
 // loses every rejected token, and with Sq the sum of what is left, r <- max(r Sq - S q', 0).
-template <bool NOREP, class Shared>
-__device__ inline double residual_chain(const Shared &sh, double r, double qd, int t, int rounds)
+template <bool NOREP>
+__device__ inline double residual_chain(const History &h, double r, double qd, int t, int rounds)
 {
     for (int k = 0; k < rounds; ++k) {
         if (NOREP) {
-            if (k > 0 && t == sh.x_hist[k - 1]) qd = 0.0;
-            r = __dmul_rn(r, sh.sq_hist[k]);
+            if (k > 0 && t == h.x[k - 1]) qd = 0.0;
+            r = __dmul_rn(r, h.sq[k]);
         }
-        const double d = __fma_rn(-sh.s_hist[k], qd, r);
+        const double d = __fma_rn(-h.s[k], qd, r);
         r = pos_part(d);
     }
     return r;
 }
 
 // Element t of the distribution after `rounds` rejections at a context with rows prow / qrow.
-template <bool NOREP, class Shared>
-__device__ inline double residual_at(const Shared &sh, const float *prow, const float *qrow, int rounds, int t)
+template <bool NOREP>
+__device__ inline double residual_at(const History &h, const float *prow, const float *qrow, int rounds, int t)
 {
     const double r = (double)prow[t];
-    return rounds > 0 ? residual_chain<NOREP>(sh, r, (double)qrow[t], t, rounds) : r;
+    return rounds > 0 ? residual_chain<NOREP>(h, r, (double)qrow[t], t, rounds) : r;
 }
 
 // A double from another lane of the row through the data-parallel-primitive path of the vector ALU (no LDS).
@@ -116,278 +123,74 @@ __device__ inline double wave_tree_sum(double v)
     return v;
 }
 
-// Block sums of the distribution (prow, qrow, rounds) recomputed from memory into leaf[buf]; any NB.  No barrier
-// at the end; s_hist[0 .. rounds) must be visible.
-constexpr int SGROUP = 8;                // blocks a wavefront streams at a time
-template <bool NOREP, class Shared>
-__device__ void stream_block_sums(Shared &sh, const VerifyParams &P, const float *prow, const float *qrow,
-                                  int rounds, int buf)
+// Target-initialised trees: the level-1 subtree with the longest accepted path wins, lowest id on ties.  Every workgroup of
+// a sequence calls this when its results are written; the one that finds all of them done copies the winner out, inside
+// the same launch (a second kernel cost 4 us).  A workgroup marks itself done, and only then looks at the others' marks:
+// the last to mark sees them all.  Two may, and then write the same values.  A mark is the launch's own id, so what the
+// workspace held before does not matter, and the copier takes all marks back, so a replay of the same launch starts clean.
+__device__ inline void select_longest(const VerifyParams &P, int b, int slot, int slots)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool vec = (((uintptr_t)prow | (uintptr_t)qrow) & 15) == 0;
-    for (int blk0 = wave; blk0 < P.NB; blk0 += SGROUP * (VT / 64)) {
-        float pe[SGROUP][4], qe[SGROUP][4];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wavefront's results are where everyone sees them ...
+    __syncthreads();                                        // ... and everyone's of the workgroup
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x;
+    unsigned long long *done = P.done + (int64_t)b * slots;
+    if (lane == 0) __hip_atomic_store(&done[slot], P.launch_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bool all = true;
+    for (int i = lane; i < slots; i += 64) all = all && __hip_atomic_load(&done[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == P.launch_id;
+    if (__builtin_amdgcn_ballot_w64(!all) != 0) return;
+    int key = -1;                                           // longest first, then lowest id (R <= 64)
+    if (lane < P.R) key = get(P.cand_len + (int64_t)b * P.R + lane) * 64 + (63 - lane);
 #pragma unroll
-        for (int k = 0; k < SGROUP; ++k) {
-            const int blk = blk0 + k * (VT / 64);
-            const int t0 = blk * BLK + lane * 4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { pe[k][e] = 0.f; qe[k][e] = 0.f; }
-            if (blk < P.NB) {
-                if (vec && t0 + 3 < P.V) {
-                    const float4 pv = *(const float4 *)(prow + t0);
-                    pe[k][0] = pv.x; pe[k][1] = pv.y; pe[k][2] = pv.z; pe[k][3] = pv.w;
-                    if (rounds > 0) {
-                        const float4 qv = *(const float4 *)(qrow + t0);
-                        qe[k][0] = qv.x; qe[k][1] = qv.y; qe[k][2] = qv.z; qe[k][3] = qv.w;
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (t0 + e < P.V) {
-                            pe[k][e] = prow[t0 + e];
-                            if (rounds > 0) qe[k][e] = qrow[t0 + e];
-                        }
-                }
-            }
-        }
-        double sblk[SGROUP];
-#pragma unroll
-        for (int k = 0; k < SGROUP; ++k) {
-            double v[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)                      // elements beyond V are 0 and stay 0
-                v[e] = residual_chain<NOREP>(sh, (double)pe[k][e], (double)qe[k][e],
-                                             (blk0 + k * (VT / 64)) * BLK + lane * 4 + e, rounds);
-            sblk[k] = __dadd_rn(__dadd_rn(v[0], v[1]), __dadd_rn(v[2], v[3]));
-        }
-#pragma unroll
-        for (int k = 0; k < SGROUP; ++k) sblk[k] = wave_tree_sum(sblk[k]);
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < SGROUP; ++k) {
-                const int blk = blk0 + k * (VT / 64);
-                if (blk < P.NB) sh.leaf[buf][blk] = sblk[k];
-            }
-        }
+    for (int m = 1; m < 64; m <<= 1) {
+        const int o = __shfl_xor(key, m, 64);
+        key = o > key ? o : key;
     }
+    const int best = 63 - (key & 63);
+    const int64_t c = (int64_t)b * P.R + best;
+    if (lane == 0) P.out_len[b] = key >> 6;
+    if (lane < P.t.gamma) P.out_path[(int64_t)b * P.t.gamma + lane] = get(P.cand_path + c * P.t.gamma + lane);
+    if (lane < P.n_new) P.out_new[(int64_t)b * P.n_new + lane] = get(P.cand_new + c * P.n_new + lane);
+    for (int i = lane; i < slots; i += 64) __hip_atomic_store(&done[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Total of leaf[buf][0 .. NB) in balanced-tree order, computed by every wavefront for itself (no further barrier):
-// a lane adds its NB/64 consecutive leaves as a small tree (zero-filled to PER: x + 0 is exact), then 64 lanes
-// combine.  PER = largest NB / 64 the caller can have.
-template <int PER, class Shared>
-__device__ inline double top_tree_sum(const Shared &sh, const VerifyParams &P, int buf)
+// What the walk needs to know about the tree's nodes, fetched at the start by one lane per node: two dependent trips to
+// memory for the whole walk instead of two per context.
+constexpr int NODE_CACHE = 256;          // trees of up to this many nodes; larger ones are read context by context
+struct NodeCache {
+    float u[NODE_CACHE], q[NODE_CACHE], p[NODE_CACHE];      // acceptance uniform, draft and target value of the node's token
+    int x[NODE_CACHE];                                      // token
+    unsigned kid[NODE_CACHE + 1];                           // of context c (node c - 1): first child, bit 31: accepted at once
+};
+struct NodeRegs { int x, par, prev; float u; bool mine; };
+
+// Node tid's token and uniform are requested ...
+__device__ inline NodeRegs node_request(const VerifyParams &P, const int32_t *tokens, const float *ua, int i)
 {
-    const int lane = threadIdx.x & 63;
-    const int per = P.NB >= 64 ? P.NB >> 6 : 1;                  // 1 .. PER
-    double v[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int idx = lane * per + i;
-        v[i] = (i < per && idx < P.NB) ? sh.leaf[buf][idx] : 0.0;
+    NodeRegs n{0, -1, -2, 0.f, false};
+    // (level 1 of a target-initialised tree goes untested)
+    n.mine = P.n_nodes <= NODE_CACHE && i < P.n_nodes && !(P.mode == MCSD_TARGET_INIT && i < P.t.off[1]);
+    if (n.mine) {
+        n.x = tokens[i];
+        n.par = P.parent[i];
+        if (i > 0) n.prev = P.parent[i - 1];
+        n.u = ua[i];
     }
-#pragma unroll
-    for (int w = PER / 2; w >= 1; w >>= 1)
-#pragma unroll
-        for (int i = 0; i < w; ++i) v[i] = __dadd_rn(v[2 * i], v[2 * i + 1]);
-    return wave_tree_sum(v[0]);
+    return n;
 }
-
-// heapB from leaf[buf].  All threads call it; ends with a barrier.
-template <class Shared>
-__device__ void build_heap(Shared &sh, const VerifyParams &P, int buf)
+// ... and its probabilities fetched.  With S = 1 the first child of a context passes or fails its test whatever happened
+// before, so that test is made here, for all contexts at once.  The caller's barrier makes the cache visible.
+__device__ inline void node_fetch(NodeCache &c, const VerifyParams &P, const float *p, const float *q, NodeRegs n, int i)
 {
-    const int tid = threadIdx.x;
-    for (int i = tid; i < P.NB; i += VT) sh.heapB[P.NB + i] = sh.leaf[buf][i];
-    __syncthreads();
-    for (int n = P.NB >> 1; n >= 1; n >>= 1) {
-        for (int i = tid; i < n; i += VT) sh.heapB[n + i] = __dadd_rn(sh.heapB[2 * (n + i)], sh.heapB[2 * (n + i) + 1]);
-        __syncthreads();
-    }
-}
-
-// Inverse-CDF draw from the distribution whose heapB is current.  All threads call it; all return the token.
-template <bool NOREP, class Shared>
-__device__ int tree_sample(Shared &sh, const VerifyParams &P, const float *prow, const float *qrow, int rounds,
-                           float u)
-{
-    const int tid = threadIdx.x;
-    const double S = sh.heapB[1];
-    double thr = __dmul_rn((double)u, S);
-    int node = 1;
-    while (node < P.NB) {
-        const double left = sh.heapB[2 * node];
-        if (thr < left) {
-            node = 2 * node;
-        } else {
-            thr = __dsub_rn(thr, left);
-            node = 2 * node + 1;
-        }
-    }
-    const int blk = node - P.NB;
-    __syncthreads();     // heapA may still be read by a previous descent
-    if (tid < BLK) {
-        const int t = blk * BLK + tid;
-        sh.heapA[BLK + tid] = t < P.V ? residual_at<NOREP>(sh, prow, qrow, rounds, t) : 0.0;
-    }
-    __syncthreads();
-    for (int n = BLK >> 1; n >= 1; n >>= 1) {
-        if (tid < n) sh.heapA[n + tid] = __dadd_rn(sh.heapA[2 * (n + tid)], sh.heapA[2 * (n + tid) + 1]);
-        __syncthreads();
-    }
-    node = 1;
-    while (node < BLK) {
-        const double left = sh.heapA[2 * node];
-        if (thr < left) {
-            node = 2 * node;
-        } else {
-            thr = __dsub_rn(thr, left);
-            node = 2 * node + 1;
-        }
-    }
-    int t = blk * BLK + (node - BLK);
-    const bool ok = t < P.V && sh.heapA[node] > 0.0;
-    if (ok) return t;
-    // Reached a zero-weight index (last-bit rounding of the subtraction, or an all-zero distribution):
-    // nearest positive-weight index below, else nearest above, else 0.
-    if (tid == 0) { sh.lo_idx = -1; sh.hi_idx = 0x7fffffff; }
-    __syncthreads();
-    int lo = -1, hi = 0x7fffffff;
-    for (int e = tid; e < P.V; e += VT) {
-        if (e == t) continue;
-        if (residual_at<NOREP>(sh, prow, qrow, rounds, e) > 0.0) {
-            if (e < t) lo = e > lo ? e : lo;
-            else hi = e < hi ? e : hi;
-        }
-    }
-    if (lo >= 0) atomicMax(&sh.lo_idx, lo);
-    if (hi != 0x7fffffff) atomicMin(&sh.hi_idx, hi);
-    __syncthreads();
-    t = sh.lo_idx >= 0 ? sh.lo_idx : (sh.hi_idx != 0x7fffffff ? sh.hi_idx : 0);
-    __syncthreads();
-    return t;
-}
-
-// Vocabularies beyond FAST_V: the rows are streamed again every round.
-// NOREP: the candidates of a context were drawn without replacement (see residual_chain).
-template <bool NOREP>
-__global__ __launch_bounds__(VT) void verify_walk_kernel(const VerifyParams P)
-{
-    using Shared = SharedT<MAX_NB>;
-    __shared__ Shared sh;
-    const int tid = threadIdx.x;
-    const int root = blockIdx.x, b = blockIdx.y;
-    const int32_t *tokens = P.tokens + (int64_t)b * P.n_nodes;
-    const float *p = P.p + (int64_t)b * P.pbs;
-    const float *q = P.q + (int64_t)b * P.qbs;
-    const float *ua = P.ua + (int64_t)b * P.n_nodes;
-    int32_t *path_out = P.cand_path + ((int64_t)b * P.R + root) * P.t.gamma;
-
-    int cur = -1, level = 0, n_acc = 0;      // context: node id (-1 = end of the prefix) and its level
-    if (P.mode == MCSD_TARGET_INIT) {         // level-1 node `root` is accepted untested
-        cur = root;
-        level = 1;
-        n_acc = 1;
-        if (tid == 0) path_out[0] = root;
-    }
-    const int lane = tid & 63;
-    const float *term_p = nullptr, *term_q = nullptr;
-    int term_rounds = 0, term_buf = -1;       // term_buf >= 0: leaf[term_buf] holds the terminal distribution's block sums
-    int buf = 0;
-    while (level < P.t.gamma) {
-        const float *prow = p + (int64_t)(cur + 1) * P.V;
-        const float *qrow = q + (int64_t)(cur + 1) * P.V;
-        const int cnt = P.t.b[level];
-        const int first = cur < 0 ? 0 : P.t.off[level] + (cur - P.t.off[level - 1]) * cnt;
-        // candidate `lane` of this context (in every wavefront): acceptance uniform, q(x) and the residual at x,
-        // which is updated in place after every rejection
-        double uc = 0.0, qc = 0.0, rc = 0.0;
-        int xc = -1;
-        if (lane < cnt) {
-            int x = tokens[first + lane];
-            x = x < 0 ? 0 : (x >= P.V ? P.V - 1 : x);   // ids outside 0..V-1 are clamped, never dereferenced
-            xc = x;
-            uc = (double)ua[first + lane];
-            qc = (double)qrow[x];
-            rc = (double)prow[x];
-        }
-        int rounds = 0, accepted = -1;
-        double S = 1.0, Sq = 1.0;                        // both rows are trusted to be normalised in round 0
-        // accept test of candidate c: the same value in every lane, read through one lane so that the walk is
-        // scalar control flow
-        auto accept = [&](int c) {
-            const double u = __shfl(uc, c, 64), qx = __shfl(qc, c, 64), rx = __shfl(rc, c, 64);
-            const double rhs = NOREP ? __dmul_rn(rx, Sq) : rx;
-            return __builtin_amdgcn_readfirstlane((int)(__dmul_rn(u, __dmul_rn(qx, S)) < rhs)) != 0;
-        };
-        if (accept(0)) {
-            accepted = first;
-        } else {
-            // First rejection at this context: from here on the residual is needed.
-            for (int c = 0;;) {
-                // candidate c was rejected: r <- max(r - S q, 0), S <- sum r
-                const int xrej = NOREP ? __builtin_amdgcn_readfirstlane(__shfl(xc, c, 64)) : 0;
-                const double qrej = NOREP ? __shfl(qc, c, 64) : 0.0;
-                if (tid == 0) {
-                    sh.s_hist[rounds] = S;
-                    if (NOREP) { sh.sq_hist[rounds] = Sq; sh.x_hist[rounds] = xrej; }
-                }
-                buf ^= 1;
-                {
-                    __syncthreads();          // s_hist[rounds] (sq_hist, x_hist) visible
-                    stream_block_sums<NOREP>(sh, P, prow, qrow, rounds + 1, buf);
-                }
-                {
-                    const double d = __fma_rn(-S, qc, NOREP ? __dmul_rn(rc, Sq) : rc);
-                    rc = pos_part(d);
-                }
-                if (NOREP) {
-                    Sq = __dsub_rn(Sq, qrej);
-                    if (xc == xrej) qc = 0.0;             // also a later duplicate of the rejected token
-                }
-                rounds += 1;
-                __syncthreads();              // block sums (and s_hist) visible
-                S = top_tree_sum<MAX_NB / 64>(sh, P, buf);
-                if (++c == cnt) break;
-                if (accept(c)) { accepted = first + c; break; }
-            }
-        }
-        if (accepted < 0) {
-            term_p = prow; term_q = qrow;
-            if (S > 0.0) { term_rounds = rounds; term_buf = rounds > 0 ? buf : -1; }
-            else { term_rounds = 0; term_buf = -1; }     // vanished residual: the context's own target row
-            break;
-        }
-        if (tid == 0) path_out[n_acc] = accepted;
-        n_acc += 1;
-        cur = accepted;
-        level += 1;
-    }
-    if (term_p == nullptr) {                  // every level accepted: bonus from the row after the last node
-        term_p = p + (int64_t)(cur + 1) * P.V;
-        term_q = term_p;                      // never read: rounds == 0
-        term_rounds = 0;
-        term_buf = -1;
-    }
-    if (tid == 0) {
-        for (int l = n_acc; l < P.t.gamma; ++l) path_out[l] = -1;
-        P.cand_len[(int64_t)b * P.R + root] = n_acc;
-    }
-    if (P.n_new > 0) {
-        if (term_buf < 0) {
-            buf ^= 1;
-            __syncthreads();
-            stream_block_sums<NOREP>(sh, P, term_p, term_q, 0, buf);
-            term_buf = buf;
-        }
-        __syncthreads();
-        build_heap(sh, P, term_buf);
-        for (int k = 0; k < P.n_new; ++k) {
-            const int t = tree_sample<NOREP>(sh, P, term_p, term_q, term_rounds, P.us[(int64_t)b * P.n_new + k]);
-            if (tid == 0) P.cand_new[((int64_t)b * P.R + root) * P.n_new + k] = t;
-        }
-    }
+    if (!n.mine) return;
+    const int x = n.x < 0 ? 0 : (n.x >= P.V ? P.V - 1 : n.x);   // ids outside 0..V-1 are clamped, never dereferenced
+    const float qx = q[(int64_t)(n.par + 1) * P.V + x], px = p[(int64_t)(n.par + 1) * P.V + x];
+    c.x[i] = x;
+    c.u[i] = n.u;
+    c.q[i] = qx;
+    c.p[i] = px;
+    if (n.prev != n.par) c.kid[n.par + 1] = (unsigned)i | (__dmul_rn((double)n.u, (double)qx) < (double)px ? 0x80000000u : 0u);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -402,9 +205,9 @@ struct FastShared {
     float qrow[FAST_V];                  // the context's draft row; wavefront w owns [2048 w, 2048 w + 2048), swizzled
     double wsum[2][NWAVE];               // sums of the wavefronts' 2048-element subtrees, double-buffered over rounds
     double heapw[NWAVE][128];            // per wavefront: heap over its 64 lane sums (root 1, leaves 64..127), for sampling
-    double s_hist[MCSD_MAX_BRANCH + 1];  // S before each rejection round of the current context
-    double sq_hist[MCSD_MAX_BRANCH + 1]; // candidates without replacement: sum of the shrunken draft row before each round
-    int x_hist[MCSD_MAX_BRANCH + 1];     // ... and the token rejected in that round
+    History hist;                        // of the current context
+    NodeCache node;
+    int path[MCSD_MAX_LEVELS];           // accepted nodes so far, written out at the end (a store in flight delays every later load)
 };
 
 // Position of chunk j (elements 4 j .. 4 j + 3 of the lane's 32) of lane l inside the wavefront's region, in 16-byte
@@ -515,7 +318,7 @@ __device__ int fast_sample(const FastShared &sh, const VerifyParams &P, int buf,
     // its 32 elements, one per lane of this wavefront (lanes 32..63 hold zeros), and the levels of their sum tree
     const int te = t0 + lane;
     double lv[6];
-    lv[0] = (lane < EPL && te < P.V) ? residual_at<NOREP>(sh, prow, qrow, rounds, te) : 0.0;
+    lv[0] = (lane < EPL && te < P.V) ? residual_at<NOREP>(sh.hist, prow, qrow, rounds, te) : 0.0;
     lv[1] = __dadd_rn(lv[0], dpp_f64<0xB1>(lv[0]));
     lv[2] = __dadd_rn(lv[1], dpp_f64<0x4E>(lv[1]));
     lv[3] = __dadd_rn(lv[2], dpp_f64<0x141>(lv[2]));
@@ -536,7 +339,7 @@ __device__ int fast_sample(const FastShared &sh, const VerifyParams &P, int buf,
     int below = -1, above = 0x7fffffff;
     for (int e = lane; e < P.V; e += 64) {
         if (e == t) continue;
-        if (residual_at<NOREP>(sh, prow, qrow, rounds, e) > 0.0) {
+        if (residual_at<NOREP>(sh.hist, prow, qrow, rounds, e) > 0.0) {
             if (e < t) below = e > below ? e : below;
             else above = e < above ? e : above;
         }
@@ -563,13 +366,15 @@ __global__ __launch_bounds__(VT) void verify_walk_fast_kernel(const VerifyParams
     const float *ua = P.ua + (int64_t)b * P.n_nodes;
     int32_t *path_out = P.cand_path + ((int64_t)b * P.R + root) * P.t.gamma;
     float4 *region = (float4 *)sh.qrow + wave * WCHUNKS;      // this wavefront's part of the parked row
+    const bool cached = P.n_nodes <= NODE_CACHE;
+    node_fetch(sh.node, P, p, q, node_request(P, tokens, ua, tid), tid);
 
     int cur = -1, level = 0, n_acc = 0;      // context: node id (-1 = end of the prefix) and its level
     if (P.mode == MCSD_TARGET_INIT) {         // level-1 node `root` is accepted untested
         cur = root;
         level = 1;
         n_acc = 1;
-        if (tid == 0) path_out[0] = root;
+        if (tid == 0) sh.path[0] = root;
     }
     double r[EPL];                            // this lane's 32 elements of the current residual
     const float *term_p = nullptr, *term_q = nullptr;
@@ -617,34 +422,63 @@ __global__ __launch_bounds__(VT) void verify_walk_fast_kernel(const VerifyParams
             if (heap) sh.heapw[wave][1] = v;
         }
         __syncthreads();
-        return row16_tree_sum(sh.wsum[buf][lane & 15]);      // the same in every lane
+        return read_lane_f64(row16_tree_sum(sh.wsum[buf][lane & 15]), 0);
     };
 
-    while (level < P.t.gamma) {
+    __syncthreads();                          // the node cache is visible
+    // The walk is the same in all lanes and has to be scalar control flow; see verify_walk_team_kernel.
+    while (true) {
+        level = __builtin_amdgcn_readfirstlane(level);
+        cur = __builtin_amdgcn_readfirstlane(cur);
+        n_acc = __builtin_amdgcn_readfirstlane(n_acc);
+        unsigned kid = 0;
+        if (cached) {                         // contexts whose first candidate passes need nothing but that fact
+            while (level < P.t.gamma) {
+                kid = __builtin_amdgcn_readfirstlane(sh.node.kid[cur + 1]);
+                if (!(kid >> 31)) break;
+                cur = (int)(kid & 0x7fffffffu);
+                if (tid == 0) sh.path[n_acc] = cur;
+                n_acc += 1;
+                level += 1;
+            }
+        }
+        if (level >= P.t.gamma) break;
         const float *prow = p + (int64_t)(cur + 1) * P.V;
         const float *qrow = q + (int64_t)(cur + 1) * P.V;
         const int cnt = P.t.b[level];
-        const int first = cur < 0 ? 0 : P.t.off[level] + (cur - P.t.off[level - 1]) * cnt;
+        const int first = cached ? (int)kid : (cur < 0 ? 0 : P.t.off[level] + (cur - P.t.off[level - 1]) * cnt);
         // candidate `lane` of this context (in every wavefront): acceptance uniform, q(x) and the residual at x,
         // which is updated in place after every rejection
         double uc = 0.0, qc = 0.0, rc = 0.0;
         int xc = -1;
-        if (lane < cnt) {
-            int x = tokens[first + lane];
-            x = x < 0 ? 0 : (x >= P.V ? P.V - 1 : x);   // ids outside 0..V-1 are clamped, never dereferenced
-            xc = x;
-            uc = (double)ua[first + lane];
-            qc = (double)qrow[x];
-            rc = (double)prow[x];
-        }
+        auto candidates = [&]() {
+            if (lane >= cnt) return;
+            const int i = first + lane;
+            if (cached) {
+                xc = sh.node.x[i];
+                uc = (double)sh.node.u[i];
+                qc = (double)sh.node.q[i];
+                rc = (double)sh.node.p[i];
+            } else {
+                int x = tokens[i];
+                x = x < 0 ? 0 : (x >= P.V ? P.V - 1 : x);   // ids outside 0..V-1 are clamped, never dereferenced
+                float u = ua[i], qx = qrow[x], px = prow[x];
+                asm volatile("" : "+v"(u), "+v"(qx), "+v"(px));      // (keeps the compiler from merging these loads with those above)
+                xc = x;
+                uc = (double)u;
+                qc = (double)qx;
+                rc = (double)px;
+            }
+        };
         int rounds = 0, accepted = -1;
         double S = 1.0, Sq = 1.0;                        // both rows are trusted to be normalised in round 0
+        // accept test of candidate c, evaluated by its lane; the same answer in every wavefront
         auto accept = [&](int c) {
-            const double u = __shfl(uc, c, 64), qx = __shfl(qc, c, 64), rx = __shfl(rc, c, 64);
-            const double rhs = NOREP ? __dmul_rn(rx, Sq) : rx;
-            return __builtin_amdgcn_readfirstlane((int)(__dmul_rn(u, __dmul_rn(qx, S)) < rhs)) != 0;
+            const double rhs = NOREP ? __dmul_rn(rc, Sq) : rc;
+            return __builtin_amdgcn_readlane((int)(__dmul_rn(uc, __dmul_rn(qc, S)) < rhs), c) != 0;
         };
-        if (accept(0)) {
+        if (!cached) candidates();
+        if (!cached && accept(0)) {
             accepted = first;
         } else {
             // First rejection at this context: from here on the residual is needed.  Both rows in flight at once
@@ -659,13 +493,14 @@ __global__ __launch_bounds__(VT) void verify_walk_fast_kernel(const VerifyParams
                 __builtin_amdgcn_sched_barrier(0);
                 fast_park_row(region, qv);
             }
+            candidates();                     // (after the rows: with them in flight there is no register to spare)
             for (int c = 0;;) {
                 // candidate c was rejected: r <- max(r - S q, 0), S <- sum r
-                const int xrej = NOREP ? __builtin_amdgcn_readfirstlane(__shfl(xc, c, 64)) : 0;
-                const double qrej = NOREP ? __shfl(qc, c, 64) : 0.0;
+                const int xrej = NOREP ? __builtin_amdgcn_readlane(xc, c) : 0;
+                const double qrej = NOREP ? read_lane_f64(qc, c) : 0.0;
                 if (tid == 0) {
-                    sh.s_hist[rounds] = S;
-                    if (NOREP) { sh.sq_hist[rounds] = Sq; sh.x_hist[rounds] = xrej; }
+                    sh.hist.s[rounds] = S;
+                    if (NOREP) { sh.hist.sq[rounds] = Sq; sh.hist.x[rounds] = xrej; }
                 }
                 buf ^= 1;
                 // two chunks at a time, the next two read from LDS while these are updated
@@ -714,7 +549,7 @@ __global__ __launch_bounds__(VT) void verify_walk_fast_kernel(const VerifyParams
             else { term_rounds = 0; term_in_regs = false; }   // vanished residual: the context's own target row
             break;
         }
-        if (tid == 0) path_out[n_acc] = accepted;
+        if (tid == 0) sh.path[n_acc] = accepted;
         n_acc += 1;
         cur = accepted;
         level += 1;
@@ -724,10 +559,6 @@ __global__ __launch_bounds__(VT) void verify_walk_fast_kernel(const VerifyParams
         term_q = term_p;                      // never read: rounds == 0
         term_rounds = 0;
         term_in_regs = false;
-    }
-    if (tid == 0) {
-        for (int l = n_acc; l < P.t.gamma; ++l) path_out[l] = -1;
-        P.cand_len[(int64_t)b * P.R + root] = n_acc;
     }
     if (P.n_new > 0) {
         if (!term_in_regs) {                  // the terminal distribution is a target row: bring it into r
@@ -739,29 +570,517 @@ __global__ __launch_bounds__(VT) void verify_walk_fast_kernel(const VerifyParams
         (void)total(true);                    // wavefront sums and lane-sum heaps of the terminal distribution; one barrier
         for (int k = wave; k < P.n_new; k += NWAVE) {       // wavefronts draw independently from here on
             const int t = fast_sample<NOREP>(sh, P, buf, term_p, term_q, term_rounds, P.us[(int64_t)b * P.n_new + k]);
-            if (lane == 0) P.cand_new[((int64_t)b * P.R + root) * P.n_new + k] = t;
+            if (lane == 0) put(P.cand_new + ((int64_t)b * P.R + root) * P.n_new + k, t);
         }
     }
+    if (wave == 0) {                          // (lane 0 wrote the path: no barrier needed)
+        if (lane < P.t.gamma) put(path_out + lane, lane < n_acc ? sh.path[lane] : -1);
+        if (lane == 0) put(P.cand_len + (int64_t)b * P.R + root, n_acc);
+    }
+    if (P.mode == MCSD_TARGET_INIT) select_longest(P, b, root, P.R);
 }
 
-// Target-initialised trees: the level-1 subtree with the longest accepted path wins, lowest id on ties.
-__global__ void verify_select_kernel(const VerifyParams P, int32_t *out_path, int32_t *out_len, int32_t *out_new)
+// ---------------------------------------------------------------------------------------------------
+// Teams: several workgroups share one walk, each holding one aligned power-of-two chunk of the vocabulary
+// ---------------------------------------------------------------------------------------------------
+// All workgroups of a team take the same decisions (they are functions of the same binary64 numbers), so the only thing
+// they exchange is the sum of their chunk once per rejection round: an all-gather through a mailbox in device memory.
+// Nothing depends on the others arriving: a workgroup that has waited TEAM_POLLS polls for a sum computes it from the
+// two rows itself (the same tree, hence the same bits) and does not wait again, so every wait ends whatever else
+// occupies the chip.
+//
+// A message is the sum in four 16-bit pieces, each in a 64-bit word of its own under the same 48-bit tag, so it needs no
+// ordering against anything: the exit count of the mailbox when the launch began (27 bits), the nonce of the walk (20
+// bits) and one bit that tells a step from the one before it in the same box.  Nonces come from a host counter, one per
+// walk.  The exit count grows by one per workgroup that leaves and so differs between two replays of one captured
+// launch.  A mailbox that two launches happen to use at once (the mailboxes are a ring of TEAM_MAILBOXES) only loses
+// messages: the tags tell them apart, and the reader computes the sum itself.
+// Two boxes in turn: a workgroup writes step s + 2 only after it has everyone's step s + 1, and whoever sent that had
+// read all of step s.
+constexpr int TEAM_MAX = 16, TEAM_MAILBOXES = 512, TEAM_POLLS = 64;
+struct TeamMailbox {
+    unsigned exits;
+    unsigned pad[31];
+    unsigned long long box[2][TEAM_MAX][TEAM_MAX][4];     // [step parity][reader][writer][piece]
+};
+__device__ __align__(128) TeamMailbox g_team[TEAM_MAILBOXES];
+
+struct TeamParams {
+    VerifyParams v;
+    unsigned long long nonce;            // of walk 0
+    int32_t C, log_c;                    // workgroups per team, a power of two
+    int32_t log_xcc;                     // dies the workgroup ids are dealt to (a power of two); a team's ids agree modulo their number
+    int32_t polls;                       // how often a sum is looked for; < 0: never (every sum computed here)
+};
+
+template <int EPL_, int NT>
+struct TeamShared {
+    float4 region[EPL_ == 16 ? NT * 4 : 1];                 // see team_load
+    double wsum[2][NT / 64];             // sums of the wavefronts' parts of the chunk, double-buffered over rounds
+    double csum[2][TEAM_MAX];            // sums of the team's chunks
+    double lsum[NT];                     // the lanes' sums of the latest round, for sampling
+    double S[2];
+    History hist;                        // of the current context
+    NodeCache node;
+    int path[MCSD_MAX_LEVELS];           // accepted nodes so far, written out at the end (a store in flight delays every later load)
+    float us[64];                        // sampling uniforms
+    double thr[64];                      // sampling: what is left of draw k's threshold inside its lane
+    int at[64];                          // ... wavefront * 64 + lane, -1 when another workgroup owns it
+};
+
+// Four floats at any 4-byte aligned address.
+struct __attribute__((packed, aligned(4))) Float4u { float x, y, z, w; };
+
+// Floats t .. t + 3 of a row (V >= 4).  The load itself is unconditional, from an address inside the row, so that a lane's
+// loads are in flight together; the few lanes at the row's end shift or clear afterwards (team_edge).
+__device__ inline float4 team_load4(const float *row, int t, int V)
 {
-    const int b = blockIdx.x;
-    __shared__ int best;
-    if (threadIdx.x == 0) {
-        int bi = 0, bl = -1;
-        for (int r = 0; r < P.R; ++r) {
-            const int len = P.cand_len[(int64_t)b * P.R + r];
-            if (len > bl) { bl = len; bi = r; }
-        }
-        best = bi;
-        out_len[b] = bl;
+    const Float4u f = *(const Float4u *)(row + (t < V - 4 ? t : V - 4));
+    return make_float4(f.x, f.y, f.z, f.w);
+}
+__device__ inline float4 team_edge(float4 v, int t, int V)
+{
+    const int over = t - (V - 4);                           // > 0: the piece starts `over` floats after what was loaded
+    if (over > 0) {
+        v.x = over == 1 ? v.y : (over == 2 ? v.z : (over == 3 ? v.w : 0.f));
+        v.y = over == 1 ? v.z : (over == 2 ? v.w : 0.f);
+        v.z = over == 1 ? v.w : 0.f;
+        v.w = 0.f;
     }
-    __syncthreads();
-    const int64_t c = (int64_t)b * P.R + best;
-    for (int l = threadIdx.x; l < P.t.gamma; l += blockDim.x) out_path[(int64_t)b * P.t.gamma + l] = P.cand_path[c * P.t.gamma + l];
-    for (int k = threadIdx.x; k < P.n_new; k += blockDim.x) out_new[(int64_t)b * P.n_new + k] = P.cand_new[c * P.n_new + k];
+    return v;
+}
+
+// The lane's N consecutive elements base + lane * N .. of a row, base = the wavefront's first.  N = 8: a lane's 32 bytes
+// straight from memory.  N = 16: fetched coalesced (16 bytes per lane, 1 KiB contiguous per instruction; 64 bytes per lane
+// would pull every line through the L1 four times) and handed to the owner lanes through the wavefront's LDS region; the XOR
+// makes both sides free of bank conflicts.  First the requests ...
+template <int N>
+__device__ inline void team_request(const float *row, int base, int V, float4 (&f)[N / 4])
+{
+    int lane = threadIdx.x & 63;
+    if constexpr (N == 16) asm volatile("" : "+v"(lane));  // (addresses recomputed here instead of kept, and spilled, all along)
+    const int first = base + (N == 8 ? lane * 8 : lane * 4);
+#pragma unroll
+    for (int j = 0; j < N / 4; ++j) f[j] = team_load4(row, first + j * (N == 8 ? 4 : 256), V);
+}
+// ... then, when they have arrived, the values.
+template <int N>
+__device__ inline void team_take(float4 (&f)[N / 4], int base, int V, float (&v)[N], float4 *region)
+{
+    int lane = threadIdx.x & 63;
+    if constexpr (N == 16) asm volatile("" : "+v"(lane));
+    const int first = base + (N == 8 ? lane * 8 : lane * 4);
+    if (base + 64 * N > V) {                                // (uniform) the wavefront reaches beyond the row
+#pragma unroll
+        for (int j = 0; j < N / 4; ++j) f[j] = team_edge(f[j], first + j * (N == 8 ? 4 : 256), V);
+    }
+    if constexpr (N == 16) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int l = j * 16 + (lane >> 2);             // owner of 16-byte unit 64 j + lane
+            region[4 * l + ((lane & 3) ^ ((l >> 2) & 3))] = f[j];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[j] = region[4 * lane + (j ^ ((lane >> 2) & 3))];
+    }
+#pragma unroll
+    for (int j = 0; j < N / 4; ++j) { v[4 * j] = f[j].x; v[4 * j + 1] = f[j].y; v[4 * j + 2] = f[j].z; v[4 * j + 3] = f[j].w; }
+}
+
+// Which of 2^K values the threshold falls into; thr becomes what is left of it.  Value i sits in lane i, or with QUAD in all
+// lanes of quad i.  lvl[j] holds in every lane the sum over its aligned group of 2^j values.
+template <int K, bool QUAD = false>
+__device__ inline int lane_descend(double v, double &thr)
+{
+    constexpr int S = QUAD ? 2 : 0;                         // lanes per value, as a power of two
+    double lvl[K];
+    lvl[0] = v;
+#pragma unroll
+    for (int j = 1; j < K; ++j) {
+        const double x = lvl[j - 1];
+        const int d = j - 1 + S;                            // partner: lane ^ 2^d (see wave_tree_sum)
+        double o;
+        if (d == 0) o = dpp_f64<0xB1>(x);
+        else if (d == 1) o = dpp_f64<0x4E>(x);
+        else if (d == 2) o = dpp_f64<0x141>(x);
+        else if (d == 3) o = dpp_f64<0x140>(x);
+        else o = __hiloint2double(__builtin_amdgcn_ds_swizzle(__double2hiint(x), 0x401F), __builtin_amdgcn_ds_swizzle(__double2loint(x), 0x401F));
+        lvl[j] = __dadd_rn(x, o);
+    }
+    static_assert(K - 2 + S <= 4, "lane ^ 32 has no case above");
+    int lo = 0;
+#pragma unroll
+    for (int j = K; j >= 1; --j) {                         // the node covers values lo .. lo + 2^j - 1
+        const double left = read_lane_f64(lvl[j - 1], lo << S);
+        const bool right = __builtin_amdgcn_readfirstlane((int)!(thr < left)) != 0;
+        if (right) {
+            thr = __dsub_rn(thr, left);
+            lo += 1 << (j - 1);
+        }
+    }
+    return lo;
+}
+
+// In-lane: which of the lane's N elements the threshold falls into.  Halves are selected, never indexed: registers
+// cannot be indexed at run time.
+template <int N>
+__device__ inline int reg_descend(const double (&r)[N], double thr, double &val)
+{
+    double x[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = r[i];
+    int at = 0;
+#pragma unroll
+    for (int h = N / 2; h >= 1; h >>= 1) {
+        double s[N / 2];                                    // the tree over the first half of what is left
+#pragma unroll
+        for (int i = 0; i < h; ++i) s[i] = x[i];
+#pragma unroll
+        for (int w = h / 2; w >= 1; w >>= 1)
+#pragma unroll
+            for (int i = 0; i < w; ++i) s[i] = __dadd_rn(s[2 * i], s[2 * i + 1]);
+        const bool right = !(thr < s[0]);
+        if (right) thr = __dsub_rn(thr, s[0]);
+        at += right ? h : 0;
+#pragma unroll
+        for (int i = 0; i < h; ++i) x[i] = right ? x[h + i] : x[i];
+    }
+    val = x[0];
+    return at;
+}
+
+// The sum of elements base .. base + chunk - 1 of the distribution (prow, qrow, rounds), computed by one wavefront from
+// memory: what a workgroup does for a sum that did not arrive.
+template <bool NOREP>
+__device__ inline double chunk_sum_alone(const History &h, int V, const float *prow, const float *qrow, int rounds,
+                                                            int base, int chunk)
+{
+    const int lane = threadIdx.x & 63;
+    double blocks = 0.0;                                    // lane i: sum of the chunk's i-th block of 256 elements
+#pragma unroll 1
+    for (int k = 0; k < chunk / 256; ++k) {
+        double e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = base + k * 256 + lane * 4 + i;
+            e[i] = t < V ? residual_at<NOREP>(h, prow, qrow, rounds, t) : 0.0;
+        }
+        const double s = wave_tree_sum(__dadd_rn(__dadd_rn(e[0], e[1]), __dadd_rn(e[2], e[3])));
+        if (lane == k) blocks = s;
+    }
+    return wave_tree_sum(blocks);
+}
+
+// NT lanes with EPL_ consecutive elements each: a chunk of EPL_ * NT elements, residual (binary64) and draft values in
+// registers.  One launch serves any number of teams; with more workgroups than the chip holds the hardware starts them
+// in id order, a team's ids lie close together, and a workgroup whose partners are late falls back to its own sums.
+template <bool NOREP, int EPL_, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void verify_walk_team_kernel(const TeamParams T)
+{
+    constexpr int NWV = NT / 64, CHUNK = EPL_ * NT;
+    __shared__ TeamShared<EPL_, NT> sh;
+    const VerifyParams &P = T.v;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // workgroup ids are dealt round-robin to the dies: ids of a team agree modulo their number, so the mailbox stays in
+    // one die's L2
+    const int group = blockIdx.x >> (T.log_xcc + T.log_c), die = blockIdx.x & ((1 << T.log_xcc) - 1);
+    const int walk = (group << T.log_xcc) + die, member = (blockIdx.x >> T.log_xcc) & (T.C - 1);
+    if (walk >= P.B * P.R) return;
+    const int b = P.R == 1 ? walk : walk / P.R, root = walk - b * P.R;
+    const int t_wave = member * CHUNK + wave * 64 * EPL_, t_lane = t_wave + lane * EPL_;   // first element of the wavefront, of the lane
+    float4 *region = EPL_ == 16 ? sh.region + wave * 256 : nullptr;
+    const int32_t *tokens = P.tokens + (int64_t)b * P.n_nodes;
+    const float *p = P.p + (int64_t)b * P.pbs;
+    const float *q = P.q + (int64_t)b * P.qbs;
+    const float *ua = P.ua + (int64_t)b * P.n_nodes;
+    int32_t *path_out = P.cand_path + (int64_t)walk * P.t.gamma;
+    TeamMailbox &mail = g_team[(T.nonce + walk) % TEAM_MAILBOXES];
+
+    // Requested together at the start: the mailbox's exit count, the rows of the first context (small chunks only: a
+    // large one would delay what follows) and token, uniform, q(x) and p(x) of every candidate of the tree, two dependent
+    // trips to memory for the whole walk.
+    const bool target = P.mode == MCSD_TARGET_INIT;
+    const bool cached = P.n_nodes <= NODE_CACHE;
+    unsigned epoch = 0;
+    if (wave == 0) epoch = __hip_atomic_load(&mail.exits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    constexpr bool AHEAD = CHUNK <= 4096;
+    double r[EPL_];                           // this lane's elements of the current residual, at first the target row
+    float qv[EPL_];                           // ... and of the draft row of that context
+    int cur = target ? root : -1;             // context: node id (-1 = end of the prefix)
+    int rows_of = -2;                         // context whose rows r and qv hold, untouched
+    float4 pf[EPL_ / 4], qf[EPL_ / 4];
+    auto take_rows = [&](bool both) {
+        float pv[EPL_];
+        team_take<EPL_>(pf, t_wave, P.V, pv, region);
+        if (both) team_take<EPL_>(qf, t_wave, P.V, qv, region);
+#pragma unroll
+        for (int i = 0; i < EPL_; ++i) r[i] = (double)pv[i];
+    };
+    const NodeRegs mine = node_request(P, tokens, ua, tid);
+    const bool ahead = AHEAD && P.t.gamma > (target ? 1 : 0);
+    if (ahead) {
+        team_request<EPL_>(p + (int64_t)(cur + 1) * P.V, t_wave, P.V, pf);
+        team_request<EPL_>(q + (int64_t)(cur + 1) * P.V, t_wave, P.V, qf);
+    }
+    node_fetch(sh.node, P, p, q, mine, tid);
+    static_assert(NODE_CACHE <= NT, "one lane per cached node");
+    if (tid < P.n_new) sh.us[tid] = P.us[(int64_t)b * P.n_new + tid];
+    if (ahead) {
+        take_rows(true);
+        rows_of = cur;
+    }
+    int level = 0, n_acc = 0;
+    if (target) {                             // level-1 node `root` is accepted untested
+        level = 1;
+        n_acc = 1;
+        if (tid == 0) sh.path[0] = root;
+    }
+    double S_term = 0.0;                      // sum of the terminal distribution
+    int buf = 0;
+    unsigned step = 0;
+    bool alone = false;                       // this workgroup has waited in vain once
+    const float *term_p = nullptr, *term_q = nullptr;
+    int term_rounds = 0;
+    bool term_in_regs = false;
+
+    // The sum of r over the vocabulary, after `rounds` rejections at the context with rows prow / qrow.
+    auto total = [&](const float *prow, const float *qrow, int rounds) -> double {
+        double v[EPL_];
+#pragma unroll
+        for (int i = 0; i < EPL_; ++i) v[i] = r[i];
+#pragma unroll
+        for (int w = EPL_ / 2; w >= 1; w >>= 1)
+#pragma unroll
+            for (int i = 0; i < w; ++i) v[i] = __dadd_rn(v[2 * i], v[2 * i + 1]);
+        sh.lsum[tid] = v[0];
+        const double ws = wave_tree_sum(v[0]);
+        buf ^= 1;
+        if (lane == 0) sh.wsum[buf][wave] = ws;
+        __syncthreads();
+        double c = 0.0;
+        if (T.C == 1 || wave == 0) {
+            c = sh.wsum[buf][lane & (NWV - 1)];
+            c = __dadd_rn(c, dpp_f64<0xB1>(c));
+            c = __dadd_rn(c, dpp_f64<0x4E>(c));
+            c = __dadd_rn(c, dpp_f64<0x141>(c));
+            if constexpr (NWV >= 16) c = __dadd_rn(c, dpp_f64<0x140>(c));
+        }
+        if (T.C == 1) return read_lane_f64(c, 0);     // (uniform by construction, and the compiler has to know: the walk is scalar)
+        if (wave == 0) {
+            // lane 4 m + k: piece k of the message to, then from member m
+            const int m = lane >> 2, k = lane & 3;
+            const unsigned long long tag = ((unsigned long long)epoch << 37) | (((T.nonce + walk) / TEAM_MAILBOXES & 0xfffffull) << 17) |
+                                           ((unsigned long long)(step >> 1 & 1u) << 16);
+            unsigned long long(*box)[TEAM_MAX][4] = mail.box[step & 1];
+            const unsigned half = (unsigned)(k & 2 ? __double2hiint(c) : __double2loint(c)), piece = k & 1 ? half >> 16 : half & 0xffffu;
+            unsigned long long w = tag | piece;
+            if (m < T.C) __hip_atomic_store(&box[m][member][k], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const bool other = m < T.C && m != member;
+            unsigned long long missing;
+            for (int polls = __builtin_amdgcn_readfirstlane(alone ? 0 : T.polls);; --polls) {
+                if (other) w = T.polls >= 0 ? __hip_atomic_load(&box[member][m][k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~tag;
+                missing = __builtin_amdgcn_ballot_w64(other && (w ^ tag) >> 16 != 0);
+                if (missing == 0 || __builtin_amdgcn_readfirstlane(polls) <= 0) break;
+            }
+            step += 1;
+            unsigned half_lo = (unsigned)w & 0xffffu;
+            const int w0 = __builtin_amdgcn_update_dpp(0, (int)half_lo, 0x00, 0xF, 0xF, false), w1 = __builtin_amdgcn_update_dpp(0, (int)half_lo, 0x55, 0xF, 0xF, false);
+            const int w2 = __builtin_amdgcn_update_dpp(0, (int)half_lo, 0xAA, 0xF, 0xF, false), w3 = __builtin_amdgcn_update_dpp(0, (int)half_lo, 0xFF, 0xF, 0xF, false);
+            double s = m < T.C ? __hiloint2double(w2 | w3 << 16, w0 | w1 << 16) : 0.0;
+            while (missing) {
+                alone = true;
+                const int mm = __builtin_ctzll(missing) >> 2;
+                missing &= ~(0xfull << (4 * mm));
+                const double a = chunk_sum_alone<NOREP>(sh.hist, P.V, prow, qrow, rounds, mm * CHUNK, CHUNK);
+                if (m == mm) s = a;
+            }
+            if (k == 0) sh.csum[buf][m] = s;
+            s = __dadd_rn(s, dpp_f64<0x141>(s));        // the tree over the 16 quads
+            s = __dadd_rn(s, dpp_f64<0x140>(s));
+            {
+                const int lo = __builtin_amdgcn_ds_swizzle(__double2loint(s), 0x401F), hi = __builtin_amdgcn_ds_swizzle(__double2hiint(s), 0x401F);
+                s = __dadd_rn(s, __hiloint2double(hi, lo));
+            }
+            {
+                const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(s), (unsigned)__double2loint(s), false, false);
+                const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(s), (unsigned)__double2hiint(s), false, false);
+                s = __dadd_rn(__hiloint2double((int)hi[0], (int)lo[0]), __hiloint2double((int)hi[1], (int)lo[1]));
+            }
+            if (lane == 0) sh.S[buf] = s;
+        }
+        __syncthreads();
+        return read_lane_f64(sh.S[buf], 0);
+    };
+
+    __syncthreads();                          // the cached candidates are visible
+    // The walk is the same in all lanes and has to be scalar control flow (tree description from scalar loads, no
+    // execution masks); the compiler loses sight of that where a lane-dependent branch joins, hence the readfirstlanes.
+    while (true) {
+        level = __builtin_amdgcn_readfirstlane(level);
+        cur = __builtin_amdgcn_readfirstlane(cur);
+        n_acc = __builtin_amdgcn_readfirstlane(n_acc);
+        unsigned kid = 0;
+        if (cached) {                         // contexts whose first candidate passes need nothing but that fact
+            while (level < P.t.gamma) {
+                kid = __builtin_amdgcn_readfirstlane(sh.node.kid[cur + 1]);
+                if (!(kid >> 31)) break;
+                cur = (int)(kid & 0x7fffffffu);
+                if (tid == 0) sh.path[n_acc] = cur;
+                n_acc += 1;
+                level += 1;
+            }
+        }
+        if (level >= P.t.gamma) break;
+        const float *prow = p + (int64_t)(cur + 1) * P.V;
+        const float *qrow = q + (int64_t)(cur + 1) * P.V;
+        const int cnt = P.t.b[level];
+        const int first = cached ? (int)kid : (cur < 0 ? 0 : P.t.off[level] + (cur - P.t.off[level - 1]) * cnt);
+        // candidate `lane` of this context (in every wavefront): acceptance uniform, q(x) and the residual at x,
+        // which is updated in place after every rejection
+        double uc = 0.0, qc = 0.0, rc = 0.0;
+        int xc = -1;
+        if (lane < cnt) {
+            const int i = first + lane;
+            if (cached) {
+                xc = sh.node.x[i];
+                uc = (double)sh.node.u[i];
+                qc = (double)sh.node.q[i];
+                rc = (double)sh.node.p[i];
+            } else {
+                int x = tokens[i];
+                x = x < 0 ? 0 : (x >= P.V ? P.V - 1 : x);
+                float u = ua[i], qx = qrow[x], px = prow[x];
+                asm volatile("" : "+v"(u), "+v"(qx), "+v"(px));      // (keeps the compiler from merging these loads with those above)
+                xc = x;
+                uc = (double)u;
+                qc = (double)qx;
+                rc = (double)px;
+            }
+        }
+        int rounds = 0, accepted = -1;
+        double S = 1.0, Sq = 1.0;                        // both rows are trusted to be normalised in round 0
+        // accept test of candidate c, evaluated by its lane; the same answer in every wavefront
+        auto accept = [&](int c) {
+            const double rhs = NOREP ? __dmul_rn(rc, Sq) : rc;
+            return __builtin_amdgcn_readlane((int)(__dmul_rn(uc, __dmul_rn(qc, S)) < rhs), c) != 0;
+        };
+        if (!cached && accept(0)) {
+            accepted = first;
+        } else {
+            if (!AHEAD || __builtin_amdgcn_readfirstlane(rows_of) != cur) {
+                team_request<EPL_>(prow, t_wave, P.V, pf);
+                team_request<EPL_>(qrow, t_wave, P.V, qf);
+                take_rows(true);
+            }
+            rows_of = -2;
+            for (int c = 0;;) {
+                // candidate c was rejected: r <- max(r - S q, 0), S <- sum r
+                const int xrej = NOREP ? __builtin_amdgcn_readlane(xc, c) : 0;
+                const double qrej = NOREP ? read_lane_f64(qc, c) : 0.0;
+                if (tid == 0) {
+                    sh.hist.s[rounds] = S;
+                    if (NOREP) { sh.hist.sq[rounds] = Sq; sh.hist.x[rounds] = xrej; }
+                }
+                if constexpr (EPL_ == 16) {   // (the conversions below stay in the loop: 32 registers fewer)
+#pragma unroll
+                    for (int i = 0; i < EPL_; ++i) asm volatile("" : "+v"(qv[i]));
+                }
+#pragma unroll
+                for (int i = 0; i < EPL_; ++i)
+                    r[i] = pos_part(__fma_rn(-S, (double)qv[i], NOREP ? __dmul_rn(r[i], Sq) : r[i]));
+                if (NOREP) {                  // the rejected token leaves the draft row after this round's update has used it
+#pragma unroll
+                    for (int i = 0; i < EPL_; ++i)
+                        if (xrej - t_lane == i) qv[i] = 0.f;
+                }
+                {
+                    const double d = __fma_rn(-S, qc, NOREP ? __dmul_rn(rc, Sq) : rc);
+                    rc = pos_part(d);
+                }
+                if (NOREP) {
+                    Sq = __dsub_rn(Sq, qrej);
+                    if (xc == xrej) qc = 0.0;             // also a later duplicate of the rejected token
+                }
+                rounds += 1;
+                S = total(prow, qrow, rounds);
+                if (++c == cnt) break;
+                if (accept(c)) { accepted = first + c; break; }
+            }
+        }
+        if (accepted < 0) {
+            term_p = prow; term_q = qrow;
+            if (S > 0.0) { term_rounds = rounds; term_in_regs = true; S_term = S; }
+            else { term_rounds = 0; term_in_regs = false; }   // vanished residual: the context's own target row
+            break;
+        }
+        if (tid == 0) sh.path[n_acc] = accepted;
+        cur = accepted;
+        n_acc += 1;
+        level += 1;
+    }
+    if (term_p == nullptr) {                  // every level accepted: bonus from the row after the last node
+        term_p = p + (int64_t)(cur + 1) * P.V;
+        term_q = term_p;                      // never read: rounds == 0
+    }
+    if (P.n_new > 0) {
+        if (!term_in_regs) {                  // the terminal distribution is a target row: bring it into r
+            team_request<EPL_>(term_p, t_wave, P.V, pf);
+            take_rows(false);
+            S_term = total(term_p, term_q, 0);
+        }
+        // Wavefront k places draws k, k + NWV, ..: chunk, wavefront and lane; a draw in another chunk is its owner's
+        // (a single draw is placed by every wavefront for itself, which saves the hand-over)
+        const bool single = P.n_new == 1;
+        int at1 = -1;
+        double thr1 = 0.0;
+        for (int k = single ? 0 : wave; k < P.n_new; k += NWV) {
+            double thr = __dmul_rn((double)sh.us[k], S_term);
+            int at = -1;
+            if (T.C == 1 || lane_descend<4, true>(sh.csum[buf][lane >> 2], thr) == member) {
+                constexpr int KW = NWV == 8 ? 3 : 4;
+                const int w = lane_descend<KW>(sh.wsum[buf][lane & (NWV - 1)], thr);
+                const int l = lane_descend<6>(sh.lsum[w * 64 + lane], thr);
+                at = w * 64 + l;
+            }
+            at1 = at;
+            thr1 = thr;
+            if (!single && lane == 0) { sh.at[k] = at; sh.thr[k] = thr; }
+        }
+        if (!single) __syncthreads();
+        for (int k = 0; k < P.n_new; ++k) {
+            const int at = single ? at1 : __builtin_amdgcn_readfirstlane(sh.at[k]);
+            if (at < 0 || (at >> 6) != wave) continue;
+            double val;
+            int t = t_lane + reg_descend<EPL_>(r, single ? thr1 : sh.thr[k], val);      // every lane for itself; lane `at` is meant
+            t = __builtin_amdgcn_readlane(t, at & 63);
+            if (!(t < P.V && read_lane_f64(val, at & 63) > 0.0)) {
+                // Reached a zero-weight index (last-bit rounding of the subtraction, or an all-zero distribution):
+                // nearest positive-weight index below, else nearest above, else 0.
+                int below = -1, above = 0x7fffffff;
+                for (int e = lane; e < P.V; e += 64) {
+                    if (e == t) continue;
+                    if (residual_at<NOREP>(sh.hist, term_p, term_q, term_rounds, e) > 0.0) {
+                        if (e < t) below = e > below ? e : below;
+                        else above = e < above ? e : above;
+                    }
+                }
+#pragma unroll
+                for (int m = 1; m < 64; m <<= 1) {
+                    const int ob = __shfl_xor(below, m, 64), oa = __shfl_xor(above, m, 64);
+                    below = ob > below ? ob : below;
+                    above = oa < above ? oa : above;
+                }
+                t = below >= 0 ? below : (above != 0x7fffffff ? above : 0);
+            }
+            if (lane == 0) put(P.cand_new + (int64_t)walk * P.n_new + k, t);
+        }
+    }
+    if (member == 0 && wave == 0) {           // (lane 0 wrote the path: no barrier needed)
+        if (lane < P.t.gamma) put(path_out + lane, lane < n_acc ? sh.path[lane] : -1);
+        if (lane == 0) put(P.cand_len + walk, n_acc);
+    }
+    if (target) select_longest(P, b, root * T.C + member, P.R * T.C);
+    if (T.C > 1 && tid == 0) (void)__hip_atomic_fetch_add(&mail.exits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -773,15 +1092,59 @@ extern "C" size_t mcsd_verify_tree_workspace(const mcsd_mask_view_t *mask, mcsd_
     if (!mask || mode != MCSD_TARGET_INIT || B < 1 || n_new < 0 || mask->gamma < 1) return 0;
     const size_t R = (size_t)mask->branching_host[0];
     return align256(sizeof(int32_t) * B * R * mask->gamma) + align256(sizeof(int32_t) * B * R) +
-           align256(sizeof(int32_t) * B * R * (n_new > 0 ? n_new : 1));
+           align256(sizeof(int32_t) * B * R * (n_new > 0 ? n_new : 1)) + align256(sizeof(unsigned long long) * B * R * TEAM_MAX);
 }
 
 namespace {
-void launch_walk(const VerifyParams &P, bool norep, dim3 grid, hipStream_t st)
+// One number per walk ever launched: the nonces of the teams' messages (a tag is never all zeros, what a mailbox starts
+// with) and, with a part of its own for every process, the id of a launch.
+std::atomic<unsigned long long> g_team_nonce{TEAM_MAILBOXES};
+const unsigned long long g_process_part = (unsigned long long)std::chrono::system_clock::now().time_since_epoch().count() << 40;
+
+// Chunk of the vocabulary a team's workgroup holds; 0: one workgroup of the fast kernel per walk.  Up to 16384 entries one
+// workgroup does it all (an exchange costs about as much as it saves there).  Beyond, the smallest chunk that leaves every
+// workgroup a compute unit of its own, at least 4096 entries, at most 16 workgroups per team.  Vocabularies up to 32768 go
+// to the fast kernel when even two workgroups per walk would not fit (200 walks: 25 us against 30).
+int team_chunk(int V, long walks, int team)
 {
-    auto kernel = P.V <= FAST_V ? (norep ? verify_walk_fast_kernel<true> : verify_walk_fast_kernel<false>)
-                                : (norep ? verify_walk_kernel<true> : verify_walk_kernel<false>);
-    mcsd_launch(MCSD_KERNEL_VERIFY_WALK, kernel, grid, dim3(VT), st, P);
+    if (V < 4) return 0;                                    // (rows shorter than one load)
+    int space = 4096;
+    while (space < V) space <<= 1;
+    int chunk = space / TEAM_MAX < 4096 ? 4096 : space / TEAM_MAX;
+    if (team > 0) {
+        while (chunk < 16384 && space / chunk > team) chunk <<= 1;
+        return chunk;
+    }
+    if (space <= 16384) return space;
+    while (chunk < 16384 && walks * (space / chunk) > 256) chunk <<= 1;
+    return space == FAST_V && walks * (space / chunk) > 256 ? 0 : chunk;
+}
+
+void launch_walk(VerifyParams &P, bool norep, const mcsd_verify_tuning_t *tune, int device, hipStream_t st)
+{
+    const long walks = (long)P.B * P.R;
+    const unsigned long long nonce = g_team_nonce.fetch_add((unsigned long long)walks, std::memory_order_relaxed);
+    P.launch_id = g_process_part | (nonce & 0xffffffffffull);
+    if (P.launch_id == 0) P.launch_id = 1;
+    const int chunk = team_chunk(P.V, walks, tune ? tune->team : 0);
+    if (chunk == 0) {
+        mcsd_launch(MCSD_KERNEL_VERIFY_WALK, norep ? verify_walk_fast_kernel<true> : verify_walk_fast_kernel<false>, dim3(P.R, P.B), dim3(VT), st, P);
+        return;
+    }
+    TeamParams T;
+    T.v = P;
+    T.C = 1;
+    while (T.C * chunk < P.V) T.C <<= 1;
+    T.nonce = nonce;
+    T.polls = tune && tune->polls != 0 ? tune->polls : TEAM_POLLS;
+    const int xcc = T.C > 1 ? mcsd_xcc_count(device) : 1;
+    T.log_c = __builtin_ctz(T.C);
+    T.log_xcc = xcc > 1 ? __builtin_ctz(xcc) : 0;
+    const long dies = 1l << T.log_xcc, groups = (walks - 1) / dies;             // whole groups of `dies` teams before the last
+    const dim3 grid((unsigned)(groups * dies * T.C + (T.C - 1) * dies + (walks - 1) % dies + 1));
+    if (chunk == 4096) mcsd_launch(MCSD_KERNEL_VERIFY_WALK, norep ? verify_walk_team_kernel<true, 8, 512> : verify_walk_team_kernel<false, 8, 512>, grid, dim3(512), st, T);
+    else if (chunk == 8192) mcsd_launch(MCSD_KERNEL_VERIFY_WALK, norep ? verify_walk_team_kernel<true, 8, 1024> : verify_walk_team_kernel<false, 8, 1024>, grid, dim3(1024), st, T);
+    else mcsd_launch(MCSD_KERNEL_VERIFY_WALK, norep ? verify_walk_team_kernel<true, 16, 1024> : verify_walk_team_kernel<false, 16, 1024>, grid, dim3(1024), st, T);
 }
 }  // namespace
 
@@ -803,6 +1166,20 @@ extern "C" int mcsd_verify_tree_sampling(const mcsd_mask_view_t *mask, mcsd_mode
                                          int32_t *out_path, int32_t *out_accept_len, int32_t *out_new_tokens,
                                          void *workspace, size_t workspace_bytes, void *hip_stream)
 {
+    return mcsd_verify_tree_tuned(nullptr, mask, mode, sampling, B, V, tokens, p_target, q_draft, p_batch_stride, q_batch_stride,
+                                  u_accept, u_sample, n_new, out_path, out_accept_len, out_new_tokens, workspace,
+                                  workspace_bytes, hip_stream);
+}
+
+extern "C" int mcsd_verify_tree_tuned(const mcsd_verify_tuning_t *tuning, const mcsd_mask_view_t *mask, mcsd_mode_t mode,
+                                      mcsd_sampling_t sampling, int32_t B, int32_t V, const int32_t *tokens,
+                                      const float *p_target, const float *q_draft, int64_t p_batch_stride,
+                                      int64_t q_batch_stride, const float *u_accept, const float *u_sample,
+                                      int32_t n_new, int32_t *out_path, int32_t *out_accept_len,
+                                      int32_t *out_new_tokens, void *workspace, size_t workspace_bytes,
+                                      void *hip_stream)
+{
+    if (tuning && (tuning->team < 0 || tuning->team > TEAM_MAX || tuning->polls < -1 || tuning->polls > 1 << 16)) return MCSD_EINVAL;
     if (sampling != MCSD_WITH_REPLACEMENT && sampling != MCSD_WITHOUT_REPLACEMENT) return MCSD_EINVAL;
     const bool norep = sampling == MCSD_WITHOUT_REPLACEMENT;
     if (!mask || !tokens || !p_target || !u_accept || !out_path || !out_accept_len) return MCSD_EINVAL;
@@ -823,20 +1200,22 @@ extern "C" int mcsd_verify_tree_sampling(const mcsd_mask_view_t *mask, mcsd_mode
     for (int l = 0; l <= mask->gamma; ++l) P.t.off[l] = mask->level_off_host[l];
     P.mode = mode; P.B = B; P.V = V; P.n_nodes = mask->n_nodes; P.n_new = n_new;
     P.R = mode == MCSD_TARGET_INIT ? mask->branching_host[0] : 1;
-    int nb = 1;
-    while (nb * BLK < V) nb <<= 1;
-    P.NB = nb;
     P.tokens = tokens; P.p = p_target; P.q = q_draft ? q_draft : p_target;
     P.pbs = p_batch_stride; P.qbs = q_batch_stride;
     P.ua = u_accept; P.us = u_sample;
+    P.parent = mask->parent_dev;
     hipStream_t st = (hipStream_t)hip_stream;
+    P.out_path = P.out_len = P.out_new = nullptr;
+    P.done = nullptr;
     if (mode == MCSD_DRAFT_INIT) {
+        if (!mask->parent_dev) return MCSD_EINVAL;          // a mask built without a device
         P.cand_path = out_path; P.cand_len = out_accept_len; P.cand_new = out_new_tokens;
-        launch_walk(P, norep, dim3(1, B), st);
+        launch_walk(P, norep, tuning, mask->device, st);
         return mcsd_hip_status(hipGetLastError());
     }
     const size_t need = mcsd_verify_tree_workspace(mask, mode, B, n_new);
     if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255)) return MCSD_EWORKSPACE;
+    if (!mask->parent_dev) return MCSD_EINVAL;
     const size_t R = (size_t)P.R;
     char *w = (char *)workspace;
     P.cand_path = (int32_t *)w;
@@ -844,9 +1223,9 @@ extern "C" int mcsd_verify_tree_sampling(const mcsd_mask_view_t *mask, mcsd_mode
     P.cand_len = (int32_t *)w;
     w += align256(sizeof(int32_t) * B * R);
     P.cand_new = (int32_t *)w;
-    launch_walk(P, norep, dim3(P.R, B), st);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return MCSD_EHIP;
-    hipLaunchKernelGGL(verify_select_kernel, dim3(B), dim3(64), 0, st, P, out_path, out_accept_len, out_new_tokens);
+    w += align256(sizeof(int32_t) * B * R * (n_new > 0 ? n_new : 1));
+    P.done = (unsigned long long *)w;
+    P.out_path = out_path; P.out_len = out_accept_len; P.out_new = out_new_tokens;
+    launch_walk(P, norep, tuning, mask->device, st);
     return mcsd_hip_status(hipGetLastError());
 }
