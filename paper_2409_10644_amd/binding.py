@@ -1,7 +1,10 @@
-"""ctypes binding of libmcsd.so: same names and argument order as include/mcsd.h, marshalling only."""
+"""Binding of libmcsd.so: same names and argument order as include/mcsd.h, marshalling only.  The calls of a decoding
+loop are marshalled natively (_pycall.so), the others through ctypes."""
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional, Sequence
 
@@ -9,6 +12,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmcsd.so")
+PYCALL_PATH = os.path.join(_HERE, "_pycall.so")
 
 MCSD_OK, MCSD_EINVAL, MCSD_ENOMEM, MCSD_EHIP, MCSD_EWORKSPACE, MCSD_EUNSUPPORTED = 0, -1, -2, -3, -4, -5
 MCSD_F32, MCSD_BF16 = 0, 1
@@ -170,6 +174,33 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+def _raise(status: int, where: str) -> None:
+    raise McsdError(status, where)
+
+
+def _load_pycall():
+    if not os.path.exists(PYCALL_PATH):
+        raise ImportError(f"{PYCALL_PATH} is missing: build it with `python -m paper_2409_10644_amd.build`")
+    loader = importlib.machinery.ExtensionFileLoader("_pycall", PYCALL_PATH)
+    mod = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_pycall", PYCALL_PATH, loader=loader))
+    loader.exec_module(mod)
+
+    def device() -> int:                 # until the GPU runtime is up in this process; then torch's own getter
+        torch.cuda.current_stream()
+        setup(torch._C._cuda_getDevice)
+        return torch._C._cuda_getDevice()
+
+    def setup(get_device):
+        mod.setup(tuple(C.cast(getattr(lib, n), C.c_void_p).value for n in mod.names()), torch.Tensor,
+                  torch._C._cuda_getCurrentRawStream, get_device, _raise)
+
+    setup(device)
+    return mod
+
+
+_pycall = _load_pycall()
+
+
 def _stream(stream=None) -> int:
     s = torch.cuda.current_stream() if stream is None else stream
     return s.cuda_stream
@@ -207,7 +238,7 @@ def build_mask(branching: Sequence[int], gamma_max: Optional[int] = None) -> Mas
 
 def slice_mask(mask: Mask, gamma: int) -> MaskView:
     view = MaskView()
-    _check(lib.mcsd_slice_mask(mask.handle, int(gamma), C.byref(view)), "mcsd_slice_mask")
+    _pycall.slice_mask(mask.handle, int(gamma), view)
     view._owner = mask          # keep the handle alive as long as the view
     return view
 
@@ -262,22 +293,16 @@ def tree_attention(view: MaskView, dtype: int, B: int, H: int, d: int, q: torch.
                    v_prefix: Optional[torch.Tensor], seq_base_dev: torch.Tensor, prefix_lens_dev: torch.Tensor,
                    head_stride: int, max_prefix: int, softmax_scale: float, out: torch.Tensor,
                    workspace: Optional[torch.Tensor], stream=None) -> None:
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib.mcsd_tree_attention(C.byref(view), dtype, B, H, d, _ptr(q), _ptr(k_tree), _ptr(v_tree), node_stride,
-                                 _ptr(k_prefix), _ptr(v_prefix), _ptr(seq_base_dev), _ptr(prefix_lens_dev),
-                                 head_stride, max_prefix, softmax_scale, _ptr(out), _ptr(workspace), ws_bytes,
-                                 _stream(stream))
-    _check(st, "mcsd_tree_attention")
+    _pycall.tree_attention(view, dtype, B, H, d, q, k_tree, v_tree, node_stride, k_prefix, v_prefix, seq_base_dev,
+                           prefix_lens_dev, head_stride, max_prefix, softmax_scale, out, workspace, stream)
 
 
 def tree_attention_static(view: MaskView, dtype: int, B: int, H: int, d: int, q: torch.Tensor, k_tree: torch.Tensor,
                           v_tree: torch.Tensor, node_stride: int, k_prefix: Optional[torch.Tensor],
                           v_prefix: Optional[torch.Tensor], seq_base_dev: torch.Tensor, prefix_lens_dev: torch.Tensor,
                           head_stride: int, max_prefix: int, softmax_scale: float, out: torch.Tensor, stream=None) -> None:
-    st = lib.mcsd_tree_attention_static(C.byref(view), dtype, B, H, d, _ptr(q), _ptr(k_tree), _ptr(v_tree), node_stride,
-                                        _ptr(k_prefix), _ptr(v_prefix), _ptr(seq_base_dev), _ptr(prefix_lens_dev),
-                                        head_stride, max_prefix, softmax_scale, _ptr(out), _stream(stream))
-    _check(st, "mcsd_tree_attention_static")
+    _pycall.tree_attention_static(view, dtype, B, H, d, q, k_tree, v_tree, node_stride, k_prefix, v_prefix, seq_base_dev,
+                                  prefix_lens_dev, head_stride, max_prefix, softmax_scale, out, stream)
 
 
 def tree_attention_plan(tuning: Optional[AttentionTuning], dtype: int, prefix_fp8: int, B: int, H_q: int, H_kv: int,
@@ -297,12 +322,8 @@ def tree_attention_rows(view: MaskView, dtype: int, B: int, H: int, d: int, row_
                         k_prefix: Optional[torch.Tensor], v_prefix: Optional[torch.Tensor],
                         seq_base_dev: torch.Tensor, prefix_lens_dev: torch.Tensor, head_stride: int, max_prefix: int,
                         softmax_scale: float, out: torch.Tensor, workspace: Optional[torch.Tensor], stream=None) -> None:
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib.mcsd_tree_attention_rows(C.byref(view), dtype, B, H, d, row_begin, _ptr(q), _ptr(k_tree), _ptr(v_tree),
-                                      node_stride, _ptr(k_prefix), _ptr(v_prefix), _ptr(seq_base_dev),
-                                      _ptr(prefix_lens_dev), head_stride, max_prefix, softmax_scale, _ptr(out),
-                                      _ptr(workspace), ws_bytes, _stream(stream))
-    _check(st, "mcsd_tree_attention_rows")
+    _pycall.tree_attention_rows(view, dtype, B, H, d, row_begin, q, k_tree, v_tree, node_stride, k_prefix, v_prefix,
+                                seq_base_dev, prefix_lens_dev, head_stride, max_prefix, softmax_scale, out, workspace, stream)
 
 
 def tree_attention_gqa_workspace(B: int, H_q: int, H_kv: int, d: int, n_nodes: int, row_begin: int,
@@ -315,12 +336,8 @@ def tree_attention_gqa(view: MaskView, dtype: int, B: int, H_q: int, H_kv: int, 
                        k_prefix: Optional[torch.Tensor], v_prefix: Optional[torch.Tensor], seq_base_dev: torch.Tensor,
                        prefix_lens_dev: torch.Tensor, head_stride: int, max_prefix: int, softmax_scale: float,
                        out: torch.Tensor, workspace: Optional[torch.Tensor], stream=None) -> None:
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib.mcsd_tree_attention_gqa(C.byref(view), dtype, B, H_q, H_kv, d, row_begin, _ptr(q), _ptr(k_tree),
-                                     _ptr(v_tree), node_stride, _ptr(k_prefix), _ptr(v_prefix), _ptr(seq_base_dev),
-                                     _ptr(prefix_lens_dev), head_stride, max_prefix, softmax_scale, _ptr(out),
-                                     _ptr(workspace), ws_bytes, _stream(stream))
-    _check(st, "mcsd_tree_attention_gqa")
+    _pycall.tree_attention_gqa(view, dtype, B, H_q, H_kv, d, row_begin, q, k_tree, v_tree, node_stride, k_prefix, v_prefix,
+                               seq_base_dev, prefix_lens_dev, head_stride, max_prefix, softmax_scale, out, workspace, stream)
 
 
 def tree_attention_fp8kv_workspace(B: int, H_q: int, H_kv: int, n_nodes: int, row_begin: int, max_prefix: int) -> int:
@@ -333,12 +350,9 @@ def tree_attention_fp8kv(view: MaskView, B: int, H_q: int, H_kv: int, row_begin:
                          v_scale: float, seq_base_dev: torch.Tensor, prefix_lens_dev: torch.Tensor, head_stride: int,
                          max_prefix: int, softmax_scale: float, out: torch.Tensor, workspace: Optional[torch.Tensor],
                          stream=None) -> None:
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib.mcsd_tree_attention_fp8kv(C.byref(view), B, H_q, H_kv, row_begin, _ptr(q), _ptr(k_tree), _ptr(v_tree),
-                                       node_stride, _ptr(k_prefix_fp8), _ptr(v_prefix_fp8), k_scale, v_scale,
-                                       _ptr(seq_base_dev), _ptr(prefix_lens_dev), head_stride, max_prefix,
-                                       softmax_scale, _ptr(out), _ptr(workspace), ws_bytes, _stream(stream))
-    _check(st, "mcsd_tree_attention_fp8kv")
+    _pycall.tree_attention_fp8kv(view, B, H_q, H_kv, row_begin, q, k_tree, v_tree, node_stride, k_prefix_fp8, v_prefix_fp8,
+                                 k_scale, v_scale, seq_base_dev, prefix_lens_dev, head_stride, max_prefix, softmax_scale, out,
+                                 workspace, stream)
 
 
 def verify_tree_workspace(view: MaskView, mode: int, B: int, n_new: int) -> int:
@@ -349,11 +363,8 @@ def verify_tree(view: MaskView, mode: int, B: int, V: int, tokens: torch.Tensor,
                 q_draft: Optional[torch.Tensor], p_batch_stride: int, q_batch_stride: int, u_accept: torch.Tensor,
                 u_sample: Optional[torch.Tensor], n_new: int, out_path: torch.Tensor, out_accept_len: torch.Tensor,
                 out_new_tokens: Optional[torch.Tensor], workspace: Optional[torch.Tensor], stream=None) -> None:
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib.mcsd_verify_tree(C.byref(view), mode, B, V, _ptr(tokens), _ptr(p_target), _ptr(q_draft), p_batch_stride,
-                              q_batch_stride, _ptr(u_accept), _ptr(u_sample), n_new, _ptr(out_path),
-                              _ptr(out_accept_len), _ptr(out_new_tokens), _ptr(workspace), ws_bytes, _stream(stream))
-    _check(st, "mcsd_verify_tree")
+    _pycall.verify_tree(view, mode, B, V, tokens, p_target, q_draft, p_batch_stride, q_batch_stride, u_accept, u_sample, n_new,
+                        out_path, out_accept_len, out_new_tokens, workspace, stream)
 
 
 def verify_tree_sampling(view: MaskView, mode: int, sampling: int, B: int, V: int, tokens: torch.Tensor,
@@ -361,12 +372,8 @@ def verify_tree_sampling(view: MaskView, mode: int, sampling: int, B: int, V: in
                          q_batch_stride: int, u_accept: torch.Tensor, u_sample: Optional[torch.Tensor], n_new: int,
                          out_path: torch.Tensor, out_accept_len: torch.Tensor, out_new_tokens: Optional[torch.Tensor],
                          workspace: Optional[torch.Tensor], stream=None) -> None:
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib.mcsd_verify_tree_sampling(C.byref(view), mode, sampling, B, V, _ptr(tokens), _ptr(p_target), _ptr(q_draft),
-                                       p_batch_stride, q_batch_stride, _ptr(u_accept), _ptr(u_sample), n_new,
-                                       _ptr(out_path), _ptr(out_accept_len), _ptr(out_new_tokens), _ptr(workspace),
-                                       ws_bytes, _stream(stream))
-    _check(st, "mcsd_verify_tree_sampling")
+    _pycall.verify_tree_sampling(view, mode, sampling, B, V, tokens, p_target, q_draft, p_batch_stride, q_batch_stride, u_accept,
+                                 u_sample, n_new, out_path, out_accept_len, out_new_tokens, workspace, stream)
 
 
 def verify_tree_tuned(tuning: Optional[VerifyTuning], view: MaskView, mode: int, sampling: int, B: int, V: int,
@@ -382,10 +389,6 @@ def verify_tree_tuned(tuning: Optional[VerifyTuning], view: MaskView, mode: int,
     _check(st, "mcsd_verify_tree_tuned")
 
 
-def _ptr_array(tensors: Sequence[torch.Tensor]):
-    return (C.c_void_p * len(tensors))(*[t.data_ptr() for t in tensors])
-
-
 def commit_path(view: MaskView, dtype: int, B: int, H: int, d: int, k_tree: Sequence[torch.Tensor],
                 v_tree: Sequence[torch.Tensor], node_stride: int, k_prefix: Sequence[torch.Tensor],
                 v_prefix: Sequence[torch.Tensor], seq_base_dev: torch.Tensor, head_stride: int, max_prefix: int,
@@ -393,13 +396,9 @@ def commit_path(view: MaskView, dtype: int, B: int, H: int, d: int, k_tree: Sequ
                 new_tokens: Optional[torch.Tensor], n_new: int, n_append: int, prefix_lens_dev: torch.Tensor,
                 out_ids: torch.Tensor, out_n_ids: torch.Tensor, stream=None) -> None:
     """One call for all layers: k_tree / v_tree / k_prefix / v_prefix are per-layer lists of device tensors."""
-    n_layers = len(k_tree)
-    assert len(v_tree) == len(k_prefix) == len(v_prefix) == n_layers
-    st = lib.mcsd_commit_path(C.byref(view), dtype, B, H, d, n_layers, _ptr_array(k_tree), _ptr_array(v_tree),
-                              node_stride, _ptr_array(k_prefix), _ptr_array(v_prefix), _ptr(seq_base_dev), head_stride,
-                              max_prefix, capacity, _ptr(out_path), _ptr(accept_len), _ptr(tokens), _ptr(new_tokens),
-                              n_new, n_append, _ptr(prefix_lens_dev), _ptr(out_ids), _ptr(out_n_ids), _stream(stream))
-    _check(st, "mcsd_commit_path")
+    _pycall.commit_path(view, dtype, B, H, d, k_tree, v_tree, node_stride, k_prefix, v_prefix, seq_base_dev, head_stride,
+                        max_prefix, capacity, out_path, accept_len, tokens, new_tokens, n_new, n_append, prefix_lens_dev, out_ids,
+                        out_n_ids, stream)
 
 
 def make_mlp(weights: Sequence[torch.Tensor], biases: Sequence[torch.Tensor]) -> Mlp:
@@ -421,15 +420,12 @@ def make_mlp(weights: Sequence[torch.Tensor], biases: Sequence[torch.Tensor]) ->
 def early_stop_distribution(mlp: Mlp, B: int, W: int, V: int, k: int, draft_rows: torch.Tensor, batch_stride: int,
                             row_stride: int, beta: float, features: Optional[torch.Tensor], prob: torch.Tensor,
                             stop: torch.Tensor, stream=None) -> None:
-    _check(lib.mcsd_early_stop_distribution(C.byref(mlp), B, W, V, k, _ptr(draft_rows), batch_stride, row_stride,
-                                            beta, _ptr(features), _ptr(prob), _ptr(stop), _stream(stream)),
-           "mcsd_early_stop_distribution")
+    _pycall.early_stop_distribution(mlp, B, W, V, k, draft_rows, batch_stride, row_stride, beta, features, prob, stop, stream)
 
 
 def early_stop_hidden(mlp: Mlp, B: int, W: int, hidden: torch.Tensor, batch_stride: int, row_stride: int,
                       beta: float, prob: torch.Tensor, stop: torch.Tensor, stream=None) -> None:
-    _check(lib.mcsd_early_stop_hidden(C.byref(mlp), B, W, _ptr(hidden), batch_stride, row_stride, beta, _ptr(prob),
-                                      _ptr(stop), _stream(stream)), "mcsd_early_stop_hidden")
+    _pycall.early_stop_hidden(mlp, B, W, hidden, batch_stride, row_stride, beta, prob, stop, stream)
 
 
 def stream_read(src: torch.Tensor, sink: torch.Tensor, workgroups: int = 0, stream=None) -> None:

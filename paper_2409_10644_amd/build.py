@@ -1,14 +1,16 @@
-"""Builds libmcsd.so (HIP, gfx950) in-tree with hipcc.  Run as `python -m paper_2409_10644_amd.build`."""
+"""Builds libmcsd.so (HIP, gfx950) and _pycall.so (host) in-tree.  Run as `python -m paper_2409_10644_amd.build`."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmcsd.so")
+PYCALL = os.path.join(HERE, "_pycall.so")           # CPython marshalling of the hot entry points (host code only)
 OBJ = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -43,6 +45,11 @@ def build_library(verbose: bool = False) -> str:
         if verbose and out.strip():
             print(out)
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
+    subprocess.run(cmd, check=True)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "pycall.cpp"), "-o", PYCALL]
+    if verbose:
+        print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     return LIB
 
