@@ -16,7 +16,7 @@
 // last folds at the end of the same kernel (a small second kernel when the splits do not share one die's L2).
 // The tree's own keys are extra tiles whose scores are masked with the packed bitmask slice.
 //
-// fp32 path: split / online-softmax structure on the vector ALU (small reference-precision shapes).
+// fp32 path: the same operation on the fp32 matrix instructions, see tree_attn_f32_kernel.
 #include <math.h>
 #include <stdlib.h>
 
@@ -53,6 +53,7 @@ struct AttnParams {
     int32_t tree_last; // 1 (no separate tree workgroup, no pairing): the last split that has keys takes the tree's keys, else split 0
     unsigned long long *ctr;   // fold == 1: arrival counter of unit u at ctr[u * CTR_STRIDE], zero before and after every launch
     const uint32_t *ws_tag;    // fold == 1: first word of the workspace, WS_TAG once prepared
+    int32_t QT;       // fp32 path: tiles of 16 query rows
     int32_t row0;     // first query row: rows row0 .. n-1 are computed (keys are always all n tree nodes)
     int32_t max_prefix;
     int64_t node_stride, head_stride;
@@ -81,6 +82,7 @@ struct AttnPlan {
     int units;             // workgroup units per sequence: kv heads x chunks (bf16), query heads (fp32)
     int QBP;   // query blocks of 32 rows, rounded up to 1, 2 or 4 (bf16 path)
     int T;     // keys per tile
+    int QT;    // tiles of 16 query rows (fp32 path), 1 on the bf16 path
     int S;     // key splits of the prefix
     int G;     // workgroups per (b,h): S, or S + 1 when the bf16 sweep gives the tree's own keys a workgroup of their own
     int NS;    // LDS stages of the bf16 sweep
@@ -111,7 +113,7 @@ void device_shape(int &n_cus, int &n_xcc)
     n_xcc = mcsd_xcc_count(dev);
 }
 
-AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int n_rows, int max_prefix, bool f8 = false,
+AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int d, int n_rows, int max_prefix, bool f8 = false,
                    const mcsd_attention_tuning_t *tune = nullptr)
 {
     AttnPlan pl;
@@ -130,24 +132,33 @@ AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int n_rows, int max_prefix
         pl.chunks = grp / pl.hpw;
         pl.units = Hkv * pl.chunks;
         pl.T = tile_keys_bf16(pl.QBP);
+        pl.QT = 1;
     } else {
         pl.bph = pl.hpw = 1;
         pl.chunks = grp;
         pl.units = Hq;
         pl.QBP = 1;
-        pl.T = 32;
+        pl.T = 16;
+        pl.QT = (n_rows + 15) / 16;
     }
     const long bh = (long)B * pl.units;
-    const long tiles_max = (max_prefix + pl.T - 1) / pl.T;
+    long tiles_max = (max_prefix + pl.T - 1) / pl.T;
+    if (dtype == MCSD_F32) tiles_max += (n_rows + pl.T - 1) / pl.T;      // (the tree's own keys are blocks like the prefix's)
     // Key splits: enough workgroups for two per compute unit, at least four tiles per split (two of the 128-key
     // tiles of a single query block: the same bytes), at most 8 splits (6 with four query blocks, whose partial result
     // is twice the bytes: six splits and the tree's workgroup are what the seven-slot fold takes in one pass): every
     // split costs a partial result of n rows that is written, read back and folded.  Measured: one query block, 1024
     // keys: 14.3 -> 11.3 us per call with four splits instead of two; four query blocks, 1024 keys: 15.2 -> 13.2 us
     // with four instead of three; 2048 keys: 16.9 us with six, 17.8 us with seven.
+    // fp32: one workgroup per compute unit while that takes splitting (more only add partial results: 12 heads of 64, 1024
+    // keys, 60 nodes: 9.2 us with 192 workgroups, 10.4 with 384), else as many as fit (4 per compute unit at d = 64, 2 at
+    // 128), which evens out ragged batches; at least five 16-key blocks per split.
     long S = (512 + bh - 1) / bh;
-    // (the vector-ALU path is slow per tile: split it all the way)
-    const long min_tiles = dtype == MCSD_BF16 ? (pl.QBP == 1 ? 2 : 4) : 1;
+    if (dtype == MCSD_F32) {
+        const long u = (bh + 7) / 8 * 8 * pl.QT;            // (a die's slots are whole (sequence, head) pairs, see grid_units)
+        S = u <= 256 ? 256 / u : (d == 64 ? (1023 + u) / u : 512 / u);
+    }
+    const long min_tiles = dtype == MCSD_BF16 ? (pl.QBP == 1 ? 2 : 4) : 5;
     if (S > tiles_max / min_tiles) S = tiles_max / min_tiles;
     if (dtype == MCSD_BF16 && S > (pl.QBP == 4 ? 6 : 8)) S = pl.QBP == 4 ? 6 : 8;
     if (S < 1) S = 1;
@@ -192,12 +203,12 @@ AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int n_rows, int max_prefix
     bool same_die = n_xcc == 1;
     if (n_xcc > 1 && pl.pair_cus == 0) {
         same_die = true;
-        if (dtype == MCSD_BF16 && pl.S > 1) pl.grid_units = (bh + n_xcc - 1) / n_xcc * n_xcc;
+        if (pl.S > 1 || pl.QT > 1) pl.grid_units = (bh + n_xcc - 1) / n_xcc * n_xcc;
         else same_die = bh % n_xcc == 0;
     }
     if (pl.pair_cus > 0) same_die = n_xcc == 1 || (n_xcc > 1 && pl.units % n_xcc == 0 && pl.pair_cus % n_xcc == 0);
-    pl.fold = dtype == MCSD_BF16 && pl.S > 1 && same_die && pl.G <= FOLD_MAX_PARTIALS &&
-              (size_t)bh * CTR_STRIDE * sizeof(unsigned long long) <= WS_CTR_BYTES && !(tune && tune->fold == 1);
+    pl.fold = pl.S > 1 && same_die && (dtype == MCSD_F32 || pl.G <= FOLD_MAX_PARTIALS) &&
+              (size_t)bh * pl.QT * CTR_STRIDE * sizeof(unsigned long long) <= WS_CTR_BYTES && !(tune && tune->fold == 1);
     return pl;
 }
 
@@ -1109,198 +1120,322 @@ __global__ __launch_bounds__(256) void tree_attn_merge_bf16_kernel(const AttnPar
 }
 
 // ---------------------------------------------------------------------------------------------------
-// fp32 / vector-ALU kernel (reference-precision shapes)
+// fp32 / MFMA kernel
 // ---------------------------------------------------------------------------------------------------
+// One workgroup of 4 wavefronts owns one (sequence, head, tile of 16 query rows, key split); its wavefronts take the split's
+// 16-key blocks in turn and never meet before the end.  v_mfma_f32_16x16x4_f32 is fp32 in and out with fused multiply-adds,
+// at twice the vector ALU's rate.  As in the bf16 sweep scores are computed transposed, so a lane holds 4 keys of one query
+// and the exponentials are the B operand of O^T += V^T P^T as they stand.  Nothing of K or V is shared between
+// wavefronts, so neither goes through LDS: the contraction's column order and the output's row order are chosen such that
+// a lane's operands are 16-byte pieces of rows (K: columns 16 t + 4 g ..; V: columns i D/16 .., whole rows per 16 lanes),
+// loaded one block ahead.  The query tiles of a (sequence, head) read the same keys at about the same time from one die's
+// L2; cutting the queries instead of the keys leaves few partial results to fold (16 rows each).
+// Bound: 16 KB per wavefront in flight against the latency of the memory system (about 30 GB/s per compute unit); at 120
+// nodes x 1000 keys x 64 heads the matrix cores are 43 % busy.  Measured against the vector ALU kernel and its fold kernel
+// that this replaced, us per call: 14 nodes, 4 heads of 64, 128 keys 19.0 -> 6.0; 81 nodes, 2 x 16 heads of 128, 329 keys
+// 459 -> 17; 80 nodes, 2 x 8 heads of 64, 1205 keys 150 -> 12; 82 nodes, 6 x 32 heads of 128, 120 keys 803 -> 40.
+constexpr int F32_ROWS = 16, F32_KEYS = 16;
+
 template <int D>
-__global__ __launch_bounds__(256) void tree_attn_f32_kernel(const AttnParams p)
+struct F32Block {
+    f32x4_t k[D / 16];          // K[key i][16 t + 4 g ..], i = lane % 16, g = lane / 16
+    f32x4_t v[4][D / 64];       // V[key 4 g + r][i D/16 + 4 j ..]
+};
+
+// Maximum / sum over the four lanes that hold one query (lanes i, i + 16, i + 32, i + 48).
+__device__ inline float quarter_max(float v)
 {
-    constexpr int T = 32;
-    constexpr int NMAX = MCSD_ATTN_MAX_NODES;
-    constexpr int RP = 256 / D;          // output rows per pass
-    constexpr int NR = NMAX / RP;        // output rows per thread
-    __shared__ float sQ[NMAX][D + 1];
-    __shared__ float sK[T][D + 1];
-    __shared__ float sV[T][D];
-    __shared__ float sS[NMAX][T + 1];
-    __shared__ float sAlpha[NMAX];
-    __shared__ float sL[NMAX];
-    __shared__ float sM[NMAX];
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return half_swap_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ inline float quarter_sum(float v)
+{
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return half_swap_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
 
-    const int s = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x;
-    int L = p.lens[b];
-    L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
-    const int tiles_b = (L + T - 1) / T;
-    const int tps = (tiles_b + p.S - 1) / p.S;
-    const int t0 = min(s * tps, tiles_b), t1 = min(t0 + tps, tiles_b);
-    const int n_tree_tiles = s == 0 ? (p.n + T - 1) / T : 0;
-    const int n_pre = t1 - t0;
-    const int n_iter = n_pre + n_tree_tiles;
-    if (n_iter == 0) return;
-
-    const int64_t bh = (int64_t)b * p.H + h;                 // query head
-    const int kvh = h / p.grp;
-    const int64_t bh_kv = (int64_t)b * p.Hkv + kvh;
-    const float *q = (const float *)p.q + bh * p.node_stride * D;
-    const float *kt = (const float *)p.kt + bh_kv * p.node_stride * D;
-    const float *vt = (const float *)p.vt + bh_kv * p.node_stride * D;
-    const int64_t pre0 = p.seq_base[b] + (int64_t)kvh * p.head_stride;
-    const float *kp = (const float *)p.kp + pre0;
-    const float *vp = (const float *)p.vp + pre0;
-
-    for (int idx = p.row0 * D + tid; idx < p.n * D; idx += 256) sQ[idx / D][idx % D] = q[idx];   // rows below row0 are not read
-    if (tid < NMAX) { sM[tid] = -INFINITY; sL[tid] = 0.f; }     // running maximum / denominator of every row
-    float acc[NR];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) acc[r] = 0.f;
-    const int oc = tid % D, oi0 = tid / D;
-
-    for (int it = 0; it < n_iter; ++it) {
-        const float *ksrc, *vsrc;
-        int valid, tree_col0 = -1;
-        if (it < n_pre) {
-            const int t = t0 + it;
-            ksrc = kp + (int64_t)t * T * D;
-            vsrc = vp + (int64_t)t * T * D;
-            valid = min(T, L - t * T);
-        } else {
-            const int tt = it - n_pre;
-            ksrc = kt + (int64_t)tt * T * D;
-            vsrc = vt + (int64_t)tt * T * D;
-            valid = min(T, p.n - tt * T);
-            tree_col0 = tt * T;
-        }
-        __syncthreads();
-        for (int idx = tid; idx < T * D; idx += 256) {
-            const int row = idx / D, col = idx % D;
-            const bool ok = row < valid;
-            sK[row][col] = ok ? ksrc[idx] : 0.f;
-            sV[row][col] = ok ? vsrc[idx] : 0.f;
-        }
-        __syncthreads();
-        {   // scores and online soft-max: the 32 lanes of a half wavefront own one row at a time, one key each
-            const int j = tid % T, i0 = tid / T;
-            for (int i = p.row0 + i0; i < p.n; i += 256 / T) {
-                float dot = 0.f;
-#pragma unroll 8
-                for (int cc = 0; cc < D; ++cc) dot = fmaf(sQ[i][cc], sK[j][cc], dot);
-                bool vis = j < valid;
-                if (tree_col0 >= 0) {
-                    const int col = tree_col0 + j;
-                    vis = vis && ((p.mask_bits[(int64_t)i * p.mask_words + (col >> 6)] >> (col & 63)) & 1ull);
-                }
-                const float sc = vis ? dot : -INFINITY;
-                float mx = sc;
-#pragma unroll
-                for (int m = 1; m < T; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-                const float m_old = sM[i];
-                const float m_new = fmaxf(m_old, mx);
-                const float mc = (m_new == -INFINITY ? 0.f : m_new) * p.c;
-                const float pv = exp2f(fmaf(sc, p.c, -mc));
-                float psum = pv;
-#pragma unroll
-                for (int m = 1; m < T; m <<= 1) psum += __shfl_xor(psum, m, 64);
-                sS[i][j] = pv;
-                if (j == 0) {
-                    const float alpha = exp2f(fmaf(m_old, p.c, -mc));
-                    sAlpha[i] = alpha;
-                    sL[i] = sL[i] * alpha + psum;
-                    sM[i] = m_new;
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int i = oi0 + RP * r;
-            if (i >= p.row0 && i < p.n) {
-                float a = acc[r] * sAlpha[i];
-#pragma unroll 8
-                for (int j = 0; j < T; ++j) a = fmaf(sS[i][j], sV[j][oc], a);
-                acc[r] = a;
-            }
-        }
+// Keys of one (sequence, head) in 16-key blocks: the prefix's, then the tree's.  Split s owns blocks s * bps ..
+struct F32Keys {
+    int L, n_pre, n_blk, bps, n_active;
+    __device__ F32Keys(const AttnParams &p, int b)
+    {
+        L = p.lens[b];
+        L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
+        n_pre = (L + F32_KEYS - 1) / F32_KEYS;
+        n_blk = n_pre + (p.n + F32_KEYS - 1) / F32_KEYS;
+        bps = (n_blk + p.S - 1) / p.S;
+        n_active = (n_blk + bps - 1) / bps;              // splits that have keys
     }
-    __syncthreads();
-    if (p.SP == 1) {
-        float *o = (float *)p.out + bh * p.node_stride * D;
+};
+
+// Output columns of lane (i, g)'s accumulators [e]: (4 g + e) D/16 .. + D/16 - 1, of query i.  acc[e] / den to out or NaN.
+template <int D>
+__device__ inline void f32_store(float *out, const float (&acc)[D / 16], float scale)
+{
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int i = oi0 + RP * r;
-            if (i >= p.row0 && i < p.n) o[(int64_t)i * D + oc] = acc[r] / sL[i];
-        }
-    } else {
-        const int64_t prow0 = (bh * p.SP + s) * p.n;
+    for (int j = 0; j < D / 64; ++j) {
+        f32x4_t v;
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int i = oi0 + RP * r;
-            if (i >= p.row0 && i < p.n) p.part_o[(prow0 + i) * D + oc] = acc[r];
+        for (int e = 0; e < 4; ++e) v[e] = acc[4 * j + e] * scale;
+        *(f32x4_t *)(out + 4 * j) = v;
+    }
+}
+
+// Folds the partial results of one query tile for output rows e of the accumulators: out += all splits in order.  A partial
+// is [e][lane][D/16] floats, its maxima and denominators 16 + 16 floats of a 128-byte line of their own.  THROUGH_L2: read
+// past the L1 (written by other workgroups of this launch, see the end of the bf16 sweep).
+template <int D, bool THROUGH_L2>
+__device__ inline void f32_fold(const float *po, const float *pml, int n_active, int e, int lane, float c, float (&acc)[D / 16], float &den)
+{
+    constexpr int W = D / 16, PART = 4 * 64 * W;
+    const int i = lane & 15;
+    const auto ro = __builtin_amdgcn_make_buffer_rsrc((void *)po, 0, n_active * PART * 4, 0x00027000);
+    const auto rm = __builtin_amdgcn_make_buffer_rsrc((void *)pml, 0, n_active * 128, 0x00027000);
+    constexpr int AUX = THROUGH_L2 ? 1 : 0;
+    float M = -INFINITY;
+    den = 0.f;
+#pragma unroll
+    for (int k = 0; k < W; ++k) acc[k] = 0.f;
+    constexpr int R = 4;                                     // partial results in flight; beyond the last one loads return zero
+    for (int s0 = 0; s0 < n_active; s0 += R) {
+        float m[R], l[R];
+        f32x4_t o[R][D / 64];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            m[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, (s0 + r) * 128 + i * 4, 0, AUX));
+            l[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, (s0 + r) * 128 + 64 + i * 4, 0, AUX));
+#pragma unroll
+            for (int j = 0; j < D / 64; ++j)
+                o[r][j] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(ro, (((s0 + r) * 4 + e) * 64 + lane) * W * 4 + j * 16, 0, AUX));
         }
-        if (tid >= p.row0 && tid < p.n) {
-            p.part_m[prow0 + tid] = sM[tid];
-            p.part_l[prow0 + tid] = sL[tid];
+        float Mn = M;
+#pragma unroll
+        for (int r = 0; r < R; ++r) Mn = fmaxf(Mn, s0 + r < n_active ? m[r] : -INFINITY);
+        if (Mn == -INFINITY) continue;                       // (per query) nothing visible so far
+        const float a = fast_exp2((M - Mn) * c);             // exp2(-inf) = 0 in the first round
+        M = Mn;
+        den *= a;
+#pragma unroll
+        for (int k = 0; k < W; ++k) acc[k] *= a;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float w = s0 + r < n_active ? fast_exp2((m[r] - M) * c) : 0.f;
+            den = fmaf(w, l[r], den);
+#pragma unroll
+            for (int k = 0; k < W; ++k) acc[k] = fmaf(w, o[r][k / 4][k % 4], acc[k]);
         }
     }
 }
 
-// ---------------------------------------------------------------------------------------------------
-// merge of the split partials:  out = sum_sp w_sp O_sp / sum_sp w_sp l_sp,  w_sp = exp2((m_sp - max m) c)
-// ---------------------------------------------------------------------------------------------------
-template <int D, bool OUT_BF16>
-__global__ __launch_bounds__(256) void tree_attn_merge_kernel(const AttnParams p, int T, int KG)
+template <int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void tree_attn_f32_kernel(const AttnParams p)
 {
-    constexpr int TPR = D / 4;            // threads per output row (4 columns each)
-    constexpr int ROWS = 256 / TPR;       // rows per workgroup
-    const int h = blockIdx.y, b = blockIdx.z;
-    const int i = blockIdx.x * ROWS + threadIdx.x / TPR, c4 = (threadIdx.x % TPR) * 4;
-    if (i >= p.n || i < p.row0) return;
-    const int64_t bh = (int64_t)b * p.H + h;
-    int L = p.lens[b];
-    L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
-    const int tiles_b = (L + T - 1) / T;
-    const int tps = (tiles_b + p.S - 1) / p.S;
-    // split s ran iff it had prefix tiles, or it is split 0 (which owns the tree tiles)
-    const int n_active = tps > 0 ? min(p.S, (tiles_b + tps - 1) / tps) : 1;
-    const int sp_active = max(n_active, 1) * KG;
-    const int64_t row0 = bh * p.SP * p.n + i;          // partial sp of this row is at row0 + sp * n
-    float M = -INFINITY;
-    for (int sp = 0; sp < sp_active; ++sp) M = fmaxf(M, p.part_m[row0 + (int64_t)sp * p.n]);
-    float den = 0.f;
-    f32x4_t num = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int sp = 0; sp < sp_active; ++sp) {
-        const int64_t prow = row0 + (int64_t)sp * p.n;
-        const float w = exp2f((p.part_m[prow] - M) * p.c);     // exp2(-inf) = 0 for partials that saw no key
-        const f32x4_t o = *(const f32x4_t *)(p.part_o + prow * D + c4);
-        den = fmaf(w, p.part_l[prow], den);
-        num += w * o;
-    }
-    const f32x4_t r = num / den;
-    const int64_t off = (bh * p.node_stride + i) * D + c4;
-    if (OUT_BF16) {
-        bf16x4_t v;
+    constexpr int W = D / 16, KT = D / 16, PART = 4 * 64 * W;
+    __shared__ __attribute__((aligned(16))) float s_o[4][4][64][W];      // [wavefront][e][lane][column]
+    __shared__ float s_m[4][16], s_l[4][16];
+    // ids are dealt round-robin to the dies: the workgroups of one (sequence, head) share one
+    const int total = gridDim.x;
+    int wg = blockIdx.x;
+    if (p.xcc > 1 && total % p.xcc == 0) wg = (wg % p.xcc) * (total / p.xcc) + wg / p.xcc;
+    const int tile = wg % p.QT, s = (wg / p.QT) % p.S, bhi = wg / (p.QT * p.S);
+    if (bhi >= p.B * p.H) return;                            // a slot of a grid rounded up to whole dies
+    const int h = bhi % p.H, b = bhi / p.H;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, g = lane >> 4;
+    const int64_t bh = bhi;
+    const int kvh = h / p.grp;
+    const int qrow = p.row0 + tile * F32_ROWS + i;
+    const bool mine = qrow < p.n;
+
+    // query tile, as B operands: Q[query i][16 t + 4 g ..]; rows beyond the tree repeat the first one and are never stored
+    f32x4_t q[KT];
+    const float *qp = (const float *)p.q + (bh * p.node_stride + (mine ? qrow : p.row0)) * D + 4 * g;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (__bf16)r[e];
-        *(bf16x4_t *)((__bf16 *)p.out + off) = v;
-    } else {
-        *(f32x4_t *)((float *)p.out + off) = r;
+    for (int t = 0; t < KT; ++t) q[t] = *(const f32x4_t *)(qp + 16 * t);
+    uint64_t mrow[2] = {0, 0};
+    {
+        const uint64_t *mb = p.mask_bits + (int64_t)(mine ? qrow : p.row0) * p.mask_words;
+        mrow[0] = mb[0];
+        if (p.mask_words > 1) mrow[1] = mb[1];
     }
+    const F32Keys ks(p, b);
+    const int blk0 = s * ks.bps, blk1 = min(blk0 + ks.bps, ks.n_blk);
+    if (blk0 >= blk1) return;                                // this split has no keys
+    const uint32_t ws_tag = p.fold ? p.ws_tag[0] : WS_TAG;
+    const int64_t pre0 = p.seq_base[b] + (int64_t)kvh * p.head_stride, tree0 = ((int64_t)b * p.Hkv + kvh) * p.node_stride * D;
+    const float *kp = (const float *)p.kp + pre0, *vp = (const float *)p.vp + pre0;
+    const float *kt = (const float *)p.kt + tree0, *vt = (const float *)p.vt + tree0;
+
+    f32x4_t o[W];                                            // O^T: [cb], rows 4 g + e are columns (4 g + e) W + cb
+#pragma unroll
+    for (int cb = 0; cb < W; ++cb) o[cb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    float m_ref = -INFINITY, l_run = 0.f;
+
+    auto load = [&](F32Block<D> &x, int blk) {
+        const bool pre = blk < ks.n_pre;                     // (uniform)
+        const int key0 = (pre ? blk : blk - ks.n_pre) * F32_KEYS, last = (pre ? ks.L : p.n) - 1;
+        const float *kb = pre ? kp : kt, *vb = pre ? vp : vt;
+        const float *kr = kb + (int64_t)min(key0 + i, last) * D + 4 * g;      // keys beyond the last repeat it, masked below
+#pragma unroll
+        for (int t = 0; t < KT; ++t) x.k[t] = *(const f32x4_t *)(kr + 16 * t);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < D / 64; ++j) x.v[r][j] = *(const f32x4_t *)(vb + (int64_t)min(key0 + 4 * g + r, last) * D + i * W + 4 * j);
+    };
+    auto compute = [&](const F32Block<D> &x, int blk) {
+        f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[t][e], q[t][e], sc, 0, 0, 0);
+        const bool pre = blk < ks.n_pre;
+        const int key0 = (pre ? blk : blk - ks.n_pre) * F32_KEYS;
+        if (!pre || key0 + F32_KEYS > ks.L) {                // (uniform) bit k: key k of the block is visible to this lane's query
+            const int left = ks.L - key0;
+            const uint32_t bits = pre ? (1u << left) - 1u : (uint32_t)((key0 >> 6 ? mrow[1] : mrow[0]) >> (key0 & 63));
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (!((bits >> (4 * g + r)) & 1u)) sc[r] = -INFINITY;
+        }
+        const float mx = quarter_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+        // the accumulators are rescaled only when the maximum outgrows the reference by more than the slack (exact either way)
+        const bool grow = (mx - m_ref) * p.c > RESCALE_SLACK;
+        if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+            const float m_new = grow ? mx : m_ref;
+            const float alpha = m_new == m_ref ? 1.f : exp2f((m_ref - m_new) * p.c);
+            m_ref = m_new;
+            l_run *= alpha;
+#pragma unroll
+            for (int cb = 0; cb < W; ++cb) o[cb] *= alpha;
+        }
+        const float mc = (m_ref == -INFINITY ? 0.f : m_ref) * p.c;
+        float pr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            pr[r] = exp2f(fmaf(sc[r], p.c, -mc));
+            l_run += pr[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int cb = 0; cb < W; ++cb) o[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[r][cb / 4][cb % 4], pr[r], o[cb], 0, 0, 0);
+    };
+    {
+        // this wavefront's blocks: every fourth one; the next is loaded while one is computed (a load beyond the last repeats it)
+        F32Block<D> x0, x1;
+        int blk = blk0 + wave;
+        if (blk < blk1) {
+            load(x0, blk);
+            while (true) {
+                load(x1, min(blk + 4, blk1 - 1));
+                __builtin_amdgcn_sched_barrier(0);
+                compute(x0, blk);
+                blk += 4;
+                if (blk >= blk1) break;
+                load(x0, min(blk + 4, blk1 - 1));
+                __builtin_amdgcn_sched_barrier(0);
+                compute(x1, blk);
+                blk += 4;
+                if (blk >= blk1) break;
+            }
+        }
+    }
+
+    // ---- merge the four wavefronts: each adds up one accumulator row e of all of them ----
+    const float l_tot = quarter_sum(l_run);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < W / 4; ++j)
+            *(f32x4_t *)&s_o[wave][e][lane][4 * j] = (f32x4_t){o[4 * j][e], o[4 * j + 1][e], o[4 * j + 2][e], o[4 * j + 3][e]};
+    if (g == 0) { s_m[wave][i] = m_ref; s_l[wave][i] = l_tot; }
+    __syncthreads();
+    float acc[W], M = -INFINITY, den = 0.f;
+#pragma unroll
+    for (int k = 0; k < W; ++k) acc[k] = 0.f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) M = fmaxf(M, s_m[v][i]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const float w = M == -INFINITY ? 0.f : exp2f((s_m[v][i] - M) * p.c);
+        den = fmaf(w, s_l[v][i], den);
+#pragma unroll
+        for (int k = 0; k < W; ++k) acc[k] = fmaf(w, s_o[v][wave][lane][k], acc[k]);
+    }
+    float *out = (float *)p.out + (bh * p.node_stride + qrow) * D + (4 * g + wave) * W;
+    if (ks.n_active == 1) {                                  // the only split of this sequence: no exchange needed
+        if (mine) f32_store<D>(out, acc, 1.f / den);
+        return;
+    }
+
+    // ---- key splits: partial results in fragment order; the workgroup that arrives last folds (protocol: bf16 sweep) ----
+    const int64_t unit = bh * p.QT + tile;
+    f32_store<D>(p.part_o + ((unit * p.S + s) * 4 + wave) * 64 * W + lane * W, acc, 1.f);
+    float *ml = p.part_m + (unit * p.S + s) * 32;
+    if (wave == 0 && g == 0) { ml[i] = M; ml[16 + i] = den; }
+    if (!p.fold) return;                                     // a second kernel folds
+    const float nan[4] = {__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+    auto store_nan = [&]() {
+        if (!mine) return;
+#pragma unroll
+        for (int j = 0; j < W / 4; ++j) f32_store<64>(out + 4 * j, nan, 1.f);
+    };
+    if (ws_tag != WS_TAG) {                                  // workspace never prepared: its counters mean nothing
+        store_nan();
+        return;
+    }
+    __shared__ unsigned long long s_prev;
+    unsigned die;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(die));
+    die &= 7u;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wavefront's partial result has reached the L2
+    __syncthreads();
+    if (tid == 0)
+        s_prev = __hip_atomic_fetch_add(p.ctr + unit * CTR_STRIDE, 1ull + (1ull << (8 + 7 * die)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const unsigned long long prev = s_prev;
+    if ((int)(prev & 0xffu) + 1 != ks.n_active) return;      // someone else arrives later
+    if (tid == 0) __hip_atomic_store(p.ctr + unit * CTR_STRIDE, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // as it was found
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    if ((int)((prev >> (8 + 7 * die)) & 0x7fu) + 1 != ks.n_active) {         // an arrival from another die
+        store_nan();
+        return;
+    }
+    f32_fold<D, true>(p.part_o + unit * p.S * PART, p.part_m + unit * p.S * 32, ks.n_active, wave, lane, p.c, acc, den);
+    if (mine) f32_store<D>(out, acc, 1.f / den);
+}
+
+// The same fold as a kernel of its own, for splits that do not share one die's L2: a workgroup per query tile.
+template <int D>
+__global__ __launch_bounds__(256) void tree_attn_merge_f32_kernel(const AttnParams p)
+{
+    constexpr int W = D / 16, PART = 4 * 64 * W;
+    const int64_t unit = blockIdx.x, bh = unit / p.QT;
+    const int tile = (int)(unit % p.QT), b = (int)(bh / p.H);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const F32Keys ks(p, b);
+    if (ks.n_active == 1) return;                            // the sweep wrote this sequence's output itself
+    const int qrow = p.row0 + tile * F32_ROWS + (lane & 15);
+    float acc[W], den;
+    f32_fold<D, false>(p.part_o + unit * p.S * PART, p.part_m + unit * p.S * 32, ks.n_active, wave, lane, p.c, acc, den);
+    if (qrow < p.n) f32_store<D>((float *)p.out + (bh * p.node_stride + qrow) * D + (4 * (lane >> 4) + wave) * W, acc, 1.f / den);
 }
 
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // workspace: [tag] [counters] [part_m] [part_l] [part_o]; nothing when the keys are not split
-size_t partial_rows(const AttnPlan &pl, int dtype, int B, int n)
+size_t partial_rows(const AttnPlan &pl, int dtype, int B)
 {
-    // per workgroup unit and split; bf16 path: whole 32-row query blocks in register-fragment order; fp32 path: n rows
-    return (size_t)B * pl.units * pl.G * (dtype == MCSD_BF16 ? (size_t)pl.QBP * 32 : (size_t)n);
+    // per workgroup unit and split; whole query blocks of 32 (bf16) or 16 (fp32) rows, in register-fragment order
+    return (size_t)B * pl.units * pl.G * (dtype == MCSD_BF16 ? (size_t)pl.QBP * 32 : (size_t)pl.QT * F32_ROWS);
 }
 
-size_t workspace_bytes_for(const AttnPlan &pl, int dtype, int B, int d, int n)
+size_t workspace_bytes_for(const AttnPlan &pl, int dtype, int B, int d)
 {
     if (pl.S == 1) return 0;
-    const size_t rows = partial_rows(pl, dtype, B, n);
+    const size_t rows = partial_rows(pl, dtype, B);
     return WS_HEADER + WS_CTR_BYTES + 2 * align256(rows * sizeof(float)) + align256(rows * d * (dtype == MCSD_BF16 ? 2 : sizeof(float)));
 }
 
@@ -1356,11 +1491,10 @@ hipError_t launch_fp8kv(const AttnParams &p, const AttnPlan &pl, hipStream_t st)
 template <int D>
 hipError_t launch_f32(const AttnParams &p, const AttnPlan &pl, hipStream_t st)
 {
-    dim3 grid(pl.S, p.H, p.B), block(256);
-    mcsd_launch(MCSD_KERNEL_ATTN_SWEEP, tree_attn_f32_kernel<D>, grid, block, st, p);
+    mcsd_launch(MCSD_KERNEL_ATTN_SWEEP, tree_attn_f32_kernel<D>, dim3((unsigned)((size_t)pl.S * pl.QT * pl.grid_units)), dim3(256), st, p);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || pl.S == 1) return e;
-    mcsd_launch(MCSD_KERNEL_ATTN_MERGE, tree_attn_merge_kernel<D, false>, dim3((p.n + 1024 / D - 1) / (1024 / D), p.H, p.B), block, st, p, pl.T, 1);
+    if (e != hipSuccess || pl.S == 1 || pl.fold) return e;
+    mcsd_launch(MCSD_KERNEL_ATTN_MERGE, tree_attn_merge_f32_kernel<D>, dim3((unsigned)((size_t)p.B * p.H * pl.QT)), dim3(256), st, p);
     return hipGetLastError();
 }
 
@@ -1370,12 +1504,12 @@ size_t workspace_query(const mcsd_attention_tuning_t *tune, bool f8, int32_t B, 
     if (B < 1 || H_q < 1 || H_kv < 1 || H_q % H_kv != 0 || (d != 64 && d != 128) || n_nodes < 1 ||
         n_nodes > MCSD_ATTN_MAX_NODES || max_prefix < 0 || row_begin < 0 || row_begin >= n_nodes || (f8 && d != 128))
         return 0;
-    const AttnPlan a = make_plan(MCSD_BF16, B, H_q, H_kv, n_nodes - row_begin, max_prefix, f8, tune);
-    const size_t wa = workspace_bytes_for(a, MCSD_BF16, B, d, n_nodes);
+    const AttnPlan a = make_plan(MCSD_BF16, B, H_q, H_kv, d, n_nodes - row_begin, max_prefix, f8, tune);
+    const size_t wa = workspace_bytes_for(a, MCSD_BF16, B, d);
     if (f8) return wa;
     // the larger of the two dtypes' needs, so one buffer serves both
-    const AttnPlan f = make_plan(MCSD_F32, B, H_q, H_kv, n_nodes - row_begin, max_prefix, false, tune);
-    const size_t wf = workspace_bytes_for(f, MCSD_F32, B, d, n_nodes);
+    const AttnPlan f = make_plan(MCSD_F32, B, H_q, H_kv, d, n_nodes - row_begin, max_prefix, false, tune);
+    const size_t wf = workspace_bytes_for(f, MCSD_F32, B, d);
     return wa > wf ? wa : wf;
 }
 
@@ -1410,9 +1544,9 @@ int attention_call(const mcsd_attention_tuning_t *tune, const mcsd_mask_view_t *
     if (align & 15) return MCSD_EINVAL;
     if (((node_stride * d) & 7) || (head_stride & (f8 ? 15 : 7))) return MCSD_EINVAL;   // 16-byte rows and heads
 
-    const AttnPlan pl = make_plan(dtype, B, H_q, H_kv, n - row_begin, max_prefix, f8, tune);
-    if ((int64_t)pl.G * pl.grid_units > 0x7fffffff) return MCSD_EUNSUPPORTED;           // one-dimensional grid
-    const size_t need = workspace_bytes_for(pl, dtype, B, d, n);
+    const AttnPlan pl = make_plan(dtype, B, H_q, H_kv, d, n - row_begin, max_prefix, f8, tune);
+    if ((int64_t)pl.G * pl.QT * pl.grid_units > 0x7fffffff) return MCSD_EUNSUPPORTED;           // one-dimensional grid
+    const size_t need = workspace_bytes_for(pl, dtype, B, d);
     if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255))) return MCSD_EWORKSPACE;
 
     AttnParams p;
@@ -1425,7 +1559,7 @@ int attention_call(const mcsd_attention_tuning_t *tune, const mcsd_mask_view_t *
     p.c = softmax_scale * 1.4426950408889634f;
     p.k_scale = f8 ? k_scale : 1.f;
     p.v_scale = f8 ? v_scale : 1.f;
-    p.S = pl.S; p.G = pl.G; p.SP = pl.G;
+    p.S = pl.S; p.G = pl.G; p.SP = pl.G; p.QT = pl.QT;
     p.pair_cus = pl.pair_cus;
     p.tree_last = pl.tree_last;
     p.xcc = pl.xcc;
@@ -1437,7 +1571,7 @@ int attention_call(const mcsd_attention_tuning_t *tune, const mcsd_mask_view_t *
     p.ctr = nullptr;
     p.ws_tag = nullptr;
     if (pl.S > 1) {
-        const size_t rows = partial_rows(pl, dtype, B, n);
+        const size_t rows = partial_rows(pl, dtype, B);
         p.ws_tag = (const uint32_t *)w;
         p.ctr = (unsigned long long *)(w + WS_HEADER);
         w += WS_HEADER + WS_CTR_BYTES;
@@ -1506,8 +1640,8 @@ extern "C" int mcsd_tree_attention_static(const mcsd_mask_view_t *mask, mcsd_dty
                               v_prefix, seq_base_dev, prefix_lens_dev, head_stride, max_prefix, softmax_scale, out, nullptr,
                               0, hip_stream);          // (reports the argument error; nothing is launched)
     // the shape's need against the array's size, before anything is enqueued
-    const AttnPlan pl = make_plan(dtype, B, H, H, mask->n_nodes, max_prefix);
-    if (workspace_bytes_for(pl, dtype, B, d, mask->n_nodes) > (size_t)MCSD_STATIC_SCRATCH_BYTES) return MCSD_EUNSUPPORTED;
+    const AttnPlan pl = make_plan(dtype, B, H, H, d, mask->n_nodes, max_prefix);
+    if (workspace_bytes_for(pl, dtype, B, d) > (size_t)MCSD_STATIC_SCRATCH_BYTES) return MCSD_EUNSUPPORTED;
     void *ws = nullptr;
     const int rc = static_scratch((hipStream_t)hip_stream, &ws);
     if (rc != MCSD_OK) return rc;
@@ -1569,11 +1703,11 @@ extern "C" int mcsd_tree_attention_plan(const mcsd_attention_tuning_t *tuning, m
                    tuning->tree_keys < 0 || tuning->tree_keys > 3 ||
                    (tuning->stages != 0 && tuning->stages != 2 && tuning->stages != 4)))
         return MCSD_EINVAL;
-    const AttnPlan pl = make_plan(dtype, B, H_q, H_kv, n_nodes - row_begin, max_prefix, prefix_fp8 != 0, tuning);
+    const AttnPlan pl = make_plan(dtype, B, H_q, H_kv, d, n_nodes - row_begin, max_prefix, prefix_fp8 != 0, tuning);
     out->mfma_path = dtype == MCSD_BF16;
     out->query_blocks = pl.QBP;
     out->key_splits = pl.S;
-    out->workgroups = (int32_t)((int64_t)pl.G * (dtype == MCSD_BF16 ? pl.grid_units : (long)pl.units * B));
+    out->workgroups = (int32_t)((int64_t)pl.G * pl.QT * pl.grid_units);
     out->stages = dtype == MCSD_BF16 ? pl.NS : 0;
     out->fold_in_kernel = pl.fold;
     out->ordered_by_length = pl.pair_cus > 0;
