@@ -8,7 +8,7 @@
 //   decision_hidden_kernel        type 1: the MLP on the draft model's hidden states, four rows per workgroup
 //   early_stop_kernel             stop[b] = every sequence of tree b below the threshold
 //
-// Type 2 is bound by reading each 128 kB vocabulary row once; type 1 by streaming the first layer's weights through
+// Type 2 is bound by reading each 128 kB vocabulary row once; type 1 by streaming the layers' weights through
 // a compute unit.  Topk values are selected, not computed, so they are exact; the entropy uses the hardware fp32
 // logarithm with binary64 sums, the networks fp32 multiply-adds with tree-combined partial sums: the probabilities
 // stay within ~1e-6 of a binary64 evaluation.
@@ -349,110 +349,190 @@ __global__ __launch_bounds__(DT) void decision_distribution_kernel(MlpDesc mlp, 
 }
 
 // ---------------------------------------------------------------------------------------------- type 1
-// First layer on HROWS hidden states of at most 256 NC entries (a multiple of 4, rows and weights 16-byte aligned):
-// a lane keeps its slice of the four rows in registers (entries 4 lane + 256 c ..+3), a wavefront takes four output
-// units per step and streams their weights once for all four rows; fp32 multiply-adds, per-lane partial sums combined as a
-// balanced tree.  (A 768-wide row has 12 entries per lane: the products' rounding stays near 1e-7 of the sum.)
-template <int NC>
-__device__ __forceinline__ void hidden_first_layer(const float *const (&x)[HROWS], int n_in, const float *__restrict__ W,
-                                   const float *__restrict__ b, int n_out, float (*out)[MCSD_MLP_MAX_WIDTH], bool relu,
-                                   int tid)
-{
-    const int lane = tid & 63, wave = tid >> 6;
-    float4 xr[HROWS][NC];
-#pragma unroll
-    for (int r = 0; r < HROWS; ++r)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const int i = lane * 4 + c * 256;               // loads are unconditional from a valid address
-            const float4 t = *reinterpret_cast<const float4 *>(x[r] + min(i, n_in - 4));
-            xr[r][c] = i < n_in ? t : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        }
-    // JB output units per step; the next step's weights are requested before this step's arithmetic starts
-    constexpr int JB = 4;
-    auto load_weights = [&](float4 (&w)[JB][NC], int j0) {
-#pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-            const float *wr = W + (size_t)min(j0 + jj, n_out - 1) * n_in;       // past the end: a valid row, unused
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const int i = lane * 4 + c * 256;
-                w[jj][c] = *reinterpret_cast<const float4 *>(wr + min(i, n_in - 4));    // beyond n_in: times zero
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-            }
+// First output unit of group grp of four: the last group starts early enough to be whole (units done twice get the same
+// value twice); with fewer than four units the weight rows beyond the last repeat it.
+__device__ __forceinline__ int group_unit(int grp, int n_out) { return min(grp * 4, max(n_out - 4, 0)); }
+
+// Sums the accumulators of four output units over the 16 blocks (lanes of equal lane % 4: rotations by 8 and 4 inside a row
+// of 16, then across the rows); lane = row stores.  bias: lane e's is that of unit e (requested with the weights).
+__device__ __forceinline__ void mfma_finish(f32x4_t a, int j0, float bias, float (*out)[MCSD_MLP_MAX_WIDTH], bool relu, int lane)
+{
+    float v[4] = {a[0], a[1], a[2], a[3]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += dpp_f32<0x128>(v[e]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += dpp_f32<0x124>(v[e]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[e]), __float_as_uint(v[e]), false, false);
+        v[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[e]), __float_as_uint(v[e]), false, false);
+        v[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    v[0] += dpp_f32<0x00>(bias);                             // (quad broadcasts)
+    v[1] += dpp_f32<0x55>(bias);
+    v[2] += dpp_f32<0xAA>(bias);
+    v[3] += dpp_f32<0xFF>(bias);
+    if (relu) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = v[e] < 0.0f ? 0.0f : v[e];
+    }
+    if (lane < HROWS) {                                      // lane = row (fewer than four units: the entries beyond are never read)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[lane][j0 + e] = v[e];
+    }
+}
+
+// One layer on HROWS rows with v_mfma_f32_4x4x1_16b_f32 (fp32 in and out, fused multiply-adds): 16 independent blocks of
+// 4 output units x 4 rows share the contraction, block b taking columns 64 t + 4 b .. + 3 of piece t; what is left is one
+// sum over the blocks per 4 units.  x(t) is row (lane % 4)'s columns of block lane / 4, zeros beyond n_in; n_in a multiple
+// of 4, weights 16-byte aligned.  A wavefront takes every NW-th group of four units.
+// The operand layout puts four different weight rows into four neighbouring lanes, and a load does 64 bytes per cycle only
+// when such a quad reads 64 contiguous bytes (16 bytes otherwise: 22 us instead of 6.5 for 0.8 MB through one compute
+// unit).  So the weights go through LDS: direct-to-LDS loads of whole 256-byte pieces of the four rows, read back as
+// operands; the source lanes are permuted by quads (an XOR with the row) so that the reads are free of bank conflicts.
+// The ring is the wavefront's own, RING batches of four pieces deep: no barriers, only its own waits.
+// Bound: the weights, once per workgroup from L2 (768 x 256: 0.8 MB at 120-150 GB/s per compute unit).  A 768-256-64-1
+// network on 1024 rows, with the stop rule: 28.4 us with vector multiply-adds and a sum over 64 lanes per unit, 21.5 us so.
+constexpr int BATCH = 4, RING = 3;
+struct HiddenShared {
+    float act[2][HROWS][MCSD_MLP_MAX_WIDTH];
+    float4 ring[NW][RING][BATCH][64];
+    float bias[MCSD_MLP_MAX_LAYERS][MCSD_MLP_MAX_WIDTH];
+};
+template <int NT, typename Rows>
+__device__ __forceinline__ void mfma_layer(Rows x, int n_in, const float *__restrict__ W, const float *bias, int n_out,
+                                           float4 (*ring)[BATCH][64], float (*out)[MCSD_MLP_MAX_WIDTH], bool relu, int tid)
+{
+    constexpr int NB = NT / BATCH;                           // batches per group
+    static_assert(NT % BATCH == 0, "whole batches");
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int groups = (n_out + 3) >> 2;
+    // as a source: row r, columns 4 kk ..; as an operand: unit i, block blk (= kk), found at slot 16 i + (blk ^ 4 i)
+    const int r = min(lane >> 4, n_out - 1), kk = (lane & 15) ^ ((lane >> 4) << 2);
+    const int slot = ((lane & 3) << 4) + ((lane >> 2) ^ ((lane & 3) << 2));
+    int g_next = wave, b_next = 0, s_next = 0;               // next batch to request, and its place in the ring
+    auto request = [&]() {
+        // (past the last group: again, unused; readfirstlane: uniform, and the compiler has to know)
+        const float *base = W + (size_t)__builtin_amdgcn_readfirstlane(group_unit(min(g_next, groups - 1), n_out)) * n_in;
+        const int at = __builtin_amdgcn_readfirstlane(s_next);
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q) {
+            const int col = min(64 * (b_next * BATCH + q) + 4 * kk, n_in - 4);                  // beyond n_in: times zero
+            load_to_lds16<false>(base, (unsigned)(r * n_in + col) * 4u, &ring[at][q][0]);
         }
+        if (++b_next == NB) { b_next = 0; g_next += NW; }
+        s_next = s_next + 1 == RING ? 0 : s_next + 1;
     };
-    float4 wn[JB][NC];
-    if (wave * JB < n_out) load_weights(wn, wave * JB);
-    for (int j0 = wave * JB; j0 < n_out; j0 += NW * JB) {
-        float4 w[JB][NC];
+    if (wave < groups) {
 #pragma unroll
-        for (int jj = 0; jj < JB; ++jj)
+        for (int k = 0; k < RING; ++k) request();
+        int s = 0;
+        for (int grp = wave; grp < groups; grp += NW) {
+            f32x4_t a = {0.f, 0.f, 0.f, 0.f}, b = a;
 #pragma unroll
-            for (int c = 0; c < NC; ++c) w[jj][c] = wn[jj][c];
-        if (j0 + NW * JB < n_out) load_weights(wn, j0 + NW * JB);
-        float s[JB * HROWS];
+            for (int bt = 0; bt < NB; ++bt) {
+                MCSD_WAIT_VMCNT((RING - 1) * BATCH);         // this batch has landed, the later ones are under way
+                asm volatile("" ::: "memory");
+                float4 w[BATCH];
 #pragma unroll
-        for (int jj = 0; jj < JB; ++jj)
+                for (int q = 0; q < BATCH; ++q) w[q] = ring[s][q][slot];
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[0].x), "+v"(w[1].x), "+v"(w[2].x), "+v"(w[3].x) :: "memory");   // read before it is overwritten
+                request();
+                s = s + 1 == RING ? 0 : s + 1;
 #pragma unroll
-            for (int r = 0; r < HROWS; ++r) {
-                float a = 0.0f;
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    a = fmaf(w[jj][c].x, xr[r][c].x, a);
-                    a = fmaf(w[jj][c].y, xr[r][c].y, a);
-                    a = fmaf(w[jj][c].z, xr[r][c].z, a);
-                    a = fmaf(w[jj][c].w, xr[r][c].w, a);
+                for (int q = 0; q < BATCH; ++q) {
+                    const float4 v = x(bt * BATCH + q);
+                    a = __builtin_amdgcn_mfma_f32_4x4x1f32(w[q].x, v.x, a, 0, 0, 0);
+                    b = __builtin_amdgcn_mfma_f32_4x4x1f32(w[q].y, v.y, b, 0, 0, 0);
+                    a = __builtin_amdgcn_mfma_f32_4x4x1f32(w[q].z, v.z, a, 0, 0, 0);
+                    b = __builtin_amdgcn_mfma_f32_4x4x1f32(w[q].w, v.w, b, 0, 0, 0);
                 }
-                s[jj * HROWS + r] = a;
             }
-        wave_sum_f32_n<JB * HROWS>(s);
-        if (lane == 0) {
-#pragma unroll
-            for (int jj = 0; jj < JB; ++jj)
-                if (j0 + jj < n_out) {
-                    const float bj = b[j0 + jj];
-#pragma unroll
-                    for (int r = 0; r < HROWS; ++r) {
-                        const float z = s[jj * HROWS + r] + bj;
-                        out[r][j0 + jj] = (relu && z < 0.0f) ? 0.0f : z;
-                    }
-                }
+            const int j0 = group_unit(grp, n_out);
+            mfma_finish(a + b, j0, bias[j0 + min(lane & 3, n_out - 1)], out, relu, lane);
         }
+        MCSD_WAIT_VMCNT(0);
     }
     __syncthreads();
 }
 
+// Row (lane % 4)'s columns for mfma_layer.
+template <int NT>
+__device__ __forceinline__ void mfma_rows(float4 (&x)[NT], const float *row, int n_in, int tid)
+{
+    const int blk = (tid & 63) >> 2;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) x[t] = *reinterpret_cast<const float4 *>(row + min(64 * t + 4 * blk, n_in - 4));
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        asm volatile("" : "+v"(x[t].x), "+v"(x[t].y), "+v"(x[t].z), "+v"(x[t].w));      // (the loads stay unconditional, all in flight)
+        if (64 * t + 4 * blk >= n_in) x[t] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+}
+constexpr int WIDE = 2048;           // widest hidden state that the matrix path takes
+
+// NT: 64-column pieces of a row held in registers; 0: rows up to WIDE in LDS ([column / 4][row]: a wavefront reads them back
+// contiguously); -1: any width and alignment.
+template <int NT>
 __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M, int W, const float *__restrict__ hidden,
                                                              int64_t batch_stride, int64_t row_stride,
                                                              float *__restrict__ prob)
 {
-    __shared__ float s_act[2][HROWS][MCSD_MLP_MAX_WIDTH];
+    __shared__ __attribute__((aligned(1024))) HiddenShared sh;
     const int tid = threadIdx.x;
     const int m0 = blockIdx.x * HROWS;
-    const float *x[HROWS];
-#pragma unroll
-    for (int r = 0; r < HROWS; ++r) {
+    auto row = [&](int r) {
         const int m = min(m0 + r, M - 1);                       // rows past the end repeat the last one, unwritten
-        x[r] = hidden + (int64_t)(m / W) * batch_stride + (int64_t)(m % W) * row_stride;
-    }
+        return hidden + (int64_t)(m / W) * batch_stride + (int64_t)(m % W) * row_stride;
+    };
     const int n_in = mlp.width[0];
-    const bool aligned = n_in % 4 == 0 && batch_stride % 4 == 0 && row_stride % 4 == 0 &&
-                         (((uintptr_t)hidden | (uintptr_t)mlp.w[0]) & 15) == 0;
-    if (aligned && n_in <= 256)
-        hidden_first_layer<1>(x, n_in, mlp.w[0], mlp.b[0], mlp.width[1], s_act[0], mlp.n_layers > 1, tid);
-    else if (aligned && n_in <= 512)
-        hidden_first_layer<2>(x, n_in, mlp.w[0], mlp.b[0], mlp.width[1], s_act[0], mlp.n_layers > 1, tid);
-    else if (aligned && n_in <= 768)
-        hidden_first_layer<3>(x, n_in, mlp.w[0], mlp.b[0], mlp.width[1], s_act[0], mlp.n_layers > 1, tid);
-    else if (aligned && n_in <= 1024)
-        hidden_first_layer<4>(x, n_in, mlp.w[0], mlp.b[0], mlp.width[1], s_act[0], mlp.n_layers > 1, tid);
-    else        // any width and alignment: straight from global memory
-        mlp_layer<HROWS>([x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3]](int r, int i) {
+    const bool relu = mlp.n_layers > 1;
+    float4 (*ring)[BATCH][64] = sh.ring[__builtin_amdgcn_readfirstlane(tid >> 6)];
+    for (int l = 0; l < mlp.n_layers; ++l)
+        for (int j = tid; j < mlp.width[l + 1]; j += DT) sh.bias[l][j] = mlp.b[l][j];
+    if constexpr (NT > 0) {
+        float4 xr[NT];
+        mfma_rows<NT>(xr, row(tid & 3), n_in, tid);
+        __syncthreads();
+        mfma_layer<NT>([&](int t) { return xr[t]; }, n_in, mlp.w[0], sh.bias[0], mlp.width[1], ring, sh.act[0], relu, tid);
+    } else if constexpr (NT == 0) {
+        __shared__ float4 s_x[WIDE];
+        for (int k = tid; k < WIDE; k += DT) {
+            const int c = 4 * (k >> 2);
+            s_x[k] = c < n_in ? *reinterpret_cast<const float4 *>(row(k & 3) + c) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        __syncthreads();
+        mfma_layer<WIDE / 64>([&](int t) { return s_x[t * 64 + (tid & 63)]; }, n_in, mlp.w[0], sh.bias[0], mlp.width[1], ring, sh.act[0], relu, tid);
+    } else {
+        mlp_layer<HROWS>([x0 = row(0), x1 = row(1), x2 = row(2), x3 = row(3)](int r, int i) {
                              return (r == 0 ? x0 : r == 1 ? x1 : r == 2 ? x2 : x3)[i];
-                         }, n_in, mlp.w[0], mlp.b[0], mlp.width[1], s_act[0], mlp.n_layers > 1, tid);
-    const int cur = mlp_tail<HROWS>(mlp.n_layers, mlp.width, mlp.w, mlp.b, 1, s_act, 0, tid);
-    if (tid < HROWS && m0 + tid < M) prob[m0 + tid] = logistic(s_act[cur][tid][0]);
+                         }, n_in, mlp.w[0], mlp.b[0], mlp.width[1], sh.act[0], relu, tid);
+    }
+    int cur = 0;
+    for (int l = 1; l < mlp.n_layers; ++l) {
+        const int width = mlp.width[l];
+        const bool more = l + 1 < mlp.n_layers;
+        float (*src)[MCSD_MLP_MAX_WIDTH] = sh.act[cur], (*dst)[MCSD_MLP_MAX_WIDTH] = sh.act[cur ^ 1];
+        if (width % 4 != 0 || ((uintptr_t)mlp.w[l] & 15) != 0) {
+            mlp_layer<HROWS>([src](int r, int i) { return src[r][i]; }, width, mlp.w[l], mlp.b[l], mlp.width[l + 1], dst, more, tid);
+        } else if (width <= 256) {
+            float4 xr[4];
+            mfma_rows<4>(xr, src[tid & 3], width, tid);
+            mfma_layer<4>([&](int t) { return xr[t]; }, width, mlp.w[l], sh.bias[l], mlp.width[l + 1], ring, dst, more, tid);
+        } else {
+            float4 xr[8];
+            mfma_rows<8>(xr, src[tid & 3], width, tid);
+            mfma_layer<8>([&](int t) { return xr[t]; }, width, mlp.w[l], sh.bias[l], mlp.width[l + 1], ring, dst, more, tid);
+        }
+        cur ^= 1;
+    }
+    if (tid < HROWS && m0 + tid < M) prob[m0 + tid] = logistic(sh.act[cur][tid][0]);
 }
 
 // ---------------------------------------------------------------------------------------------- stop rule
@@ -533,8 +613,11 @@ extern "C" int mcsd_early_stop_hidden(const mcsd_mlp_t *mlp, int32_t B, int32_t 
     if (!hidden_dev || !prob_dev || !stop_dev) return MCSD_EINVAL;
     if ((int64_t)B * W > 0x7fffffff / 2) return MCSD_EUNSUPPORTED;
     hipStream_t st = (hipStream_t)hip_stream;
-    const int M = B * W;
-    mcsd_launch(MCSD_KERNEL_DECISION, decision_hidden_kernel, dim3((M + HROWS - 1) / HROWS), dim3(DT), st, d, M, (int)W,
+    const int M = B * W, n_in = d.width[0];
+    const bool aligned = n_in % 4 == 0 && batch_stride % 4 == 0 && row_stride % 4 == 0 && (((uintptr_t)hidden_dev | (uintptr_t)d.w[0]) & 15) == 0;
+    auto kernel = !aligned || n_in > WIDE ? decision_hidden_kernel<-1> : n_in <= 256 ? decision_hidden_kernel<4> : n_in <= 512 ? decision_hidden_kernel<8>
+                  : n_in <= 768 ? decision_hidden_kernel<12> : n_in <= 1024 ? decision_hidden_kernel<16> : decision_hidden_kernel<0>;
+    mcsd_launch(MCSD_KERNEL_DECISION, kernel, dim3((M + HROWS - 1) / HROWS), dim3(DT), st, d, M, (int)W,
                 hidden_dev, batch_stride, row_stride, prob_dev);
     if (int rc = mcsd_hip_status(hipGetLastError())) return rc;
     return launch_stop(prob_dev, B, W, beta, stop_dev, st);

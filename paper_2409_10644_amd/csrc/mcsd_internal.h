@@ -54,3 +54,33 @@ inline void mcsd_launch(int which, void (*kernel)(Args...), dim3 grid, dim3 bloc
         hipLaunchKernelGGL(kernel, grid, block, 0, st, args...);
     }
 }
+
+// 16 bytes per lane from global memory straight into LDS: lane l reads gbase + voff and lands at lds_base + 16*l
+// (gbase and lds_base uniform).  Written as assembly on purpose: the compiler knows nothing about where such a
+// load writes in LDS unless alias information happens to survive inlining, and otherwise makes the next LDS
+// read wait for it (vmcnt(0)), which serialises the stream with the compute.  Here it is just an opaque
+// instruction; the kernel waits for it itself (MCSD_WAIT_VMCNT + barrier) before anyone reads the stage.
+// An untracked load can only make compiler-placed vmcnt waits longer, never shorter (loads retire in order).
+// M0 carries the LDS address; nothing else in these kernels uses M0 (the toolchain rejects it as a clobber).
+// NT marks the load non-temporal, for prefix K/V that exactly one workgroup reads: keeping a read-once stream out
+// of the caches' retained set is worth 5-12 % of the sweep (measured; the coherence-scope bits make no
+// difference).  Where several workgroups share a stream (grouped-query heads cut into several query chunks) the
+// second reader needs the lines in L2 and the plain load is the faster one.
+template <bool NT>
+static __device__ inline void load_to_lds16(const void *gbase, uint32_t voff, void *lds_base)
+{
+    const uint32_t lds_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds_base;
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(lds_addr), "v"(voff), "s"(gbase)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(lds_addr), "v"(voff), "s"(gbase)
+                     : "memory");
+}
+
+// s_waitcnt vmcnt(N) only (expcnt / lgkmcnt left at their maxima)
+#define MCSD_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14))

@@ -166,6 +166,15 @@ def test_hidden_state_model(binding, oracle, widths, B, W):
     assert want.std() > 1e-3 or B * W == 1
 
 
+# Register pieces (256, 512, 768, 1024 inputs), rows in LDS up to 2048, the generic first layer beyond and for widths that are
+# no multiple of 4; layers of fewer than four units, of a last group that is not whole, and behind an odd width.
+@pytest.mark.parametrize("widths,B,W", [((4, 1), 1, 1), ((256, 3, 1), 3, 3), ((260, 6, 258, 1), 1, 5), ((512, 260, 1), 5, 1),
+                                        ((764, 33, 7, 1), 2, 3), ((1024, 512, 512, 1), 1, 9), ((1028, 31, 1), 1, 4),
+                                        ((2044, 64, 8, 1), 2, 7), ((2052, 12, 1), 1, 3), ((257, 256, 64, 1), 2, 2)])
+def test_hidden_state_model_layer_edges(binding, oracle, widths, B, W):
+    test_hidden_state_model(binding, oracle, widths, B, W)
+
+
 def test_hidden_state_model_padded_rows(binding, oracle):
     B, W, n_in, pad = 2, 3, 40, 5
     ws, bs = mlp_weights((n_in, 16, 8, 1), seed=11)
