@@ -15,7 +15,9 @@ OBJ = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
+          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          # leading scalar kernel arguments arrive in registers, so a kernel's first loads need not wait for the argument block
+          "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wall", "-Wno-unused-function"]
 # per-file extra flags: the verification kernels must perform exactly the IEEE operations written
 SOURCES = {
     "mask.cpp": ["-x", "hip"],

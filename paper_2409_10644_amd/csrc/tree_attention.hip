@@ -207,6 +207,7 @@ AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int d, int n_rows, int max
         else same_die = bh % n_xcc == 0;
     }
     if (pl.pair_cus > 0) same_die = n_xcc == 1 || (n_xcc > 1 && pl.units % n_xcc == 0 && pl.pair_cus % n_xcc == 0);
+    if (pl.xcc & (pl.xcc - 1)) same_die = false;           // (the kernel renumbers by shifts)
     pl.fold = pl.S > 1 && same_die && (dtype == MCSD_F32 || pl.G <= FOLD_MAX_PARTIALS) &&
               (size_t)bh * pl.QT * CTR_STRIDE * sizeof(unsigned long long) <= WS_CTR_BYTES && !(tune && tune->fold == 1);
     return pl;
@@ -485,6 +486,26 @@ __device__ inline void attn_tile(const unsigned char *stage, const LaneAddr la, 
     qs.l_run += psum;
 }
 
+// What a workgroup of the sweep needs before it can ask for its first key comes as the kernel's leading scalar arguments,
+// which the hardware preloads into registers (see the build's kernarg-preload option), and its place in the grid follows
+// without integer division (some 50 dependent instructions each): multiplication by a reciprocal that the host rounded up,
+// floor(a / d) = a * mul >> (31 + shift) for 0 <= a < 2^31 with shift = ceil(log2 d), mul = ceil(2^(31 + shift) / d).
+// Measured, start of a workgroup to its prefix length known: 1.45 us without.
+struct FastDiv { uint32_t mul, shift; };
+inline FastDiv fast_div_of(uint32_t d)
+{
+    FastDiv f = {0, 0};
+    while ((1ull << f.shift) < d) ++f.shift;
+    f.mul = (uint32_t)(((1ull << (31 + f.shift)) + d - 1) / d);
+    return f;
+}
+__device__ __forceinline__ int fast_div(int a, uint32_t mul, uint32_t shift) { return (int)(((uint64_t)(uint32_t)a * mul) >> (31 + shift)); }
+// `how`: bits 0-4 shift of G, 5-9 shift of H, 10-13 log2 of the dies, and flags
+constexpr uint32_t HOW_RENUMBER = 1u << 14, HOW_PAIR = 1u << 15;
+__device__ __forceinline__ uint32_t how_shift_G(uint32_t how) { return how & 31u; }
+__device__ __forceinline__ uint32_t how_shift_H(uint32_t how) { return (how >> 5) & 31u; }
+__device__ __forceinline__ uint32_t how_xcc(uint32_t how) { return (how >> 10) & 15u; }
+
 // The fold of the partial results of one query block by one wavefront of the workgroup that arrived last (see the
 // end of the sweep kernel): rows = the wavefront's 32 queries (lane ln, half g), columns = the 32-column blocks
 // kg, kg + KG, ..  ro / rm / rl describe the unit's partial O (fragment order), maxima and denominators and end after
@@ -587,7 +608,9 @@ __device__ __attribute__((always_inline)) inline void fold_partials(const __amdg
 
 template <int D, int QBP, int NS, bool F8 = false>
 __global__ __launch_bounds__((SweepCfg<D, QBP, NS, F8>::THREADS)) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void tree_attn_bf16_kernel(const AttnParams p)
+void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const uint32_t per_die, const int32_t G,
+                           const uint32_t mul_G, const int32_t H, const uint32_t mul_H, const int32_t BH,
+                           const uint32_t how, const int32_t max_prefix, const int32_t tps, const AttnParams p)
 {
     using C = SweepCfg<D, QBP, NS, F8>;
     __shared__ __attribute__((aligned(1024))) unsigned char ring[C::LDS_BYTES];
@@ -595,14 +618,14 @@ void tree_attn_bf16_kernel(const AttnParams p)
     // Workgroup ids are dealt round-robin to the accelerator dies (p.xcc of them, each with its own L2): renumber so
     // that the key splits of one (sequence, head), which read the same Q, tree K/V and mask rows, write neighbouring
     // partial results and fold them through that L2, share one die.
-    const int total = gridDim.x;
     int wg = blockIdx.x;
-    if (p.G > 1 && p.pair_cus == 0 && p.xcc > 1 && total % p.xcc == 0) wg = (wg % p.xcc) * (total / p.xcc) + wg / p.xcc;
-    int s = wg % p.G;
-    int bhi = wg / p.G;
+    if (how & HOW_RENUMBER) wg = (wg & ((1 << how_xcc(how)) - 1)) * per_die + (wg >> how_xcc(how));
+    int bhi = fast_div(wg, mul_G, how_shift_G(how));
+    int s = wg - bhi * G;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // the same in all lanes: keep it in a scalar register
-    if (p.pair_cus > 0) {
+    if (how & HOW_PAIR) {
+        const int total = gridDim.x;
         // More workgroups than compute units.  Up to two per compute unit they are all resident at once, and on this
         // machine workgroups i and i + #CUs of such a grid land on the same compute unit (measured; nothing but
         // speed depends on it): that pair gets a long and a short piece of work, so that every compute unit has
@@ -632,22 +655,22 @@ void tree_attn_bf16_kernel(const AttnParams p)
             r = (cnt % p.xcc == 0) ? p.pair_cus + (cnt / p.xcc - 1 - w2 / p.xcc) * p.xcc + w2 % p.xcc
                                    : total + p.pair_cus - 1 - wg;
         }
-        const int cls = s_cls_at[r / p.H];
+        const int rank = fast_div(r, mul_H, how_shift_H(how));
+        const int cls = __builtin_amdgcn_readfirstlane(s_cls_at[rank]);
         s = cls % p.S;
-        bhi = (cls / p.S) * p.H + r % p.H;
+        bhi = (cls / p.S) * H + (r - rank * H);
     }
-    if (bhi >= p.B * p.H) return;                            // a slot of a grid rounded up to whole dies
-    const int h = bhi % p.H, b = bhi / p.H;
+    if (bhi >= BH) return;                                   // a slot of a grid rounded up to whole dies
+    const int b = fast_div(bhi, mul_H, how_shift_H(how)), h = bhi - b * H;
 
     const int g = lane >> 5, ln = lane & 31;
     const int qb = wave % QBP, kg = wave / QBP;
 
-    int L = p.lens[b];
-    L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
-    const uint32_t ws_tag = p.fold ? p.ws_tag[0] : WS_TAG;  // (read early: needed only at the very end)
-    const int tiles_b = (L + C::T - 1) / C::T;
-    const int tps = p.tps;                                  // fixed per call: short sequences use fewer splits
-    const bool sep = p.G > p.S;                             // the tree's own keys have a workgroup of their own
+    int L = lens[b];
+    const int64_t seq_at = seq_base[b];
+    L = L < 0 ? 0 : (L > max_prefix ? max_prefix : L);
+    const int tiles_b = (L + C::T - 1) / C::T;              // (tps is fixed per call: short sequences use fewer splits)
+    const bool sep = G > p.S;                               // the tree's own keys have a workgroup of their own
     const int np = (tiles_b + tps - 1) / tps;               // prefix splits that have keys for this sequence (<= S)
     const bool tree_wg = sep ? s == p.S : s == (p.tree_last ? max(np, 1) - 1 : 0);
     const int t0 = (sep && tree_wg) ? tiles_b : min(s * tps, tiles_b), t1 = min(t0 + tps, tiles_b);
@@ -659,14 +682,14 @@ void tree_attn_bf16_kernel(const AttnParams p)
     // leading tiles of this split that are full (only the sequence's last tile can be ragged)
     const int n_hot = (n_pre > 0 && t1 * C::T > L) ? n_pre - 1 : n_pre;
 
-    const int64_t bh = (int64_t)b * p.H + h;                 // workgroup unit: indexes the partial results
-    const int kvh = h / p.chunks;                              // key/value head of this unit
+    const int64_t bh = bhi;                                  // workgroup unit: indexes the partial results
+    const int kvh = p.chunks == 1 ? h : h / p.chunks;          // key/value head of this unit
     const int hq = kvh * p.grp + (h % p.chunks) * p.hpw + qb / p.bph;   // query head of this wavefront's block
     const int64_t bh_kv = (int64_t)b * p.Hkv + kvh, bh_q = (int64_t)b * p.Hq + hq;
     const __bf16 *q = (const __bf16 *)p.q + bh_q * p.node_stride * D;
     const __bf16 *kt = (const __bf16 *)p.kt + bh_kv * p.node_stride * D;
     const __bf16 *vt = (const __bf16 *)p.vt + bh_kv * p.node_stride * D;
-    const int64_t pre0 = p.seq_base[b] + (int64_t)kvh * p.head_stride;     // in elements: 2 bytes each, 1 when fp8
+    const int64_t pre0 = seq_at + (int64_t)kvh * p.head_stride;     // in elements: 2 bytes each, 1 when fp8
     const unsigned char *kp = (const unsigned char *)p.kp + pre0 * (F8 ? 1 : 2);
     const unsigned char *vp = (const unsigned char *)p.vp + pre0 * (F8 ? 1 : 2);
     // softmax scale of a prefix tile and the factor its V values carry; the tree's own tiles use p.c and 1
@@ -735,7 +758,10 @@ void tree_attn_bf16_kernel(const AttnParams p)
         // Every workgroup walks its full tiles in a rotated order (soft-max does not care): workgroups that start
         // together would otherwise sweep their equally aligned K/V streams in lock-step and crowd the same
         // memory channels.  `nxt` is the tile the next issue fetches.
-        int nxt = (int)(((unsigned)wg * 37u) % (unsigned)n_hot);
+        // Workgroups that stream the same keys for different query heads keep step instead: the second finds them in L2
+        // (16 sequences of 512-4096 keys, 32 query heads over 8: 69 -> 65 us).
+        const unsigned turn = p.chunks == 1 ? (unsigned)wg : (unsigned)((int)bh_kv * G + s);
+        int nxt = (int)((turn * 37u) % (unsigned)n_hot);
         // load number i (0 .. DPT-1) of tile `nxt` into a stage: even i fetch K row groups, odd i the same of V
         // (uniform tile base + 32-bit lane offset: the load takes its base from scalar registers)
         const unsigned char *kbase = ksrc + (int64_t)nxt * C::TILE_K, *vbase = vsrc + (int64_t)nxt * C::TILE_K;
@@ -775,7 +801,7 @@ void tree_attn_bf16_kernel(const AttnParams p)
         static_assert(!F8, "fp8 tiles use the ring below");
         using S0 = std::integral_constant<int, 0>;
         using S1 = std::integral_constant<int, 1>;
-        issue_tile(S0());
+        issue_tile(S0());                                   // (behind Q: requested ahead of Q it costs 2 %)
         // all steps but the last fetch the next tile while they compute
         int it = 0;
         for (; it + 2 < n_hot; it += 2) {
@@ -821,6 +847,9 @@ void tree_attn_bf16_kernel(const AttnParams p)
         MCSD_WAIT_VMCNT(0);
     }
     __syncthreads();
+
+    // (requested here: at the start the wait for the first keys' addresses would include it)
+    const uint32_t ws_tag = p.fold ? __hip_atomic_load(p.ws_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) : WS_TAG;
 
     // ---- ragged last prefix tile and the tree's own tiles: through registers, rows beyond `valid` zero-filled ----
     const int n_rest = (n_pre - n_hot) + n_tree_tiles;
@@ -1419,8 +1448,15 @@ __global__ __launch_bounds__(256) void workspace_init_kernel(uint4 *ws)
 template <int D, int QBP, int NS, bool F8 = false>
 void launch_sweep(const AttnParams &p, const AttnPlan &pl, hipStream_t st)
 {
-    const dim3 grid((unsigned)((size_t)pl.G * pl.grid_units));
-    mcsd_launch(MCSD_KERNEL_ATTN_SWEEP, tree_attn_bf16_kernel<D, QBP, NS, F8>, grid, dim3(SweepCfg<D, QBP, NS, F8>::THREADS), st, p);
+    const uint32_t total = (uint32_t)((size_t)pl.G * pl.grid_units);
+    const FastDiv g = fast_div_of(pl.G), h = fast_div_of(p.H);
+    uint32_t log2_xcc = 0;
+    while ((2 << log2_xcc) <= p.xcc) ++log2_xcc;
+    uint32_t how = g.shift | h.shift << 5 | log2_xcc << 10;
+    if (pl.G > 1 && p.pair_cus == 0 && p.xcc > 1 && total % p.xcc == 0 && (1 << log2_xcc) == p.xcc) how |= HOW_RENUMBER;
+    if (p.pair_cus > 0) how |= HOW_PAIR;
+    mcsd_launch(MCSD_KERNEL_ATTN_SWEEP, tree_attn_bf16_kernel<D, QBP, NS, F8>, dim3(total), dim3(SweepCfg<D, QBP, NS, F8>::THREADS), st,
+                p.lens, p.seq_base, total >> log2_xcc, (int32_t)pl.G, g.mul, p.H, h.mul, (int32_t)(p.B * p.H), how, p.max_prefix, p.tps, p);
 }
 
 template <int D, int QBP>
