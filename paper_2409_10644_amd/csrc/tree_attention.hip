@@ -741,80 +741,110 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
 #pragma unroll
     for (int u = 0; u < C::KPW; ++u) all_keys[u] = 0xffffffffu;
 
-    // ---- full prefix tiles: HBM -> LDS directly, one tile ahead of the compute ----
-    if (n_hot > 0) {
-        // lane's source offset inside a tile for instruction i: row G*RPI + lane/CPR, logical chunk (lane%CPR)^swz(row)
-        uint32_t goff[C::NI];
+    // ---- keys: HBM -> LDS directly, NS - 1 tiles ahead of the compute ----
+    // Lane's source offset inside a tile for instruction 0: row wave * RPI + lane / CPR, logical chunk (lane % CPR) ^ swz(row);
+    // instruction i covers the rows i * WAVES * RPI further down, whose swizzle is the same.
+    constexpr int STEP = C::WAVES * C::RPI;
+    const int row0 = wave * C::RPI + lane / C::CPR;
+    const uint32_t goff = (uint32_t)(row0 * C::RBP + (((lane % C::CPR) ^ (F8 ? swz8(row0) : swz<D>(row0))) * 16));
+    uint32_t goffs[C::NI];                                  // (registers rather than scalar additions per load: 1.5 % of the long sweeps)
 #pragma unroll
-        for (int i = 0; i < C::NI; ++i) {
-            const int G = i * C::WAVES + wave;
-            const int r = G * C::RPI + lane / C::CPR;
-            goff[i] = (uint32_t)(r * C::RBP + (((lane % C::CPR) ^ (F8 ? swz8(r) : swz<D>(r))) * 16));
+    for (int i = 0; i < C::NI; ++i) {
+        goffs[i] = goff + (uint32_t)(i * STEP * C::RBP);
+        asm("" : "+v"(goffs[i]));
+    }
+    static_assert(STEP % (F8 || D == 128 ? 16 : 8) == 0, "the swizzle repeats");
+    // Every workgroup walks its full tiles in a rotated order (soft-max does not care): workgroups that start
+    // together would otherwise sweep their equally aligned K/V streams in lock-step and crowd the same
+    // memory channels.  `nxt` is the full tile the next request fetches.
+    // Workgroups that stream the same keys for different query heads keep step instead: the second finds them in L2
+    // (16 sequences of 512-4096 keys, 32 query heads over 8: 69 -> 65 us).
+    const unsigned turn = p.chunks == 1 ? (unsigned)wg : (unsigned)((int)bh_kv * G + s);
+    int nxt = n_hot > 0 ? (int)((turn * 37u) % (unsigned)n_hot) : 0;
+    const unsigned char *ksrc = kp + (int64_t)t0 * C::TILE_K, *vsrc = vp + (int64_t)t0 * C::TILE_K;
+    // (uniform tile base + 32-bit lane offset: a load takes its base from scalar registers)
+    const unsigned char *kbase = ksrc + (int64_t)nxt * C::TILE_K, *vbase = vsrc + (int64_t)nxt * C::TILE_K;
+    const bool read_once = p.chunks == 1;                   // no other workgroup streams these keys (uniform)
+    auto issue_full = [&](unsigned char *stage) {
+        stage += wave * 1024;
+        if (read_once) {
+#pragma unroll
+            for (int i = 0; i < C::DPT; ++i)
+                load_to_lds16<true>((i & 1) ? vbase : kbase, goffs[i >> 1], stage + (i & 1) * C::TILE_K + (i >> 1) * C::WAVES * 1024);
+        } else {
+#pragma unroll
+            for (int i = 0; i < C::DPT; ++i)
+                load_to_lds16<false>((i & 1) ? vbase : kbase, goffs[i >> 1], stage + (i & 1) * C::TILE_K + (i >> 1) * C::WAVES * 1024);
         }
-        const unsigned char *ksrc = kp + (int64_t)t0 * C::TILE_K;
-        const unsigned char *vsrc = vp + (int64_t)t0 * C::TILE_K;
-        // Stage numbers are compile-time constants so that the compiler can tell the stage being filled from
-        // the stage being read (otherwise it makes every LDS read wait for the loads just issued).
-        // Every workgroup walks its full tiles in a rotated order (soft-max does not care): workgroups that start
-        // together would otherwise sweep their equally aligned K/V streams in lock-step and crowd the same
-        // memory channels.  `nxt` is the tile the next issue fetches.
-        // Workgroups that stream the same keys for different query heads keep step instead: the second finds them in L2
-        // (16 sequences of 512-4096 keys, 32 query heads over 8: 69 -> 65 us).
-        const unsigned turn = p.chunks == 1 ? (unsigned)wg : (unsigned)((int)bh_kv * G + s);
-        int nxt = (int)((turn * 37u) % (unsigned)n_hot);
-        // load number i (0 .. DPT-1) of tile `nxt` into a stage: even i fetch K row groups, odd i the same of V
-        // (uniform tile base + 32-bit lane offset: the load takes its base from scalar registers)
-        const unsigned char *kbase = ksrc + (int64_t)nxt * C::TILE_K, *vbase = vsrc + (int64_t)nxt * C::TILE_K;
-        auto issue_load = [&](int i, auto stage, auto read_once) {
-            unsigned char *dst = ring + decltype(stage)::value * C::TILE + wave * 1024;
-            static_assert(decltype(stage)::value < NS, "stage out of range");
-            load_to_lds16<decltype(read_once)::value>((i & 1) ? vbase : kbase, goff[i >> 1],
-                                                      dst + (i & 1) * C::TILE_K + (i >> 1) * C::WAVES * 1024);
-        };
-        auto advance = [&]() {
-            nxt = nxt + 1 == n_hot ? 0 : nxt + 1;
-            kbase = ksrc + (int64_t)nxt * C::TILE_K;
-            vbase = vsrc + (int64_t)nxt * C::TILE_K;
-        };
-        const bool read_once = p.chunks == 1;               // no other workgroup streams these keys (uniform)
-        auto issue_tile = [&](auto stage) {
-            if (read_once) {
+        nxt = nxt + 1 == n_hot ? 0 : nxt + 1;
+        kbase = ksrc + (int64_t)nxt * C::TILE_K;
+        vbase = vsrc + (int64_t)nxt * C::TILE_K;
+    };
+    // behind the full tiles: the ragged last prefix tile, if it is here, and the tree's own tiles, if they are
+    const int n_tail = n_pre - n_hot, n_all = n_hot + n_tail + n_tree_tiles;
+    const int tail_rows = L - (t1 - 1) * C::T;
+    // Tile i of those: which keys of this wavefront's blocks exist (ragged tile) or are ancestors of its queries (tree)
+    auto rest_bits = [&](int i, uint32_t (&bits)[C::KPW]) {
 #pragma unroll
-                for (int i = 0; i < C::DPT; ++i) issue_load(i, stage, std::true_type());
+        for (int u = 0; u < C::KPW; ++u) {
+            const int key0 = (kg * C::KPW + u) * 32;        // first key of this block inside the tile
+            if (i < 0) {                                    // (a full tile)
+                bits[u] = 0xffffffffu;
+            } else if (i < n_tail) {
+                const int left = tail_rows - key0;          // keys of the block that exist
+                bits[u] = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : ((1u << left) - 1u));
             } else {
-#pragma unroll
-                for (int i = 0; i < C::DPT; ++i) issue_load(i, stage, std::false_type());
+                const int col = (i - n_tail) * C::T + key0;
+                bits[u] = (uint32_t)(((col >> 6) ? mrow[1] : mrow[0]) >> (col & 63));
             }
-            advance();
+        }
+    };
+    if constexpr (NS == 2) {
+        // The tiles that are not full come the same way, a row beyond the last one as that row again (masked out): through
+        // registers behind the last full tile each of them cost its whole latency once more, 1.7 us.
+        auto issue_rest = [&](int i, unsigned char *stage) {
+            const bool tail = i < n_tail;
+            const unsigned char *ks = tail ? kp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)kt + (int64_t)(i - n_tail) * C::TILE_K;
+            const unsigned char *vs = tail ? vp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)vt + (int64_t)(i - n_tail) * C::TILE_K;
+            const int last = (tail ? tail_rows : p.n - (i - n_tail) * C::T) - 1;
+            stage += wave * 1024;
+#pragma unroll
+            for (int j = 0; j < C::NI; ++j) {
+                const uint32_t off = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
+                load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
+                load_to_lds16<false>(vs, off, stage + C::TILE_K + j * C::WAVES * 1024);
+            }
         };
-        if constexpr (NS == 2) {
-        auto step = [&](int it, auto stage, auto prefetching) {
-            constexpr int ST = decltype(stage)::value;
-            constexpr bool PF = decltype(prefetching)::value;    // a later tile is fetched into the stage just freed
-            // this wavefront's part of tile `it` has landed once at most NS-2 later tiles are outstanding
-            MCSD_WAIT_VMCNT(0);
-            __builtin_amdgcn_s_barrier();                     // ... and everyone's; the stage of tile it-1 is free again
-            // (spreading these loads over the tile's MFMAs instead of issuing them in one burst was measured: no gain)
-            if (PF) issue_tile(std::integral_constant<int, (ST + NS - 1) % NS>());
-            attn_tile<D, QBP, NS, 0, false, false>(ring + ST * C::TILE, la, qs, p.c, g, all_keys);
+        auto arrived = [&]() {
+            MCSD_WAIT_VMCNT(0);                             // this wavefront's part of the tile has landed ...
+            __builtin_amdgcn_s_barrier();                   // ... and everyone's; the stage of the tile before is free again
         };
-        static_assert(!F8, "fp8 tiles use the ring below");
-        using S0 = std::integral_constant<int, 0>;
-        using S1 = std::integral_constant<int, 1>;
-        issue_tile(S0());                                   // (behind Q: requested ahead of Q it costs 2 %)
-        // all steps but the last fetch the next tile while they compute
+        if (n_hot > 0) issue_full(ring);                    // (behind Q: requested ahead of Q it costs 2 %)
+        else issue_rest(0, ring);
         int it = 0;
-        for (; it + 2 < n_hot; it += 2) {
-            step(it, S0(), std::true_type());
-            step(it + 1, S1(), std::true_type());
+        // (spreading the loads over the tile's MFMAs instead of issuing them in one burst was measured: no gain)
+        for (; it + 1 < n_hot; it += 2) {
+            arrived();
+            issue_full(ring + C::TILE);
+            attn_tile<D, QBP, NS, 0, false, false>(ring, la, qs, p.c, g, all_keys);
+            arrived();
+            if (it + 2 < n_hot) issue_full(ring);
+            else if (it + 2 < n_all) issue_rest(it + 2 - n_hot, ring);
+            attn_tile<D, QBP, NS, 0, false, false>(ring + C::TILE, la, qs, p.c, g, all_keys);
         }
-        if (it + 1 < n_hot) {
-            step(it, S0(), std::true_type());
-            step(it + 1, S1(), std::false_type());
-        } else {
-            step(it, S0(), std::false_type());
+        for (; it < n_all; ++it) {                          // an odd full tile among them; one copy of the tile's code, no spills
+            arrived();
+            unsigned char *stage = ring + (it & 1) * C::TILE, *other = ring + (~it & 1) * C::TILE;
+            if (it + 1 < n_hot) issue_full(other);
+            else if (it + 1 < n_all) issue_rest(it + 1 - n_hot, other);
+            uint32_t bits[C::KPW];
+            rest_bits(it - n_hot, bits);
+            attn_tile<D, QBP, NS, 1, false, false>(stage, la, qs, p.c, g, bits);
         }
-        } else {
+        __syncthreads();
+        static_assert(!F8, "fp8 tiles use the ring below");
+    } else {
+    if (n_hot > 0) {
         // A ring of NS stages keeps NS-1 tiles in flight: fp8 tiles (half the bytes); bf16 tiles only on request (it
         // needs a compute unit's LDS per workgroup and measured slower, see make_plan).  Tile t lives in stage
         // t % NS.  A step waits until exactly the tiles requested after its own are still outstanding: NS-2 of them in
@@ -826,7 +856,7 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
             else if (later == 1) MCSD_WAIT_VMCNT(C::DPT);
             else MCSD_WAIT_VMCNT(0);
             __builtin_amdgcn_s_barrier();
-            if (it + NS - 1 < n_hot) issue_tile(std::integral_constant<int, (ST + NS - 1) % NS>());
+            if (it + NS - 1 < n_hot) issue_full(ring + (ST + NS - 1) % NS * C::TILE);
             attn_tile<D, QBP, NS, 0, F8, F8>(ring + ST * C::TILE, la, qs, c_pre, g, all_keys, vs_pre);
         };
         static_assert(NS == 4, "the step sequence below is unrolled for four stages");
@@ -834,31 +864,26 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
         // with a non-zero count, and the compiler, which does not see those loads, would otherwise place its own
         // wait for Q at the first MFMA inside the loop, where it would also wait for the tiles in flight.
         MCSD_WAIT_VMCNT(0);
-        if (0 < n_hot) issue_tile(std::integral_constant<int, 0>());
-        if (1 < n_hot) issue_tile(std::integral_constant<int, 1 % NS>());
-        if (2 < n_hot) issue_tile(std::integral_constant<int, 2 % NS>());
+        if (0 < n_hot) issue_full(ring + 0 * C::TILE);
+        if (1 < n_hot) issue_full(ring + 1 * C::TILE);
+        if (2 < n_hot) issue_full(ring + 2 * C::TILE);
         for (int it = 0; it < n_hot; it += 4) {
             step(std::integral_constant<int, 0>(), it);
             if (it + 1 < n_hot) step(std::integral_constant<int, 1 % NS>(), it + 1);
             if (it + 2 < n_hot) step(std::integral_constant<int, 2 % NS>(), it + 2);
             if (it + 3 < n_hot) step(std::integral_constant<int, 3 % NS>(), it + 3);
         }
-        }
         MCSD_WAIT_VMCNT(0);
     }
     __syncthreads();
 
-    // (requested here: at the start the wait for the first keys' addresses would include it)
-    const uint32_t ws_tag = p.fold ? __hip_atomic_load(p.ws_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) : WS_TAG;
-
     // ---- ragged last prefix tile and the tree's own tiles: through registers, rows beyond `valid` zero-filled ----
-    const int n_rest = (n_pre - n_hot) + n_tree_tiles;
-    for (int it = 0; it < n_rest; ++it) {
-        const bool tail = it < n_pre - n_hot;
-        const int tt = tail ? 0 : it - (n_pre - n_hot);
+    for (int it = 0; it < n_all - n_hot; ++it) {
+        const bool tail = it < n_tail;
+        const int tt = tail ? 0 : it - n_tail;
         const unsigned char *ksrc = tail ? kp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)kt + (int64_t)tt * C::BTILE_K;
         const unsigned char *vsrc = tail ? vp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)vt + (int64_t)tt * C::BTILE_K;
-        const int valid = tail ? L - (t1 - 1) * C::T : min(C::T, p.n - tt * C::T);
+        const int valid = tail ? tail_rows : min(C::T, p.n - tt * C::T);
 #pragma unroll
         for (int i0 = 0; i0 < C::CPT; i0 += 4) {           // four chunks of K and V at a time keeps the staging small
             uint4 kreg[4], vreg[4];
@@ -891,20 +916,13 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
         }
         __syncthreads();
         uint32_t bits[C::KPW];
-#pragma unroll
-        for (int u = 0; u < C::KPW; ++u) {
-            const int key0 = (kg * C::KPW + u) * 32;          // first key of this block inside the tile
-            if (tail) {
-                const int left = valid - key0;                 // keys of the block that exist
-                bits[u] = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : ((1u << left) - 1u));
-            } else {
-                const int col = tt * C::T + key0;
-                bits[u] = (uint32_t)(((col >> 6) ? mrow[1] : mrow[0]) >> (col & 63));
-            }
-        }
+        rest_bits(it, bits);
         attn_tile<D, QBP, NS, 1, F8, false>(ring, la, qs, tail ? c_pre : p.c, g, bits, tail ? vs_pre : 1.f);
         __syncthreads();
     }
+    }
+    // (requested here: at the start the wait for the first keys' addresses would include it)
+    const uint32_t ws_tag = p.fold ? __hip_atomic_load(p.ws_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) : WS_TAG;
 
     // ---- merge the key groups of each query block through LDS (layout [c/4][query] keeps lanes contiguous) ----
     float l_tot = half_swap_sum(qs.l_run);
