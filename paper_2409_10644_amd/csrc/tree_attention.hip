@@ -47,6 +47,9 @@ struct AttnParams {
     int32_t hpw;      // query heads one workgroup of the bf16 sweep serves (they share its K/V stream)
     int32_t bph;      // 32-row query blocks per query head in a workgroup (1, 2 or 4); QBP = bph * hpw
     int32_t chunks;   // grp / hpw: workgroup units per key/value head
+    uint32_t mul_chunks, shift_chunks;   // its reciprocal (see fast_div), and that of tps
+    uint32_t mul_tps, shift_tps;
+    int32_t log2_bph;
     int32_t pair_cus; // > 0: compute units; the grid has more workgroups than that and no separate tree workgroup (see the kernel)
     int32_t xcc;      // accelerator dies the hardware deals workgroup ids to round-robin (>= 1)
     int32_t fold;     // 1: the workgroup of a (sequence, unit) that finishes last folds the partial results itself
@@ -267,9 +270,9 @@ struct SweepCfg {
     static constexpr int KS = D / 16;                  // k-steps of S^T = K Q^T
     static constexpr int CB = D / 32;                  // 32-row blocks of O^T
     static constexpr int CPT = T * BCPR / THREADS;     // 16-byte bf16 chunks per thread for K (same for V), register path
-    static constexpr int MSLOT = 32 * D * 4 + 256;     // LDS bytes to hand one query block's (O, m, l) to another wavefront
+    static constexpr int XCHG = (KG - 1) * QBP * 32 * D * 4;   // LDS bytes in which key groups hand over their outputs; maxima and denominators follow
     static constexpr int RING = NS * TILE > 2 * BTILE_K ? NS * TILE : 2 * BTILE_K;
-    static constexpr int LDS_BYTES = RING > (KG - 1) * QBP * MSLOT ? RING : (KG - 1) * QBP * MSLOT;
+    static constexpr int LDS_BYTES = RING > XCHG + 1024 ? RING : XCHG + 1024;
     static_assert(NI >= 1 && CPT >= 1 && (NS - 2) * DPT < 64 && LDS_BYTES <= 160 * 1024 - 64, "tile does not map onto the workgroup");
     static_assert(!F8 || D == 128, "fp8 tiles are laid out for 128-byte rows");
 };
@@ -624,6 +627,11 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
     int s = wg - bhi * G;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // the same in all lanes: keep it in a scalar register
+    // The rest of the argument block is needed here, before the loads below leave: scalar loads come back in any order, so a
+    // wait for one is a wait for all.
+    asm("" : "+s"(bhi) : "s"(p.q), "s"(p.kt), "s"(p.vt), "s"(p.kp), "s"(p.vp), "s"(p.mask_bits), "s"(p.mask_words), "s"(p.n), "s"(p.Hq),
+        "s"(p.Hkv), "s"(p.grp), "s"(p.hpw), "s"(p.bph), "s"(p.chunks), "s"(p.mul_chunks), "s"(p.shift_chunks), "s"(p.log2_bph),
+        "s"(p.S), "s"(p.tree_last), "s"(p.row0), "s"(p.node_stride), "s"(p.head_stride), "s"(p.mul_tps), "s"(p.shift_tps));
     if (how & HOW_PAIR) {
         const int total = gridDim.x;
         // More workgroups than compute units.  Up to two per compute unit they are all resident at once, and on this
@@ -660,6 +668,8 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
         s = cls % p.S;
         bhi = (cls / p.S) * H + (r - rank * H);
     }
+    bhi = __builtin_amdgcn_readfirstlane(bhi);              // (uniform, and the compiler has to know)
+    s = __builtin_amdgcn_readfirstlane(s);
     if (bhi >= BH) return;                                   // a slot of a grid rounded up to whole dies
     const int b = fast_div(bhi, mul_H, how_shift_H(how)), h = bhi - b * H;
 
@@ -667,53 +677,29 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
     const int qb = wave % QBP, kg = wave / QBP;
 
     int L = lens[b];
-    const int64_t seq_at = seq_base[b];
-    L = L < 0 ? 0 : (L > max_prefix ? max_prefix : L);
-    const int tiles_b = (L + C::T - 1) / C::T;              // (tps is fixed per call: short sequences use fewer splits)
-    const bool sep = G > p.S;                               // the tree's own keys have a workgroup of their own
-    const int np = (tiles_b + tps - 1) / tps;               // prefix splits that have keys for this sequence (<= S)
-    const bool tree_wg = sep ? s == p.S : s == (p.tree_last ? max(np, 1) - 1 : 0);
-    const int t0 = (sep && tree_wg) ? tiles_b : min(s * tps, tiles_b), t1 = min(t0 + tps, tiles_b);
-    const int n_tree_tiles = tree_wg ? (p.n + C::T - 1) / C::T : 0;
-    const int n_pre = t1 - t0;
-    if (n_pre + n_tree_tiles == 0) return;                  // this split has no keys
-    const int n_active = sep ? np + 1 : max(1, np);         // partial results of this sequence: slots 0 .. n_active-1
-    const int slot_id = (sep && tree_wg) ? np : s;
-    // leading tiles of this split that are full (only the sequence's last tile can be ragged)
-    const int n_hot = (n_pre > 0 && t1 * C::T > L) ? n_pre - 1 : n_pre;
-
+    int64_t seq_at = seq_base[b];
+    __builtin_amdgcn_sched_barrier(0);
     const int64_t bh = bhi;                                  // workgroup unit: indexes the partial results
-    const int kvh = p.chunks == 1 ? h : h / p.chunks;          // key/value head of this unit
-    const int hq = kvh * p.grp + (h % p.chunks) * p.hpw + qb / p.bph;   // query head of this wavefront's block
+    const int kvh = fast_div(h, p.mul_chunks, p.shift_chunks); // key/value head of this unit
+    const int hq = kvh * p.grp + (h - kvh * p.chunks) * p.hpw + (qb >> p.log2_bph);   // query head of this wavefront's block
     const int64_t bh_kv = (int64_t)b * p.Hkv + kvh, bh_q = (int64_t)b * p.Hq + hq;
     const __bf16 *q = (const __bf16 *)p.q + bh_q * p.node_stride * D;
     const __bf16 *kt = (const __bf16 *)p.kt + bh_kv * p.node_stride * D;
     const __bf16 *vt = (const __bf16 *)p.vt + bh_kv * p.node_stride * D;
-    const int64_t pre0 = seq_at + (int64_t)kvh * p.head_stride;     // in elements: 2 bytes each, 1 when fp8
-    const unsigned char *kp = (const unsigned char *)p.kp + pre0 * (F8 ? 1 : 2);
-    const unsigned char *vp = (const unsigned char *)p.vp + pre0 * (F8 ? 1 : 2);
-    // softmax scale of a prefix tile and the factor its V values carry; the tree's own tiles use p.c and 1
-    const float c_pre = F8 ? p.c * p.k_scale : p.c, vs_pre = F8 ? p.v_scale : 1.f;
-
-    // query block of this wavefront; mask row of this lane's query (zero for padded rows)
+    // Query block of this wavefront; mask row of this lane's query.  A padded row (beyond the last) is the last one again, unwritten.
     QBlock<D> qs;
-    const int qrow = p.row0 + (qb % p.bph) * 32 + ln;
+    const int qrow = p.row0 + (qb & (p.bph - 1)) * 32 + ln, qclamped = min(qrow, p.n - 1);
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks) {
-        uint4 v = make_uint4(0, 0, 0, 0);
         // Columns of k-step ks in lane half g: 16 ks + 8 g .. +7.  With an fp8 prefix cache the halves trade places
         // with the k-step's parity, 32 (ks/2) + 16 g + 8 (ks%2) .. +7, so that a lane's columns of two consecutive
         // k-steps are 16 consecutive bytes of an fp8 row (one conflict-free 16-byte LDS read); the contraction is
         // over all columns either way.
         const int col = F8 ? (ks >> 1) * 32 + g * 16 + (ks & 1) * 8 : ks * 16 + g * 8;
-        if (qrow < p.n) v = *(const uint4 *)(q + (int64_t)qrow * D + col);
-        qs.q[ks] = __builtin_bit_cast(bf16x8_t, v);
+        qs.q[ks] = *(const bf16x8_t *)(q + (int64_t)qclamped * D + col);
     }
-    uint64_t mrow[2] = {0, 0};
-    if (qrow < p.n) {
-        mrow[0] = p.mask_bits[(int64_t)qrow * p.mask_words];
-        if (p.mask_words > 1) mrow[1] = p.mask_bits[(int64_t)qrow * p.mask_words + 1];
-    }
+    uint64_t mrow[2] = {p.mask_bits[(int64_t)qclamped * p.mask_words], p.mask_bits[(int64_t)qclamped * p.mask_words + p.mask_words - 1]};
+    asm volatile("" ::: "memory");                          // (requested here, not where they are first used)
 #pragma unroll
     for (int cb = 0; cb < C::CB; ++cb) qs.o[cb] = (f32x16_t){0};
     qs.m_ref = -INFINITY;
@@ -737,11 +723,6 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
             la.v8 = row8 * C::RBP + ((grp ^ swz8(row8)) * 16) + (j & 1) * 8;
         }
     }
-    uint32_t all_keys[C::KPW];
-#pragma unroll
-    for (int u = 0; u < C::KPW; ++u) all_keys[u] = 0xffffffffu;
-
-    // ---- keys: HBM -> LDS directly, NS - 1 tiles ahead of the compute ----
     // Lane's source offset inside a tile for instruction 0: row wave * RPI + lane / CPR, logical chunk (lane % CPR) ^ swz(row);
     // instruction i covers the rows i * WAVES * RPI further down, whose swizzle is the same.
     constexpr int STEP = C::WAVES * C::RPI;
@@ -751,16 +732,43 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
 #pragma unroll
     for (int i = 0; i < C::NI; ++i) {
         goffs[i] = goff + (uint32_t)(i * STEP * C::RBP);
-        asm("" : "+v"(goffs[i]));
+        asm volatile("" : "+v"(goffs[i]));
     }
     static_assert(STEP % (F8 || D == 128 ? 16 : 8) == 0, "the swizzle repeats");
+    asm volatile("" : "+v"(la.k), "+v"(la.v));
+    asm volatile("" : "+s"(L), "+s"(seq_at));               // (keeps everything above where it is)
+    L = L < 0 ? 0 : (L > max_prefix ? max_prefix : L);
+    const int tiles_b = (int)((unsigned)(L + C::T - 1) / C::T);   // (tps is fixed per call: short sequences use fewer splits)
+    const bool sep = G > p.S;                               // the tree's own keys have a workgroup of their own
+    const int np = fast_div(tiles_b + tps - 1, p.mul_tps, p.shift_tps);   // prefix splits that have keys for this sequence (<= S)
+    const bool tree_wg = sep ? s == p.S : s == (p.tree_last ? max(np, 1) - 1 : 0);
+    const int t0 = (sep && tree_wg) ? tiles_b : min(s * tps, tiles_b), t1 = min(t0 + tps, tiles_b);
+    const int n_tree_tiles = tree_wg ? (p.n + C::T - 1) / C::T : 0;
+    const int n_pre = t1 - t0;
+    if (n_pre + n_tree_tiles == 0) return;                  // this split has no keys
+    const int n_active = sep ? np + 1 : max(1, np);         // partial results of this sequence: slots 0 .. n_active-1
+    const int slot_id = (sep && tree_wg) ? np : s;
+    // leading tiles of this split that are full (only the sequence's last tile can be ragged)
+    const int n_hot = (n_pre > 0 && t1 * C::T > L) ? n_pre - 1 : n_pre;
+
+    const int64_t pre0 = seq_at + (int64_t)kvh * p.head_stride;     // in elements: 2 bytes each, 1 when fp8
+    const unsigned char *kp = (const unsigned char *)p.kp + pre0 * (F8 ? 1 : 2);
+    const unsigned char *vp = (const unsigned char *)p.vp + pre0 * (F8 ? 1 : 2);
+    // softmax scale of a prefix tile and the factor its V values carry; the tree's own tiles use p.c and 1
+    const float c_pre = F8 ? p.c * p.k_scale : p.c, vs_pre = F8 ? p.v_scale : 1.f;
+
+    uint32_t all_keys[C::KPW];
+#pragma unroll
+    for (int u = 0; u < C::KPW; ++u) all_keys[u] = 0xffffffffu;
+
+    // ---- keys: HBM -> LDS directly, NS - 1 tiles ahead of the compute ----
     // Every workgroup walks its full tiles in a rotated order (soft-max does not care): workgroups that start
     // together would otherwise sweep their equally aligned K/V streams in lock-step and crowd the same
     // memory channels.  `nxt` is the full tile the next request fetches.
     // Workgroups that stream the same keys for different query heads keep step instead: the second finds them in L2
     // (16 sequences of 512-4096 keys, 32 query heads over 8: 69 -> 65 us).
     const unsigned turn = p.chunks == 1 ? (unsigned)wg : (unsigned)((int)bh_kv * G + s);
-    int nxt = n_hot > 0 ? (int)((turn * 37u) % (unsigned)n_hot) : 0;
+    int nxt = (int)(((turn * 37u) & 127u) * (unsigned)n_hot >> 7);
     const unsigned char *ksrc = kp + (int64_t)t0 * C::TILE_K, *vsrc = vp + (int64_t)t0 * C::TILE_K;
     // (uniform tile base + 32-bit lane offset: a load takes its base from scalar registers)
     const unsigned char *kbase = ksrc + (int64_t)nxt * C::TILE_K, *vbase = vsrc + (int64_t)nxt * C::TILE_K;
@@ -795,7 +803,7 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
                 bits[u] = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : ((1u << left) - 1u));
             } else {
                 const int col = (i - n_tail) * C::T + key0;
-                bits[u] = (uint32_t)(((col >> 6) ? mrow[1] : mrow[0]) >> (col & 63));
+                bits[u] = (uint32_t)(((col >> 6) ? (p.mask_words > 1 ? mrow[1] : 0) : mrow[0]) >> (col & 63));
             }
         }
     };
@@ -924,87 +932,93 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
     // (requested here: at the start the wait for the first keys' addresses would include it)
     const uint32_t ws_tag = p.fold ? __hip_atomic_load(p.ws_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) : WS_TAG;
 
-    // ---- merge the key groups of each query block through LDS (layout [c/4][query] keeps lanes contiguous) ----
+    // ---- merge the key groups of each query block through LDS ----
+    // A wavefront's output is CB * 4 pieces (16 bytes per lane: four columns of one query); key group kg ends up with pieces
+    // kg * PP .. of all groups.  Every group hands over the pieces that are not its own, so all wavefronts merge and store
+    // (one of them merging everything: 0.65 us for two groups, 0.9 us for four).
+    constexpr int PP = C::CB * 4 / C::KG;
     float l_tot = half_swap_sum(qs.l_run);
-    if (C::KG > 1) {
-        if (kg > 0) {
-            unsigned char *slot = ring + ((kg - 1) * QBP + qb) * C::MSLOT;
+    const float cm = F8 ? 1.f : p.c;                           // reference maxima are in log2 units already with fp8 tiles
+    f32x4_t acc[PP];
+    const auto piece = [&](int x) {
+        f32x4_t v;
 #pragma unroll
-            for (int cb = 0; cb < C::CB; ++cb)
+        for (int e = 0; e < 4; ++e) v[e] = qs.o[x >> 2][4 * (x & 3) + e];
+        return v;
+    };
+    if constexpr (C::KG == 1) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    f32x4_t v;
+        for (int x = 0; x < PP; ++x) acc[x] = piece(x);
+    } else {
+        float *ml = (float *)(ring + C::XCHG);                  // [key group][query block][m: 32, l: 32]
+        // pieces for owner o from the key group that is number r among the others
+        auto at = [&](int o, int r, int x) { return (f32x4_t *)(ring + ((((o * (C::KG - 1) + r) * QBP + qb) * PP + x) * 64 + lane) * 16); };
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = qs.o[cb][4 * j + e];
-                    *(f32x4_t *)(slot + (((cb * 4 + j) * 2 + g) * 32 + ln) * 16) = v;
-                }
-            if (g == 0) {
-                ((float *)(slot + 32 * D * 4))[ln] = qs.m_ref;
-                ((float *)(slot + 32 * D * 4))[32 + ln] = l_tot;
+        for (int o = 0; o < C::KG; ++o) {
+            if (o == kg) {
+#pragma unroll
+                for (int x = 0; x < PP; ++x) acc[x] = piece(o * PP + x);
+            } else {
+#pragma unroll
+                for (int x = 0; x < PP; ++x) *at(o, kg < o ? kg : kg - 1, x) = piece(o * PP + x);
             }
+        }
+        if (g == 0) {
+            ml[(kg * QBP + qb) * 64 + ln] = qs.m_ref;
+            ml[(kg * QBP + qb) * 64 + 32 + ln] = l_tot;
         }
         __syncthreads();
-    }
-    // wavefronts of key group 0 now own one query block each; the others are done
-    const float cm = F8 ? 1.f : p.c;                           // reference maxima are in log2 units already with fp8 tiles
-    auto merge_from = [&](const float *src_o, float m_k, float l_k) {
-        // (O, m, l) of the same query block from elsewhere, fragments in this lane's register layout
-        const float m_new = fmaxf(qs.m_ref, m_k);
-        const bool any = m_new != -INFINITY;                  // false: neither side has seen a key
-        const float a = any ? fast_exp2((qs.m_ref - m_new) * cm) : 1.f, bsc = any ? fast_exp2((m_k - m_new) * cm) : 0.f;
-        qs.m_ref = m_new;
-        l_tot = l_tot * a + l_k * bsc;
+        float m[C::KG], l[C::KG], M = -INFINITY;
 #pragma unroll
-        for (int cb = 0; cb < C::CB; ++cb)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const f32x4_t v = *(const f32x4_t *)(src_o + (((cb * 4 + j) * 2 + g) * 32 + ln) * 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) qs.o[cb][4 * j + e] = qs.o[cb][4 * j + e] * a + v[e] * bsc;
-            }
-    };
-    if (kg == 0) {
-#pragma unroll 1
-        for (int k = 1; k < C::KG; ++k) {
-            const unsigned char *slot = ring + ((k - 1) * QBP + qb) * C::MSLOT;
-            merge_from((const float *)slot, ((const float *)(slot + 32 * D * 4))[ln], ((const float *)(slot + 32 * D * 4))[32 + ln]);
+        for (int k = 0; k < C::KG; ++k) {
+            m[k] = ml[(k * QBP + qb) * 64 + ln];
+            l[k] = ml[(k * QBP + qb) * 64 + 32 + ln];
+            M = fmaxf(M, m[k]);
         }
+        const float Mf = M == -INFINITY ? 0.f : M;              // (nobody has seen a key: every weight is exp2(-inf) = 0)
+        l_tot = 0.f;
+#pragma unroll
+        for (int k = 0; k < C::KG; ++k) l_tot = fmaf(l[k], fast_exp2((m[k] - Mf) * cm), l_tot);
+        const float own = fast_exp2((qs.m_ref - Mf) * cm);
+#pragma unroll
+        for (int x = 0; x < PP; ++x) acc[x] *= own;
+#pragma unroll
+        for (int r = 0; r < C::KG - 1; ++r) {
+            const float w = fast_exp2((ml[((r < kg ? r : r + 1) * QBP + qb) * 64 + ln] - Mf) * cm);
+#pragma unroll
+            for (int x = 0; x < PP; ++x) acc[x] += *at(kg, r, x) * w;
+        }
+        qs.m_ref = M;
     }
-    auto store_out = [&]() {
+    if (n_active == 1) {                                   // the only split of this sequence: no exchange needed
         if (qrow >= p.n) return;
         const float inv = 1.f / l_tot;
         __bf16 *o = (__bf16 *)p.out + (bh_q * p.node_stride + qrow) * D;
 #pragma unroll
-        for (int cb = 0; cb < C::CB; ++cb)
+        for (int x = 0; x < PP; ++x) {
+            bf16x4_t v;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                bf16x4_t v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = (__bf16)(qs.o[cb][4 * j + e] * inv);
-                *(bf16x4_t *)(o + cb * 32 + 8 * j + 4 * g) = v;
-            }
-    };
-    if (n_active == 1) {                                   // the only split of this sequence: no exchange needed
-        if (kg == 0) store_out();
+            for (int e = 0; e < 4; ++e) v[e] = (__bf16)(acc[x][e] * inv);
+            const int y = kg * PP + x;
+            *(bf16x4_t *)(o + (y >> 2) * 32 + 8 * (y & 3) + 4 * g) = v;
+        }
         return;
     }
 
     // ---- key splits: every split writes (O, m, l) in register-fragment order (fully coalesced) ----
-    if (kg == 0 && qrow < p.n) {                           // padded query rows are never read back
+    if (qrow < p.n) {                                      // padded query rows are never read back
         // O goes out rounded to bf16, the precision the output itself has (one more rounding of 2^-9 relative to the
         // partial's own magnitude; maxima and denominators stay fp32): half the bytes to write, acknowledge and fold.
-        // A lane's 16-byte chunk (cb, jp) holds its accumulator registers 8 jp .. 8 jp + 7 of column block cb.
+        // A lane's 16-byte chunk is two pieces.
         __bf16 *po = (__bf16 *)p.part_o + ((bh * p.SP + slot_id) * (int64_t)(QBP * 32 * D)) + qb * 32 * D;
 #pragma unroll
-        for (int cb = 0; cb < C::CB; ++cb)
+        for (int x2 = 0; x2 < PP / 2; ++x2) {
+            bf16x8_t v;
 #pragma unroll
-            for (int jp = 0; jp < 2; ++jp) {
-                bf16x8_t v;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = (__bf16)qs.o[cb][8 * jp + e];
-                *(bf16x8_t *)(po + (((cb * 2 + jp) * 2 + g) * 32 + ln) * 8) = v;
-            }
-        if (g == 0) {
+            for (int e = 0; e < 8; ++e) v[e] = (__bf16)acc[2 * x2 + (e >> 2)][e & 3];
+            *(bf16x8_t *)(po + (((kg * (PP / 2) + x2) * 2 + g) * 32 + ln) * 8) = v;
+        }
+        if (kg == 0 && g == 0) {
             const int64_t prow = (bh * p.SP + slot_id) * (QBP * 32) + qb * 32 + ln;
             p.part_m[prow] = qs.m_ref;
             p.part_l[prow] = l_tot;
@@ -1046,8 +1060,8 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
     __syncthreads();
     const unsigned long long prev = s_prev;
     if ((int)(prev & 0xffu) + 1 != n_active) return;       // someone else arrives later
+    asm volatile("" ::: "memory");                         // (the loads below go past the L1: nothing to invalidate)
     if (tid == 0) __hip_atomic_store(p.ctr + bh * CTR_STRIDE, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // as it was found
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     if ((int)((prev >> (8 + 7 * die)) & 0x7fu) + 1 != n_active) {   // an arrival from another die
         store_nan();
         return;
@@ -1579,6 +1593,9 @@ int attention_call(const mcsd_attention_tuning_t *tune, const mcsd_mask_view_t *
     p.mask_bits = mask->bits_dev; p.mask_words = mask->words_per_row;
     p.B = B; p.H = pl.units; p.n = n; p.row0 = row_begin; p.max_prefix = max_prefix;
     p.Hq = H_q; p.Hkv = H_kv; p.grp = H_q / H_kv; p.hpw = pl.hpw; p.bph = pl.bph; p.chunks = pl.chunks;
+    p.log2_bph = pl.bph == 4 ? 2 : pl.bph - 1;
+    const FastDiv chunks = fast_div_of(pl.chunks);
+    p.mul_chunks = chunks.mul; p.shift_chunks = chunks.shift;
     p.node_stride = node_stride; p.head_stride = head_stride;
     p.c = softmax_scale * 1.4426950408889634f;
     p.k_scale = f8 ? k_scale : 1.f;
@@ -1590,6 +1607,8 @@ int attention_call(const mcsd_attention_tuning_t *tune, const mcsd_mask_view_t *
     p.fold = pl.fold;
     p.tps = (int32_t)((((int64_t)max_prefix + pl.T - 1) / pl.T + pl.S - 1) / pl.S);
     if (p.tps < 1) p.tps = 1;
+    const FastDiv tps = fast_div_of(p.tps);
+    p.mul_tps = tps.mul; p.shift_tps = tps.shift;
     char *w = (char *)workspace;
     p.part_o = p.part_m = p.part_l = nullptr;
     p.ctr = nullptr;
