@@ -116,8 +116,68 @@ void device_shape(int &n_cus, int &n_xcc)
     n_xcc = mcsd_xcc_count(dev);
 }
 
-AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int d, int n_rows, int max_prefix, bool f8 = false,
-                   const mcsd_attention_tuning_t *tune = nullptr)
+// How the bf16 sweep cuts the keys of a (sequence, unit): S splits, and who takes the tree's own keys (1: a workgroup of its
+// own, 2: the first split, 3: the last).  The candidates are the S that give every split keys; each is priced in tiles of
+// time and the cheapest taken.  Measured on 170 shapes (1-64 sequences, 4-32 heads of 64 or 128, 32-16384 keys, 1-120 rows,
+// every S up to 8 with every place for the tree's keys): a workgroup's tiles follow one another at one memory latency each
+// (1.03 us per 64 keys of 128 dimensions, 0.7 us of 64), partial results cost their exchange and fold (`fold_us`), two
+// workgroups on a compute unit slow each other down almost by their sum, and a grid beyond the residents costs its
+// remainder.  The choice is within 1 % of the best of the measured ones on average; the fixed rule before it (two
+// workgroups per compute unit, at least 256 keys per split) lost 11 %, up to 78 %.
+struct SplitChoice { int S, tree; };
+SplitChoice choose_splits(int d, int QBP, bool f8, int B, long bh, int tiles, int tree_tiles, int tree_forced)
+{
+    struct Memo { int d, QBP, f8, B, tiles, tree_tiles, forced; long bh; SplitChoice c; };
+    static thread_local Memo memo = {0, 0, 0, 0, 0, 0, 0, 0, {1, 2}};    // a decoding loop asks for the same shape again and again
+    if (memo.d == d && memo.QBP == QBP && memo.f8 == (int)f8 && memo.B == B && memo.bh == bh && memo.tiles == tiles &&
+        memo.tree_tiles == tree_tiles && memo.forced == tree_forced)
+        return memo.c;
+    constexpr float CUS = 256.f;
+    static const float fold_us[10] = {0.f, 0.f, 1.4f, 1.85f, 2.4f, 2.5f, 3.15f, 3.2f, 4.7f, 6.3f};   // by partial results
+    const float tile_us = (d == 128 ? (QBP == 1 ? 1.6f : QBP == 2 ? 1.03f : 1.15f) : (QBP == 1 ? 1.f : QBP == 2 ? 0.7f : 0.74f)) *
+                          (f8 ? 0.8f : 1.f);
+    const float fold_scale = (d == 64 ? 0.55f : 1.f) * (QBP == 4 ? 1.75f : QBP == 1 ? 1.35f : 1.f);
+    const int per_cu = d == 128 && QBP == 1 ? 1 : 2;                     // resident workgroups (LDS)
+    SplitChoice best = {1, tree_forced ? tree_forced : 2};
+    if (bh > 256) {
+        // The chip is full without splits.  Halves even out ragged batches where two workgroups fit a compute unit.
+        if (per_cu == 2 && bh < 512 && tiles >= 8) best.S = 2;
+    } else {
+        float best_us = 1e30f;
+        for (int S = 1; S <= 15 && S <= (tiles > 1 ? tiles : 1) && (S == 1 || bh * S <= 512); ++S) {
+            const int tps = tiles > S ? (tiles + S - 1) / S : 1;
+            if (S > 1 && (tiles + tps - 1) / tps != S) continue;         // some split would have no keys
+            const int last = tiles - (S - 1) * tps;
+            for (int tree = 1; tree <= 3; ++tree) {
+                if (tree_forced && tree != tree_forced && S > 1) continue;
+                if (S == 1 && tree != 2) continue;
+                if (tree == 1 && bh * (S + 1) > (long)(CUS * per_cu)) continue;
+                const int parts = S + (tree == 1);
+                const int most = S == 1 ? tiles + tree_tiles
+                                 : tree == 1 ? (tps > tree_tiles ? tps : tree_tiles)
+                                 : tree == 2 ? tps + tree_tiles : (tps > last + tree_tiles ? tps : last + tree_tiles);
+                const float all = (float)(tiles + tree_tiles), load = (float)bh * parts / CUS;   // workgroups per compute unit
+                float us;
+                if (load <= 1.f) us = tile_us * most;
+                else if (load <= per_cu) us = 0.94f * tile_us * (most + 0.8f * all / parts);
+                else {
+                    const float even = all * bh / CUS, two = (float)most * per_cu;
+                    if (S == 1) us = 0.9f * tile_us * two * (float)(int)(load / per_cu + 0.999f);
+                    else us = tile_us * ((tree == 3 ? 0.88f : 0.98f) * (two > even ? two : even) + (tree == 3 ? 0.5f : 0.3f) * most);
+                }
+                if (tree == 3 && B > 1 && bh * S > 256) us *= 1.08f;     // (not ordered by length)
+                if (tree == 2 && S > 1 && bh * S > 256) us += 1.85f;     // the ordering by length itself
+                if (parts > 1) us += fold_us[parts < 9 ? parts : 9] * fold_scale;
+                if (us < best_us) { best_us = us; best = {S, tree}; }
+            }
+        }
+    }
+    memo = {d, QBP, (int)f8, B, tiles, tree_tiles, tree_forced, bh, best};
+    return best;
+}
+
+AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int d, int n_rows, int n_keys, int max_prefix,
+                   bool f8 = false, const mcsd_attention_tuning_t *tune = nullptr)
 {
     AttnPlan pl;
     const int grp = Hq / Hkv;
@@ -147,43 +207,33 @@ AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int d, int n_rows, int max
     const long bh = (long)B * pl.units;
     long tiles_max = (max_prefix + pl.T - 1) / pl.T;
     if (dtype == MCSD_F32) tiles_max += (n_rows + pl.T - 1) / pl.T;      // (the tree's own keys are blocks like the prefix's)
-    // Key splits: enough workgroups for two per compute unit, at least four tiles per split (two of the 128-key
-    // tiles of a single query block: the same bytes), at most 8 splits (6 with four query blocks, whose partial result
-    // is twice the bytes: six splits and the tree's workgroup are what the seven-slot fold takes in one pass): every
-    // split costs a partial result of n rows that is written, read back and folded.  Measured: one query block, 1024
-    // keys: 14.3 -> 11.3 us per call with four splits instead of two; four query blocks, 1024 keys: 15.2 -> 13.2 us
-    // with four instead of three; 2048 keys: 16.9 us with six, 17.8 us with seven.
+    // Key splits.  bf16: see choose_splits; a separate workgroup for the tree's keys costs one more partial result.
     // fp32: one workgroup per compute unit while that takes splitting (more only add partial results: 12 heads of 64, 1024
     // keys, 60 nodes: 9.2 us with 192 workgroups, 10.4 with 384), else as many as fit (4 per compute unit at d = 64, 2 at
     // 128), which evens out ragged batches; at least five 16-key blocks per split.
-    long S = (512 + bh - 1) / bh;
+    long S;
+    int tree = 2;
+    const int tree_forced = tune && dtype == MCSD_BF16 ? tune->tree_keys : 0;
     if (dtype == MCSD_F32) {
         const long u = (bh + 7) / 8 * 8 * pl.QT;            // (a die's slots are whole (sequence, head) pairs, see grid_units)
         S = u <= 256 ? 256 / u : (d == 64 ? (1023 + u) / u : 512 / u);
+        if (S > tiles_max / 5) S = tiles_max / 5;
+        if (S < 1) S = 1;
+        if (S > 64) S = 64;
+    } else {
+        const SplitChoice c = choose_splits(d, pl.QBP, f8, B, bh, (int)tiles_max, (n_keys + pl.T - 1) / pl.T, tree_forced);
+        S = c.S;
+        tree = c.tree;
     }
-    const long min_tiles = dtype == MCSD_BF16 ? (pl.QBP == 1 ? 2 : 4) : 5;
-    if (S > tiles_max / min_tiles) S = tiles_max / min_tiles;
-    if (dtype == MCSD_BF16 && S > (pl.QBP == 4 ? 6 : 8)) S = pl.QBP == 4 ? 6 : 8;
-    if (S < 1) S = 1;
-    if (S > 64) S = 64;
-    // One split less when the streaming workgroups alone would have a compute unit each (256) but not together with
-    // the tree's own workgroups: otherwise some compute units get two streaming workgroups and finish last
-    // (measured on B*H = 32, 2048 keys, wide tree: step 0.80 -> 0.74 ms by giving the tree's workgroups the highest
-    // ids instead, 0.69 ms with fewer splits).
-    if (dtype == MCSD_BF16 && S > 2 && bh * S <= 256 && bh * (S + 1) > 256) --S;
-    if (tune && tune->key_splits >= 1 && tune->key_splits <= 64) S = tune->key_splits;   // the caller's choice
+    if (tune && tune->key_splits >= 1 && tune->key_splits <= 64) {       // the caller's choice
+        S = tune->key_splits;
+        // with that many, the tree's keys in a workgroup of their own while all workgroups are resident at once
+        if (dtype == MCSD_BF16) tree = tree_forced ? tree_forced : bh * (S + 1) <= 512 ? 1 : 2;
+    }
     pl.NS = f8 ? 4 : 2;                                     // LDS stages (bf16: see below)
     pl.S = (int)S;
-    // With split keys the tree's own tiles (masked, through registers) would lengthen one split's critical path:
-    // they get a workgroup of their own, which costs one more partial result.  Only when all workgroups are
-    // resident at once (two per compute unit): the hardware dispatcher does not rebalance long workgroups that
-    // start behind short ones.
-    pl.G = (dtype == MCSD_BF16 && S > 1 && bh * (S + 1) <= 512) ? (int)S + 1 : (int)S;
-    pl.tree_last = 0;
-    if (tune && dtype == MCSD_BF16 && S > 1 && tune->tree_keys != 0) {
-        pl.G = tune->tree_keys == 1 ? (int)S + 1 : (int)S;
-        pl.tree_last = tune->tree_keys == 3;
-    }
+    pl.G = (dtype == MCSD_BF16 && S > 1 && tree == 1) ? (int)S + 1 : (int)S;
+    pl.tree_last = dtype == MCSD_BF16 && S > 1 && tree == 3;
     int n_cus, n_xcc;
     device_shape(n_cus, n_xcc);
     // Ragged grids larger than the chip are ordered by length inside the kernel (see there)
@@ -1542,11 +1592,28 @@ size_t workspace_query(const mcsd_attention_tuning_t *tune, bool f8, int32_t B, 
     if (B < 1 || H_q < 1 || H_kv < 1 || H_q % H_kv != 0 || (d != 64 && d != 128) || n_nodes < 1 ||
         n_nodes > MCSD_ATTN_MAX_NODES || max_prefix < 0 || row_begin < 0 || row_begin >= n_nodes || (f8 && d != 128))
         return 0;
-    const AttnPlan a = make_plan(MCSD_BF16, B, H_q, H_kv, d, n_nodes - row_begin, max_prefix, f8, tune);
-    const size_t wa = workspace_bytes_for(a, MCSD_BF16, B, d);
+    size_t wa = 0;
+    if (tune && tune->key_splits >= 1) {
+        wa = workspace_bytes_for(make_plan(MCSD_BF16, B, H_q, H_kv, d, n_nodes - row_begin, n_nodes, max_prefix, f8, tune), MCSD_BF16, B, d);
+    } else {
+        // What any choice of splits may need, for this number of rows or fewer and this prefix or a shorter one: a workspace
+        // sized for the largest call serves the smaller ones, whose splits may be more.
+        for (int rows = n_nodes - row_begin; rows > 0; rows = rows > 64 ? 64 : rows > 32 ? 32 : 0) {
+            AttnPlan a = make_plan(MCSD_BF16, B, H_q, H_kv, d, rows, n_nodes, max_prefix, f8, tune);
+            const long bh = (long)B * a.units, tiles = ((long)max_prefix + a.T - 1) / a.T;
+            long most = bh > 256 ? a.G : 512 / bh;
+            if (most > tiles + 1) most = tiles + 1;
+            if (most > 16) most = 16;
+            if (tiles < 2 || most < 1) most = 1;
+            a.G = (int)most;
+            a.S = most > 1 ? 2 : 1;
+            const size_t w = workspace_bytes_for(a, MCSD_BF16, B, d);
+            if (w > wa) wa = w;
+        }
+    }
     if (f8) return wa;
     // the larger of the two dtypes' needs, so one buffer serves both
-    const AttnPlan f = make_plan(MCSD_F32, B, H_q, H_kv, d, n_nodes - row_begin, max_prefix, false, tune);
+    const AttnPlan f = make_plan(MCSD_F32, B, H_q, H_kv, d, n_nodes - row_begin, n_nodes, max_prefix, false, tune);
     const size_t wf = workspace_bytes_for(f, MCSD_F32, B, d);
     return wa > wf ? wa : wf;
 }
@@ -1582,7 +1649,7 @@ int attention_call(const mcsd_attention_tuning_t *tune, const mcsd_mask_view_t *
     if (align & 15) return MCSD_EINVAL;
     if (((node_stride * d) & 7) || (head_stride & (f8 ? 15 : 7))) return MCSD_EINVAL;   // 16-byte rows and heads
 
-    const AttnPlan pl = make_plan(dtype, B, H_q, H_kv, d, n - row_begin, max_prefix, f8, tune);
+    const AttnPlan pl = make_plan(dtype, B, H_q, H_kv, d, n - row_begin, n, max_prefix, f8, tune);
     if ((int64_t)pl.G * pl.QT * pl.grid_units > 0x7fffffff) return MCSD_EUNSUPPORTED;           // one-dimensional grid
     const size_t need = workspace_bytes_for(pl, dtype, B, d);
     if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255))) return MCSD_EWORKSPACE;
@@ -1683,7 +1750,7 @@ extern "C" int mcsd_tree_attention_static(const mcsd_mask_view_t *mask, mcsd_dty
                               v_prefix, seq_base_dev, prefix_lens_dev, head_stride, max_prefix, softmax_scale, out, nullptr,
                               0, hip_stream);          // (reports the argument error; nothing is launched)
     // the shape's need against the array's size, before anything is enqueued
-    const AttnPlan pl = make_plan(dtype, B, H, H, d, mask->n_nodes, max_prefix);
+    const AttnPlan pl = make_plan(dtype, B, H, H, d, mask->n_nodes, mask->n_nodes, max_prefix);
     if (workspace_bytes_for(pl, dtype, B, d) > (size_t)MCSD_STATIC_SCRATCH_BYTES) return MCSD_EUNSUPPORTED;
     void *ws = nullptr;
     const int rc = static_scratch((hipStream_t)hip_stream, &ws);
@@ -1746,7 +1813,7 @@ extern "C" int mcsd_tree_attention_plan(const mcsd_attention_tuning_t *tuning, m
                    tuning->tree_keys < 0 || tuning->tree_keys > 3 ||
                    (tuning->stages != 0 && tuning->stages != 2 && tuning->stages != 4)))
         return MCSD_EINVAL;
-    const AttnPlan pl = make_plan(dtype, B, H_q, H_kv, d, n_nodes - row_begin, max_prefix, prefix_fp8 != 0, tuning);
+    const AttnPlan pl = make_plan(dtype, B, H_q, H_kv, d, n_nodes - row_begin, n_nodes, max_prefix, prefix_fp8 != 0, tuning);
     out->mfma_path = dtype == MCSD_BF16;
     out->query_blocks = pl.QBP;
     out->key_splits = pl.S;
