@@ -890,14 +890,18 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
             else if (it + 2 < n_all) issue_rest(it + 2 - n_hot, ring);
             attn_tile<D, QBP, NS, 0, false, false>(ring + C::TILE, la, qs, p.c, g, all_keys);
         }
-        for (; it < n_all; ++it) {                          // an odd full tile among them; one copy of the tile's code, no spills
+        auto rest = [&](int i, unsigned char *stage, unsigned char *other) {
             arrived();
-            unsigned char *stage = ring + (it & 1) * C::TILE, *other = ring + (~it & 1) * C::TILE;
-            if (it + 1 < n_hot) issue_full(other);
-            else if (it + 1 < n_all) issue_rest(it + 1 - n_hot, other);
+            if (i + 1 < n_all) issue_rest(i + 1 - n_hot, other);
             uint32_t bits[C::KPW];
-            rest_bits(it - n_hot, bits);
+            rest_bits(i - n_hot, bits);
             attn_tile<D, QBP, NS, 1, false, false>(stage, la, qs, p.c, g, bits);
+        };
+        while (it < n_all) {                                // an odd full tile among them
+            rest(it, ring, ring + C::TILE);
+            if (__builtin_expect(it + 1 >= n_all, 0)) break;
+            rest(it + 1, ring + C::TILE, ring);
+            it += 2;
         }
         __syncthreads();
         static_assert(!F8, "fp8 tiles use the ring below");
