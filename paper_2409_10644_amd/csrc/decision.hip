@@ -213,19 +213,47 @@ __device__ __forceinline__ int mlp_tail(int n_layers, const int32_t *width, cons
 
 __device__ __forceinline__ float logistic(float z) { return 1.0f / (1.0f + expf(-z)); }
 
+// ---------------------------------------------------------------------------------------------- stop rule, in the launch
+// The stop flag of a tree depends on probabilities that several workgroups write.  For few rows, instead of a second launch
+// behind them (4 us, and 2.5 on the host), each workgroup, once its own probability is where everyone sees it, evaluates the
+// flag from what it finds, writes it and looks again until what it wrote is still true.  The last write is then right: a
+// workgroup that wrote from an old probability either looked again after that probability was replaced, and wrote again, or
+// looked before, and then the workgroup that replaced it looks and writes later still.
+__device__ __forceinline__ void settle_stop(const float *prob, int b, int W, float beta, int32_t *stop, int lane)
+{
+    auto look = [&]() {
+        bool below = true;
+        for (int w = lane; w < W; w += 64) below = below && __hip_atomic_load(prob + (int64_t)b * W + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < beta;
+        return __ballot(!below) == 0 ? 1 : 0;
+    };
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // the probability has arrived
+    int all_below = look();
+    while (true) {                                              // (a probability changes once: at most W + 1 rounds)
+        if (lane == 0) __hip_atomic_store(stop + b, all_below, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const int now = look();
+        if (now == all_below) break;
+        all_below = now;
+    }
+}
+
 // ---------------------------------------------------------------------------------------------- type 2
+// FEW: the launch does not fill the chip, so what counts is one workgroup's chain of steps, not its registers: the threshold
+// comes from 32 maxima in one exchange, one wavefront ranks the candidates, the first layer's weights are in registers before
+// they are needed, the stop flags are settled here.  With 16 rows of 32000, with the flags: 14.3 us -> 9.9 us.  Otherwise other workgroups
+// hide the chain and registers are what counts (a compute unit holds three workgroups).
 // MODE 0: the row lives in registers (V a multiple of 4, <= 32768, 16-byte aligned): one trip to HBM, all loads in
 // flight at once.  MODE 1: float4 loads, MODE 2: scalar loads; both stream the row twice (the second pass is served
 // by the cache).
-template <int MODE>
+template <int MODE, bool FEW>
 __global__ __launch_bounds__(DT) void decision_distribution_kernel(MlpDesc mlp, int W, int V, int k,
                                                                    const float *__restrict__ rows, int64_t batch_stride,
                                                                    int64_t row_stride, float *__restrict__ features,
-                                                                   float *__restrict__ prob)
+                                                                   float *prob, float beta, int32_t *stop)
 {
     constexpr int CAP = MODE == 0 ? CAND_REG : CAND_MEM;
     __shared__ float s_cand[CAP];
-    __shared__ float s_part[NW * K];
+    __shared__ __attribute__((aligned(16))) float s_part[NW * K];
     __shared__ float s_top[K];
     __shared__ double s_ent[NW];
     __shared__ float s_act[2][1][MCSD_MLP_MAX_WIDTH];
@@ -233,7 +261,19 @@ __global__ __launch_bounds__(DT) void decision_distribution_kernel(MlpDesc mlp, 
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = blockIdx.x;
-    const float *y = rows + (int64_t)(m / W) * batch_stride + (int64_t)(m % W) * row_stride;
+    const int tree = m / W;
+    const float *y = rows + (int64_t)tree * batch_stride + (int64_t)(m - tree * W) * row_stride;
+    // two layers: lane j's row of the first and its weight of the second, requested first
+    const bool fused = FEW && mlp.n_layers == 2;
+    float w1[FEW ? K + 1 : 1], b1 = 0.0f, w2 = 0.0f, b2 = 0.0f;
+    if (fused) {
+        const int j = min(tid, mlp.width[1] - 1);
+#pragma unroll
+        for (int u = 0; u <= K; ++u) w1[FEW ? u : 0] = mlp.w[0][j * (k + 1) + min(u, k)];
+        b1 = mlp.b[0][j];
+        w2 = mlp.w[1][j];
+        b2 = mlp.b[1][0];
+    }
 
     float4 reg[MODE == 0 ? REG_F4 : 1];
     if (MODE == 0) {
@@ -280,72 +320,150 @@ __global__ __launch_bounds__(DT) void decision_distribution_kernel(MlpDesc mlp, 
         if (lane == 0) s_ent[wave] = h;
     }
     if (tid == 0) s_cnt = 0;
-    // tau = k-th largest lane maximum: at least k entries of the row are >= tau, and every entry above tau sits in
-    // one of the at most k-1 lanes whose maximum is above it.  First the k largest of every wavefront (those above
-    // its own k-th largest, then copies of that) ...
-    {
-        const unsigned key = order_key(tmax);
-        const unsigned tw = wave_kth_key(key, 0u, k);
-        const unsigned long long above = __ballot(key > tw);
-        const int n_above = __popcll(above);
-        if (key > tw) s_part[wave * K + __popcll(above & ((1ull << lane) - 1ull))] = tmax;
-        if (lane >= n_above && lane < k) s_part[wave * K + lane] = key_value(tw);
-    }
-    __syncthreads();
-    // ... then, in every wavefront for itself, the k-th largest of those 8 k values
     float tau;
-    {
-        const int ia = (lane / k) * K + lane % k, ib = ((lane + 64) / k) * K + (lane + 64) % k;
-        const unsigned ka = lane < NW * k ? order_key(s_part[ia]) : 0u;
-        const unsigned kb = lane + 64 < NW * k ? order_key(s_part[ib]) : 0u;
-        tau = key_value(wave_kth_key(ka, kb, k));
-    }
-
-    // pass 2, only in the lanes that have any: the entries above tau, in any order
-    if (tmax > tau) {
-        int mine = 0;
-        for_each([&](float p, int) { mine += p > tau ? 1 : 0; });
-        int pos = atomicAdd(&s_cnt, mine);
-        if (mine == 1) {                                        // the usual case: the lane's maximum and nothing else
-            if (pos < CAP) s_cand[pos] = tmax;
-        } else {
-            for_each([&](float p, int) {
-                if (p > tau) {
-                    if (pos < CAP) s_cand[pos] = p;
-                    ++pos;
-                }
-            });
+    auto exact_threshold = [&]() {
+        // tau = k-th largest lane maximum: at least k entries of the row are >= tau, and every entry above tau sits in
+        // one of the at most k-1 lanes whose maximum is above it.  First the k largest of every wavefront (those above
+        // its own k-th largest, then copies of that) ...
+        {
+            const unsigned key = order_key(tmax);
+            const unsigned tw = wave_kth_key(key, 0u, k);
+            const unsigned long long above = __ballot(key > tw);
+            const int n_above = __popcll(above);
+            if (key > tw) s_part[wave * K + __popcll(above & ((1ull << lane) - 1ull))] = tmax;
+            if (lane >= n_above && lane < k) s_part[wave * K + lane] = key_value(tw);
         }
-    }
-    __syncthreads();
-
-    // Topk = those candidates by rank (ties in list order), then copies of tau (entries equal to tau exist in
-    // sufficient number), or zeros when the row has fewer than k entries
-    {
-        const int n = min(s_cnt, CAP);
-        for (int i = tid; i < n; i += DT) {
-            const float c = s_cand[i];
-            int rank = 0;
-            for (int j = 0; j < n; ++j) {
-                const float o = s_cand[j];
-                rank += (o > c || (o == c && j < i)) ? 1 : 0;
+        __syncthreads();
+        // ... then, in every wavefront for itself, the k-th largest of those 8 k values
+        {
+            const int ia = (lane / k) * K + lane % k, ib = ((lane + 64) / k) * K + (lane + 64) % k;
+            const unsigned ka = lane < NW * k ? order_key(s_part[ia]) : 0u;
+            const unsigned kb = lane + 64 < NW * k ? order_key(s_part[ib]) : 0u;
+            tau = key_value(wave_kth_key(ka, kb, k));
+        }
+    };
+    auto collect = [&]() {
+        // pass 2, only in the lanes that have any: the entries above tau, in any order
+        if (tmax > tau) {
+            int mine = 0;
+            for_each([&](float p, int) { mine += p > tau ? 1 : 0; });
+            int pos = atomicAdd(&s_cnt, mine);
+            if (mine == 1) {                                        // the usual case: the lane's maximum and nothing else
+                if (pos < CAP) s_cand[pos] = tmax;
+            } else {
+                for_each([&](float p, int) {
+                    if (p > tau) {
+                        if (pos < CAP) s_cand[pos] = p;
+                        ++pos;
+                    }
+                });
             }
-            if (rank < k) s_top[rank] = c;
         }
-        if (tid >= n && tid < k) s_top[tid] = tau > -INFINITY ? tau : 0.0f;
+        __syncthreads();
+    };
+    if (FEW && V >= 4 * DT) {
+        // A threshold that at least k entries reach: the k-th largest of the 32 maxima of 16 lanes each.  In practice little
+        // more than k entries lie above it; if it is more than the list holds, the exact one after all.
+        float g = tmax;
+        g = fmaxf(g, dpp_f32<0xB1>(g));
+        g = fmaxf(g, dpp_f32<0x4E>(g));
+        g = fmaxf(g, dpp_f32<0x141>(g));
+        g = fmaxf(g, dpp_f32<0x140>(g));
+        if ((lane & 15) == 0) s_part[tid >> 4] = g;
+        __syncthreads();
+        const int me = lane & (DT / 16 - 1);                    // by rank, in every wavefront for itself
+        const float mine = s_part[me];
+        int rank = 0;
+#pragma unroll
+        for (int j4 = 0; j4 < DT / 64; ++j4) {
+            const float4 o4 = *reinterpret_cast<const float4 *>(&s_part[4 * j4]);
+            const float o[4] = {o4.x, o4.y, o4.z, o4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rank += (o[e] > mine || (o[e] == mine && 4 * j4 + e < me)) ? 1 : 0;
+        }
+        tau = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), __builtin_ctzll(__ballot(rank == k - 1))));
+        collect();
+        const int found = s_cnt;
+        if (found > CAP) {                                      // (uniform)
+            __syncthreads();                                    // everyone has read the count
+            if (tid == 0) s_cnt = 0;
+            __syncthreads();
+            exact_threshold();
+            collect();
+        }
+    } else {
+        exact_threshold();
+        collect();
     }
-    __syncthreads();
-    if (tid < k) s_act[0][0][tid] = s_top[tid];
-    if (tid == 0) {
-        double e = 0.0;
-        for (int w = 0; w < NW; ++w) e += s_ent[w];
-        s_act[0][0][k] = (float)(e * 0.69314718055994530942);   // log2 -> nats
+    if (FEW && s_cnt <= 64) {
+        // one wavefront ranks the candidates: entries > tau, then copies of tau (or zeros when the row has fewer than k)
+        if (wave == 0) {
+            const int n = s_cnt;
+            const float c = lane < n ? s_cand[lane] : -INFINITY;
+            int rank = lane < n ? 0 : k;
+            for (int j = 0; j < n; ++j) {
+                const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c), j));
+                rank += (o > c || (o == c && j < lane)) ? 1 : 0;
+            }
+            if (rank < k) s_act[0][0][rank] = c;
+            if (lane >= n && lane < k) s_act[0][0][lane] = tau > -INFINITY ? tau : 0.0f;
+        } else if (tid == 64) {
+            double e = 0.0;
+            for (int w = 0; w < NW; ++w) e += s_ent[w];
+            s_act[0][0][k] = (float)(e * 0.69314718055994530942);   // log2 -> nats
+        }
+    } else {
+        // Topk = those candidates by rank (ties in list order), then copies of tau (entries equal to tau exist in
+        // sufficient number), or zeros when the row has fewer than k entries
+        {
+            const int n = min(s_cnt, CAP);
+            for (int i = tid; i < n; i += DT) {
+                const float c = s_cand[i];
+                int rank = 0;
+                for (int j = 0; j < n; ++j) {
+                    const float o = s_cand[j];
+                    rank += (o > c || (o == c && j < i)) ? 1 : 0;
+                }
+                if (rank < k) s_top[rank] = c;
+            }
+            if (tid >= n && tid < k) s_top[tid] = tau > -INFINITY ? tau : 0.0f;
+        }
+        __syncthreads();
+        if (tid < k) s_act[0][0][tid] = s_top[tid];
+        if (tid == 0) {
+            double e = 0.0;
+            for (int w = 0; w < NW; ++w) e += s_ent[w];
+            s_act[0][0][k] = (float)(e * 0.69314718055994530942);   // log2 -> nats
+        }
     }
     __syncthreads();
     if (features && tid <= k) features[(int64_t)m * (k + 1) + tid] = s_act[0][0][tid];
 
-    const int cur = mlp_tail<1>(mlp.n_layers, mlp.width, mlp.w, mlp.b, 0, s_act, 0, tid);
-    if (tid == 0) prob[m] = logistic(s_act[cur][0][0]);
+    float z;
+    if (fused) {
+        float h = b1;
+#pragma unroll
+        for (int u = 0; u <= K; ++u)
+            if (u <= k) h = fmaf(w1[FEW ? u : 0], s_act[0][0][u], h);
+        h = tid < mlp.width[1] && h > 0.0f ? h * w2 : 0.0f;
+        float v[1] = {h};
+        wave_sum_f32_n<1>(v);
+        if (mlp.width[1] > 64) {
+            if (lane == 0) s_part[wave] = v[0];
+            __syncthreads();
+            v[0] = ((s_part[0] + s_part[1]) + (s_part[2] + s_part[3])) + ((s_part[4] + s_part[5]) + (s_part[6] + s_part[7]));
+        }
+        z = v[0] + b2;
+    } else {
+        const int cur = mlp_tail<1>(mlp.n_layers, mlp.width, mlp.w, mlp.b, 0, s_act, 0, tid);
+        z = s_act[cur][0][0];
+    }
+    if (!FEW) {
+        if (tid == 0) prob[m] = logistic(z);
+    } else if (tid < 64) {
+        if (tid == 0) __hip_atomic_store(prob + m, logistic(z), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (stop) settle_stop(prob, tree, W, beta, stop, lane);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------- type 1
@@ -566,6 +684,9 @@ int check_mlp(const mcsd_mlp_t *mlp, int32_t n_in, MlpDesc *out)
     return MCSD_OK;
 }
 
+constexpr int FEW_ROWS = 256;        // one workgroup per compute unit
+constexpr int SETTLE_ROWS = 64;      // beyond, the flags' and probabilities' cache lines are fought over: 180 rows 15.7 us, 12.8 with a launch
+
 int launch_stop(const float *prob, int32_t B, int32_t W, float beta, int32_t *stop, hipStream_t st)
 {
     hipLaunchKernelGGL(early_stop_kernel, dim3((B + 255) / 256), dim3(256), 0, st, prob, (int)B, (int)W, beta, stop);
@@ -593,12 +714,15 @@ extern "C" int mcsd_early_stop_distribution(const mcsd_mlp_t *mlp, int32_t B, in
     const int mode = !vec ? 2 : (V <= REG_F4 * 4 * DT ? 0 : 1);
     hipStream_t st = (hipStream_t)hip_stream;
     const dim3 grid((unsigned)(B * W)), block(DT);
-    auto kernel = mode == 0 ? decision_distribution_kernel<0> : mode == 1 ? decision_distribution_kernel<1>
-                                                                         : decision_distribution_kernel<2>;
+    const bool few = (int64_t)B * W <= FEW_ROWS, settle = (int64_t)B * W <= SETTLE_ROWS;
+    auto kernel = few ? (mode == 0 ? decision_distribution_kernel<0, true> : mode == 1 ? decision_distribution_kernel<1, true>
+                                                                                     : decision_distribution_kernel<2, true>)
+                      : (mode == 0 ? decision_distribution_kernel<0, false> : mode == 1 ? decision_distribution_kernel<1, false>
+                                                                                      : decision_distribution_kernel<2, false>);
     mcsd_launch(MCSD_KERNEL_DECISION, kernel, grid, block, st, d, (int)W, (int)V, (int)k, draft_rows_dev, batch_stride,
-                row_stride, features_dev, prob_dev);
+                row_stride, features_dev, prob_dev, beta, settle ? stop_dev : (int32_t *)nullptr);
     if (int rc = mcsd_hip_status(hipGetLastError())) return rc;
-    return launch_stop(prob_dev, B, W, beta, stop_dev, st);
+    return settle ? MCSD_OK : launch_stop(prob_dev, B, W, beta, stop_dev, st);
 }
 
 extern "C" int mcsd_early_stop_hidden(const mcsd_mlp_t *mlp, int32_t B, int32_t W, const float *hidden_dev,

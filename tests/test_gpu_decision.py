@@ -145,6 +145,24 @@ def test_distribution_model_many_trees_three_layers_no_feature_output(binding, o
     binding.early_stop_distribution(mlp, 0, 16, w.V, k, None, 0, 0, BETA, None, None, None)    # B = 0: nothing to do
 
 
+@pytest.mark.parametrize("V", [2044, 2048, 4096, 32768, 32772])
+@pytest.mark.parametrize("widths,B,W", [((1,), 1, 2), ((64, 1), 3, 5), ((65, 1), 1, 70), ((512, 1), 16, 16), ((20, 9, 1), 13, 20)])
+def test_distribution_model_few_and_many_rows(binding, oracle, V, widths, B, W):
+    """Launches that do not fill the chip (up to 256 rows: threshold from 32 maxima, two-layer networks from registers, flags
+    settled in the launch) and the first that does; large entries spread out, all in 16 lanes of the vectorised layout (more
+    candidates above the threshold than the list holds), and tied."""
+    k = 16 if W == 2 else 10
+    rng = np.random.default_rng(V + B)
+    rows = (rng.random((B, W, V)).astype(np.float32) ** 4 / np.float32(V)).astype(np.float32)
+    block = [i for j in range(0, V, 2048) for i in range(j + 64, min(j + 128, V))]
+    rows[0, 0, block] = np.float32(0.5) + np.arange(len(block), dtype=np.float32) * np.float32(1e-5)
+    rows[0, 1] = np.float32(2.0) ** -11
+    ws, bs = mlp_weights((k + 1,) + widths, seed=V, out_bias=-0.2)
+    mlp = _dev_mlp(binding, ws, bs)
+    feat, prob, stop = _run_distribution(binding, mlp, torch.from_numpy(rows).cuda(), B, W, V, k, W * V, V)
+    _check_against_oracle(oracle, rows, ws, bs, k, feat, prob, stop)
+
+
 # ---------------------------------------------------------------------------------------------------- type 1
 @pytest.mark.parametrize("widths,B,W", [((768, 256, 64, 1), 1, 16), ((2048, 512, 128, 1), 3, 5), ((5, 3, 2, 1), 2, 2),
                                         ((8192, 512, 1), 1, 7), ((16, 1), 4, 4), ((768, 256, 64, 1), 33, 16),
