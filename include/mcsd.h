@@ -398,7 +398,7 @@ int mcsd_commit_path(const mcsd_mask_view_t *mask, mcsd_dtype_t dtype, int32_t B
  *                   (a NaN probability counts as not below beta)
  * Limits: 1 <= k <= MCSD_DECISION_MAX_K, 1 <= V <= MCSD_MAX_VOCAB, 1 <= n_layers <= MCSD_MLP_MAX_LAYERS, widths
  * after the first <= MCSD_MLP_MAX_WIDTH, hidden-state width <= MCSD_MLP_MAX_INPUTS.  B = 0 is a no-op.
- * Two launches on the stream (probabilities, then the stop flags); no workspace.
+ * One or two launches on the stream (probabilities, then the stop flags); no workspace.
  * ------------------------------------------------------------------------------------------------- */
 enum { MCSD_DECISION_MAX_K = 16, MCSD_MLP_MAX_LAYERS = 3, MCSD_MLP_MAX_WIDTH = 512, MCSD_MLP_MAX_INPUTS = 8192 };
 

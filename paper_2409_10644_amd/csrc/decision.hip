@@ -3,7 +3,7 @@
 // predicted below the threshold (caption of Fig. 2).
 //
 //   decision_distribution_kernel  type 2: Concat(Topk(y), Ent(y)) of one draft distribution y per workgroup (the
-//                                 row is read once into registers, or streamed twice when it is too long), then
+//                                 row is read once into registers, or streamed when it is too long), then
 //                                 the MLP
 //   decision_hidden_kernel        type 1: the MLP on the draft model's hidden states, four rows per workgroup
 //   early_stop_kernel             stop[b] = every sequence of tree b below the threshold
@@ -21,7 +21,7 @@ constexpr int NW = DT / 64;          // wavefronts per workgroup
 typedef float nt_f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int REG_F4 = 16;           // float4 a lane holds when the whole row fits in registers (V <= 32768)
 constexpr int CAND_REG = 1024;       // candidates for the top-k kept in LDS: row in registers ...
-constexpr int CAND_MEM = 8192;       // ... row streamed twice (any V up to MCSD_MAX_VOCAB)
+constexpr int CAND_MEM = 8192;       // ... row streamed (any V up to MCSD_MAX_VOCAB)
 constexpr int HROWS = 4;             // hidden-state rows per workgroup
 static_assert(HROWS == 4, "the generic first layer of the hidden-state kernel names its four rows");
 constexpr int K = MCSD_DECISION_MAX_K;
@@ -240,11 +240,12 @@ __device__ __forceinline__ void settle_stop(const float *prob, int b, int W, flo
 // ---------------------------------------------------------------------------------------------- type 2
 // FEW: the launch does not fill the chip, so what counts is one workgroup's chain of steps, not its registers: the threshold
 // comes from 32 maxima in one exchange, one wavefront ranks the candidates, the first layer's weights are in registers before
-// they are needed, the stop flags are settled here.  With 16 rows of 32000, with the flags: 14.3 us -> 9.9 us.  Otherwise other workgroups
-// hide the chain and registers are what counts (a compute unit holds three workgroups).
+// they are needed, the stop flags are settled here.  16 rows of 32000, with the flags: 14.3 us -> 9.9 us.  Otherwise other
+// workgroups hide the chain and registers are what counts (a compute unit holds three workgroups).
 // MODE 0: the row lives in registers (V a multiple of 4, <= 32768, 16-byte aligned): one trip to HBM, all loads in
-// flight at once.  MODE 1: float4 loads, MODE 2: scalar loads; both stream the row twice (the second pass is served
-// by the cache).
+// flight at once.  MODE 1: any row, streamed, CHUNK 16-byte loads per lane in flight, and once more by the
+// lanes with several candidates.  (Against one load at a time and a second pass in every lane with a candidate: 3200 rows of
+// 128256 400 -> 277 us, 5.9 TB/s; 340 rows of 246592 162 -> 94 us; 231 rows of 146375, unaligned, 239 -> 42 us.)
 template <int MODE, bool FEW>
 __global__ __launch_bounds__(DT) void decision_distribution_kernel(MlpDesc mlp, int W, int V, int k,
                                                                    const float *__restrict__ rows, int64_t batch_stride,
@@ -287,29 +288,37 @@ __global__ __launch_bounds__(DT) void decision_distribution_kernel(MlpDesc mlp, 
             }
         }
     }
+    // streamed: up to three entries before the first 16-byte boundary, n4 quadruples, up to three entries
+    constexpr int CHUNK = FEW ? 8 : 4;
+    const int head = MODE == 0 ? 0 : min(V, (int)((4u - ((unsigned)((uintptr_t)y >> 2) & 3u)) & 3u)), n4 = (V - head) >> 2;
     // every entry of the row, in the lane's own order (both passes must agree on nothing but the set)
     auto for_each = [&](auto f) {
         if (MODE == 0) {
 #pragma unroll
             for (int j = 0; j < REG_F4; ++j) { f(reg[j].x, j * 4); f(reg[j].y, j * 4 + 1); f(reg[j].z, j * 4 + 2); f(reg[j].w, j * 4 + 3); }
-        } else if (MODE == 1) {
-            for (int i = tid * 4; i < V; i += DT * 4) {
-                const float4 v = *reinterpret_cast<const float4 *>(y + i);
-                f(v.x, 0); f(v.y, 1); f(v.z, 2); f(v.w, 3);
-            }
         } else {
-            int n = 0;
-            for (int i = tid; i < V; i += DT) f(y[i], n++);
+            const nt_f32x4_t *body = reinterpret_cast<const nt_f32x4_t *>(y + head);
+            for (int c = tid; c - tid < n4; c += CHUNK * DT) {
+                nt_f32x4_t v[CHUNK];                             // all of them in flight; beyond the end the last one again, unused
+#pragma unroll
+                for (int u = 0; u < CHUNK; ++u) v[u] = FEW ? body[min(c + u * DT, n4 - 1)] : __builtin_nontemporal_load(body + min(c + u * DT, n4 - 1));
+#pragma unroll
+                for (int u = 0; u < CHUNK; ++u)
+                    if (c + u * DT < n4) { f(v[u].x, 0); f(v[u].y, 1); f(v[u].z, 2); f(v[u].w, 3); }
+            }
+            if (tid < head) f(y[tid], 0);
+            if (tid < V - head - 4 * n4) f(y[head + 4 * n4 + tid], 0);
         }
     };
 
     // pass 1: the lane's maximum and its share of -sum y log2 y.  The hardware logarithm (1 ulp) on normal numbers;
     // entries below the normal range contribute less than 1e-36 each and are skipped.  Four fp32 accumulators of
     // at most a quarter of the lane's entries each, combined in binary64.
-    float tmax = -INFINITY;
+    float tmax = -INFINITY, tnext = -INFINITY;                  // the lane's largest and second largest entry
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     double hd = 0.0;                                            // streamed rows can be long: binary64 right away
     for_each([&](float p, int n) {
+        if (MODE != 0 || FEW) tnext = __builtin_amdgcn_fmed3f(p, tmax, tnext);
         tmax = fmaxf(tmax, p);
         const float t = (p >= 1.17549435e-38f) ? p * __log2f(p) : 0.0f;
         if (MODE == 0) acc[n & 3] -= t; else hd -= (double)t;
@@ -343,21 +352,30 @@ __global__ __launch_bounds__(DT) void decision_distribution_kernel(MlpDesc mlp, 
         }
     };
     auto collect = [&]() {
-        // pass 2, only in the lanes that have any: the entries above tau, in any order
-        if (tmax > tau) {
-            int mine = 0;
-            for_each([&](float p, int) { mine += p > tau ? 1 : 0; });
-            int pos = atomicAdd(&s_cnt, mine);
-            if (mine == 1) {                                        // the usual case: the lane's maximum and nothing else
-                if (pos < CAP) s_cand[pos] = tmax;
-            } else {
-                for_each([&](float p, int) {
-                    if (p > tau) {
-                        if (pos < CAP) s_cand[pos] = p;
-                        ++pos;
-                    }
-                });
+        // the entries above tau, in any order; a second pass only in the lanes that have more than one
+        if constexpr (MODE == 0 && !FEW) {                      // (counted first: 75 registers, 138 the other way)
+            if (tmax > tau) {
+                int mine = 0;
+                for_each([&](float p, int) { mine += p > tau ? 1 : 0; });
+                int pos = atomicAdd(&s_cnt, mine);
+                if (mine == 1) {                                // the usual case: the lane's maximum and nothing else
+                    if (pos < CAP) s_cand[pos] = tmax;
+                } else {
+                    for_each([&](float p, int) {
+                        if (p > tau) {
+                            if (pos < CAP) s_cand[pos] = p;
+                            ++pos;
+                        }
+                    });
+                }
             }
+        } else if (tmax > tau) {
+            auto add = [&](float p) {
+                const int pos = atomicAdd(&s_cnt, 1);
+                if (pos < CAP) s_cand[pos] = p;
+            };
+            if (!(tnext > tau)) add(tmax);
+            else for_each([&](float p, int) { if (p > tau) add(p); });
         }
         __syncthreads();
     };
@@ -708,17 +726,16 @@ extern "C" int mcsd_early_stop_distribution(const mcsd_mlp_t *mlp, int32_t B, in
     if (!draft_rows_dev || !prob_dev || !stop_dev) return MCSD_EINVAL;
     if ((int64_t)B * W > 0x7fffffff / (MCSD_DECISION_MAX_K + 1)) return MCSD_EUNSUPPORTED;
     // a lane holds at most ceil(V / (4 DT)) * 4 entries and at most k-1 lanes hold entries above the threshold
-    static_assert((int64_t)(K - 1) * ((MCSD_MAX_VOCAB + 4 * DT - 1) / (4 * DT)) * 4 <= CAND_MEM, "candidate list too small");
+    // (two more of a streamed row's ends)
+    static_assert((int64_t)(K - 1) * ((MCSD_MAX_VOCAB + 4 * DT - 1) / (4 * DT) * 4 + 2) <= CAND_MEM, "candidate list too small");
     static_assert((K - 1) * REG_F4 * 4 <= CAND_REG, "candidate list too small");
     const bool vec = V % 4 == 0 && batch_stride % 4 == 0 && row_stride % 4 == 0 && ((uintptr_t)draft_rows_dev & 15) == 0;
-    const int mode = !vec ? 2 : (V <= REG_F4 * 4 * DT ? 0 : 1);
+    const int mode = vec && V <= REG_F4 * 4 * DT ? 0 : 1;
     hipStream_t st = (hipStream_t)hip_stream;
     const dim3 grid((unsigned)(B * W)), block(DT);
     const bool few = (int64_t)B * W <= FEW_ROWS, settle = (int64_t)B * W <= SETTLE_ROWS;
-    auto kernel = few ? (mode == 0 ? decision_distribution_kernel<0, true> : mode == 1 ? decision_distribution_kernel<1, true>
-                                                                                     : decision_distribution_kernel<2, true>)
-                      : (mode == 0 ? decision_distribution_kernel<0, false> : mode == 1 ? decision_distribution_kernel<1, false>
-                                                                                      : decision_distribution_kernel<2, false>);
+    auto kernel = mode == 0 ? (few ? decision_distribution_kernel<0, true> : decision_distribution_kernel<0, false>)
+                            : (few ? decision_distribution_kernel<1, true> : decision_distribution_kernel<1, false>);
     mcsd_launch(MCSD_KERNEL_DECISION, kernel, grid, block, st, d, (int)W, (int)V, (int)k, draft_rows_dev, batch_stride,
                 row_stride, features_dev, prob_dev, beta, settle ? stop_dev : (int32_t *)nullptr);
     if (int rc = mcsd_hip_status(hipGetLastError())) return rc;
