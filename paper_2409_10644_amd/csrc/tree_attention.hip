@@ -716,7 +716,12 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
         const int rank = fast_div(r, mul_H, how_shift_H(how));
         const int cls = __builtin_amdgcn_readfirstlane(s_cls_at[rank]);
         s = cls % p.S;
-        bhi = (cls / p.S) * H + (r - rank * H);
+        // Units that stream the same keys for different query heads are neighbours: give them one die, and so one L2 (a die's
+        // share of a class is then H / dies neighbours; ids modulo the dies stay what they were for every split of a unit).
+        int unit = r - rank * H;
+        const int xb = how_xcc(how);
+        if (p.chunks > 1 && (H & ((1 << xb) - 1)) == 0) unit = (unit & ((1 << xb) - 1)) * (H >> xb) + (unit >> xb);
+        bhi = (cls / p.S) * H + unit;
     }
     bhi = __builtin_amdgcn_readfirstlane(bhi);              // (uniform, and the compiler has to know)
     s = __builtin_amdgcn_readfirstlane(s);
