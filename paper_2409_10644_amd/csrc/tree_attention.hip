@@ -306,25 +306,25 @@ struct SweepCfg {
     static constexpr int KPW = QBP == 4 ? 2 : 1;       // 32-key blocks per wavefront per tile
     static constexpr int THREADS = WAVES * 64;
     static constexpr int T = 32 * KG * KPW;            // keys per tile (64, 64, 128 for QBP = 4, 2, 1)
-    static constexpr int RB = D * 2;                   // bytes per bf16 K/V row (tree tiles, register path)
+    static constexpr int RB = D * 2;                   // bytes per bf16 K/V row (tree tiles)
     static constexpr int RBP = F8 ? D : D * 2;         // bytes per prefix K/V row (ring stages)
     static constexpr int CPR = RBP / 16;               // 16-byte chunks per prefix row
     static constexpr int RPI = 64 / CPR;               // rows covered by one direct-to-LDS instruction (1 KiB)
     static constexpr int TILE_K = T * RBP;             // bytes of the K half of a ring stage; V follows
     static constexpr int TILE = 2 * TILE_K;
-    static constexpr int BTILE_K = T * RB;             // the same for a bf16 tile written through registers
+    static constexpr int BTILE_K = T * RB;             // the same for a bf16 tile (the tree's own; beside fp8 stages its halves take one each)
     static constexpr int BCPR = RB / 16;
     static constexpr int NI = T / RPI / WAVES;         // direct-to-LDS instructions per wavefront for K (same for V)
     static constexpr int DPT = 2 * NI;                 // ... per tile
     static constexpr int NS = NS_;                     // LDS stages: one being computed, NS - 1 being filled
     static constexpr int KS = D / 16;                  // k-steps of S^T = K Q^T
     static constexpr int CB = D / 32;                  // 32-row blocks of O^T
-    static constexpr int CPT = T * BCPR / THREADS;     // 16-byte bf16 chunks per thread for K (same for V), register path
     static constexpr int XCHG = (KG - 1) * QBP * 32 * D * 4;   // LDS bytes in which key groups hand over their outputs; maxima and denominators follow
-    static constexpr int RING = NS * TILE > 2 * BTILE_K ? NS * TILE : 2 * BTILE_K;
+    static constexpr int RING = NS * TILE;
     static constexpr int LDS_BYTES = RING > XCHG + 1024 ? RING : XCHG + 1024;
-    static_assert(NI >= 1 && CPT >= 1 && (NS - 2) * DPT < 64 && LDS_BYTES <= 160 * 1024 - 64, "tile does not map onto the workgroup");
+    static_assert(NI >= 1 && (NS - 2) * DPT < 64 && LDS_BYTES <= 160 * 1024 - 64, "tile does not map onto the workgroup");
     static_assert(!F8 || D == 128, "fp8 tiles are laid out for 128-byte rows");
+    static_assert(!F8 || (BTILE_K == TILE && BTILE_K / 1024 / WAVES == DPT), "half a tree tile is a slot of the ring");
 };
 
 // XOR swizzle of the 16-byte chunk index inside row r.  With it, 16 consecutive rows read at the same logical
@@ -404,7 +404,7 @@ __device__ inline void softmax_exp2(const f32x16_t &sacc, int r, float c, float 
 // scale share it) and P carries the V scale `vs` of the tile.  F8T: this stage is a raw fp8 tile.
 template <int D, int QBP, int NS, int MODE, bool F8K = false, bool F8T = false>
 __device__ inline void attn_tile(const unsigned char *stage, const LaneAddr la, QBlock<D> &qs, float c, int g,
-                                 const uint32_t *bits, float vs = 1.f)
+                                 const uint32_t *bits, float vs = 1.f, const unsigned char *vstage = nullptr)
 {
     using C = SweepCfg<D, QBP, NS, F8K>;
     constexpr int U = C::KPW;
@@ -445,7 +445,7 @@ __device__ inline void attn_tile(const unsigned char *stage, const LaneAddr la, 
     // V^T fragments via the LDS transpose load, issued ahead of their use: block 0's during the softmax, block 1's
     // before the first PV MFMA.  The reads of one k-step pair (ks2, e4) sit 16*ks2 + 8*e4 rows below the lane's
     // base row; the chunk select is cb*4 ^ e4*2.
-    const unsigned char *vst = stage + VOFF;
+    const unsigned char *vst = vstage ? vstage : stage + VOFF;   // (null or not at compile time)
     bf16x8_t vf[U][2][C::CB];
     auto read_v = [&](int u) {
 #pragma unroll
@@ -908,86 +908,88 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
             rest(it + 1, ring + C::TILE, ring);
             it += 2;
         }
-        __syncthreads();
         static_assert(!F8, "fp8 tiles use the ring below");
     } else {
-    if (n_hot > 0) {
-        // A ring of NS stages keeps NS-1 tiles in flight: fp8 tiles (half the bytes); bf16 tiles only on request (it
-        // needs a compute unit's LDS per workgroup and measured slower, see make_plan).  Tile t lives in stage
-        // t % NS.  A step waits until exactly the tiles requested after its own are still outstanding: NS-2 of them in
-        // the steady state, fewer at the end.
-        auto step = [&](auto stage, int it) {
-            constexpr int ST = decltype(stage)::value;
-            const int later = min(n_hot - it - 1, NS - 2);        // uniform
+        // A ring of NS stages keeps NS-1 slots in flight: fp8 tiles (half the bytes); bf16 tiles only on request (it
+        // needs a compute unit's LDS per workgroup and measured slower, see make_plan).  Slot x lives in stage x % NS and is
+        // DPT loads per wavefront: a full tile, the ragged one, or of the tree's own tiles a whole one (bf16) or, beside an
+        // fp8 prefix, its K or its V half.  A step waits until exactly the slots requested after its own are still
+        // outstanding: NS-2 of them in the steady state, fewer at the end.
+        constexpr int TS = F8 ? 2 : 1;                       // slots of a tree tile
+        const int n8 = n_hot + n_tail, n_slots = n8 + TS * n_tree_tiles;
+        auto stage_of = [&](int x) { return ring + (x & (NS - 1)) * C::TILE; };
+        auto issue_rest = [&](int x) {                       // a slot behind the full tiles
+            unsigned char *stage = stage_of(x) + wave * 1024;
+            if (F8 && x >= n8) {
+                const int t = (x - n8) >> 1, last = p.n - t * C::T - 1;
+                const unsigned char *src = (const unsigned char *)(((x - n8) & 1) ? vt : kt) + (int64_t)t * C::BTILE_K;
+#pragma unroll
+                for (int j = 0; j < C::DPT; ++j) {           // 1 KiB of bf16 rows per instruction
+                    const int r = (j * C::WAVES + wave) * (1024 / C::RB) + lane / C::BCPR;
+                    load_to_lds16<false>(src, (uint32_t)(min(r, last) * C::RB + (((lane % C::BCPR) ^ swz<D>(r)) * 16)), stage + j * C::WAVES * 1024);
+                }
+                return;
+            }
+            const bool tail = x < n8;
+            const unsigned char *ks = tail ? kp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)kt + (int64_t)(x - n8) * C::TILE_K;
+            const unsigned char *vs = tail ? vp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)vt + (int64_t)(x - n8) * C::TILE_K;
+            const int last = (tail ? tail_rows : p.n - (x - n8) * C::T) - 1;
+#pragma unroll
+            for (int j = 0; j < C::NI; ++j) {
+                const uint32_t off = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
+                load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
+                load_to_lds16<false>(vs, off, stage + C::TILE_K + j * C::WAVES * 1024);
+            }
+        };
+        auto issue = [&](int x) {
+            if (x < n_hot) issue_full(stage_of(x));
+            else if (x < n_slots) issue_rest(x);
+        };
+        auto arrived = [&](int later) {                      // all but `later` slots, and everywhere; the slot before is free again
             if (later >= 2) MCSD_WAIT_VMCNT(2 * C::DPT);
             else if (later == 1) MCSD_WAIT_VMCNT(C::DPT);
             else MCSD_WAIT_VMCNT(0);
             __builtin_amdgcn_s_barrier();
+        };
+        auto step = [&](auto stage, int it) {
+            constexpr int ST = decltype(stage)::value;
+            arrived(min(n_slots - it - 1, NS - 2));
             if (it + NS - 1 < n_hot) issue_full(ring + (ST + NS - 1) % NS * C::TILE);
+            else if (it + NS - 1 < n_slots) issue_rest(it + NS - 1);
             attn_tile<D, QBP, NS, 0, F8, F8>(ring + ST * C::TILE, la, qs, c_pre, g, all_keys, vs_pre);
         };
         static_assert(NS == 4, "the step sequence below is unrolled for four stages");
-        // Q and the mask row must have arrived before the first direct-to-LDS load is issued: the steps below wait
-        // with a non-zero count, and the compiler, which does not see those loads, would otherwise place its own
-        // wait for Q at the first MFMA inside the loop, where it would also wait for the tiles in flight.
+        // Q and the mask row must have arrived before the first direct-to-LDS load is issued: the steps wait with a non-zero
+        // count, and the compiler, which does not see those loads, would otherwise place its own wait for Q at the first
+        // MFMA inside the loop, where it would also wait for the tiles in flight.  (Waiting behind the first loads: 1-4 % more.)
         MCSD_WAIT_VMCNT(0);
-        if (0 < n_hot) issue_full(ring + 0 * C::TILE);
-        if (1 < n_hot) issue_full(ring + 1 * C::TILE);
-        if (2 < n_hot) issue_full(ring + 2 * C::TILE);
+        issue(0);
+        issue(1);
+        issue(2);
         for (int it = 0; it < n_hot; it += 4) {
             step(std::integral_constant<int, 0>(), it);
             if (it + 1 < n_hot) step(std::integral_constant<int, 1 % NS>(), it + 1);
             if (it + 2 < n_hot) step(std::integral_constant<int, 2 % NS>(), it + 2);
             if (it + 3 < n_hot) step(std::integral_constant<int, 3 % NS>(), it + 3);
         }
-        MCSD_WAIT_VMCNT(0);
+        if (n_tail) {
+            arrived(min(n_slots - n_hot - 1, NS - 2));
+            issue(n_hot + NS - 1);
+            uint32_t bits[C::KPW];
+            rest_bits(0, bits);
+            attn_tile<D, QBP, NS, 1, F8, F8>(stage_of(n_hot), la, qs, c_pre, g, bits, vs_pre);
+        }
+        for (int t = 0; t < n_tree_tiles; ++t) {
+            // requested so far: NS - 1 slots from the first tree slot on, or (second fp8 tile) up to this tile's own last
+            const int x = n8 + TS * t, have = min(n_slots, TS == 2 && t == 1 ? x + TS : x + NS - 1);
+            arrived(have - x - TS);
+            issue(x + NS - 1);
+            uint32_t bits[C::KPW];
+            rest_bits(n_tail + t, bits);
+            attn_tile<D, QBP, NS, 1, F8, false>(stage_of(x), la, qs, p.c, g, bits, 1.f, F8 ? stage_of(x + 1) : nullptr);
+        }
     }
     __syncthreads();
-
-    // ---- ragged last prefix tile and the tree's own tiles: through registers, rows beyond `valid` zero-filled ----
-    for (int it = 0; it < n_all - n_hot; ++it) {
-        const bool tail = it < n_tail;
-        const int tt = tail ? 0 : it - n_tail;
-        const unsigned char *ksrc = tail ? kp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)kt + (int64_t)tt * C::BTILE_K;
-        const unsigned char *vsrc = tail ? vp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)vt + (int64_t)tt * C::BTILE_K;
-        const int valid = tail ? tail_rows : min(C::T, p.n - tt * C::T);
-#pragma unroll
-        for (int i0 = 0; i0 < C::CPT; i0 += 4) {           // four chunks of K and V at a time keeps the staging small
-            uint4 kreg[4], vreg[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int x = (i0 + i) * C::THREADS + tid, row = x / C::BCPR, ch = x % C::BCPR;
-                kreg[i] = make_uint4(0, 0, 0, 0);
-                vreg[i] = make_uint4(0, 0, 0, 0);
-                if (i0 + i < C::CPT && row < valid) {
-                    if (F8 && tail) {                      // 8 fp8 values become this 16-byte bf16 chunk
-                        const uint2 k8 = *(const uint2 *)(ksrc + row * C::RBP + ch * 8);
-                        const uint2 v8 = *(const uint2 *)(vsrc + row * C::RBP + ch * 8);
-                        kreg[i] = __builtin_bit_cast(uint4, fp8x8_to_bf16(k8.x, k8.y));
-                        vreg[i] = __builtin_bit_cast(uint4, fp8x8_to_bf16(v8.x, v8.y));
-                    } else {
-                        kreg[i] = *(const uint4 *)(ksrc + row * C::RB + ch * 16);
-                        vreg[i] = *(const uint4 *)(vsrc + row * C::RB + ch * 16);
-                    }
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int x = (i0 + i) * C::THREADS + tid, row = x / C::BCPR, ch = x % C::BCPR;
-                const int off = row * C::RB + ((ch ^ swz<D>(row)) * 16);
-                if (i0 + i < C::CPT) {
-                    *(uint4 *)(ring + off) = kreg[i];
-                    *(uint4 *)(ring + C::BTILE_K + off) = vreg[i];
-                }
-            }
-        }
-        __syncthreads();
-        uint32_t bits[C::KPW];
-        rest_bits(it, bits);
-        attn_tile<D, QBP, NS, 1, F8, false>(ring, la, qs, tail ? c_pre : p.c, g, bits, tail ? vs_pre : 1.f);
-        __syncthreads();
-    }
-    }
     // (requested here: at the start the wait for the first keys' addresses would include it)
     const uint32_t ws_tag = p.fold ? __hip_atomic_load(p.ws_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) : WS_TAG;
 
