@@ -29,6 +29,7 @@
 #include <chrono>
 
 #include "mcsd_internal.h"
+#include "team_protocol.h"
 
 namespace {
 
@@ -590,14 +591,11 @@ __global__ __launch_bounds__(VT) void verify_walk_fast_kernel(const VerifyParams
 // occupies the chip.
 //
 // A message is the sum in four 16-bit pieces, each in a 64-bit word of its own under the same 48-bit tag, so it needs no
-// ordering against anything: the exit count of the mailbox when the launch began (27 bits), the nonce of the walk (20
-// bits) and one bit that tells a step from the one before it in the same box.  Nonces come from a host counter, one per
-// walk.  The exit count grows by one per workgroup that leaves and so differs between two replays of one captured
-// launch.  A mailbox that two launches happen to use at once (the mailboxes are a ring of TEAM_MAILBOXES) only loses
-// messages: the tags tell them apart, and the reader computes the sum itself.
-// Two boxes in turn: a workgroup writes step s + 2 only after it has everyone's step s + 1, and whoever sent that had
-// read all of step s.
-constexpr int TEAM_MAX = 16, TEAM_MAILBOXES = 512, TEAM_POLLS = 64;
+// ordering against anything: the tag says which walk, which run and which step the sum is of (see team_protocol.h), and the
+// value under a tag is always the same.  Nonces come from a host counter, one per walk.  The exit count grows by one per
+// workgroup that leaves and so differs between two replays of one captured launch.  A mailbox that two launches happen to
+// use at once only loses messages: the reader finds other tags and computes the sum itself.
+constexpr int TEAM_POLLS = 64;
 struct TeamMailbox {
     unsigned exits;
     unsigned pad[31];
@@ -869,9 +867,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void ve
         if (wave == 0) {
             // lane 4 m + k: piece k of the message to, then from member m
             const int m = lane >> 2, k = lane & 3;
-            const unsigned long long tag = ((unsigned long long)epoch << 37) | (((T.nonce + walk) / TEAM_MAILBOXES & 0xfffffull) << 17) |
-                                           ((unsigned long long)(step >> 1 & 1u) << 16);
-            unsigned long long(*box)[TEAM_MAX][4] = mail.box[step & 1];
+            const unsigned long long tag = team_tag(epoch, T.nonce + walk, step);
+            unsigned long long(*box)[TEAM_MAX][4] = mail.box[team_box(step)];
             const unsigned half = (unsigned)(k & 2 ? __double2hiint(c) : __double2loint(c)), piece = k & 1 ? half >> 16 : half & 0xffffu;
             unsigned long long w = tag | piece;
             if (m < T.C) __hip_atomic_store(&box[m][member][k], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -879,7 +876,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void ve
             unsigned long long missing;
             for (int polls = __builtin_amdgcn_readfirstlane(alone ? 0 : T.polls);; --polls) {
                 if (other) w = T.polls >= 0 ? __hip_atomic_load(&box[member][m][k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~tag;
-                missing = __builtin_amdgcn_ballot_w64(other && (w ^ tag) >> 16 != 0);
+                missing = __builtin_amdgcn_ballot_w64(other && !team_carries(w, tag));
                 if (missing == 0 || __builtin_amdgcn_readfirstlane(polls) <= 0) break;
             }
             step += 1;
@@ -1096,9 +1093,9 @@ extern "C" size_t mcsd_verify_tree_workspace(const mcsd_mask_view_t *mask, mcsd_
 }
 
 namespace {
-// One number per walk ever launched: the nonces of the teams' messages (a tag is never all zeros, what a mailbox starts
-// with) and, with a part of its own for every process, the id of a launch.
-std::atomic<unsigned long long> g_team_nonce{TEAM_MAILBOXES};
+// One number per walk ever launched: the nonces of the teams' messages and, with a part of its own for every process, the id
+// of a launch.
+std::atomic<unsigned long long> g_team_nonce{0};
 const unsigned long long g_process_part = (unsigned long long)std::chrono::system_clock::now().time_since_epoch().count() << 40;
 
 // Chunk of the vocabulary a team's workgroup holds; 0: one workgroup of the fast kernel per walk.  Up to 16384 entries one
