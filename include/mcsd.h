@@ -140,7 +140,8 @@ int mcsd_tree_attention(const mcsd_mask_view_t *mask, mcsd_dtype_t dtype, int32_
  * node j < n_nodes that the mask shows to the row.  This is the draft side of Fig. 1 step 3 and Sec. 3.2: the tree
  * grows level by level, each step takes the next slice of the mask built once and needs outputs only for the newest
  * level, row_begin = level_off_host[gamma-1].  Arguments, limits and workspace rules as above, with the workspace
- * sized by mcsd_tree_attention_rows_workspace (never more than mcsd_tree_attention_workspace of the same shape). */
+ * sized by mcsd_tree_attention_rows_workspace (never more than mcsd_tree_attention_workspace of the same shape, which
+ * serves every call of the same B, H and d with fewer rows, fewer nodes or a shorter prefix bound). */
 size_t mcsd_tree_attention_rows_workspace(int32_t B, int32_t H, int32_t d, int32_t n_nodes, int32_t row_begin,
                                           int32_t max_prefix);
 

@@ -1623,10 +1623,15 @@ size_t workspace_query(const mcsd_attention_tuning_t *tune, bool f8, int32_t B, 
         }
     }
     if (f8) return wa;
-    // the larger of the two dtypes' needs, so one buffer serves both
-    const AttnPlan f = make_plan(MCSD_F32, B, H_q, H_kv, d, n_nodes - row_begin, n_nodes, max_prefix, false, tune);
-    const size_t wf = workspace_bytes_for(f, MCSD_F32, B, d);
-    return wa > wf ? wa : wf;
+    // the larger of the two dtypes' needs, so one buffer serves both; fp32: for every number of query tiles up to this one
+    // (fewer tiles mean more splits: 9 x 32 heads of 64, 243 keys: none with 6 tiles, 3.7 MB with 1) and this prefix, whose
+    // splits are at least a shorter one's
+    for (int rows = n_nodes - row_begin; rows > 0; rows = tune && tune->key_splits >= 1 ? 0 : (rows - 1) / F32_ROWS * F32_ROWS) {
+        const AttnPlan f = make_plan(MCSD_F32, B, H_q, H_kv, d, rows, n_nodes, max_prefix, false, tune);
+        const size_t w = workspace_bytes_for(f, MCSD_F32, B, d);
+        if (w > wa) wa = w;
+    }
+    return wa;
 }
 
 int attention_call(const mcsd_attention_tuning_t *tune, const mcsd_mask_view_t *mask, mcsd_dtype_t dtype, bool f8,
