@@ -463,7 +463,8 @@ __global__ __launch_bounds__(DT) void decision_distribution_kernel(MlpDesc mlp, 
 #pragma unroll
         for (int u = 0; u <= K; ++u)
             if (u <= k) h = fmaf(w1[FEW ? u : 0], s_act[0][0][u], h);
-        h = tid < mlp.width[1] && h > 0.0f ? h * w2 : 0.0f;
+        h = h < 0.0f ? 0.0f : h;                                // (a NaN stays one, as in mlp_layer)
+        h = tid < mlp.width[1] ? h * w2 : 0.0f;
         float v[1] = {h};
         wave_sum_f32_n<1>(v);
         if (mlp.width[1] > 64) {
