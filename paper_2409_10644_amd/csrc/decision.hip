@@ -560,7 +560,7 @@ __device__ __forceinline__ void mfma_layer(Rows x, int n_in, const float *__rest
         const int at = __builtin_amdgcn_readfirstlane(s_next);
 #pragma unroll
         for (int q = 0; q < BATCH; ++q) {
-            const int col = min(64 * (b_next * BATCH + q) + 4 * kk, n_in - 4);                  // beyond n_in: times zero
+            const int col = min(64 * (b_next * BATCH + q) + 4 * kk, n_in - 4);                  // beyond n_in: cleared below
             load_to_lds16<false>(base, (unsigned)(r * n_in + col) * 4u, &ring[at][q][0]);
         }
         if (++b_next == NB) { b_next = 0; g_next += NW; }
@@ -582,6 +582,11 @@ __device__ __forceinline__ void mfma_layer(Rows x, int n_in, const float *__rest
                 asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[0].x), "+v"(w[1].x), "+v"(w[2].x), "+v"(w[3].x) :: "memory");   // read before it is overwritten
                 request();
                 s = s + 1 == RING ? 0 : s + 1;
+                if (64 * (bt + 1) * BATCH > n_in) {          // (uniform) beyond n_in both are zero: an infinite weight read again there would make NaN
+#pragma unroll
+                    for (int q = 0; q < BATCH; ++q)
+                        if (64 * (bt * BATCH + q) + 4 * (lane >> 2) >= n_in) w[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                }
 #pragma unroll
                 for (int q = 0; q < BATCH; ++q) {
                     const float4 v = x(bt * BATCH + q);

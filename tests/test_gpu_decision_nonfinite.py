@@ -60,3 +60,25 @@ def test_rows_network_few_and_many_rows(binding, hidden, what, at, value):
         assert np.abs(np.nan_to_num(got) - np.nan_to_num(want)).max() <= 1e-5
         assert stop.tolist() == [int(np.all(got[b] < np.float32(0.4))) for b in range(B)]
 
+
+
+@pytest.mark.parametrize("widths", [(40, 1), (260, 8, 1), (768, 70, 5, 1), (100, 300, 1)])
+@pytest.mark.parametrize("what,value", [("weight", INF), ("weight", -INF), ("weight", NAN), ("row", INF)])
+def test_hidden_state_network(binding, widths, what, value):
+    rng = np.random.default_rng(widths[0])
+    ws, bs = mlp_weights(widths, seed=widths[0])
+    x = rng.standard_normal((2, 3, widths[0])).astype(np.float32)
+    if what == "row":
+        x[1, 2, -1] = value
+    else:
+        ws[0][0, -1] = value                    # the last column: what a kernel may read again beyond it
+    mlp = _mlp(binding, ws, bs)
+    prob = torch.full((2, 3), -7.0, device="cuda")
+    stop = torch.full((2,), -7, dtype=torch.int32, device="cuda")
+    binding.early_stop_hidden(mlp, 2, 3, torch.from_numpy(x).cuda(), 3 * widths[0], widths[0], 0.4, prob, stop)
+    torch.cuda.synchronize()
+    got = prob.cpu().numpy()
+    want = _expected(ws, bs, x.reshape(6, -1).astype(np.float64)).reshape(2, 3)
+    assert np.array_equal(np.isnan(got), np.isnan(want)), (widths, what, value)
+    assert np.abs(np.nan_to_num(got) - np.nan_to_num(want)).max() <= 1e-5
+    assert stop.tolist() == [int(np.all(got[b] < np.float32(0.4))) for b in range(2)]
