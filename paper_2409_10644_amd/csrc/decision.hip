@@ -541,12 +541,16 @@ struct HiddenShared {
     float act[2][HROWS][MCSD_MLP_MAX_WIDTH];
     float4 ring[NW][RING][BATCH][64];
     float bias[MCSD_MLP_MAX_LAYERS][MCSD_MLP_MAX_WIDTH];
+    float4 zero;
 };
 template <int NT, typename Rows>
 __device__ __forceinline__ void mfma_layer(Rows x, int n_in, const float *__restrict__ W, const float *bias, int n_out,
-                                           float4 (*ring)[BATCH][64], float (*out)[MCSD_MLP_MAX_WIDTH], bool relu, int tid)
+                                           float4 (*ring)[BATCH][64], const float4 *zero, float (*out)[MCSD_MLP_MAX_WIDTH], bool relu, int tid)
 {
     constexpr int NB = NT / BATCH;                           // batches per group
+    // Batches that lie inside the row for every width this NT is chosen for.  In the others both operands are zero beyond n_in
+    // (zero times an infinite weight, read again there, would be NaN).
+    constexpr int FULL = NT > 16 ? 16 / BATCH : NB - 1;
     static_assert(NT % BATCH == 0, "whole batches");
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int groups = (n_out + 3) >> 2;
@@ -578,15 +582,14 @@ __device__ __forceinline__ void mfma_layer(Rows x, int n_in, const float *__rest
                 asm volatile("" ::: "memory");
                 float4 w[BATCH];
 #pragma unroll
-                for (int q = 0; q < BATCH; ++q) w[q] = ring[s][q][slot];
+                for (int q = 0; q < BATCH; ++q) {
+                    const float4 *at = &ring[s][q][slot];
+                    if (bt >= FULL && 64 * (bt * BATCH + q) + 4 * (lane >> 2) >= n_in) at = zero;
+                    w[q] = *at;
+                }
                 asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[0].x), "+v"(w[1].x), "+v"(w[2].x), "+v"(w[3].x) :: "memory");   // read before it is overwritten
                 request();
                 s = s + 1 == RING ? 0 : s + 1;
-                if (64 * (bt + 1) * BATCH > n_in) {          // (uniform) beyond n_in both are zero: an infinite weight read again there would make NaN
-#pragma unroll
-                    for (int q = 0; q < BATCH; ++q)
-                        if (64 * (bt * BATCH + q) + 4 * (lane >> 2) >= n_in) w[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                }
 #pragma unroll
                 for (int q = 0; q < BATCH; ++q) {
                     const float4 v = x(bt * BATCH + q);
@@ -636,13 +639,14 @@ __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M,
     const int n_in = mlp.width[0];
     const bool relu = mlp.n_layers > 1;
     float4 (*ring)[BATCH][64] = sh.ring[__builtin_amdgcn_readfirstlane(tid >> 6)];
+    if (tid == 0) sh.zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int l = 0; l < mlp.n_layers; ++l)
         for (int j = tid; j < mlp.width[l + 1]; j += DT) sh.bias[l][j] = mlp.b[l][j];
     if constexpr (NT > 0) {
         float4 xr[NT];
         mfma_rows<NT>(xr, row(tid & 3), n_in, tid);
         __syncthreads();
-        mfma_layer<NT>([&](int t) { return xr[t]; }, n_in, mlp.w[0], sh.bias[0], mlp.width[1], ring, sh.act[0], relu, tid);
+        mfma_layer<NT>([&](int t) { return xr[t]; }, n_in, mlp.w[0], sh.bias[0], mlp.width[1], ring, &sh.zero, sh.act[0], relu, tid);
     } else if constexpr (NT == 0) {
         __shared__ float4 s_x[WIDE];
         for (int k = tid; k < WIDE; k += DT) {
@@ -650,7 +654,7 @@ __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M,
             s_x[k] = c < n_in ? *reinterpret_cast<const float4 *>(row(k & 3) + c) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
         __syncthreads();
-        mfma_layer<WIDE / 64>([&](int t) { return s_x[t * 64 + (tid & 63)]; }, n_in, mlp.w[0], sh.bias[0], mlp.width[1], ring, sh.act[0], relu, tid);
+        mfma_layer<WIDE / 64>([&](int t) { return s_x[t * 64 + (tid & 63)]; }, n_in, mlp.w[0], sh.bias[0], mlp.width[1], ring, &sh.zero, sh.act[0], relu, tid);
     } else {
         mlp_layer<HROWS>([x0 = row(0), x1 = row(1), x2 = row(2), x3 = row(3)](int r, int i) {
                              return (r == 0 ? x0 : r == 1 ? x1 : r == 2 ? x2 : x3)[i];
@@ -666,11 +670,11 @@ __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M,
         } else if (width <= 256) {
             float4 xr[4];
             mfma_rows<4>(xr, src[tid & 3], width, tid);
-            mfma_layer<4>([&](int t) { return xr[t]; }, width, mlp.w[l], sh.bias[l], mlp.width[l + 1], ring, dst, more, tid);
+            mfma_layer<4>([&](int t) { return xr[t]; }, width, mlp.w[l], sh.bias[l], mlp.width[l + 1], ring, &sh.zero, dst, more, tid);
         } else {
             float4 xr[8];
             mfma_rows<8>(xr, src[tid & 3], width, tid);
-            mfma_layer<8>([&](int t) { return xr[t]; }, width, mlp.w[l], sh.bias[l], mlp.width[l + 1], ring, dst, more, tid);
+            mfma_layer<8>([&](int t) { return xr[t]; }, width, mlp.w[l], sh.bias[l], mlp.width[l + 1], ring, &sh.zero, dst, more, tid);
         }
         cur ^= 1;
     }
