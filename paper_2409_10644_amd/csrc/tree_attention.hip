@@ -80,6 +80,11 @@ constexpr size_t WS_HEADER = 256, WS_CTR_BYTES = 64 * 1024;
 constexpr int CTR_STRIDE = 16;                          // in 8-byte counters
 constexpr int FOLD_MAX_PARTIALS = 16;     // the in-kernel fold keeps one weight per partial result in registers
 
+// What a value row beyond the last one is read as.  Its weight is zero whatever stands there, but zero times an infinity is
+// not; a key row may be any (its score is replaced).  Four lanes read 64 contiguous bytes: the same 16 would take four times
+// as long.
+__device__ __align__(64) const unsigned char zeros[128] = {};
+
 struct AttnPlan {
     int bph, hpw, chunks;  // bf16: query blocks per head, heads per workgroup, units per kv head (see AttnParams)
     int units;             // workgroup units per sequence: kv heads x chunks (bf16), query heads (fp32)
@@ -863,19 +868,22 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
         }
     };
     if constexpr (NS == 2) {
-        // The tiles that are not full come the same way, a row beyond the last one as that row again (masked out): through
-        // registers behind the last full tile each of them cost its whole latency once more, 1.7 us.
+        // The tiles that are not full come the same way, a key beyond the last one as that one again (masked out), a value as
+        // zeros: through registers behind the last full tile each of them cost its whole latency once more, 1.7 us.
         auto issue_rest = [&](int i, unsigned char *stage) {
             const bool tail = i < n_tail;
             const unsigned char *ks = tail ? kp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)kt + (int64_t)(i - n_tail) * C::TILE_K;
             const unsigned char *vs = tail ? vp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)vt + (int64_t)(i - n_tail) * C::TILE_K;
             const int last = (tail ? tail_rows : p.n - (i - n_tail) * C::T) - 1;
             stage += wave * 1024;
+            int l = lane;
+            asm volatile("" : "+v"(l));                     // (worked out here, not kept in registers all along)
+            const unsigned char *no_row = zeros + (l & 3) * 16;
 #pragma unroll
             for (int j = 0; j < C::NI; ++j) {
                 const uint32_t off = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
                 load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
-                load_to_lds16<false>(vs, off, stage + C::TILE_K + j * C::WAVES * 1024);
+                load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off, stage + C::TILE_K + j * C::WAVES * 1024);
             }
         };
         auto arrived = [&]() {
@@ -922,11 +930,18 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
             unsigned char *stage = stage_of(x) + wave * 1024;
             if (F8 && x >= n8) {
                 const int t = (x - n8) >> 1, last = p.n - t * C::T - 1;
-                const unsigned char *src = (const unsigned char *)(((x - n8) & 1) ? vt : kt) + (int64_t)t * C::BTILE_K;
+                const bool values = (x - n8) & 1;
+                const unsigned char *src = (const unsigned char *)(values ? vt : kt) + (int64_t)t * C::BTILE_K;
+                int l = lane;
+                asm volatile("" : "+v"(l));                  // (addresses worked out here, not kept in registers all along)
+                auto row = [&](int j) { return (j * C::WAVES + wave) * (1024 / C::RB) + l / C::BCPR; };        // 1 KiB of bf16 rows per instruction
+                auto off = [&](int j) { return (uint32_t)(min(row(j), last) * C::RB + (((l % C::BCPR) ^ swz<D>(row(j))) * 16)); };
+                if (values) {
 #pragma unroll
-                for (int j = 0; j < C::DPT; ++j) {           // 1 KiB of bf16 rows per instruction
-                    const int r = (j * C::WAVES + wave) * (1024 / C::RB) + lane / C::BCPR;
-                    load_to_lds16<false>(src, (uint32_t)(min(r, last) * C::RB + (((lane % C::BCPR) ^ swz<D>(r)) * 16)), stage + j * C::WAVES * 1024);
+                    for (int j = 0; j < C::DPT; ++j) load_to_lds16_at(row(j) > last ? zeros + (l & 3) * 16 : src + off(j), stage + j * C::WAVES * 1024);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < C::DPT; ++j) load_to_lds16<false>(src, off(j), stage + j * C::WAVES * 1024);
                 }
                 return;
             }
@@ -934,11 +949,15 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
             const unsigned char *ks = tail ? kp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)kt + (int64_t)(x - n8) * C::TILE_K;
             const unsigned char *vs = tail ? vp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)vt + (int64_t)(x - n8) * C::TILE_K;
             const int last = (tail ? tail_rows : p.n - (x - n8) * C::T) - 1;
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            const unsigned char *no_row = zeros + (l & 3) * 16;
 #pragma unroll
             for (int j = 0; j < C::NI; ++j) {
                 const uint32_t off = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
                 load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
-                load_to_lds16<false>(vs, off, stage + C::TILE_K + j * C::WAVES * 1024);
+                if constexpr (F8) load_to_lds16<false>(vs, off, stage + C::TILE_K + j * C::WAVES * 1024);   // (the format has no infinity)
+                else load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off, stage + C::TILE_K + j * C::WAVES * 1024);
             }
         };
         auto issue = [&](int x) {
@@ -1228,6 +1247,8 @@ __global__ __launch_bounds__(256) void tree_attn_merge_bf16_kernel(const AttnPar
 // 459 -> 17; 80 nodes, 2 x 8 heads of 64, 1205 keys 150 -> 12; 82 nodes, 6 x 32 heads of 128, 120 keys 803 -> 40.
 constexpr int F32_ROWS = 16, F32_KEYS = 16;
 
+typedef __attribute__((address_space(1))) f32x4_t global_f32x4_t;   // (told apart from LDS: a choice of two addresses loses that)
+
 template <int D>
 struct F32Block {
     f32x4_t k[D / 16];          // K[key i][16 t + 4 g ..], i = lane % 16, g = lane / 16
@@ -1367,13 +1388,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
         const bool pre = blk < ks.n_pre;                     // (uniform)
         const int key0 = (pre ? blk : blk - ks.n_pre) * F32_KEYS, last = (pre ? ks.L : p.n) - 1;
         const float *kb = pre ? kp : kt, *vb = pre ? vp : vt;
-        const float *kr = kb + (int64_t)min(key0 + i, last) * D + 4 * g;      // keys beyond the last repeat it, masked below
+        const float *kr = kb + (int64_t)min(key0 + i, last) * D + 4 * g;      // keys beyond the last repeat it, masked below; values: zeros
 #pragma unroll
         for (int t = 0; t < KT; ++t) x.k[t] = *(const f32x4_t *)(kr + 16 * t);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < 4; ++r) {
+            const int key = key0 + 4 * g + r;
+            const global_f32x4_t *vr = key > last ? (const global_f32x4_t *)zeros + (lane & 3) : (const global_f32x4_t *)(vb + (int64_t)key * D + i * W);
 #pragma unroll
-            for (int j = 0; j < D / 64; ++j) x.v[r][j] = *(const f32x4_t *)(vb + (int64_t)min(key0 + 4 * g + r, last) * D + i * W + 4 * j);
+            for (int j = 0; j < D / 64; ++j) x.v[r][j] = vr[j];
+        }
     };
     auto compute = [&](const F32Block<D> &x, int blk) {
         f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
