@@ -879,11 +879,15 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
             int l = lane;
             asm volatile("" : "+v"(l));                     // (worked out here, not kept in registers all along)
             const unsigned char *no_row = zeros + (l & 3) * 16;
-#pragma unroll
+            int left = last - row0;                         // rows between the lane's and the last one
+            uint32_t off = goff;
+#pragma unroll 1
             for (int j = 0; j < C::NI; ++j) {
-                const uint32_t off = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
-                load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
-                load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off, stage + C::TILE_K + j * C::WAVES * 1024);
+                load_to_lds16<false>(ks, off + (uint32_t)(min(left, 0) * C::RBP), stage);
+                load_to_lds16_at(left < 0 ? no_row : vs + off, stage + C::TILE_K);
+                left -= STEP;
+                off += STEP * C::RBP;
+                stage += C::WAVES * 1024;
             }
         };
         auto arrived = [&]() {
@@ -930,18 +934,11 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
             unsigned char *stage = stage_of(x) + wave * 1024;
             if (F8 && x >= n8) {
                 const int t = (x - n8) >> 1, last = p.n - t * C::T - 1;
-                const bool values = (x - n8) & 1;
-                const unsigned char *src = (const unsigned char *)(values ? vt : kt) + (int64_t)t * C::BTILE_K;
-                int l = lane;
-                asm volatile("" : "+v"(l));                  // (addresses worked out here, not kept in registers all along)
-                auto row = [&](int j) { return (j * C::WAVES + wave) * (1024 / C::RB) + l / C::BCPR; };        // 1 KiB of bf16 rows per instruction
-                auto off = [&](int j) { return (uint32_t)(min(row(j), last) * C::RB + (((l % C::BCPR) ^ swz<D>(row(j))) * 16)); };
-                if (values) {
+                const unsigned char *src = (const unsigned char *)(((x - n8) & 1) ? vt : kt) + (int64_t)t * C::BTILE_K;
 #pragma unroll
-                    for (int j = 0; j < C::DPT; ++j) load_to_lds16_at(row(j) > last ? zeros + (l & 3) * 16 : src + off(j), stage + j * C::WAVES * 1024);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < C::DPT; ++j) load_to_lds16<false>(src, off(j), stage + j * C::WAVES * 1024);
+                for (int j = 0; j < C::DPT; ++j) {           // 1 KiB of bf16 rows per instruction
+                    const int r = (j * C::WAVES + wave) * (1024 / C::RB) + lane / C::BCPR;
+                    load_to_lds16<false>(src, (uint32_t)(min(r, last) * C::RB + (((lane % C::BCPR) ^ swz<D>(r)) * 16)), stage + j * C::WAVES * 1024);
                 }
                 return;
             }
@@ -957,7 +954,7 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
                 const uint32_t off = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
                 load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
                 if constexpr (F8) load_to_lds16<false>(vs, off, stage + C::TILE_K + j * C::WAVES * 1024);   // (the format has no infinity)
-                else load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off, stage + C::TILE_K + j * C::WAVES * 1024);
+                else load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + j * STEP * C::RBP + goff, stage + C::TILE_K + j * C::WAVES * 1024);
             }
         };
         auto issue = [&](int x) {
@@ -1003,6 +1000,13 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
             const int x = n8 + TS * t, have = min(n_slots, TS == 2 && t == 1 ? x + TS : x + NS - 1);
             arrived(have - x - TS);
             issue(x + NS - 1);
+            if (F8 && p.n - t * C::T < C::T) {               // (uniform) the values behind the last row: zeros after all
+                // (as addresses of their own for every lane, like above, they cost a small call 4 %: eight loads per slot)
+                for (int r = p.n - t * C::T + tid / C::BCPR; r < C::T; r += C::THREADS / C::BCPR)
+                    *(uint4 *)(stage_of(x + 1) + r * C::RB + (tid % C::BCPR) * 16) = make_uint4(0, 0, 0, 0);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+            }
             uint32_t bits[C::KPW];
             rest_bits(n_tail + t, bits);
             attn_tile<D, QBP, NS, 1, F8, false>(stage_of(x), la, qs, p.c, g, bits, 1.f, F8 ? stage_of(x + 1) : nullptr);
