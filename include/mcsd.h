@@ -109,8 +109,10 @@ void mcsd_free_mask(mcsd_mask_t *mask);
  *                          0..max_prefix (larger values are clamped to max_prefix).
  * dtype                  : element type of q/k/v/out.  MCSD_BF16: bf16 in, fp32 accumulate on MFMA, bf16 out
  *                          (when the keys of a (sequence, head) are split over workgroups, each workgroup's
- *                          unnormalised partial output is exchanged as bf16 with fp32 maxima and denominators: one
- *                          more rounding of the output's own precision).  MCSD_F32: fp32 end to end on the vector ALU.
+ *                          unnormalised partial output is exchanged with fp32 maxima and denominators: as bf16, one
+ *                          more rounding of the output's own precision, or, where max_prefix is so short that splitting
+ *                          only saves latency (at most 448 keys, 384 for up to 32 query rows per workgroup), as fp32).
+ *                          MCSD_F32: fp32 end to end on the fp32 matrix instructions.
  * Limits: d in {64, 128}; 1 <= n_nodes <= MCSD_ATTN_MAX_NODES; softmax_scale finite and > 0; all tensor
  * base addresses 16-byte aligned; node_stride*d and head_stride and seq_base multiples of 8 elements.
  * workspace: DEVICE, at least mcsd_tree_attention_workspace(...) bytes (0 when the keys are not split: then it may
@@ -250,7 +252,7 @@ int mcsd_tree_attention_tuned(const mcsd_attention_tuning_t *tuning, const mcsd_
  * when the library learns how workgroups are dealt to the chip's dies).  HOST only, nothing is launched.  For
  * measurement: it names the kernel instantiation and grid that profiler output has to be matched with. */
 typedef struct {
-    int32_t mfma_path;          /* 1: bf16 sweep on the matrix cores; 0: fp32 kernels on the vector ALU */
+    int32_t mfma_path;          /* 1: the bf16 kernel (also over an fp8 cache); 0: the fp32 kernel (fp32 matrix instructions) */
     int32_t query_blocks;       /* 32-row query blocks per workgroup: 1, 2 or 4 */
     int32_t key_splits;         /* workgroups that share the prefix keys of one (sequence, head [chunk]) */
     int32_t workgroups;         /* grid of the sweep launch */

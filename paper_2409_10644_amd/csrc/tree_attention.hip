@@ -66,7 +66,8 @@ struct AttnParams {
     int32_t G;        // workgroups per (b,h): S, plus one for the tree's own keys when the bf16 sweep splits the prefix
     int32_t tps;      // tiles per split (bf16 sweep): split s owns tiles [s*tps, (s+1)*tps) of every sequence
     int32_t SP;       // partial results per (b,h) (== G)
-    float *part_o;    // [B*H][SP][n][D]; the bf16 sweep keeps its partial O there as bf16 (see the end of the sweep kernel)
+    int32_t part_f32; // bf16 sweep: partial O as fp32, not bf16 (see PART_F32_KEYS)
+    float *part_o;    // [B*H][SP][n][D]; the bf16 sweep keeps its partial O there as bf16 unless part_f32
     float *part_m;    // [B*H][SP][n]   reference maximum of the raw scores
     float *part_l;    // [B*H][SP][n]   sum of exp2((s - m) * c)
 };
@@ -79,6 +80,11 @@ constexpr size_t WS_HEADER = 256, WS_CTR_BYTES = 64 * 1024;
 // machine), so counters of different (sequence, unit) pairs that share a line would queue behind each other.
 constexpr int CTR_STRIDE = 16;                          // in 8-byte counters
 constexpr int FOLD_MAX_PARTIALS = 16;     // the in-kernel fold keeps one weight per partial result in registers
+// Partial O of the bf16 sweep travel as bf16, half the bytes to store and fold, except for prefix bounds below this one: those
+// are split for latency alone, and an unsplit sequence is rounded once, from fp32.  With fp32 partial results a split one is
+// too.  Up to PART_F32_MAX partial results (what the fold holds at once); more only come from the caller's own plan.
+constexpr int PART_F32_KEYS = 512, PART_F32_MAX = 7;
+constexpr long PART_F32_BYTES = 16l << 20;  // all of a call's, as much as bf16 ones take when they fill the chip
 
 // What a value row beyond the last one is read as.  Its weight is zero whatever stands there, but zero times an infinity is
 // not; a key row may be any (its score is replaced).  Four lanes read 64 contiguous bytes: the same 16 would take four times
@@ -99,6 +105,7 @@ struct AttnPlan {
     int tree_last; // see AttnParams
     long grid_units; // (sequence, unit) slots of the grid: B * units, rounded up to a multiple of the dies where that lets the fold run in the kernel
     int fold;  // 1: folded inside the sweep kernel through the L2 its workgroups share
+    int part_f32;  // see AttnParams
 };
 
 __host__ __device__ inline int tile_keys_bf16(int QBP) { return QBP == 1 ? 128 : 64; }   // == SweepCfg::T
@@ -128,7 +135,9 @@ void device_shape(int &n_cus, int &n_xcc)
 // (1.03 us per 64 keys of 128 dimensions, 0.7 us of 64), partial results cost their exchange and fold (`fold_us`), two
 // workgroups on a compute unit slow each other down almost by their sum, and a grid beyond the residents costs its
 // remainder.  The choice is within 1 % of the best of the measured ones on average; the fixed rule before it (two
-// workgroups per compute unit, at least 256 keys per split) lost 11 %, up to 78 %.
+// workgroups per compute unit, at least 256 keys per split) lost 11 %, up to 78 %.  Prefixes of fewer than PART_F32_KEYS keys,
+// whose partial results are fp32, on another 140 shapes (8-256 units, 110-440 keys): the same prices but for two query blocks,
+// where the fold costs half as much again, are within 0.6 % of the best; not splitting at all would lose 11 %, up to 49 %.
 struct SplitChoice { int S, tree; };
 SplitChoice choose_splits(int d, int QBP, bool f8, int B, long bh, int tiles, int tree_tiles, int tree_forced)
 {
@@ -141,7 +150,8 @@ SplitChoice choose_splits(int d, int QBP, bool f8, int B, long bh, int tiles, in
     static const float fold_us[10] = {0.f, 0.f, 1.4f, 1.85f, 2.4f, 2.5f, 3.15f, 3.2f, 4.7f, 6.3f};   // by partial results
     const float tile_us = (d == 128 ? (QBP == 1 ? 1.6f : QBP == 2 ? 1.03f : 1.15f) : (QBP == 1 ? 1.f : QBP == 2 ? 0.7f : 0.74f)) *
                           (f8 ? 0.8f : 1.f);
-    const float fold_scale = (d == 64 ? 0.55f : 1.f) * (QBP == 4 ? 1.75f : QBP == 1 ? 1.35f : 1.f);
+    const bool part_f32 = tiles * tile_keys_bf16(QBP) < PART_F32_KEYS;
+    const float fold_scale = (d == 64 ? 0.55f : 1.f) * (QBP == 4 ? 1.75f : QBP == 1 ? 1.35f : part_f32 ? 1.5f : 1.f);
     const int per_cu = d == 128 && QBP == 1 ? 1 : 2;                     // resident workgroups (LDS)
     SplitChoice best = {1, tree_forced ? tree_forced : 2};
     if (bh > 256) {
@@ -158,6 +168,7 @@ SplitChoice choose_splits(int d, int QBP, bool f8, int B, long bh, int tiles, in
                 if (S == 1 && tree != 2) continue;
                 if (tree == 1 && bh * (S + 1) > (long)(CUS * per_cu)) continue;
                 const int parts = S + (tree == 1);
+                if (S > 1 && part_f32 && (parts > PART_F32_MAX || (long)bh * parts * QBP * 32 * d * 4 > PART_F32_BYTES)) continue;
                 const int most = S == 1 ? tiles + tree_tiles
                                  : tree == 1 ? (tps > tree_tiles ? tps : tree_tiles)
                                  : tree == 2 ? tps + tree_tiles : (tps > last + tree_tiles ? tps : last + tree_tiles);
@@ -252,6 +263,7 @@ AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int d, int n_rows, int n_k
     // a bare ring of direct-to-LDS loads needs ~5 us for 128 KB per workgroup on 128 compute units at any depth: a
     // cold burst of this size is bound by the memory system's ramp-up, not by the bytes a compute unit has in flight).
     if (tune && !f8 && tune->stages == 4 && dtype == MCSD_BF16 && pl.QBP != 1) pl.NS = 4;
+    pl.part_f32 = dtype == MCSD_BF16 && S > 1 && tiles_max * pl.T < PART_F32_KEYS && pl.G <= PART_F32_MAX && (f8 || pl.NS == 2);
     pl.xcc = n_xcc > 0 ? n_xcc : 8;        // unknown: the renumbering is then only a guess that may help locality
     // The fold runs inside the sweep when all workgroups of one (sequence, unit) share a die's L2: the dealing of
     // workgroup ids to dies is known, and the kernel's numbering keeps a unit's workgroups at one id modulo dies.
@@ -575,17 +587,20 @@ __device__ __forceinline__ uint32_t how_xcc(uint32_t how) { return (how >> 10) &
 // of a position is overwritten by the complete one: same lane, same address, program order).  The loads of the next
 // round are issued before this one is added up (two register buffers); a round beyond the last loads from beyond the
 // end, i.e. nothing, and is not added up.
+// PF32: the partial O are fp32.  A round is then one half of a column block (the same 16-byte chunks, four columns each), and
+// all partial results are one group.
 // Partial results are added in slot order whoever arrived last, so the result is reproducible.
 // Nothing here may spill: a workgroup's scratch memory is cold at this point, every first touch a trip to HBM (a
 // variant that spilled its weights took 9.7 us for five partial results, against 3).
-template <int D, int QBP, int KG, int NSLOT>
+template <int D, int QBP, int KG, int NSLOT, bool PF32 = false>
 __device__ __attribute__((always_inline)) inline void fold_partials(const __amdgpu_buffer_rsrc_t ro, const __amdgpu_buffer_rsrc_t rm,
                                      const __amdgpu_buffer_rsrc_t rl, const int n_active, const int kg, const int g,
                                      const int ln, const float cm, __bf16 *orow, f32x4_t *wlds)
 {
     constexpr int CB = D / 32;
     constexpr int NW = NSLOT == 8 ? FOLD_MAX_PARTIALS : NSLOT;      // partial results this variant can hold
-    constexpr int SLOT_BYTES = QBP * 32 * D * 2;
+    constexpr int SLOT_BYTES = QBP * 32 * D * (PF32 ? 4 : 2);
+    static_assert(!PF32 || NSLOT <= PART_F32_MAX, "one group");
     float wgt[NW], lw[NW];
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
@@ -593,11 +608,11 @@ __device__ __attribute__((always_inline)) inline void fold_partials(const __amdg
         lw[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rl, (i * QBP * 32 + ln) * 4, 0, 1));
     }
     const int ngrp = NSLOT == 8 && n_active > NSLOT ? 2 : 1;
-    const int rounds = ((CB - kg + KG - 1) / KG) * ngrp;
+    const int rounds = ((CB - kg + KG - 1) / KG) * (PF32 ? 2 : ngrp);
     typedef u32x4_t Round[NSLOT][2];
     auto issue = [&](Round &buf, int r) {
-        const int grp = r % ngrp, cb = kg + (r / ngrp) * KG;
-        int off = ((cb * 4 + g) * 32 + ln) * 16 + grp * NSLOT * SLOT_BYTES;
+        const int grp = r % ngrp, cb = kg + (PF32 ? r >> 1 : r / ngrp) * KG;
+        int off = PF32 ? ((cb * 8 + (r & 1) * 4 + g) * 32 + ln) * 16 : ((cb * 4 + g) * 32 + ln) * 16 + grp * NSLOT * SLOT_BYTES;
         if (r >= rounds) off = 0x40000000;                          // (uniform select) beyond every workspace
 #pragma unroll
         for (int i = 0; i < NSLOT; ++i)
@@ -626,6 +641,20 @@ __device__ __attribute__((always_inline)) inline void fold_partials(const __amdg
     }
     f32x4_t acc[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     auto add_up = [&](Round &buf, int r) {
+        if constexpr (PF32) {
+            const int cb = kg + (r >> 1) * KG;
+#pragma unroll
+            for (int jp = 0; jp < 2; ++jp) {
+                f32x4_t a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < NSLOT; ++i) a += wgt[i] * __builtin_bit_cast(f32x4_t, buf[i][jp]);        // slot order
+                bf16x4_t v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (__bf16)(a[e] * inv);
+                *(bf16x4_t *)(orow + cb * 32 + 16 * (r & 1) + 8 * jp + 4 * g) = v;
+            }
+            return;
+        }
         const int grp = r % ngrp, cb = kg + (r / ngrp) * KG;
         float w[NSLOT];
         if constexpr (NSLOT == 8) {
@@ -664,11 +693,11 @@ __device__ __attribute__((always_inline)) inline void fold_partials(const __amdg
     }
 }
 
-template <int D, int QBP, int NS, bool F8 = false>
-__global__ __launch_bounds__((SweepCfg<D, QBP, NS, F8>::THREADS)) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const uint32_t per_die, const int32_t G,
-                           const uint32_t mul_G, const int32_t H, const uint32_t mul_H, const int32_t BH,
-                           const uint32_t how, const int32_t max_prefix, const int32_t tps, const AttnParams p)
+// PF32: partial O as fp32 (see PART_F32_KEYS).
+template <int D, int QBP, int NS, bool F8, bool PF32>
+__device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_base, const uint32_t per_die, const int32_t G, const uint32_t mul_G,
+                                      const int32_t H, const uint32_t mul_H, const int32_t BH, const uint32_t how, const int32_t max_prefix,
+                                      const int32_t tps, const AttnParams &p)
 {
     using C = SweepCfg<D, QBP, NS, F8>;
     __shared__ __attribute__((aligned(1024))) unsigned char ring[C::LDS_BYTES];
@@ -1093,14 +1122,21 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
     if (qrow < p.n) {                                      // padded query rows are never read back
         // O goes out rounded to bf16, the precision the output itself has (one more rounding of 2^-9 relative to the
         // partial's own magnitude; maxima and denominators stay fp32): half the bytes to write, acknowledge and fold.
-        // A lane's 16-byte chunk is two pieces.
-        __bf16 *po = (__bf16 *)p.part_o + ((bh * p.SP + slot_id) * (int64_t)(QBP * 32 * D)) + qb * 32 * D;
+        // A lane's 16-byte chunk is two pieces.  Short prefixes: fp32, a chunk per piece.
+        const int64_t slot0 = (bh * p.SP + slot_id) * (int64_t)(QBP * 32 * D) + qb * 32 * D;
+        if constexpr (PF32) {
+            float *po = p.part_o + slot0;
 #pragma unroll
-        for (int x2 = 0; x2 < PP / 2; ++x2) {
-            bf16x8_t v;
+            for (int x = 0; x < PP; ++x) *(f32x4_t *)(po + (((kg * PP + x) * 2 + g) * 32 + ln) * 4) = acc[x];
+        } else {
+            __bf16 *po = (__bf16 *)p.part_o + slot0;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = (__bf16)acc[2 * x2 + (e >> 2)][e & 3];
-            *(bf16x8_t *)(po + (((kg * (PP / 2) + x2) * 2 + g) * 32 + ln) * 8) = v;
+            for (int x2 = 0; x2 < PP / 2; ++x2) {
+                bf16x8_t v;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = (__bf16)acc[2 * x2 + (e >> 2)][e & 3];
+                *(bf16x8_t *)(po + (((kg * (PP / 2) + x2) * 2 + g) * 32 + ln) * 8) = v;
+            }
         }
         if (kg == 0 && g == 0) {
             const int64_t prow = (bh * p.SP + slot_id) * (QBP * 32) + qb * 32 + ln;
@@ -1154,19 +1190,34 @@ void tree_attn_bf16_kernel(const int32_t *lens, const int64_t *seq_base, const u
     // Every wavefront folds its query block's rows for its share of the columns (32-column blocks kg, kg + KG, ..),
     // all partial results read back in slot order, its own included: the result does not depend on who came last.
     // Loads go through buffer descriptors that end after the last partial result in use (see fold_partials).
+    constexpr int part_bytes = QBP * 32 * D * (PF32 ? 4 : 2);
     const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)((__bf16 *)p.part_o + (bh * p.SP) * (int64_t)(QBP * 32 * D) + qb * 32 * D), 0, (int)(n_active * QBP * 32 * D * 2), 0x00027000);
+        (void *)((char *)p.part_o + (bh * p.SP) * (int64_t)part_bytes + qb * (part_bytes / QBP)), 0, n_active * part_bytes, 0x00027000);
     const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(p.part_m + bh * p.SP * (QBP * 32) + qb * 32), 0, (int)(n_active * QBP * 32 * 4), 0x00027000);
     const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(p.part_l + bh * p.SP * (QBP * 32) + qb * 32), 0, (int)(n_active * QBP * 32 * 4), 0x00027000);
     __bf16 *orow = (__bf16 *)p.out + (bh_q * p.node_stride + qrow) * D;
     // as few slots per round as hold the partial results: a load beyond the end still costs its turn in the L1
-    if (n_active <= 3) fold_partials<D, QBP, C::KG, 3>(ro, rm, rl, n_active, kg, g, ln, cm, orow, (f32x4_t *)ring + tid);
-    else if (n_active <= 5) fold_partials<D, QBP, C::KG, 5>(ro, rm, rl, n_active, kg, g, ln, cm, orow, (f32x4_t *)ring + tid);
-    else if (n_active <= 7) fold_partials<D, QBP, C::KG, 7>(ro, rm, rl, n_active, kg, g, ln, cm, orow, (f32x4_t *)ring + tid);
-    else fold_partials<D, QBP, C::KG, 8>(ro, rm, rl, n_active, kg, g, ln, cm, orow, (f32x4_t *)ring + tid);
+    if (n_active <= 3) fold_partials<D, QBP, C::KG, 3, PF32>(ro, rm, rl, n_active, kg, g, ln, cm, orow, (f32x4_t *)ring + tid);
+    else if (n_active <= 5) fold_partials<D, QBP, C::KG, 5, PF32>(ro, rm, rl, n_active, kg, g, ln, cm, orow, (f32x4_t *)ring + tid);
+    else if (PF32 || n_active <= 7) fold_partials<D, QBP, C::KG, 7, PF32>(ro, rm, rl, n_active, kg, g, ln, cm, orow, (f32x4_t *)ring + tid);
+    else fold_partials<D, QBP, C::KG, PF32 ? 7 : 8, PF32>(ro, rm, rl, n_active, kg, g, ln, cm, orow, (f32x4_t *)ring + tid);
 }
+
+#define SWEEP_KERNEL(NAME, PF32)                                                                                                    \
+    template <int D, int QBP, int NS, bool F8 = false>                                                                              \
+    __global__ __launch_bounds__((SweepCfg<D, QBP, NS, F8>::THREADS)) __attribute__((amdgpu_waves_per_eu(2, 2)))                    \
+    void NAME(const int32_t *lens, const int64_t *seq_base, const uint32_t per_die, const int32_t G, const uint32_t mul_G,          \
+              const int32_t H, const uint32_t mul_H, const int32_t BH, const uint32_t how, const int32_t max_prefix,                \
+              const int32_t tps, const AttnParams p)                                                                                \
+    {                                                                                                                               \
+        sweep<D, QBP, NS, F8, PF32>(lens, seq_base, per_die, G, mul_G, H, mul_H, BH, how, max_prefix, tps, p);                      \
+    }
+SWEEP_KERNEL(tree_attn_bf16_kernel, false)
+// (a kernel of its own: as a branch the second set of folds cost calls that never fold up to 3.6 %)
+SWEEP_KERNEL(tree_attn_bf16_short_kernel, true)
+#undef SWEEP_KERNEL
 
 // Folds the partial results of the key splits of the bf16 sweep.  One thread per 4 output columns of one query;
 // fragment order makes the loads of a wavefront contiguous.  Partials are folded in split order.
@@ -1206,9 +1257,13 @@ __global__ __launch_bounds__(256) void tree_attn_merge_bf16_kernel(const AttnPar
                 const int64_t prow = (bh * p.SP + s0 + i) * (QBP * 32) + lrow;
                 m[i] = p.part_m[prow];
                 l[i] = p.part_l[prow];
-                const bf16x4_t ob = *(const bf16x4_t *)((const __bf16 *)p.part_o + ((bh * p.SP + s0 + i) * (int64_t)(QBP * 32 * D)) +
-                                                        qb * 32 * D + ((((f >> 2) * 2 + ((f >> 1) & 1)) * 2 + g) * 32 + ln) * 8 + (f & 1) * 4);
-                o[i] = (f32x4_t){(float)ob[0], (float)ob[1], (float)ob[2], (float)ob[3]};
+                const int64_t slot0 = (bh * p.SP + s0 + i) * (int64_t)(QBP * 32 * D) + qb * 32 * D;
+                if (p.part_f32) {
+                    o[i] = *(const f32x4_t *)(p.part_o + slot0 + ((f * 2 + g) * 32 + ln) * 4);
+                } else {
+                    const bf16x4_t ob = *(const bf16x4_t *)((const __bf16 *)p.part_o + slot0 + ((((f >> 2) * 2 + ((f >> 1) & 1)) * 2 + g) * 32 + ln) * 8 + (f & 1) * 4);
+                    o[i] = (f32x4_t){(float)ob[0], (float)ob[1], (float)ob[2], (float)ob[3]};
+                }
             }
         }
         float Mn = M;
@@ -1556,7 +1611,7 @@ size_t workspace_bytes_for(const AttnPlan &pl, int dtype, int B, int d)
 {
     if (pl.S == 1) return 0;
     const size_t rows = partial_rows(pl, dtype, B);
-    return WS_HEADER + WS_CTR_BYTES + 2 * align256(rows * sizeof(float)) + align256(rows * d * (dtype == MCSD_BF16 ? 2 : sizeof(float)));
+    return WS_HEADER + WS_CTR_BYTES + 2 * align256(rows * sizeof(float)) + align256(rows * d * (dtype == MCSD_BF16 && !pl.part_f32 ? 2 : sizeof(float)));
 }
 
 // Prepares a workspace: tag word, zero counters.  One thread per 16 bytes of the header and counter area.
@@ -1576,7 +1631,10 @@ void launch_sweep(const AttnParams &p, const AttnPlan &pl, hipStream_t st)
     uint32_t how = g.shift | h.shift << 5 | log2_xcc << 10;
     if (pl.G > 1 && p.pair_cus == 0 && p.xcc > 1 && total % p.xcc == 0 && (1 << log2_xcc) == p.xcc) how |= HOW_RENUMBER;
     if (p.pair_cus > 0) how |= HOW_PAIR;
-    mcsd_launch(MCSD_KERNEL_ATTN_SWEEP, tree_attn_bf16_kernel<D, QBP, NS, F8>, dim3(total), dim3(SweepCfg<D, QBP, NS, F8>::THREADS), st,
+    auto kernel = tree_attn_bf16_kernel<D, QBP, NS, F8>;
+    if constexpr (F8 || NS == 2)
+        if (pl.part_f32) kernel = tree_attn_bf16_short_kernel<D, QBP, NS, F8>;
+    mcsd_launch(MCSD_KERNEL_ATTN_SWEEP, kernel, dim3(total), dim3(SweepCfg<D, QBP, NS, F8>::THREADS), st,
                 p.lens, p.seq_base, total >> log2_xcc, (int32_t)pl.G, g.mul, p.H, h.mul, (int32_t)(p.B * p.H), how, p.max_prefix, p.tps, p);
 }
 
@@ -1646,8 +1704,19 @@ size_t workspace_query(const mcsd_attention_tuning_t *tune, bool f8, int32_t B, 
             if (tiles < 2 || most < 1) most = 1;
             a.G = (int)most;
             a.S = most > 1 ? 2 : 1;
+            a.part_f32 = 0;
             const size_t w = workspace_bytes_for(a, MCSD_BF16, B, d);
             if (w > wa) wa = w;
+            // a short prefix: fewer partial results, each twice the bytes
+            const long part = bh * a.QBP * 32 * d * 4, few = (PART_F32_KEYS - 1) / a.T < tiles ? (PART_F32_KEYS - 1) / a.T : tiles;
+            if (most > few + 1) most = few + 1;
+            if (most > PART_F32_MAX) most = PART_F32_MAX;
+            if (most * part > PART_F32_BYTES) most = PART_F32_BYTES / part;
+            if (few < 2 || most < 2) continue;
+            a.G = (int)most;
+            a.part_f32 = 1;
+            const size_t w32 = workspace_bytes_for(a, MCSD_BF16, B, d);
+            if (w32 > wa) wa = w32;
         }
     }
     if (f8) return wa;
@@ -1716,6 +1785,7 @@ int attention_call(const mcsd_attention_tuning_t *tune, const mcsd_mask_view_t *
     p.tree_last = pl.tree_last;
     p.xcc = pl.xcc;
     p.fold = pl.fold;
+    p.part_f32 = pl.part_f32;
     p.tps = (int32_t)((((int64_t)max_prefix + pl.T - 1) / pl.T + pl.S - 1) / pl.S);
     if (p.tps < 1) p.tps = 1;
     const FastDiv tps = fast_div_of(p.tps);

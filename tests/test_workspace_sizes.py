@@ -36,6 +36,9 @@ def _need(kind, dtype, B, Hq, Hkv, d, n, row0, L):
         # (a grid rounded up to whole dies has empty slots, without partial results)
         units = B * Hq // hpw
         slots = min(slots, units * (slots // units))
+        keys = 128 if p.query_blocks == 1 else 64
+        if (L + keys - 1) // keys * keys < 512 and slots // units <= 7:     # short prefixes: partial outputs in fp32
+            size = 4
     up = lambda x: (x + 255) // 256 * 256
     return 256 + 65536 + 2 * up(slots * rows * 4) + up(slots * rows * d * size)
 
