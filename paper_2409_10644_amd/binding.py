@@ -192,7 +192,7 @@ def _load_pycall():
 
     def setup(get_device):
         mod.setup(tuple(C.cast(getattr(lib, n), C.c_void_p).value for n in mod.names()), torch.Tensor,
-                  torch._C._cuda_getCurrentRawStream, get_device, _raise)
+                  torch._C._cuda_getCurrentRawStream, get_device, _raise, MaskView, Mlp, C.ArgumentError)
 
     setup(device)
     return mod

@@ -21,6 +21,8 @@ const char *const FN_NAME[N_FN] = {"mcsd_tree_attention", "mcsd_tree_attention_r
 void *g_fn[N_FN];
 // torch.Tensor and its methods, torch's raw stream and device getters, and what raises on a status
 PyObject *g_tensor, *g_data_ptr, *g_numel, *g_element_size, *g_raw_stream, *g_device, *g_raise;
+// the binding's structures, and ctypes' error for an argument that is another one
+PyObject *g_mask_view, *g_mlp, *g_argument_error;
 PyObject *g_str_data_ptr, *g_str_cuda_stream, *g_str_numel, *g_str_element_size;
 
 int64_t call_int(PyObject *method, PyObject *name, PyObject *self)
@@ -90,18 +92,19 @@ struct Args {
         }
         return p;
     }
-    // the memory of a ctypes structure of at least `size` bytes, which the caller's argument keeps alive
-    void *structure(size_t size)
+    // the memory of a ctypes structure of the given class, which the caller's argument keeps alive
+    void *structure(PyObject *cls)
     {
         if (!ok) return nullptr;
         PyObject *o = next();
+        if (!PyObject_TypeCheck(o, (PyTypeObject *)cls)) {
+            PyErr_Format(g_argument_error, "argument %zd: expected %s, got %s", i, ((PyTypeObject *)cls)->tp_name, Py_TYPE(o)->tp_name);
+            ok = false;
+            return nullptr;
+        }
         Py_buffer b;
         if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) { ok = false; return nullptr; }
         void *p = b.buf;
-        if ((size_t)b.len < size) {
-            PyErr_SetString(PyExc_TypeError, "structure too small");
-            ok = false;
-        }
         PyBuffer_Release(&b);
         return p;
     }
@@ -165,7 +168,7 @@ template <Fn FN>
 PyObject *py_attention(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     Args a(args, nargs, FN == ATTN ? 19 : (FN == ATTN_ROWS ? 20 : (FN == ATTN_GQA ? 21 : 18)));
-    auto view = (const mcsd_mask_view_t *)a.structure(sizeof(mcsd_mask_view_t));
+    auto view = (const mcsd_mask_view_t *)a.structure(g_mask_view);
     const auto dtype = (mcsd_dtype_t)a.i32();
     const int32_t B = a.i32(), H = a.i32();
     const int32_t Hkv = FN == ATTN_GQA ? a.i32() : 0;
@@ -197,7 +200,7 @@ PyObject *py_attention(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 PyObject *py_attention_fp8(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     Args a(args, nargs, 21);
-    auto view = (const mcsd_mask_view_t *)a.structure(sizeof(mcsd_mask_view_t));
+    auto view = (const mcsd_mask_view_t *)a.structure(g_mask_view);
     const int32_t B = a.i32(), H = a.i32(), Hkv = a.i32(), row = a.i32();
     void *q = a.tensor(), *kt = a.tensor(), *vt = a.tensor();
     const int64_t node_stride = a.integer();
@@ -219,7 +222,7 @@ template <Fn FN>
 PyObject *py_verify(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     Args a(args, nargs, FN == VERIFY ? 17 : 18);
-    auto view = (const mcsd_mask_view_t *)a.structure(sizeof(mcsd_mask_view_t));
+    auto view = (const mcsd_mask_view_t *)a.structure(g_mask_view);
     const auto mode = (mcsd_mode_t)a.i32();
     const auto sampling = FN == VERIFY ? MCSD_WITH_REPLACEMENT : (mcsd_sampling_t)a.i32();
     const int32_t B = a.i32(), V = a.i32();
@@ -242,7 +245,7 @@ PyObject *py_verify(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 PyObject *py_commit(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     Args a(args, nargs, 24);
-    auto view = (const mcsd_mask_view_t *)a.structure(sizeof(mcsd_mask_view_t));
+    auto view = (const mcsd_mask_view_t *)a.structure(g_mask_view);
     const auto dtype = (mcsd_dtype_t)a.i32();
     const int32_t B = a.i32(), H = a.i32(), d = a.i32();
     constexpr int32_t MOST = MCSD_COMMIT_MAX_LAYERS;
@@ -269,7 +272,7 @@ PyObject *py_commit(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 PyObject *py_stop_distribution(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     Args a(args, nargs, 13);
-    auto mlp = (const mcsd_mlp_t *)a.structure(sizeof(mcsd_mlp_t));
+    auto mlp = (const mcsd_mlp_t *)a.structure(g_mlp);
     const int32_t B = a.i32(), W = a.i32(), V = a.i32(), k = a.i32();
     auto rows = (const float *)a.tensor();
     const int64_t bs = a.integer(), rs = a.integer();
@@ -283,7 +286,7 @@ PyObject *py_stop_distribution(PyObject *, PyObject *const *args, Py_ssize_t nar
 PyObject *py_stop_hidden(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     Args a(args, nargs, 10);
-    auto mlp = (const mcsd_mlp_t *)a.structure(sizeof(mcsd_mlp_t));
+    auto mlp = (const mcsd_mlp_t *)a.structure(g_mlp);
     const int32_t B = a.i32(), W = a.i32();
     auto hidden = (const float *)a.tensor();
     const int64_t bs = a.integer(), rs = a.integer();
@@ -300,22 +303,23 @@ PyObject *py_slice(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     Args a(args, nargs, 3);
     auto mask = nargs == 3 && args[0] == Py_None ? (a.i++, nullptr) : (const mcsd_mask_t *)(uintptr_t)a.integer();
     const int32_t gamma = a.i32();
-    auto view = (mcsd_mask_view_t *)a.structure(sizeof(mcsd_mask_view_t));
+    auto view = (mcsd_mask_view_t *)a.structure(g_mask_view);
     if (!a.ok) return nullptr;
     return done(((decltype(&mcsd_slice_mask))g_fn[SLICE])(mask, gamma, view), SLICE);
 }
 
-// setup(addresses of the entry points in the order of Fn, torch.Tensor, raw_stream, device, raise)
+// setup(addresses of the entry points in the order of Fn, torch.Tensor, raw_stream, device, raise, MaskView, Mlp, ctypes.ArgumentError)
 PyObject *py_setup(PyObject *, PyObject *args)
 {
     PyObject *addr;
-    if (!PyArg_ParseTuple(args, "O!OOOO", &PyTuple_Type, &addr, &g_tensor, &g_raw_stream, &g_device, &g_raise)) return nullptr;
+    if (!PyArg_ParseTuple(args, "O!OOOOO!O!O", &PyTuple_Type, &addr, &g_tensor, &g_raw_stream, &g_device, &g_raise, &PyType_Type, &g_mask_view,
+                          &PyType_Type, &g_mlp, &g_argument_error)) return nullptr;
     if (PyTuple_GET_SIZE(addr) != N_FN) {
         PyErr_SetString(PyExc_ValueError, "one address per entry point");
         return nullptr;
     }
     for (int i = 0; i < N_FN; ++i) g_fn[i] = (void *)(uintptr_t)PyLong_AsUnsignedLongLongMask(PyTuple_GET_ITEM(addr, i));
-    for (PyObject *o : {g_tensor, g_raw_stream, g_device, g_raise}) Py_INCREF(o);       // held for the life of the process
+    for (PyObject *o : {g_tensor, g_raw_stream, g_device, g_raise, g_mask_view, g_mlp, g_argument_error}) Py_INCREF(o);       // held for the life of the process
     g_data_ptr = PyObject_GetAttr(g_tensor, g_str_data_ptr);
     g_numel = PyObject_GetAttr(g_tensor, g_str_numel);
     g_element_size = PyObject_GetAttr(g_tensor, g_str_element_size);
