@@ -106,7 +106,10 @@ struct AttnPlan {
     long grid_units; // (sequence, unit) slots of the grid: B * units, rounded up to a multiple of the dies where that lets the fold run in the kernel
     int fold;  // 1: folded inside the sweep kernel through the L2 its workgroups share
     int part_f32;  // see AttnParams
+    int cus;       // compute units the plan is made for
 };
+
+constexpr int MCSD_CUS = 256;             // of the whole chip: what a plan is made for where there is no device to ask
 
 __host__ __device__ inline int tile_keys_bf16(int QBP) { return QBP == 1 ? 128 : 64; }   // == SweepCfg::T
 
@@ -139,14 +142,13 @@ void device_shape(int &n_cus, int &n_xcc)
 // whose partial results are fp32, on another 140 shapes (8-256 units, 110-440 keys): the same prices but for two query blocks,
 // where the fold costs half as much again, are within 0.6 % of the best; not splitting at all would lose 11 %, up to 49 %.
 struct SplitChoice { int S, tree; };
-SplitChoice choose_splits(int d, int QBP, bool f8, int B, long bh, int tiles, int tree_tiles, int tree_forced)
+SplitChoice choose_splits(int cus, int d, int QBP, bool f8, int B, long bh, int tiles, int tree_tiles, int tree_forced)
 {
-    struct Memo { int d, QBP, f8, B, tiles, tree_tiles, forced; long bh; SplitChoice c; };
-    static thread_local Memo memo = {0, 0, 0, 0, 0, 0, 0, 0, {1, 2}};    // a decoding loop asks for the same shape again and again
-    if (memo.d == d && memo.QBP == QBP && memo.f8 == (int)f8 && memo.B == B && memo.bh == bh && memo.tiles == tiles &&
+    struct Memo { int cus, d, QBP, f8, B, tiles, tree_tiles, forced; long bh; SplitChoice c; };
+    static thread_local Memo memo = {0, 0, 0, 0, 0, 0, 0, 0, 0, {1, 2}}; // a decoding loop asks for the same shape again and again
+    if (memo.cus == cus && memo.d == d && memo.QBP == QBP && memo.f8 == (int)f8 && memo.B == B && memo.bh == bh && memo.tiles == tiles &&
         memo.tree_tiles == tree_tiles && memo.forced == tree_forced)
         return memo.c;
-    constexpr float CUS = 256.f;
     static const float fold_us[10] = {0.f, 0.f, 1.4f, 1.85f, 2.4f, 2.5f, 3.15f, 3.2f, 4.7f, 6.3f};   // by partial results
     const float tile_us = (d == 128 ? (QBP == 1 ? 1.6f : QBP == 2 ? 1.03f : 1.15f) : (QBP == 1 ? 1.f : QBP == 2 ? 0.7f : 0.74f)) *
                           (f8 ? 0.8f : 1.f);
@@ -154,41 +156,41 @@ SplitChoice choose_splits(int d, int QBP, bool f8, int B, long bh, int tiles, in
     const float fold_scale = (d == 64 ? 0.55f : 1.f) * (QBP == 4 ? 1.75f : QBP == 1 ? 1.35f : part_f32 ? 1.5f : 1.f);
     const int per_cu = d == 128 && QBP == 1 ? 1 : 2;                     // resident workgroups (LDS)
     SplitChoice best = {1, tree_forced ? tree_forced : 2};
-    if (bh > 256) {
+    if (bh > cus) {
         // The chip is full without splits.  Halves even out ragged batches where two workgroups fit a compute unit.
-        if (per_cu == 2 && bh < 512 && tiles >= 8) best.S = 2;
+        if (per_cu == 2 && bh < 2 * cus && tiles >= 8) best.S = 2;
     } else {
         float best_us = 1e30f;
-        for (int S = 1; S <= 15 && S <= (tiles > 1 ? tiles : 1) && (S == 1 || bh * S <= 512); ++S) {
+        for (int S = 1; S <= 15 && S <= (tiles > 1 ? tiles : 1) && (S == 1 || bh * S <= 2 * cus); ++S) {
             const int tps = tiles > S ? (tiles + S - 1) / S : 1;
             if (S > 1 && (tiles + tps - 1) / tps != S) continue;         // some split would have no keys
             const int last = tiles - (S - 1) * tps;
             for (int tree = 1; tree <= 3; ++tree) {
                 if (tree_forced && tree != tree_forced && S > 1) continue;
                 if (S == 1 && tree != 2) continue;
-                if (tree == 1 && bh * (S + 1) > (long)(CUS * per_cu)) continue;
+                if (tree == 1 && bh * (S + 1) > (long)cus * per_cu) continue;
                 const int parts = S + (tree == 1);
                 if (S > 1 && part_f32 && (parts > PART_F32_MAX || (long)bh * parts * QBP * 32 * d * 4 > PART_F32_BYTES)) continue;
                 const int most = S == 1 ? tiles + tree_tiles
                                  : tree == 1 ? (tps > tree_tiles ? tps : tree_tiles)
                                  : tree == 2 ? tps + tree_tiles : (tps > last + tree_tiles ? tps : last + tree_tiles);
-                const float all = (float)(tiles + tree_tiles), load = (float)bh * parts / CUS;   // workgroups per compute unit
+                const float all = (float)(tiles + tree_tiles), load = (float)bh * parts / cus;   // workgroups per compute unit
                 float us;
                 if (load <= 1.f) us = tile_us * most;
                 else if (load <= per_cu) us = 0.94f * tile_us * (most + 0.8f * all / parts);
                 else {
-                    const float even = all * bh / CUS, two = (float)most * per_cu;
+                    const float even = all * bh / cus, two = (float)most * per_cu;
                     if (S == 1) us = 0.9f * tile_us * two * (float)(int)(load / per_cu + 0.999f);
                     else us = tile_us * ((tree == 3 ? 0.88f : 0.98f) * (two > even ? two : even) + (tree == 3 ? 0.5f : 0.3f) * most);
                 }
-                if (tree == 3 && B > 1 && bh * S > 256) us *= 1.08f;     // (not ordered by length)
-                if (tree == 2 && S > 1 && bh * S > 256) us += 1.85f;     // the ordering by length itself
+                if (tree == 3 && B > 1 && bh * S > cus) us *= 1.08f;     // (not ordered by length)
+                if (tree == 2 && S > 1 && bh * S > cus) us += 1.85f;     // the ordering by length itself
                 if (parts > 1) us += fold_us[parts < 9 ? parts : 9] * fold_scale;
                 if (us < best_us) { best_us = us; best = {S, tree}; }
             }
         }
     }
-    memo = {d, QBP, (int)f8, B, tiles, tree_tiles, tree_forced, bh, best};
+    memo = {cus, d, QBP, (int)f8, B, tiles, tree_tiles, tree_forced, bh, best};
     return best;
 }
 
@@ -227,31 +229,33 @@ AttnPlan make_plan(int dtype, int B, int Hq, int Hkv, int d, int n_rows, int n_k
     // fp32: one workgroup per compute unit while that takes splitting (more only add partial results: 12 heads of 64, 1024
     // keys, 60 nodes: 9.2 us with 192 workgroups, 10.4 with 384), else as many as fit (4 per compute unit at d = 64, 2 at
     // 128), which evens out ragged batches; at least five 16-key blocks per split.
+    int n_cus, n_xcc;
+    device_shape(n_cus, n_xcc);
+    const int cus = n_cus > 0 ? n_cus : MCSD_CUS;
     long S;
     int tree = 2;
     const int tree_forced = tune && dtype == MCSD_BF16 ? tune->tree_keys : 0;
     if (dtype == MCSD_F32) {
         const long u = (bh + 7) / 8 * 8 * pl.QT;            // (a die's slots are whole (sequence, head) pairs, see grid_units)
-        S = u <= 256 ? 256 / u : (d == 64 ? (1023 + u) / u : 512 / u);
+        S = u <= cus ? cus / u : (d == 64 ? (4 * cus - 1 + u) / u : 2 * cus / u);
         if (S > tiles_max / 5) S = tiles_max / 5;
         if (S < 1) S = 1;
         if (S > 64) S = 64;
     } else {
-        const SplitChoice c = choose_splits(d, pl.QBP, f8, B, bh, (int)tiles_max, (n_keys + pl.T - 1) / pl.T, tree_forced);
+        const SplitChoice c = choose_splits(cus, d, pl.QBP, f8, B, bh, (int)tiles_max, (n_keys + pl.T - 1) / pl.T, tree_forced);
         S = c.S;
         tree = c.tree;
     }
     if (tune && tune->key_splits >= 1 && tune->key_splits <= 64) {       // the caller's choice
         S = tune->key_splits;
         // with that many, the tree's keys in a workgroup of their own while all workgroups are resident at once
-        if (dtype == MCSD_BF16) tree = tree_forced ? tree_forced : bh * (S + 1) <= 512 ? 1 : 2;
+        if (dtype == MCSD_BF16) tree = tree_forced ? tree_forced : bh * (S + 1) <= 2 * cus ? 1 : 2;
     }
     pl.NS = f8 ? 4 : 2;                                     // LDS stages (bf16: see below)
     pl.S = (int)S;
+    pl.cus = cus;
     pl.G = (dtype == MCSD_BF16 && S > 1 && tree == 1) ? (int)S + 1 : (int)S;
     pl.tree_last = dtype == MCSD_BF16 && S > 1 && tree == 3;
-    int n_cus, n_xcc;
-    device_shape(n_cus, n_xcc);
     // Ragged grids larger than the chip are ordered by length inside the kernel (see there)
     pl.pair_cus = 0;
     if (dtype == MCSD_BF16 && pl.G == pl.S && (long)B * pl.S <= 256 && n_cus > 0 && bh * pl.S > n_cus &&
@@ -1698,7 +1702,7 @@ size_t workspace_query(const mcsd_attention_tuning_t *tune, bool f8, int32_t B, 
         for (int rows = n_nodes - row_begin; rows > 0; rows = rows > 64 ? 64 : rows > 32 ? 32 : 0) {
             AttnPlan a = make_plan(MCSD_BF16, B, H_q, H_kv, d, rows, n_nodes, max_prefix, f8, tune);
             const long bh = (long)B * a.units, tiles = ((long)max_prefix + a.T - 1) / a.T;
-            long most = bh > 256 ? a.G : 512 / bh;
+            long most = bh > a.cus ? a.G : 2 * a.cus / bh;
             if (most > tiles + 1) most = tiles + 1;
             if (most > 16) most = 16;
             if (tiles < 2 || most < 1) most = 1;
