@@ -13,7 +13,8 @@ import subprocess
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+from paper_2409_10644_amd.build import COMMON, CSRC, SOURCES
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
@@ -22,10 +23,9 @@ def sweep_asm(tmp_path_factory):
     if not (os.path.exists(HIPCC) or shutil.which(HIPCC)):
         pytest.skip("hipcc not available")
     out = tmp_path_factory.mktemp("asm") / "tree_attention.s"
-    csrc = os.path.join(ROOT, "paper_2409_10644_amd", "csrc")
-    cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", csrc,
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-S", "--cuda-device-only", "-o", str(out),
-           os.path.join(csrc, "tree_attention.hip")]
+    # with the flags of the build itself: what they do to the kernels (arguments preloaded into registers, say) is in what ships
+    cmd = [HIPCC, *COMMON, *SOURCES["tree_attention.hip"], "-S", "--cuda-device-only", "-o", str(out),
+           os.path.join(CSRC, "tree_attention.hip")]
     subprocess.run(cmd, check=True, capture_output=True)
     return out.read_text().split("\n")
 
@@ -52,7 +52,7 @@ def test_m0_is_only_touched_by_the_kernels_own_assembly(sweep_asm):
 def test_steady_state_loops_wait_for_memory_once_per_tile(sweep_asm):
     checked = 0
     for name, body in _functions(sweep_asm):
-        if "tree_attn_bf16_kernel" not in name:
+        if "tree_attn_bf16_kernel" not in name and "tree_attn_bf16_short_kernel" not in name:
             continue
         labels = {m.group(1): i for i, l in enumerate(body) if (m := re.match(r"^(\.LBB\d+_\d+):", l))}
         loops = []
@@ -91,5 +91,12 @@ def test_steady_state_loops_wait_for_memory_once_per_tile(sweep_asm):
                 [0, loads_per_tile, 2 * loads_per_tile], name
         assert not any("scratch_" in x for x in code), f"{name}: register spills inside the streaming loop"
         checked += 1
-    # head_dim 64 / 128 x 1, 2, 4 query blocks with two stages, x 2, 4 query blocks with four; fp8 prefix: head_dim 128 x 2, 4
-    assert checked == 12
+    # head_dim 64 / 128 x 1, 2, 4 query blocks with two stages, x 2, 4 query blocks with four; fp8 prefix: head_dim 128 x 2, 4;
+    # and those of two stages and of the fp8 prefix once more, with fp32 partial results (short prefixes)
+    assert checked == 12 + 8
+
+
+def test_the_checked_code_takes_its_leading_arguments_in_registers(sweep_asm):
+    """The compile above is the shipped one: its kernels say how many argument registers are preloaded."""
+    preloaded = [int(m.group(1)) for l in sweep_asm if (m := re.match(r"\s*\.amdhsa_user_sgpr_kernarg_preload_length\s+(\d+)", l))]
+    assert preloaded and max(preloaded) > 0
