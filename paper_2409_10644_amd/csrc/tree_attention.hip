@@ -909,18 +909,12 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
             const unsigned char *vs = tail ? vp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)vt + (int64_t)(i - n_tail) * C::TILE_K;
             const int last = (tail ? tail_rows : p.n - (i - n_tail) * C::T) - 1;
             stage += wave * 1024;
-            int l = lane;
-            asm volatile("" : "+v"(l));                     // (worked out here, not kept in registers all along)
-            const unsigned char *no_row = zeros + (l & 3) * 16;
-            int left = last - row0;                         // rows between the lane's and the last one
-            uint32_t off = goff;
-#pragma unroll 1
+            const unsigned char *no_row = zeros + (lane & 3) * 16;
+#pragma unroll
             for (int j = 0; j < C::NI; ++j) {
-                load_to_lds16<false>(ks, off + (uint32_t)(min(left, 0) * C::RBP), stage);
-                load_to_lds16_at(left < 0 ? no_row : vs + off, stage + C::TILE_K);
-                left -= STEP;
-                off += STEP * C::RBP;
-                stage += C::WAVES * 1024;
+                const uint32_t off = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
+                load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
+                load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off, stage + C::TILE_K + j * C::WAVES * 1024);
             }
         };
         auto arrived = [&]() {

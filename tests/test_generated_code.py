@@ -65,7 +65,11 @@ def test_steady_state_loops_wait_for_memory_once_per_tile(sweep_asm):
         assert loops, f"no streaming loop found in {name}"
         D, QBP, NS, F8 = (int(x) for x in re.search(r"ILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)E", name).groups())
         if NS == 2:
-            loop = min(loops, key=len)                                # the innermost one
+            # the loop that requests full tiles (nothing else loads non-temporally) with both of its barriers; of the backward
+            # branches that span it the innermost (block placement may put a backward jump inside it: half a loop)
+            both = [x for x in loops if sum("s_barrier" in y.split(";")[0] for y in x) == 2 and any(re.search(r"global_load_lds.*\bnt\b", y) for y in x)]
+            assert both, f"{name}: no two-tile loop found"
+            loop = min(both, key=len)
             code = [x.split(";")[0] for x in loop]
             waits = sum("vmcnt" in x for x in code)
             barriers = sum("s_barrier" in x for x in code)

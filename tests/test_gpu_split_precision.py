@@ -1,8 +1,8 @@
 """Splitting the keys of a short prefix over workgroups costs no precision: partial outputs travel as fp32, so the output is
-rounded once, as without splits.  The error against binary64 is measured over all elements and compared with that of the same
-call in one split: both are the rounding of P to bf16 and one rounding of the output, so their root mean squares agree to the
-sampling error (1 / sqrt(elements) of independent roundings, below 0.5 % here).  A second rounding of the partial outputs
-to bf16 adds its own variance: 10 to 40 %."""
+rounded once, as without splits.  The root mean square error against binary64 over all elements is compared with that of the
+same call in one split.  Both hold the rounding of P to bf16 and one rounding of the output (measured: 0.90 to 1.00 of the
+unsplit error); a second rounding, of the partial outputs to bf16, makes it 1.17.  The bound leaves the sampling error of the
+57 000 elements and more, below 0.5 %, four times."""
 import numpy as np
 import pytest
 import torch
