@@ -145,7 +145,9 @@ class Step:
     def kernel_name(self):
         if not self.plan.mfma_path:
             return f"tree_attn_f32_kernel<{self.w.d}>"
-        return f"tree_attn_bf16_kernel<{self.w.d}, {self.plan.query_blocks}, {self.plan.stages}, false>"
+        keys = 128 if self.plan.query_blocks == 1 else 64       # of a tile; split prefixes below 512 keys exchange fp32
+        short = "_short" if self.plan.key_splits > 1 and -(-self.cap // keys) * keys < 512 else ""
+        return f"tree_attn_bf16{short}_kernel<{self.w.d}, {self.plan.query_blocks}, {self.plan.stages}, false>"
 
     def attention(self, layer):
         ad, w, b = self.layers[layer % len(self.layers)], self.w, self.binding
@@ -313,6 +315,12 @@ def flush_caches(torch, i):
     _FLUSH.fill_(i & 1)
 
 
+def walk_kernel(V, walks):
+    """The verification kernel of a launch: teams of workgroups, or one workgroup per walk where a vocabulary of up to 32768
+    entries meets more walks than leave two compute units each."""
+    return "verify_walk_fast_kernel" if V < 4 or (16384 < V <= 32768 and 2 * walks > 256) else "verify_walk_team_kernel"
+
+
 def verify_section(st, hip, reps):
     """The verification call of a Step as it stands: kernel time, the vocabulary bytes its walks need, acceptance.
     The probability rows of one call (a few MB) would stay in the last-level cache between launches, so the figure
@@ -330,7 +338,7 @@ def verify_section(st, hip, reps):
     vb = walk_bytes(st.w, st.gamma, st.mode, st.n_new, paths, lens)
     alen = st.alen.cpu().numpy().astype(float)
     tested = st.gamma - (1 if st.mode else 0)
-    return {"bound": "hbm", "kernel": "verify_walk_fast_kernel" if st.w.V <= 32768 else "verify_walk_kernel",
+    return {"bound": "hbm", "kernel": walk_kernel(st.w.V, len(lens)),
             "mode": "target-init" if st.mode else "draft-init", "walks": int(len(lens)),
             "achieved": round(vb / (v_avg * 1e-3) / 1e9, 2), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
             "frac": round(vb / (v_avg * 1e-3) / 1e9 / HBM_PEAK_GBPS, 5), "algorithmic_bytes_per_launch": int(vb),
@@ -898,7 +906,7 @@ def main():
             vb_avg = time_kernel(vs, hip, binding.KERNEL_VERIFY_WALK, vcall_cold, 24, warm=2)[0]
             vbytes = walk_bytes(wb, vv.gamma, 0, 1, got[0], got[1])
             extra["verify_batch%d" % wb.B] = {
-                "bound": "hbm", "kernel": "verify_walk_fast_kernel", "achieved": round(vbytes / (vb_avg * 1e-3) / 1e9, 1),
+                "bound": "hbm", "kernel": walk_kernel(wb.V, wb.B), "achieved": round(vbytes / (vb_avg * 1e-3) / 1e9, 1),
                 "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(vbytes / (vb_avg * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
                 "algorithmic_bytes_per_launch": int(vbytes), "avg_launch_us": round(vb_avg * 1e3, 2),
                 "rows_still_cached_launch_us": round(vb_warm * 1e3, 2),

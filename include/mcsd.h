@@ -322,7 +322,7 @@ int mcsd_verify_tree_sampling(const mcsd_mask_view_t *mask, mcsd_mode_t mode, mc
 
 /* The same walk with the launch in the caller's hands, for measurement and tests; results do not depend on it.
  * team : 0: the library chooses; 1..16: at most this many workgroups share a walk where the vocabulary allows it (a
- *        workgroup holds 2048 to 16384 entries, so large vocabularies need several in any case)
+ *        workgroup holds 4096 to 16384 entries, so large vocabularies need several in any case)
  * polls: how often a workgroup of a team looks for another one's partial sum before it computes that sum itself;
  *        0: the library chooses; -1: it never looks
  * MCSD_EINVAL for values outside these ranges.  tuning == NULL means all zeros. */
