@@ -1213,7 +1213,7 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         sweep<D, QBP, NS, F8, PF32>(lens, seq_base, per_die, G, mul_G, H, mul_H, BH, how, max_prefix, tps, p);                      \
     }
 SWEEP_KERNEL(tree_attn_bf16_kernel, false)
-// (a kernel of its own: as a branch the second set of folds cost calls that never fold up to 3.6 %)
+// (a kernel of its own: as a branch the second set of folds cost calls that do not use it up to 1 %, 32 layers of 1024 keys 352 -> 357 us)
 SWEEP_KERNEL(tree_attn_bf16_short_kernel, true)
 #undef SWEEP_KERNEL
 
