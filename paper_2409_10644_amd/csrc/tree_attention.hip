@@ -791,7 +791,8 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         const int col = F8 ? (ks >> 1) * 32 + g * 16 + (ks & 1) * 8 : ks * 16 + g * 8;
         qs.q[ks] = *(const bf16x8_t *)(q + (int64_t)qclamped * D + col);
     }
-    uint64_t mrow[2] = {p.mask_bits[(int64_t)qclamped * p.mask_words], p.mask_bits[(int64_t)qclamped * p.mask_words + p.mask_words - 1]};
+    // (rows are as long as the full mask's, which may have more words than the at most 128 columns in use)
+    uint64_t mrow[2] = {p.mask_bits[(int64_t)qclamped * p.mask_words], p.mask_bits[(int64_t)qclamped * p.mask_words + (p.mask_words > 1)]};
     asm volatile("" ::: "memory");                          // (requested here, not where they are first used)
 #pragma unroll
     for (int cb = 0; cb < C::CB; ++cb) qs.o[cb] = (f32x16_t){0};
