@@ -1041,8 +1041,6 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         }
     }
     __syncthreads();
-    // (requested here: at the start the wait for the first keys' addresses would include it)
-    const uint32_t ws_tag = p.fold ? __hip_atomic_load(p.ws_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) : WS_TAG;
 
     // ---- merge the key groups of each query block through LDS ----
     // A wavefront's output is CB * 4 pieces (16 bytes per lane: four columns of one query); key group kg ends up with pieces
@@ -1144,6 +1142,9 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         }
     }
     if (!p.fold) return;                                   // a second kernel folds
+    // Requested here, so that its latency is the stores' own: ahead of the merge above, the wait for it came right behind it
+    // and held up every workgroup (32 layers of 1024 keys: 352.2 -> 350.9 us).
+    const uint32_t ws_tag = __hip_atomic_load(p.ws_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 
     // ---- fold inside this kernel: the workgroup of this (sequence, unit) that arrives last does it ----
     // All workgroups of the unit run on one die (see the numbering above), so their partial results meet in that
