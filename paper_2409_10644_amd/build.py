@@ -21,7 +21,9 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", os.path.j
 # per-file extra flags: the verification kernels must perform exactly the IEEE operations written
 SOURCES = {
     "mask.cpp": ["-x", "hip"],
-    "tree_attention.hip": [],
+    # matrix instructions on ordinary registers also in kernels whose LDS leaves one workgroup per compute unit (the compiler
+    # otherwise keeps their accumulators in the other half of the register file and copies them to and fro)
+    "tree_attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "verify_tree.hip": ["-ffp-contract=off"],
     "commit_path.hip": [],
     "decision.hip": [],
