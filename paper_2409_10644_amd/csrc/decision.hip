@@ -22,8 +22,6 @@ typedef float nt_f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int REG_F4 = 16;           // float4 a lane holds when the whole row fits in registers (V <= 32768)
 constexpr int CAND_REG = 1024;       // candidates for the top-k kept in LDS: row in registers ...
 constexpr int CAND_MEM = 8192;       // ... row streamed (any V up to MCSD_MAX_VOCAB)
-constexpr int HROWS = 4;             // hidden-state rows per workgroup
-static_assert(HROWS == 4, "the generic first layer of the hidden-state kernel names its four rows");
 constexpr int K = MCSD_DECISION_MAX_K;
 
 struct MlpDesc {
@@ -129,9 +127,9 @@ __device__ __forceinline__ unsigned wave_kth_key(unsigned ka, unsigned kb, int k
 // Narrow layers (<= 64 inputs, >= 64 outputs): a lane per output unit.  Otherwise a wavefront takes four output
 // units per step, lanes over the inputs (coalesced weight reads), and the per-lane partial sums are combined as a
 // balanced tree.  Weight loads are issued in batches ahead of their use.  Ends with a barrier.
-template <int R, typename In>
+template <int R, typename In, int PITCH>
 __device__ __forceinline__ void mlp_layer(In in, int n_in, const float *W, const float *b, int n_out,
-                                          float (*out)[MCSD_MLP_MAX_WIDTH], bool relu, int tid)
+                                          float (*out)[PITCH], bool relu, int tid)
 {
     const int lane = tid & 63, wave = tid >> 6;
     if (n_in <= 64 && n_out >= 64) {
@@ -488,197 +486,277 @@ __global__ __launch_bounds__(DT) void decision_distribution_kernel(MlpDesc mlp, 
 // ---------------------------------------------------------------------------------------------- type 1
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-// First output unit of group grp of four: the last group starts early enough to be whole (units done twice get the same
-// value twice); with fewer than four units the weight rows beyond the last repeat it.
-__device__ __forceinline__ int group_unit(int grp, int n_out) { return min(grp * 4, max(n_out - 4, 0)); }
+// What a column beyond a row's end is read as, weights and inputs alike (zero times an infinite weight would be NaN).
+__device__ __align__(64) const float zeros[16] = {};
 
-// Sums the accumulators of four output units over the 16 blocks (lanes of equal lane % 4: rotations by 8 and 4 inside a row
-// of 16, then across the rows); lane = row stores.  bias: lane e's is that of unit e (requested with the weights).
-__device__ __forceinline__ void mfma_finish(f32x4_t a, int j0, float bias, float (*out)[MCSD_MLP_MAX_WIDTH], bool relu, int lane)
-{
-    float v[4] = {a[0], a[1], a[2], a[3]};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] += dpp_f32<0x128>(v[e]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] += dpp_f32<0x124>(v[e]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[e]), __float_as_uint(v[e]), false, false);
-        v[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[e]), __float_as_uint(v[e]), false, false);
-        v[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    v[0] += dpp_f32<0x00>(bias);                             // (quad broadcasts)
-    v[1] += dpp_f32<0x55>(bias);
-    v[2] += dpp_f32<0xAA>(bias);
-    v[3] += dpp_f32<0xFF>(bias);
-    if (relu) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = v[e] < 0.0f ? 0.0f : v[e];
-    }
-    if (lane < HROWS) {                                      // lane = row (fewer than four units: the entries beyond are never read)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[lane][j0 + e] = v[e];
-    }
-}
-
-// One layer on HROWS rows with v_mfma_f32_4x4x1_16b_f32 (fp32 in and out, fused multiply-adds): 16 independent blocks of
-// 4 output units x 4 rows share the contraction, block b taking columns 64 t + 4 b .. + 3 of piece t; what is left is one
-// sum over the blocks per 4 units.  x(t) is row (lane % 4)'s columns of block lane / 4, zeros beyond n_in; n_in a multiple
-// of 4, weights 16-byte aligned.  A wavefront takes every NW-th group of four units.
-// The operand layout puts four different weight rows into four neighbouring lanes, and a load does 64 bytes per cycle only
-// when such a quad reads 64 contiguous bytes (16 bytes otherwise: 22 us instead of 6.5 for 0.8 MB through one compute
-// unit).  So the weights go through LDS: direct-to-LDS loads of whole 256-byte pieces of the four rows, read back as
-// operands; the source lanes are permuted by quads (an XOR with the row) so that the reads are free of bank conflicts.
-// The ring is the wavefront's own, RING batches of four pieces deep: no barriers, only its own waits.
-// Bound: the weights, once per workgroup from L2 (768 x 256: 0.8 MB at 120-150 GB/s per compute unit).  A 768-256-64-1
-// network on 1024 rows, with the stop rule: 28.4 us with vector multiply-adds and a sum over 64 lanes per unit, 21.5 us so.
-constexpr int BATCH = 4, RING = 3;
+// The networks on four hidden states per workgroup.  A layer is v_mfma_f32_4x4x1_16b_f32 (fp32 in and out, fused multiply-adds):
+// its 16 blocks are four of four output units at one column, and the same units at columns 16, 32 and 48 further; A holds
+// those columns of the four rows, broadcast from the blocks that have them (cbsz, abid).  So a wavefront has 16 units at a time,
+// and what is left is the sum of four quarters of the columns.  Fewer than eight groups of 16 units: the wavefronts split the
+// columns too and add up through LDS.  A sum is four columns in one accumulator, a tree of four of them per batch, the
+// batches one after the other, a tree of the quarters (error against binary64, seven networks of 288 to 2048 columns: 0.95 of that
+// of the 16 column blocks and a tree over them that this replaced, 0.87 to 1.05).
+// Weights go through LDS: batches of 16 units x 64 columns come by direct-to-LDS loads into the wavefront's own ring of RING
+// batches (no barriers, only its own waits), whole 256-byte pieces of rows (128-byte ones reach the same rate only where
+// rows are a multiple of that long, 64-byte ones use half of every line), swizzled so that the operand reads are free of bank
+// conflicts.  The ring runs on into the next layer, whose first batches are there when it starts.  Rows are staged through LDS as
+// they lie in memory (read as operands from memory, four rows in four neighbouring lanes, they cost 6000 cycles).
+// Bound: the weights, once per workgroup from L2; 256 workgroups at once get 48 bytes per cycle each (768 x 256: 6.8 us; fewer
+// get 64).  Eight rows per workgroup halve that but not the time: the matrix instructions then take as long.
+// 768-256-64-1 with the stop rule: 1024 rows 20.0 -> 17.9 us, 64 rows 19.4 -> 15.8; 288-256-64-1, 1024 rows 17.7 -> 12.8;
+// 1000-256-64-1, whose rows are not whole lines, 22.8 -> 22.6.
+constexpr int BATCH = 64, UNITS = 16, RING = 3;          // columns and units per batch; batches per wavefront
+constexpr int R = 4;                                     // rows per workgroup
+constexpr int ACT_PITCH = MCSD_MLP_MAX_WIDTH + 16;       // floats; rows 16 banks apart
+constexpr int WIDE = 2048;                               // widest hidden state of the matrix path
 struct HiddenShared {
-    float act[2][HROWS][MCSD_MLP_MAX_WIDTH];
-    float4 ring[NW][RING][BATCH][64];
+    float4 ring[NW][RING][UNITS * BATCH / 4];
+    float x[R][WIDE + 16];                               // the rows; later partial sums
+    float act[R][ACT_PITCH];
     float bias[MCSD_MLP_MAX_LAYERS][MCSD_MLP_MAX_WIDTH];
-    float4 zero;
+    float last[MCSD_MLP_MAX_WIDTH];                      // weights of the last layer
 };
-template <int NT, typename Rows>
-__device__ __forceinline__ void mfma_layer(Rows x, int n_in, const float *__restrict__ W, const float *bias, int n_out,
-                                           float4 (*ring)[BATCH][64], const float4 *zero, float (*out)[MCSD_MLP_MAX_WIDTH], bool relu, int tid)
+
+// What one wavefront does of a layer: batches b0 .. b1 - 1 of unit group ug, of unit group ug + NW, ..
+struct HiddenPart { int groups, ug, kp, parts, b0, b1, units; };
+__device__ __forceinline__ HiddenPart hidden_part(int n_in, int n_out, int wave)
 {
-    constexpr int NB = NT / BATCH;                           // batches per group
-    // Batches that lie inside the row for every width this NT is chosen for.  In the others both operands are zero beyond n_in
-    // (zero times an infinite weight, read again there, would be NaN).
-    constexpr int FULL = NT > 16 ? 16 / BATCH : NB - 1;
-    static_assert(NT % BATCH == 0, "whole batches");
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int groups = (n_out + 3) >> 2;
-    // as a source: row r, columns 4 kk ..; as an operand: unit i, block blk (= kk), found at slot 16 i + (blk ^ 4 i)
-    const int r = min(lane >> 4, n_out - 1), kk = (lane & 15) ^ ((lane >> 4) << 2);
-    const int slot = ((lane & 3) << 4) + ((lane >> 2) ^ ((lane & 3) << 2));
-    int g_next = wave, b_next = 0, s_next = 0;               // next batch to request, and its place in the ring
-    auto request = [&]() {
-        // (past the last group: again, unused; readfirstlane: uniform, and the compiler has to know)
-        const float *base = W + (size_t)__builtin_amdgcn_readfirstlane(group_unit(min(g_next, groups - 1), n_out)) * n_in;
-        const int at = __builtin_amdgcn_readfirstlane(s_next);
-#pragma unroll
-        for (int q = 0; q < BATCH; ++q) {
-            const int col = min(64 * (b_next * BATCH + q) + 4 * kk, n_in - 4);                  // beyond n_in: cleared below
-            load_to_lds16<false>(base, (unsigned)(r * n_in + col) * 4u, &ring[at][q][0]);
-        }
-        if (++b_next == NB) { b_next = 0; g_next += NW; }
-        s_next = s_next + 1 == RING ? 0 : s_next + 1;
-    };
-    if (wave < groups) {
-#pragma unroll
-        for (int k = 0; k < RING; ++k) request();
-        int s = 0;
-        for (int grp = wave; grp < groups; grp += NW) {
-            f32x4_t a = {0.f, 0.f, 0.f, 0.f}, b = a;
-#pragma unroll
-            for (int bt = 0; bt < NB; ++bt) {
-                MCSD_WAIT_VMCNT((RING - 1) * BATCH);         // this batch has landed, the later ones are under way
-                asm volatile("" ::: "memory");
-                float4 w[BATCH];
-#pragma unroll
-                for (int q = 0; q < BATCH; ++q) {
-                    const float4 *at = &ring[s][q][slot];
-                    if (bt >= FULL && 64 * (bt * BATCH + q) + 4 * (lane >> 2) >= n_in) at = zero;
-                    w[q] = *at;
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[0].x), "+v"(w[1].x), "+v"(w[2].x), "+v"(w[3].x) :: "memory");   // read before it is overwritten
-                request();
-                s = s + 1 == RING ? 0 : s + 1;
-#pragma unroll
-                for (int q = 0; q < BATCH; ++q) {
-                    const float4 v = x(bt * BATCH + q);
-                    a = __builtin_amdgcn_mfma_f32_4x4x1f32(w[q].x, v.x, a, 0, 0, 0);
-                    b = __builtin_amdgcn_mfma_f32_4x4x1f32(w[q].y, v.y, b, 0, 0, 0);
-                    a = __builtin_amdgcn_mfma_f32_4x4x1f32(w[q].z, v.z, a, 0, 0, 0);
-                    b = __builtin_amdgcn_mfma_f32_4x4x1f32(w[q].w, v.w, b, 0, 0, 0);
-                }
-            }
-            const int j0 = group_unit(grp, n_out);
-            mfma_finish(a + b, j0, bias[j0 + min(lane & 3, n_out - 1)], out, relu, lane);
-        }
-        MCSD_WAIT_VMCNT(0);
-    }
-    __syncthreads();
+    HiddenPart p;
+    p.units = (n_out + UNITS - 1) / UNITS;
+    const int lg = p.units <= 1 ? 0 : p.units <= 2 ? 1 : p.units <= 4 ? 2 : 3;
+    p.groups = 1 << lg;
+    p.parts = NW >> lg;
+    p.ug = wave & (p.groups - 1);
+    p.kp = wave >> lg;
+    const int nb = (n_in + BATCH - 1) / BATCH, per = (nb + p.parts - 1) >> (3 - lg);
+    p.b0 = min(p.kp * per, nb);
+    p.b1 = min(p.b0 + per, nb);
+    return p;
 }
 
-// Row (lane % 4)'s columns for mfma_layer.
-template <int NT>
-__device__ __forceinline__ void mfma_rows(float4 (&x)[NT], const float *row, int n_in, int tid)
-{
-    const int blk = (tid & 63) >> 2;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) x[t] = *reinterpret_cast<const float4 *>(row + min(64 * t + 4 * blk, n_in - 4));
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        asm volatile("" : "+v"(x[t].x), "+v"(x[t].y), "+v"(x[t].z), "+v"(x[t].w));      // (the loads stay unconditional, all in flight)
-        if (64 * t + 4 * blk >= n_in) x[t] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
-}
-constexpr int WIDE = 2048;           // widest hidden state that the matrix path takes
-
-// NT: 64-column pieces of a row held in registers; 0: rows up to WIDE in LDS ([column / 4][row]: a wavefront reads them back
-// contiguously); -1: any width and alignment.
-template <int NT>
+// GEN: rows of any width, stride and alignment: their layer is evaluated without the matrix cores.
+template <bool GEN>
 __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M, int W, const float *__restrict__ hidden,
                                                              int64_t batch_stride, int64_t row_stride,
-                                                             float *__restrict__ prob)
+                                                             float *prob, float beta, int32_t *stop)
 {
+    constexpr int GROUPS = MCSD_MLP_MAX_WIDTH / UNITS / NW;
     __shared__ __attribute__((aligned(1024))) HiddenShared sh;
-    const int tid = threadIdx.x;
-    const int m0 = blockIdx.x * HROWS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = blockIdx.x * R, n_layers = mlp.n_layers;
     auto row = [&](int r) {
-        const int m = min(m0 + r, M - 1);                       // rows past the end repeat the last one, unwritten
-        return hidden + (int64_t)(m / W) * batch_stride + (int64_t)(m % W) * row_stride;
+        const unsigned m = min(m0 + r, M - 1), tree = m / (unsigned)W;      // rows past the end repeat the last one, unwritten
+        return hidden + (int64_t)tree * batch_stride + (int64_t)(m - tree * W) * row_stride;
     };
-    const int n_in = mlp.width[0];
-    const bool relu = mlp.n_layers > 1;
-    float4 (*ring)[BATCH][64] = sh.ring[__builtin_amdgcn_readfirstlane(tid >> 6)];
-    if (tid == 0) sh.zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    for (int l = 0; l < mlp.n_layers; ++l)
-        for (int j = tid; j < mlp.width[l + 1]; j += DT) sh.bias[l][j] = mlp.b[l][j];
-    if constexpr (NT > 0) {
-        float4 xr[NT];
-        mfma_rows<NT>(xr, row(tid & 3), n_in, tid);
-        __syncthreads();
-        mfma_layer<NT>([&](int t) { return xr[t]; }, n_in, mlp.w[0], sh.bias[0], mlp.width[1], ring, &sh.zero, sh.act[0], relu, tid);
-    } else if constexpr (NT == 0) {
-        __shared__ float4 s_x[WIDE];
-        for (int k = tid; k < WIDE; k += DT) {
-            const int c = 4 * (k >> 2);
-            s_x[k] = c < n_in ? *reinterpret_cast<const float4 *>(row(k & 3) + c) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    // layers whose weights come through the ring (the last one has a single unit)
+    auto streamed = [&](int l) {
+        return l < n_layers - 1 && (GEN ? l > 0 : true) && (l == 0 || (mlp.width[l] % 4 == 0 && ((uintptr_t)mlp.w[l] & 15) == 0));
+    };
+
+    // ---- the wavefront's stream of weights through all layers ----
+    // as a source: of instruction j, lane l takes row 4 j + l / 16 and there piece (l % 16) ^ row; as an operand: unit u's piece c is
+    // at 16 u + (c ^ u)
+    float4 *const ring = &sh.ring[wave][0][0];
+    int rq_l = -1, rq_u = 0, rq_units = 0, rq_full = 0, rq_tail = 0, rq_at = 0;     // whole batches to come, columns of a last one that is not
+    const float *rq_w = zeros;
+    uint32_t rq_off[4] = {0, 0, 0, 0};
+    auto next_group = [&]() {                                               // this wavefront's next group of units, or layer
+        rq_u += NW;
+        while (rq_u >= rq_units) {
+            if (++rq_l >= n_layers - 1) {                                   // none: the count goes on, unused
+                rq_w = zeros;
+                rq_full = 0x7fffffff;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) rq_off[j] = 0;
+                return;
+            }
+            rq_units = rq_u = 0;
+            if (!streamed(rq_l)) continue;
+            const HiddenPart p = hidden_part(mlp.width[rq_l], mlp.width[rq_l + 1], wave);
+            if (p.b0 == p.b1) continue;
+            rq_units = p.units;
+            rq_u = p.ug;
         }
-        __syncthreads();
-        mfma_layer<WIDE / 64>([&](int t) { return s_x[t * 64 + (tid & 63)]; }, n_in, mlp.w[0], sh.bias[0], mlp.width[1], ring, &sh.zero, sh.act[0], relu, tid);
-    } else {
-        mlp_layer<HROWS>([x0 = row(0), x1 = row(1), x2 = row(2), x3 = row(3)](int r, int i) {
-                             return (r == 0 ? x0 : r == 1 ? x1 : r == 2 ? x2 : x3)[i];
-                         }, n_in, mlp.w[0], mlp.b[0], mlp.width[1], sh.act[0], relu, tid);
-    }
-    int cur = 0;
-    for (int l = 1; l < mlp.n_layers; ++l) {
-        const int width = mlp.width[l];
-        const bool more = l + 1 < mlp.n_layers;
-        float (*src)[MCSD_MLP_MAX_WIDTH] = sh.act[cur], (*dst)[MCSD_MLP_MAX_WIDTH] = sh.act[cur ^ 1];
-        if (width % 4 != 0 || ((uintptr_t)mlp.w[l] & 15) != 0) {
-            mlp_layer<HROWS>([src](int r, int i) { return src[r][i]; }, width, mlp.w[l], mlp.b[l], mlp.width[l + 1], dst, more, tid);
-        } else if (width <= 256) {
-            float4 xr[4];
-            mfma_rows<4>(xr, src[tid & 3], width, tid);
-            mfma_layer<4>([&](int t) { return xr[t]; }, width, mlp.w[l], sh.bias[l], mlp.width[l + 1], ring, &sh.zero, dst, more, tid);
+        const int n_in = mlp.width[rq_l], n_out = mlp.width[rq_l + 1];
+        const HiddenPart p = hidden_part(n_in, n_out, wave);
+        rq_w = (rq_l == 0 ? mlp.w[0] : mlp.w[1]) + BATCH * p.b0;
+        const int cols = min(BATCH * p.b1, n_in) - BATCH * p.b0;
+        rq_full = cols / BATCH;
+        rq_tail = cols % BATCH;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = 4 * j + (lane >> 4);
+            rq_off[j] = (uint32_t)(min(rq_u * UNITS + r, n_out - 1) * n_in + ((lane & 15) ^ r) * 4) * 4u;
+        }
+    };
+    auto request = [&]() {
+        if (rq_full == 0 && rq_tail == 0) next_group();
+        float4 *at = ring + rq_at;
+        rq_at = rq_at == (RING - 1) * 256 ? 0 : rq_at + 256;
+        if (rq_full > 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) load_to_lds16<false>(rq_w, rq_off[j], at + 64 * j);
+            --rq_full;
+            rq_w += rq_l < n_layers - 1 ? BATCH : 0;
         } else {
-            float4 xr[8];
-            mfma_rows<8>(xr, src[tid & 3], width, tid);
-            mfma_layer<8>([&](int t) { return xr[t]; }, width, mlp.w[l], sh.bias[l], mlp.width[l + 1], ring, &sh.zero, dst, more, tid);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int col = ((lane & 15) ^ (4 * j + (lane >> 4))) * 4;
+                load_to_lds16_at(col < rq_tail ? (const void *)((const char *)rq_w + rq_off[j]) : (const void *)zeros, at + 64 * j);
+            }
+            rq_tail = 0;
         }
-        cur ^= 1;
+    };
+#pragma unroll
+    for (int k = 0; k < RING; ++k) request();
+
+    // ---- rows, biases, last weights: HBM -> LDS ----
+    if constexpr (!GEN) {
+        const int chunks = (mlp.width[0] + 255) >> 8;                       // 1 KiB of a row per instruction
+        const int r = wave & (R - 1);                                       // (a wavefront keeps to one row)
+        const float *src = row(r);
+        for (int c = wave / R; c < chunks; c += NW / R) {
+            const int col = 256 * c + 4 * lane;
+            load_to_lds16_at(col < mlp.width[0] ? (const void *)(src + col) : (const void *)zeros, &sh.x[r][256 * c]);
+        }
     }
-    if (tid < HROWS && m0 + tid < M) prob[m0 + tid] = logistic(sh.act[cur][tid][0]);
+#pragma unroll
+    for (int l = 0; l < MCSD_MLP_MAX_LAYERS; ++l)
+        if (l < n_layers)
+            for (int c = wave; c * 64 < mlp.width[l + 1]; c += NW)
+                load_to_lds4_at(mlp.b[l] + min(64 * c + lane, mlp.width[l + 1] - 1), &sh.bias[l][64 * c]);
+    const int n_last = mlp.width[n_layers - 1];
+    const float *w_last = n_layers == 1 ? mlp.w[0] : n_layers == 2 ? mlp.w[1] : mlp.w[2];
+    if (n_layers > 1)
+        for (int c = wave; c * 64 < n_last; c += NW) load_to_lds4_at(w_last + min(64 * c + lane, n_last - 1), &sh.last[64 * c]);
+    // (a layer reads its input in whole batches, and zero times what happens to be there may be NaN)
+    for (int i = tid; i < R * ACT_PITCH / 4; i += DT) reinterpret_cast<float4 *>(&sh.act[0][0])[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    MCSD_WAIT_VMCNT(0);
+    __syncthreads();
+
+    // ---- layers ----
+    const float *h = &sh.x[0][0];            // input of the layer: rows `pitch` floats apart
+    int pitch = sizeof(sh.x[0]) / sizeof(float), slot = 0;
+    for (int l = 0; l < n_layers - 1; ++l) {
+        const int n_in = mlp.width[l], n_out = mlp.width[l + 1];
+        if (!streamed(l)) {
+            if (GEN && l == 0) {
+                mlp_layer<R>([x0 = row(0), x1 = row(1), x2 = row(2), x3 = row(3)](int r, int i) {
+                                 return (r == 0 ? x0 : r == 1 ? x1 : r == 2 ? x2 : x3)[i];
+                             }, n_in, mlp.w[0], mlp.b[0], n_out, sh.act, true, tid);
+                h = &sh.act[0][0];
+            } else {
+                mlp_layer<R>([h, pitch](int r, int i) { return h[r * pitch + i]; }, n_in, mlp.w[l], mlp.b[l], n_out,
+                             (float (*)[ACT_PITCH])&sh.x[0][0], true, tid);                    // (the last but one: its input is in act)
+                h = &sh.x[0][0];
+            }
+            pitch = ACT_PITCH;
+            continue;
+        }
+        const HiddenPart p = hidden_part(n_in, n_out, wave);
+        f32x4_t sum[GROUPS];                                 // of the wavefront's groups of units; [row]
+#pragma unroll
+        for (int u = 0; u < GROUPS; ++u) sum[u] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        const int blk = lane >> 2, quarter = blk >> 2, unit = lane & 15;
+        const float *xr = h + (lane & 3) * pitch + quarter * 16 + (blk & 3) + BATCH * p.b0;
+        const int op = unit * 16 + ((quarter * 4) ^ unit);
+#pragma unroll
+        for (int u = 0; u < GROUPS; ++u) {
+            if (p.ug + u * NW >= p.units) break;             // (uniform)
+            const float *xb = xr;
+#pragma unroll 1
+            for (int b = p.b0; b < p.b1; ++b, xb += BATCH) {
+                MCSD_WAIT_VMCNT((RING - 1) * 4);             // this batch has landed, the later ones are under way
+                asm volatile("" ::: "memory");
+                const float4 *at = ring + slot;
+                slot = slot == (RING - 1) * 256 ? 0 : slot + 256;
+                float4 w[4];
+                float x[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) w[c] = at[op ^ c];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x[c] = xb[4 * c];
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[0].x), "+v"(w[1].x), "+v"(w[2].x), "+v"(w[3].x) :: "memory");   // read before it is overwritten
+                request();
+                f32x4_t a[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[c], w[c].x, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 2, 0, 0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[c], w[c].y, a[c], 2, 1, 0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[c], w[c].z, a[c], 2, 2, 0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[c], w[c].w, a[c], 2, 3, 0);
+                sum[u] += (a[0] + a[1]) + (a[2] + a[3]);
+            }
+            // the quarters' columns: lanes l, l + 16, l + 32, l + 48
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const unsigned v = __float_as_uint(sum[u][r]);
+                const auto o = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+                sum[u][r] = __uint_as_float(o[0]) + __uint_as_float(o[1]);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const unsigned v = __float_as_uint(sum[u][r]);
+                const auto o = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+                sum[u][r] = __uint_as_float(o[0]) + __uint_as_float(o[1]);
+            }
+        }
+        __syncthreads();                                     // everyone has read the layer's input
+        float *part = &sh.x[0][0];                           // [column part][unit group][row][unit]
+        if (p.parts > 1) {
+            if (p.ug < p.units && p.kp > 0 && quarter == 0) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) part[(((p.kp - 1) * p.groups + p.ug) * R + r) * UNITS + unit] = sum[0][r];
+            }
+            __syncthreads();
+        }
+        if (p.kp == 0 && quarter == 0) {
+#pragma unroll 1
+            for (int k = 1; k < p.parts; ++k)
+#pragma unroll
+                for (int r = 0; r < R; ++r) sum[0][r] += part[(((k - 1) * p.groups + p.ug) * R + r) * UNITS + unit];
+#pragma unroll
+            for (int u = 0; u < GROUPS; ++u) {
+                const int j = (p.ug + u * NW) * UNITS + unit;
+                if (p.ug + u * NW >= p.units) break;
+                const float bias = sh.bias[l][j];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    float v = sum[u][r] + bias;
+                    v = v < 0.0f ? 0.0f : v;                 // (a NaN stays one)
+                    if (j < n_out) sh.act[r][j] = v;
+                }
+            }
+        }
+        __syncthreads();
+        h = &sh.act[0][0];
+        pitch = ACT_PITCH;
+    }
+    // ---- the last layer, one unit: a wavefront per row ----
+    for (int r = wave; r < R; r += NW) {
+        float v[1] = {0.0f};
+        if (n_layers == 1) {
+            const float *x = row(r);
+            for (int j = lane; j < n_last; j += 64) v[0] = fmaf(w_last[j], x[j], v[0]);
+        } else {
+            for (int j = lane; j < n_last; j += 64) v[0] = fmaf(sh.last[j], h[r * pitch + j], v[0]);
+        }
+        wave_sum_f32_n<1>(v);
+        if (lane == 0 && m0 + r < M) {
+            const float y = logistic(v[0] + sh.bias[n_layers - 1][0]);
+            if (stop) __hip_atomic_store(prob + m0 + r, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else prob[m0 + r] = y;
+        }
+    }
+    if (stop) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const int first = m0 / W, last = min(m0 + R, M) - 1;
+        for (int tree = first + wave; tree * W <= last; tree += NW) settle_stop(prob, tree, W, beta, stop, lane);
+    }
+    MCSD_WAIT_VMCNT(0);                                      // (nothing lands in LDS that is no longer this workgroup's)
 }
 
 // ---------------------------------------------------------------------------------------------- stop rule
@@ -713,6 +791,7 @@ int check_mlp(const mcsd_mlp_t *mlp, int32_t n_in, MlpDesc *out)
 }
 
 constexpr int FEW_ROWS = 256;        // one workgroup per compute unit
+constexpr int SETTLE_HIDDEN = 256;   // (four rows share a workgroup: 64 rows 17.7 us, 16.7 so; 512 rows 17.6 and 17.8)
 constexpr int SETTLE_ROWS = 64;      // beyond, the flags' and probabilities' cache lines are fought over: 180 rows 15.7 us, 12.8 with a launch
 
 int launch_stop(const float *prob, int32_t B, int32_t W, float beta, int32_t *stop, hipStream_t st)
@@ -766,10 +845,10 @@ extern "C" int mcsd_early_stop_hidden(const mcsd_mlp_t *mlp, int32_t B, int32_t 
     hipStream_t st = (hipStream_t)hip_stream;
     const int M = B * W, n_in = d.width[0];
     const bool aligned = n_in % 4 == 0 && batch_stride % 4 == 0 && row_stride % 4 == 0 && (((uintptr_t)hidden_dev | (uintptr_t)d.w[0]) & 15) == 0;
-    auto kernel = !aligned || n_in > WIDE ? decision_hidden_kernel<-1> : n_in <= 256 ? decision_hidden_kernel<4> : n_in <= 512 ? decision_hidden_kernel<8>
-                  : n_in <= 768 ? decision_hidden_kernel<12> : n_in <= 1024 ? decision_hidden_kernel<16> : decision_hidden_kernel<0>;
-    mcsd_launch(MCSD_KERNEL_DECISION, kernel, dim3((M + HROWS - 1) / HROWS), dim3(DT), st, d, M, (int)W,
-                hidden_dev, batch_stride, row_stride, prob_dev);
+    const bool settle = M <= SETTLE_HIDDEN;
+    auto kernel = !aligned || n_in > WIDE ? decision_hidden_kernel<true> : decision_hidden_kernel<false>;
+    mcsd_launch(MCSD_KERNEL_DECISION, kernel, dim3((M + R - 1) / R), dim3(DT), st, d, M, (int)W,
+                hidden_dev, batch_stride, row_stride, prob_dev, beta, settle ? stop_dev : (int32_t *)nullptr);
     if (int rc = mcsd_hip_status(hipGetLastError())) return rc;
-    return launch_stop(prob_dev, B, W, beta, stop_dev, st);
+    return settle ? MCSD_OK : launch_stop(prob_dev, B, W, beta, stop_dev, st);
 }

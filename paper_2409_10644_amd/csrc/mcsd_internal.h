@@ -89,5 +89,12 @@ static __device__ inline void load_to_lds16_at(const void *src, void *lds_base)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(src) : "memory");
 }
 
+// 4 bytes per lane, at an address of its own: lane l lands at lds_base + 4*l.
+static __device__ inline void load_to_lds4_at(const void *src, void *lds_base)
+{
+    const uint32_t lds_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds_base;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(lds_addr), "v"(src) : "memory");
+}
+
 // s_waitcnt vmcnt(N) only (expcnt / lgkmcnt left at their maxima)
 #define MCSD_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14))
