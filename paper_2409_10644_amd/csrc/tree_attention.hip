@@ -342,8 +342,17 @@ struct SweepCfg {
     static constexpr int CB = D / 32;                  // 32-row blocks of O^T
     static constexpr int XCHG = (KG - 1) * QBP * 32 * D * 4;   // LDS bytes in which key groups hand over their outputs; maxima and denominators follow
     static constexpr int RING = NS * TILE;
-    static constexpr int LDS_BYTES = RING > XCHG + 1024 ? RING : XCHG + 1024;
-    static_assert(NI >= 1 && (NS - 2) * DPT < 64 && LDS_BYTES <= 160 * 1024 - 64, "tile does not map onto the workgroup");
+    // Two stages: behind the ring, and where two workgroups' share of a compute unit (80 KB) ends before, over its last halves,
+    // lie Q and the first two mask words of every row until they have been read; the first HALVES_FIRST halves of the first two
+    // tiles are requested beside them.
+    static constexpr int Q_BYTES = QBP * 32 * RB, MASK_BYTES = QBP * 32 * 16;
+    static constexpr int LDS_BYTES = NS > 2 ? (RING > XCHG + 1040 ? RING : XCHG + 1040)
+                                   : QBP == 1 ? RING + Q_BYTES + MASK_BYTES : D * 640;
+    static constexpr int MASK_AT = LDS_BYTES - MASK_BYTES, Q_AT = MASK_AT - Q_BYTES;
+    static constexpr int HALVES_FIRST = Q_AT / TILE_K < 4 ? Q_AT / TILE_K : 4;
+    static constexpr int PAIR_AT = NS == 2 ? MASK_AT + MASK_BYTES - 2048 : 0;                       // the table that orders ragged grids
+    static_assert(NI >= 1 && (NS - 2) * DPT < 64 && LDS_BYTES <= 160 * 1024 && XCHG + 1040 <= LDS_BYTES, "tile does not map onto the workgroup");
+    static_assert(NS > 2 || HALVES_FIRST >= 2, "the first tile is requested beside Q");
     static_assert(!F8 || D == 128, "fp8 tiles are laid out for 128-byte rows");
     static_assert(!F8 || (BTILE_K == TILE && BTILE_K / 1024 / WAVES == DPT), "half a tree tile is a slot of the ring");
 };
@@ -419,13 +428,16 @@ __device__ inline void softmax_exp2(const f32x16_t &sacc, int r, float c, float 
 // One tile: the wavefront's KPW blocks of 32 keys against its 32 queries.  With two blocks the instruction stream
 // is laid out so that the matrix pipe and the vector ALU overlap inside the wavefront:
 //     QK_0, QK_1 | block maxima, rare rescale | exp(0) | PV_0 with exp(1) in its shadow | PV_1
-// Operand reads are issued ahead of their use.  MODE 0: all keys visible; otherwise bit k of bits[u] says whether
-// key k of block u is visible to this lane's query.
+// Operand reads are issued ahead of their use.  MODE 0: all keys visible; MODE 1: bit k of bits[u] says whether
+// key k of block u is visible to this lane's query; MODE 2: the one or the other, as `masked` (uniform) says.
 // F8K: the kernel serves an fp8 prefix cache: the reference maximum is kept in log2 units (tiles of different
 // scale share it) and P carries the V scale `vs` of the tile.  F8T: this stage is a raw fp8 tile.
-template <int D, int QBP, int NS, int MODE, bool F8K = false, bool F8T = false>
-__device__ inline void attn_tile(const unsigned char *stage, const LaneAddr la, QBlock<D> &qs, float c, int g,
-                                 const uint32_t *bits, float vs = 1.f, const unsigned char *vstage = nullptr)
+// `values` is called when the scores are under way and before the first value is read.
+struct NothingToDo { __device__ void operator()() const {} };
+template <int D, int QBP, int NS, int MODE, bool F8K = false, bool F8T = false, typename Values = NothingToDo>
+__device__ __forceinline__ void attn_tile(const unsigned char *stage, const LaneAddr la, QBlock<D> &qs, float c, int g,
+                                          const uint32_t *bits, float vs = 1.f, const unsigned char *vstage = nullptr,
+                                          bool masked = false, Values values = Values())
 {
     using C = SweepCfg<D, QBP, NS, F8K>;
     constexpr int U = C::KPW;
@@ -463,6 +475,7 @@ __device__ inline void attn_tile(const unsigned char *stage, const LaneAddr la, 
         for (int ks = 0; ks < C::KS; ++ks) sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[u][ks], qs.q[ks], sacc[u], 0, 0, 0);
     }
     __builtin_amdgcn_s_setprio(0);
+    values();
     // V^T fragments via the LDS transpose load, issued ahead of their use: block 0's during the softmax, block 1's
     // before the first PV MFMA.  The reads of one k-step pair (ks2, e4) sit 16*ks2 + 8*e4 rows below the lane's
     // base row; the chunk select is cb*4 ^ e4*2.
@@ -489,12 +502,11 @@ __device__ inline void attn_tile(const unsigned char *stage, const LaneAddr la, 
     float mx = -INFINITY;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        if (MODE != 0) {
+        if (MODE == 1 || (MODE == 2 && masked)) {
+            const uint32_t own = bits[u] >> (4 * g);            // (tested at constant places)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = 8 * (r / 4) + 4 * g + (r % 4);
-                if (!((bits[u] >> key) & 1u)) sacc[u][r] = -INFINITY;
-            }
+            for (int r = 0; r < 16; ++r)
+                if (!((own >> (8 * (r / 4) + r % 4)) & 1u)) sacc[u][r] = -INFINITY;
         }
         mx = fmaxf(fmaxf(mx, sacc[u][0]), sacc[u][1]);
 #pragma unroll
@@ -728,7 +740,8 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         // about the same number of keys to stream however ragged the batch is.  With more than two per compute unit
         // the hardware hands out workgroups in id order as slots free up: longest first.  The pieces are the
         // (sequence, key split) classes, p.H equal items each, ranked by their number of tiles here (B * S <= 256).
-        __shared__ int32_t s_work[256], s_cls_at[256];
+        typedef __attribute__((address_space(3))) int32_t lds_int;
+        lds_int *const s_work = (lds_int *)(ring + C::PAIR_AT), *const s_cls_at = s_work + 256;
         const int n_cls = p.B * p.S;
         if (tid < n_cls) {
             const int Lt = p.lens[tid / p.S], sp = tid % p.S;
@@ -753,6 +766,7 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         }
         const int rank = fast_div(r, mul_H, how_shift_H(how));
         const int cls = __builtin_amdgcn_readfirstlane(s_cls_at[rank]);
+        __syncthreads();                                     // (the first loads land there)
         s = cls % p.S;
         // Units that stream the same keys for different query heads are neighbours: give them one die, and so one L2 (a die's
         // share of a class is then H / dies neighbours; ids modulo the dies stay what they were for every split of a unit).
@@ -782,17 +796,42 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
     // Query block of this wavefront; mask row of this lane's query.  A padded row (beyond the last) is the last one again, unwritten.
     QBlock<D> qs;
     const int qrow = p.row0 + (qb & (p.bph - 1)) * 32 + ln, qclamped = min(qrow, p.n - 1);
+    uint64_t mrow[2] = {0, 0};
+    if constexpr (NS == 2) {
+        // Through LDS, in the layout of the keys: every row comes once and whole, where each wavefront of a query block would
+        // fetch it for itself in pieces of 32 bytes, and the compiler, which knows nothing of the tiles' loads and would wait
+        // for all of them where Q is first used, has nothing to wait for.  (Q in registers and two tiles requested at once:
+        // 14.2 us where this takes 13.7, and nothing gained where a workgroup has one tile.)
+        const int hq0 = kvh * p.grp + (h - kvh * p.chunks) * p.hpw;
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) {
-        // Columns of k-step ks in lane half g: 16 ks + 8 g .. +7.  With an fp8 prefix cache the halves trade places
-        // with the k-step's parity, 32 (ks/2) + 16 g + 8 (ks%2) .. +7, so that a lane's columns of two consecutive
-        // k-steps are 16 consecutive bytes of an fp8 row (one conflict-free 16-byte LDS read); the contraction is
-        // over all columns either way.
-        const int col = F8 ? (ks >> 1) * 32 + g * 16 + (ks & 1) * 8 : ks * 16 + g * 8;
-        qs.q[ks] = *(const bf16x8_t *)(q + (int64_t)qclamped * D + col);
+        for (int j = 0; j < C::Q_BYTES / 1024 / C::WAVES; ++j) {
+            const int piece = j * C::WAVES + wave, r = piece * (1024 / C::RB) + lane / C::BCPR, qbr = piece * (1024 / C::RB) >> 5;
+            const int node = min(p.row0 + (qbr & (p.bph - 1)) * 32 + (r & 31), p.n - 1);
+            const int64_t row = ((int64_t)b * p.Hq + hq0 + (qbr >> p.log2_bph)) * p.node_stride + node;
+            load_to_lds16_at((const unsigned char *)p.q + row * C::RB + ((lane % C::BCPR) ^ swz<D>(r)) * 16, ring + C::Q_AT + piece * 1024);
+        }
+        // (rows are as long as the full mask's, which may have more words than the at most 128 columns in use)
+#pragma unroll
+        for (int j = 0; j * C::WAVES < C::MASK_BYTES / 256; ++j) {
+            const int piece = j * C::WAVES + wave, i = piece * 64 + lane;                    // dword i % 4 of row i / 4
+            const int64_t at = (int64_t)min(p.row0 + (i >> 2), p.n - 1) * p.mask_words * 2 + min(i & 3, p.mask_words * 2 - 1);
+            if (C::MASK_BYTES / 256 % C::WAVES == 0 || piece < C::MASK_BYTES / 256)
+                load_to_lds4_at((const uint32_t *)p.mask_bits + at, ring + C::MASK_AT + piece * 256);
+        }
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < C::KS; ++ks) {
+            // Columns of k-step ks in lane half g: 16 ks + 8 g .. +7.  With an fp8 prefix cache the halves trade places
+            // with the k-step's parity, 32 (ks/2) + 16 g + 8 (ks%2) .. +7, so that a lane's columns of two consecutive
+            // k-steps are 16 consecutive bytes of an fp8 row (one conflict-free 16-byte LDS read); the contraction is
+            // over all columns either way.
+            const int col = F8 ? (ks >> 1) * 32 + g * 16 + (ks & 1) * 8 : ks * 16 + g * 8;
+            qs.q[ks] = *(const bf16x8_t *)(q + (int64_t)qclamped * D + col);
+        }
+        // (rows are as long as the full mask's, which may have more words than the at most 128 columns in use)
+        mrow[0] = p.mask_bits[(int64_t)qclamped * p.mask_words];
+        mrow[1] = p.mask_bits[(int64_t)qclamped * p.mask_words + (p.mask_words > 1)];
     }
-    // (rows are as long as the full mask's, which may have more words than the at most 128 columns in use)
-    uint64_t mrow[2] = {p.mask_bits[(int64_t)qclamped * p.mask_words], p.mask_bits[(int64_t)qclamped * p.mask_words + (p.mask_words > 1)]};
     asm volatile("" ::: "memory");                          // (requested here, not where they are first used)
 #pragma unroll
     for (int cb = 0; cb < C::CB; ++cb) qs.o[cb] = (f32x16_t){0};
@@ -867,17 +906,26 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
     // (uniform tile base + 32-bit lane offset: a load takes its base from scalar registers)
     const unsigned char *kbase = ksrc + (int64_t)nxt * C::TILE_K, *vbase = vsrc + (int64_t)nxt * C::TILE_K;
     const bool read_once = p.chunks == 1;                   // no other workgroup streams these keys (uniform)
-    auto issue_full = [&](unsigned char *stage) {
+    constexpr std::integral_constant<int, 0> KEYS;
+    constexpr std::integral_constant<int, 1> VALUES;
+    constexpr std::integral_constant<int, 2> BOTH;
+    auto issue_full = [&](unsigned char *stage, auto half) __attribute__((always_inline)) {      // (the values come last)
+        constexpr int HALF = decltype(half)::value, PER = HALF == 2 ? 2 : 1;
         stage += wave * 1024;
         if (read_once) {
 #pragma unroll
-            for (int i = 0; i < C::DPT; ++i)
-                load_to_lds16<true>((i & 1) ? vbase : kbase, goffs[i >> 1], stage + (i & 1) * C::TILE_K + (i >> 1) * C::WAVES * 1024);
+            for (int i = 0; i < PER * C::NI; ++i) {
+                const int w = HALF == 2 ? (i & 1) : HALF, j = i / PER;
+                load_to_lds16<true>(w ? vbase : kbase, goffs[j], stage + w * C::TILE_K + j * C::WAVES * 1024);
+            }
         } else {
 #pragma unroll
-            for (int i = 0; i < C::DPT; ++i)
-                load_to_lds16<false>((i & 1) ? vbase : kbase, goffs[i >> 1], stage + (i & 1) * C::TILE_K + (i >> 1) * C::WAVES * 1024);
+            for (int i = 0; i < PER * C::NI; ++i) {
+                const int w = HALF == 2 ? (i & 1) : HALF, j = i / PER;
+                load_to_lds16<false>(w ? vbase : kbase, goffs[j], stage + w * C::TILE_K + j * C::WAVES * 1024);
+            }
         }
+        if constexpr (HALF == 0) return;
         nxt = nxt + 1 == n_hot ? 0 : nxt + 1;
         kbase = ksrc + (int64_t)nxt * C::TILE_K;
         vbase = vsrc + (int64_t)nxt * C::TILE_K;
@@ -904,7 +952,8 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
     if constexpr (NS == 2) {
         // The tiles that are not full come the same way, a key beyond the last one as that one again (masked out), a value as
         // zeros: through registers behind the last full tile each of them cost its whole latency once more, 1.7 us.
-        auto issue_rest = [&](int i, unsigned char *stage) {
+        auto issue_rest = [&](int i, unsigned char *stage, auto half) __attribute__((always_inline)) {
+            constexpr int HALF = decltype(half)::value;
             const bool tail = i < n_tail;
             const unsigned char *ks = tail ? kp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)kt + (int64_t)(i - n_tail) * C::TILE_K;
             const unsigned char *vs = tail ? vp + (int64_t)(t1 - 1) * C::TILE_K : (const unsigned char *)vt + (int64_t)(i - n_tail) * C::TILE_K;
@@ -914,38 +963,74 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
 #pragma unroll
             for (int j = 0; j < C::NI; ++j) {
                 const uint32_t off = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
-                load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
-                load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off, stage + C::TILE_K + j * C::WAVES * 1024);
+                if (HALF != 1) load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
+                if (HALF != 0) load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off, stage + C::TILE_K + j * C::WAVES * 1024);
             }
         };
         auto arrived = [&]() {
             MCSD_WAIT_VMCNT(0);                             // this wavefront's part of the tile has landed ...
             __builtin_amdgcn_s_barrier();                   // ... and everyone's; the stage of the tile before is free again
         };
-        if (n_hot > 0) issue_full(ring);                    // (behind Q: requested ahead of Q it costs 2 %)
-        else issue_rest(0, ring);
-        int it = 0;
+        auto issue = [&](int i, unsigned char *stage, auto half) __attribute__((always_inline)) {
+            if (i < n_hot) issue_full(stage, half);
+            else issue_rest(i - n_hot, stage, half);
+        };
+        // A short call is one or two tiles per workgroup, and what it takes is their way from memory: the first tile waits for its
+        // keys alone, with the values and what fits of the second tile already under way behind them.  32 heads of 128 columns:
+        // one sequence of 1024 keys 5.5 % of a whole step, of 2000 keys under 60 nodes 17.1 -> 16.8 us; four of 700 under 8
+        // nodes 14.8 -> 13.7 (waiting for the whole first tile, with the second behind it: 13.7 too, but 1.5 % of the step).
+        issue(0, ring, KEYS);                                // (behind Q: requested ahead of Q it costs 2 %)
+        issue(0, ring, VALUES);
+        if (n_all > 1) {
+            if constexpr (C::HALVES_FIRST > 2) issue(1, ring + C::TILE, KEYS);
+            if constexpr (C::HALVES_FIRST > 3) issue(1, ring + C::TILE, VALUES);
+            MCSD_WAIT_VMCNT((C::HALVES_FIRST - 1) * C::NI);
+        } else {
+            MCSD_WAIT_VMCNT(C::NI);
+        }
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        {
+            const unsigned char *qr = ring + C::Q_AT + (qb * 32 + ln) * C::RB;
+#pragma unroll
+            for (int ks = 0; ks < C::KS; ++ks) qs.q[ks] = *(const bf16x8_t *)(qr + (((2 * ks + g) ^ swz<D>(ln)) * 16));
+            const uint64_t *mr = (const uint64_t *)(ring + C::MASK_AT) + ((qb & (p.bph - 1)) * 32 + ln) * 2;
+            mrow[0] = mr[0];
+            mrow[1] = mr[1];
+            uint32_t bits[C::KPW];
+            rest_bits(-n_hot, bits);
+            attn_tile<D, QBP, NS, 2, false, false>(ring, la, qs, p.c, g, bits, 1.f, nullptr, n_hot == 0, [&]() __attribute__((always_inline)) {
+                if (n_all > 1) MCSD_WAIT_VMCNT((C::HALVES_FIRST - 2) * C::NI);
+                else MCSD_WAIT_VMCNT(0);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // Q has been read
+                __builtin_amdgcn_s_barrier();
+                if (C::HALVES_FIRST < 4 && n_all > 1) {      // where Q was comes the rest of the second tile
+                    if constexpr (C::HALVES_FIRST == 3) issue(1, ring + C::TILE, VALUES);
+                    if constexpr (C::HALVES_FIRST == 2) issue(1, ring + C::TILE, BOTH);
+                }
+            });
+        }
+        int it = 1;
         // (spreading the loads over the tile's MFMAs instead of issuing them in one burst was measured: no gain)
         for (; it + 1 < n_hot; it += 2) {
             arrived();
-            issue_full(ring + C::TILE);
-            attn_tile<D, QBP, NS, 0, false, false>(ring, la, qs, p.c, g, all_keys);
-            arrived();
-            if (it + 2 < n_hot) issue_full(ring);
-            else if (it + 2 < n_all) issue_rest(it + 2 - n_hot, ring);
+            issue_full(ring, BOTH);
             attn_tile<D, QBP, NS, 0, false, false>(ring + C::TILE, la, qs, p.c, g, all_keys);
+            arrived();
+            if (it + 2 < n_all) issue(it + 2, ring + C::TILE, BOTH);
+            attn_tile<D, QBP, NS, 0, false, false>(ring, la, qs, p.c, g, all_keys);
         }
         auto rest = [&](int i, unsigned char *stage, unsigned char *other) {
             arrived();
-            if (i + 1 < n_all) issue_rest(i + 1 - n_hot, other);
+            if (i + 1 < n_all) issue_rest(i + 1 - n_hot, other, BOTH);
             uint32_t bits[C::KPW];
             rest_bits(i - n_hot, bits);
             attn_tile<D, QBP, NS, 1, false, false>(stage, la, qs, p.c, g, bits);
         };
         while (it < n_all) {                                // an odd full tile among them
-            rest(it, ring, ring + C::TILE);
+            rest(it, ring + C::TILE, ring);
             if (__builtin_expect(it + 1 >= n_all, 0)) break;
-            rest(it + 1, ring + C::TILE, ring);
+            rest(it + 1, ring, ring + C::TILE);
             it += 2;
         }
         static_assert(!F8, "fp8 tiles use the ring below");
@@ -986,7 +1071,7 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
             }
         };
         auto issue = [&](int x) {
-            if (x < n_hot) issue_full(stage_of(x));
+            if (x < n_hot) issue_full(stage_of(x), BOTH);
             else if (x < n_slots) issue_rest(x);
         };
         auto arrived = [&](int later) {                      // all but `later` slots, and everywhere; the slot before is free again
@@ -998,7 +1083,7 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         auto step = [&](auto stage, int it) {
             constexpr int ST = decltype(stage)::value;
             arrived(min(n_slots - it - 1, NS - 2));
-            if (it + NS - 1 < n_hot) issue_full(ring + (ST + NS - 1) % NS * C::TILE);
+            if (it + NS - 1 < n_hot) issue_full(ring + (ST + NS - 1) % NS * C::TILE, BOTH);
             else if (it + NS - 1 < n_slots) issue_rest(it + NS - 1);
             attn_tile<D, QBP, NS, 0, F8, F8>(ring + ST * C::TILE, la, qs, c_pre, g, all_keys, vs_pre);
         };
@@ -1167,7 +1252,7 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         store_nan();
         return;
     }
-    __shared__ unsigned long long s_prev;
+    unsigned long long &s_prev = *(unsigned long long *)(ring + C::LDS_BYTES - 16);
     unsigned die;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(die));
     die &= 7u;
