@@ -709,8 +709,13 @@ __device__ __attribute__((always_inline)) inline void fold_partials(const __amdg
     }
 }
 
-// PF32: partial O as fp32 (see PART_F32_KEYS).
-template <int D, int QBP, int NS, bool F8, bool PF32>
+// Whether there is a kernel for grids of long and short workgroups in pairs.  Not for four query blocks, where a second loop
+// does not fit the registers (40 of them spilled), nor where a workgroup has the compute unit to itself anyway.
+template <int D, int QBP, int NS, bool F8>
+constexpr bool has_ragged_kernel() { return NS == 2 && !F8 && QBP != 4 && !(D == 128 && QBP == 1); }
+
+// PF32: partial O as fp32 (see PART_F32_KEYS).  RAGGED: a grid of such pairs.
+template <int D, int QBP, int NS, bool F8, bool PF32, bool RAGGED>
 __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_base, const uint32_t per_die, const int32_t G, const uint32_t mul_G,
                                       const int32_t H, const uint32_t mul_H, const int32_t BH, const uint32_t how, const int32_t max_prefix,
                                       const int32_t tps, const AttnParams &p)
@@ -732,6 +737,9 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
     asm("" : "+s"(bhi) : "s"(p.q), "s"(p.kt), "s"(p.vt), "s"(p.kp), "s"(p.vp), "s"(p.mask_bits), "s"(p.mask_words), "s"(p.n), "s"(p.Hq),
         "s"(p.Hkv), "s"(p.grp), "s"(p.hpw), "s"(p.bph), "s"(p.chunks), "s"(p.mul_chunks), "s"(p.shift_chunks), "s"(p.log2_bph),
         "s"(p.S), "s"(p.tree_last), "s"(p.row0), "s"(p.node_stride), "s"(p.head_stride), "s"(p.mul_tps), "s"(p.shift_tps));
+    // Two tiles' halves are kept under way by a workgroup that will have its compute unit to itself: one query block of 128
+    // columns always (its stages fill the LDS), the long one of a pair while the short one is at least a fifth shorter.
+    bool alone = NS == 2 && !PF32 && D == 128 && QBP == 1;
     if (how & HOW_PAIR) {
         const int total = gridDim.x;
         // More workgroups than compute units.  Up to two per compute unit they are all resident at once, and on this
@@ -758,14 +766,19 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         __syncthreads();
         // rank i with rank total-1-i, in groups of p.xcc ids so that a rank keeps its id modulo the number of dies
         // (every key split of a (sequence, unit) then runs on the die of unit % dies)
-        int r = wg;                                                              // longest first
-        if (total <= 2 * p.pair_cus && wg >= p.pair_cus) {
-            const int w2 = wg - p.pair_cus, cnt = total - p.pair_cus;
-            r = (cnt % p.xcc == 0) ? p.pair_cus + (cnt / p.xcc - 1 - w2 / p.xcc) * p.xcc + w2 % p.xcc
-                                   : total + p.pair_cus - 1 - wg;
+        int r = wg, r_other = total;                                             // longest first
+        if (total <= 2 * p.pair_cus) {
+            const int w2 = wg >= p.pair_cus ? wg - p.pair_cus : wg, cnt = total - p.pair_cus;
+            const int second = (cnt % p.xcc == 0) ? p.pair_cus + (cnt / p.xcc - 1 - w2 / p.xcc) * p.xcc + w2 % p.xcc : total - 1 - w2;
+            if (wg >= p.pair_cus) r = second;
+            else if (wg < cnt) r_other = second;
         }
         const int rank = fast_div(r, mul_H, how_shift_H(how));
         const int cls = __builtin_amdgcn_readfirstlane(s_cls_at[rank]);
+        if (RAGGED && wg < p.pair_cus) {
+            const int others = r_other < total ? s_work[s_cls_at[fast_div(r_other, mul_H, how_shift_H(how))]] : 0;
+            alone = __builtin_amdgcn_readfirstlane(4 * s_work[cls]) > 5 * __builtin_amdgcn_readfirstlane(others);
+        }
         __syncthreads();                                     // (the first loads land there)
         s = cls % p.S;
         // Units that stream the same keys for different query heads are neighbours: give them one die, and so one L2 (a die's
@@ -967,9 +980,10 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
                 if (HALF != 0) load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off, stage + C::TILE_K + j * C::WAVES * 1024);
             }
         };
-        auto arrived = [&]() {
-            MCSD_WAIT_VMCNT(0);                             // this wavefront's part of the tile has landed ...
-            __builtin_amdgcn_s_barrier();                   // ... and everyone's; the stage of the tile before is free again
+        // This wavefront's reads of the half tile that is asked for next are done, and what it has waited for has landed; now everyone's.
+        auto meet = []() __attribute__((always_inline)) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
         };
         auto issue = [&](int i, unsigned char *stage, auto half) __attribute__((always_inline)) {
             if (i < n_hot) issue_full(stage, half);
@@ -977,7 +991,7 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         };
         // A short call is one or two tiles per workgroup, and what it takes is their way from memory: the first tile waits for its
         // keys alone, with the values and what fits of the second tile already under way behind them.  32 heads of 128 columns:
-        // one sequence of 1024 keys 5.5 % of a whole step, of 2000 keys under 60 nodes 17.1 -> 16.8 us; four of 700 under 8
+        // one sequence of 1024 keys 5.5 % of a whole step, of 2000 keys under 120 nodes 17.1 -> 16.8 us; four of 700 under 14
         // nodes 14.8 -> 13.7 (waiting for the whole first tile, with the second behind it: 13.7 too, but 1.5 % of the step).
         issue(0, ring, KEYS);                                // (behind Q: requested ahead of Q it costs 2 %)
         issue(0, ring, VALUES);
@@ -1002,32 +1016,64 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
             attn_tile<D, QBP, NS, 2, false, false>(ring, la, qs, p.c, g, bits, 1.f, nullptr, n_hot == 0, [&]() __attribute__((always_inline)) {
                 if (n_all > 1) MCSD_WAIT_VMCNT((C::HALVES_FIRST - 2) * C::NI);
                 else MCSD_WAIT_VMCNT(0);
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // Q has been read
-                __builtin_amdgcn_s_barrier();
-                if (C::HALVES_FIRST < 4 && n_all > 1) {      // where Q was comes the rest of the second tile
+                meet();                                      // (Q has been read, too)
+                if (n_all > 1) {                             // the rest of the second tile, partly where Q was, and the third's keys
                     if constexpr (C::HALVES_FIRST == 3) issue(1, ring + C::TILE, VALUES);
                     if constexpr (C::HALVES_FIRST == 2) issue(1, ring + C::TILE, BOTH);
+                    if (alone && n_all > 2) issue(2, ring, KEYS);
                 }
             });
         }
+        // The workgroup that shares its compute unit asks for a tile when the tile before has landed and waits for all of it: the
+        // other one's loads are under way meanwhile, and where memory is the limit more requests cost 1-2 % (8 x 32 heads of 16384
+        // keys: 345 us so, 355 with the loop for one that is alone; 16 x 32 of 2300: 97.7, 98.9).  The one that is alone asks for
+        // a half as soon as its place is free, two barriers and waits per tile, and never waits for the last two: 16 sequences of
+        // 1000-4000 keys, 16 heads, one query block 68.9 -> 59.9 us; of 512-4096 keys, 32 heads, 60 nodes 113.7 -> 106; 12 heads
+        // of 64 columns 37.9 -> 32.5.  (A ring of five halves with one barrier per tile: 60.5, 106.7, 35.0, and 355 above, for the
+        // reads' addresses are then made for every tile.)
         int it = 1;
-        // (spreading the loads over the tile's MFMAs instead of issuing them in one burst was measured: no gain)
-        for (; it + 1 < n_hot; it += 2) {
-            arrived();
-            issue_full(ring, BOTH);
-            attn_tile<D, QBP, NS, 0, false, false>(ring + C::TILE, la, qs, p.c, g, all_keys);
-            arrived();
-            if (it + 2 < n_all) issue(it + 2, ring + C::TILE, BOTH);
-            attn_tile<D, QBP, NS, 0, false, false>(ring, la, qs, p.c, g, all_keys);
+        auto full = [&](unsigned char *stage, unsigned char *other) __attribute__((always_inline)) {
+            MCSD_WAIT_VMCNT(2 * C::NI);
+            meet();
+            issue_full(other, VALUES);
+            attn_tile<D, QBP, NS, 0, false, false>(stage, la, qs, p.c, g, all_keys, 1.f, nullptr, false, [&]() __attribute__((always_inline)) {
+                MCSD_WAIT_VMCNT(2 * C::NI);
+                meet();
+                issue_full(stage, KEYS);
+            });
+        };
+        bool ahead = alone && n_all > 2;                     // the keys of the tile after this one have been requested
+        auto arrived = [&]() __attribute__((always_inline)) {
+            MCSD_WAIT_VMCNT(0);
+            meet();
+        };
+        if (alone) {
+            for (; it + 3 < n_hot; it += 2) {
+                full(ring + C::TILE, ring);
+                full(ring, ring + C::TILE);
+            }
+        } else {
+            for (; it + 2 < n_hot; it += 2) {
+                arrived();
+                issue_full(ring, BOTH);
+                attn_tile<D, QBP, NS, 0, false, false>(ring + C::TILE, la, qs, p.c, g, all_keys);
+                arrived();
+                issue_full(ring + C::TILE, BOTH);
+                attn_tile<D, QBP, NS, 0, false, false>(ring, la, qs, p.c, g, all_keys);
+            }
         }
-        auto rest = [&](int i, unsigned char *stage, unsigned char *other) {
+        auto rest = [&](int i, unsigned char *stage, unsigned char *other) __attribute__((always_inline)) {
             arrived();
-            if (i + 1 < n_all) issue_rest(i + 1 - n_hot, other, BOTH);
+            if (i + 1 < n_all) {
+                if (!ahead) issue(i + 1, other, KEYS);
+                issue(i + 1, other, VALUES);
+            }
+            ahead = false;
             uint32_t bits[C::KPW];
             rest_bits(i - n_hot, bits);
-            attn_tile<D, QBP, NS, 1, false, false>(stage, la, qs, p.c, g, bits);
+            attn_tile<D, QBP, NS, 2, false, false>(stage, la, qs, p.c, g, bits, 1.f, nullptr, i >= n_hot);
         };
-        while (it < n_all) {                                // an odd full tile among them
+        while (it < n_all) {
             rest(it, ring + C::TILE, ring);
             if (__builtin_expect(it + 1 >= n_all, 0)) break;
             rest(it + 1, ring, ring + C::TILE);
@@ -1290,18 +1336,20 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
     else fold_partials<D, QBP, C::KG, PF32 ? 7 : 8, PF32>(ro, rm, rl, n_active, kg, g, ln, cm, orow, (f32x4_t *)ring + tid);
 }
 
-#define SWEEP_KERNEL(NAME, PF32)                                                                                                    \
+#define SWEEP_KERNEL(NAME, PF32, RAGGED)                                                                                                 \
     template <int D, int QBP, int NS, bool F8 = false>                                                                              \
     __global__ __launch_bounds__((SweepCfg<D, QBP, NS, F8>::THREADS)) __attribute__((amdgpu_waves_per_eu(2, 2)))                    \
     void NAME(const int32_t *lens, const int64_t *seq_base, const uint32_t per_die, const int32_t G, const uint32_t mul_G,          \
               const int32_t H, const uint32_t mul_H, const int32_t BH, const uint32_t how, const int32_t max_prefix,                \
               const int32_t tps, const AttnParams p)                                                                                \
     {                                                                                                                               \
-        sweep<D, QBP, NS, F8, PF32>(lens, seq_base, per_die, G, mul_G, H, mul_H, BH, how, max_prefix, tps, p);                      \
+        sweep<D, QBP, NS, F8, PF32, RAGGED>(lens, seq_base, per_die, G, mul_G, H, mul_H, BH, how, max_prefix, tps, p);              \
     }
-SWEEP_KERNEL(tree_attn_bf16_kernel, false)
+SWEEP_KERNEL(tree_attn_bf16_kernel, false, false)
 // (a kernel of its own: as a branch the second set of folds cost calls that do not use it up to 1 %, 32 layers of 1024 keys 352 -> 357 us)
-SWEEP_KERNEL(tree_attn_bf16_short_kernel, true)
+SWEEP_KERNEL(tree_attn_bf16_short_kernel, true, false)
+// (a kernel of its own, too: the second loop costs 50 registers, and calls that never take it 0.1 us: that step 334 -> 336 us)
+SWEEP_KERNEL(tree_attn_bf16_ragged_kernel, false, true)
 #undef SWEEP_KERNEL
 
 // Folds the partial results of the key splits of the bf16 sweep.  One thread per 4 output columns of one query;
@@ -1719,6 +1767,8 @@ void launch_sweep(const AttnParams &p, const AttnPlan &pl, hipStream_t st)
     auto kernel = tree_attn_bf16_kernel<D, QBP, NS, F8>;
     if constexpr (F8 || NS == 2)
         if (pl.part_f32) kernel = tree_attn_bf16_short_kernel<D, QBP, NS, F8>;
+    if constexpr (has_ragged_kernel<D, QBP, NS, F8>())
+        if (!pl.part_f32 && p.pair_cus > 0 && total <= 2u * p.pair_cus) kernel = tree_attn_bf16_ragged_kernel<D, QBP, NS, F8>;
     mcsd_launch(MCSD_KERNEL_ATTN_SWEEP, kernel, dim3(total), dim3(SweepCfg<D, QBP, NS, F8>::THREADS), st,
                 p.lens, p.seq_base, total >> log2_xcc, (int32_t)pl.G, g.mul, p.H, h.mul, (int32_t)(p.B * p.H), how, p.max_prefix, p.tps, p);
 }

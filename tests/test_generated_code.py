@@ -100,6 +100,27 @@ def test_steady_state_loops_wait_for_memory_once_per_tile(sweep_asm):
     assert checked == 12 + 8
 
 
+def test_the_loop_of_a_workgroup_alone_waits_for_halves(sweep_asm):
+    """Grids of pairs: the loop of two tiles with two waits and barriers each leaves exactly two half tiles' loads under way."""
+    checked = 0
+    for name, body in _functions(sweep_asm):
+        if "tree_attn_bf16_ragged_kernel" not in name:
+            continue
+        D, QBP = (int(x) for x in re.search(r"ILi(\d+)ELi(\d+)ELi2ELb0E", name).groups())
+        labels = {m.group(1): i for i, l in enumerate(body) if (m := re.match(r"^(\.LBB\d+_\d+):", l))}
+        spans = [body[labels[m.group(1)]:i + 1] for i, l in enumerate(body)
+                 if (m := re.search(r"s_c?branch\w*\s+(\.LBB\d+_\d+)", l)) and labels.get(m.group(1), i) < i]
+        four = [x for x in spans if sum("s_barrier" in y.split(";")[0] for y in x) == 4 and any(re.search(r"global_load_lds.*\bnt\b", y) for y in x)]
+        assert four, f"{name}: no such loop found"
+        code = [x.split(";")[0] for x in min(four, key=len)]
+        keys = {1: 128, 2: 64}[QBP]
+        loads_per_half = keys * D * 2 // 1024 // 4
+        assert [int(x) for y in code for x in re.findall(r"vmcnt\((\d+)\)", y)] == [2 * loads_per_half] * 4, name
+        assert not any("scratch_" in x for x in code), name
+        checked += 1
+    assert checked == 3                                         # 64 columns x 1, 2 query blocks, 128 x 2
+
+
 def test_the_checked_code_takes_its_leading_arguments_in_registers(sweep_asm):
     """The compile above is the shipped one: its kernels say how many argument registers are preloaded."""
     preloaded = [int(m.group(1)) for l in sweep_asm if (m := re.match(r"\s*\.amdhsa_user_sgpr_kernarg_preload_length\s+(\d+)", l))]
