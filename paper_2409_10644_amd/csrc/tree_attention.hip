@@ -133,14 +133,15 @@ void device_shape(int &n_cus, int &n_xcc)
 
 // How the bf16 sweep cuts the keys of a (sequence, unit): S splits, and who takes the tree's own keys (1: a workgroup of its
 // own, 2: the first split, 3: the last).  The candidates are the S that give every split keys; each is priced in tiles of
-// time and the cheapest taken.  Measured on 170 shapes (1-64 sequences, 4-32 heads of 64 or 128, 32-16384 keys, 1-120 rows,
-// every S up to 8 with every place for the tree's keys): a workgroup's tiles follow one another at one memory latency each
-// (1.03 us per 64 keys of 128 dimensions, 0.7 us of 64), partial results cost their exchange and fold (`fold_us`), two
-// workgroups on a compute unit slow each other down almost by their sum, and a grid beyond the residents costs its
-// remainder.  The choice is within 1 % of the best of the measured ones on average; the fixed rule before it (two
-// workgroups per compute unit, at least 256 keys per split) lost 11 %, up to 78 %.  Prefixes of fewer than PART_F32_KEYS keys,
-// whose partial results are fp32, on another 140 shapes (8-256 units, 110-440 keys): the same prices but for two query blocks,
-// where the fold costs half as much again, are within 0.6 % of the best; not splitting at all would lose 11 %, up to 49 %.
+// time and the cheapest taken.  Measured on 900 bf16 and 350 fp8 shapes (1-8 sequences of L/2..L keys, 4-32 heads of 64 or 128,
+// 64-6000 keys, 8-120 rows, every S up to 15 with every place for the tree's keys) and on 350 of L/8..L keys: a workgroup's
+// tiles follow one another (0.88 us per 64 keys of 128 dimensions, 0.62 of 64), partial results cost their exchange and fold
+// (`fold_us`), two workgroups on a compute unit slow each other down almost by their sum, and a grid beyond the residents costs
+// its remainder.  The choice is within 0.8 % of the best of the measured ones on average, 1.5 % where the lengths vary most; the
+// prices of the sweep that asked for its second tile when the first was there (1.03 and 0.7 us, folds 10-20 % cheaper for two
+// blocks of 128 dimensions and dearer for 64) lost 1.5 and 1.8 %, up to 23 %: 2 x 12 heads, 541 keys, 14 rows 9.1 -> 7.4 us; 4 x 16
+// heads of 64, 2846 keys, 44 rows 14.6 -> 13.8.  Two workgroups per compute unit and at least 256 keys per split lost 11 %.
+// Prefixes of fewer than PART_F32_KEYS keys, whose partial results are fp32: not splitting at all would lose 11 %, up to 49 %.
 struct SplitChoice { int S, tree; };
 SplitChoice choose_splits(int cus, int d, int QBP, bool f8, int B, long bh, int tiles, int tree_tiles, int tree_forced)
 {
@@ -149,11 +150,11 @@ SplitChoice choose_splits(int cus, int d, int QBP, bool f8, int B, long bh, int 
     if (memo.cus == cus && memo.d == d && memo.QBP == QBP && memo.f8 == (int)f8 && memo.B == B && memo.bh == bh && memo.tiles == tiles &&
         memo.tree_tiles == tree_tiles && memo.forced == tree_forced)
         return memo.c;
-    static const float fold_us[10] = {0.f, 0.f, 1.4f, 1.85f, 2.4f, 2.5f, 3.15f, 3.2f, 4.7f, 6.3f};   // by partial results
-    const float tile_us = (d == 128 ? (QBP == 1 ? 1.6f : QBP == 2 ? 1.03f : 1.15f) : (QBP == 1 ? 1.f : QBP == 2 ? 0.7f : 0.74f)) *
-                          (f8 ? 0.8f : 1.f);
+    static const float fold_us[10] = {0.f, 0.f, 2.f, 2.f, 2.6f, 2.6f, 3.1f, 3.1f, 6.f, 6.3f};   // by partial results
+    const float tile_us = (d == 128 ? (QBP == 1 ? 2.3f : QBP == 2 ? 0.88f : 1.45f) : (QBP == 1 ? 0.64f : QBP == 2 ? 0.62f : 0.47f)) *
+                          (f8 ? 0.95f : 1.f);
     const bool part_f32 = tiles * tile_keys_bf16(QBP) < PART_F32_KEYS;
-    const float fold_scale = (d == 64 ? 0.55f : 1.f) * (QBP == 4 ? 1.75f : QBP == 1 ? 1.35f : part_f32 ? 1.5f : 1.f);
+    const float fold_scale = (d == 64 ? 0.42f : 1.f) * (QBP == 4 ? 2.f : QBP == 1 ? 1.16f : part_f32 ? 1.28f : 1.f);
     const int per_cu = d == 128 && QBP == 1 ? 1 : 2;                     // resident workgroups (LDS)
     SplitChoice best = {1, tree_forced ? tree_forced : 2};
     if (bh > cus) {
@@ -177,14 +178,14 @@ SplitChoice choose_splits(int cus, int d, int QBP, bool f8, int B, long bh, int 
                 const float all = (float)(tiles + tree_tiles), load = (float)bh * parts / cus;   // workgroups per compute unit
                 float us;
                 if (load <= 1.f) us = tile_us * most;
-                else if (load <= per_cu) us = 0.94f * tile_us * (most + 0.8f * all / parts);
+                else if (load <= per_cu) us = 0.85f * tile_us * (most + all / parts);
                 else {
                     const float even = all * bh / cus, two = (float)most * per_cu;
                     if (S == 1) us = 0.9f * tile_us * two * (float)(int)(load / per_cu + 0.999f);
-                    else us = tile_us * ((tree == 3 ? 0.88f : 0.98f) * (two > even ? two : even) + (tree == 3 ? 0.5f : 0.3f) * most);
+                    else us = tile_us * ((tree == 3 ? 1.05f : 1.2f) * (two > even ? two : even) + (tree == 3 ? 0.6f : 0.4f) * most);
                 }
-                if (tree == 3 && B > 1 && bh * S > cus) us *= 1.08f;     // (not ordered by length)
-                if (tree == 2 && S > 1 && bh * S > cus) us += 1.85f;     // the ordering by length itself
+                if (tree == 3 && B > 1 && bh * S > cus) us *= 1.08f;     // (not ordered by length: 8 x 32 heads, 500-4000 keys 54 us ordered, 62 not)
+                if (tree == 2 && S > 1 && bh * S > cus) us += 2.2f;     // the ordering by length itself
                 if (parts > 1) us += fold_us[parts < 9 ? parts : 9] * fold_scale;
                 if (us < best_us) { best_us = us; best = {S, tree}; }
             }
@@ -347,7 +348,7 @@ struct SweepCfg {
     // tiles are requested beside them.
     static constexpr int Q_BYTES = QBP * 32 * RB, MASK_BYTES = QBP * 32 * 16;
     static constexpr int LDS_BYTES = NS > 2 ? (RING > XCHG + 1040 ? RING : XCHG + 1040)
-                                   : QBP == 1 ? RING + Q_BYTES + MASK_BYTES : D * 640;
+                                   : D == 64 || QBP == 1 ? RING + Q_BYTES + MASK_BYTES : 80 * 1024;
     static constexpr int MASK_AT = LDS_BYTES - MASK_BYTES, Q_AT = MASK_AT - Q_BYTES;
     static constexpr int HALVES_FIRST = Q_AT / TILE_K < 4 ? Q_AT / TILE_K : 4;
     static constexpr int PAIR_AT = NS == 2 ? MASK_AT + MASK_BYTES - 2048 : 0;                       // the table that orders ragged grids
@@ -710,7 +711,8 @@ __device__ __attribute__((always_inline)) inline void fold_partials(const __amdg
 }
 
 // Whether there is a kernel for grids of long and short workgroups in pairs.  Not for four query blocks, where a second loop
-// does not fit the registers (40 of them spilled), nor where a workgroup has the compute unit to itself anyway.
+// does not fit the registers (40 of them spilled), nor for split keys (16 x 16 heads, 851-3407 keys: 53.4 us without, 56.1 with
+// it), nor where a workgroup has the compute unit to itself anyway.
 template <int D, int QBP, int NS, bool F8>
 constexpr bool has_ragged_kernel() { return NS == 2 && !F8 && QBP != 4 && !(D == 128 && QBP == 1); }
 
@@ -1768,7 +1770,7 @@ void launch_sweep(const AttnParams &p, const AttnPlan &pl, hipStream_t st)
     if constexpr (F8 || NS == 2)
         if (pl.part_f32) kernel = tree_attn_bf16_short_kernel<D, QBP, NS, F8>;
     if constexpr (has_ragged_kernel<D, QBP, NS, F8>())
-        if (!pl.part_f32 && p.pair_cus > 0 && total <= 2u * p.pair_cus) kernel = tree_attn_bf16_ragged_kernel<D, QBP, NS, F8>;
+        if (pl.S == 1 && p.pair_cus > 0 && total <= 2u * p.pair_cus) kernel = tree_attn_bf16_ragged_kernel<D, QBP, NS, F8>;
     mcsd_launch(MCSD_KERNEL_ATTN_SWEEP, kernel, dim3(total), dim3(SweepCfg<D, QBP, NS, F8>::THREADS), st,
                 p.lens, p.seq_base, total >> log2_xcc, (int32_t)pl.G, g.mul, p.H, h.mul, (int32_t)(p.B * p.H), how, p.max_prefix, p.tps, p);
 }
