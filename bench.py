@@ -147,7 +147,9 @@ class Step:
             return f"tree_attn_f32_kernel<{self.w.d}>"
         keys = 128 if self.plan.query_blocks == 1 else 64       # of a tile; split prefixes below 512 keys exchange fp32
         short = "_short" if self.plan.key_splits > 1 and -(-self.cap // keys) * keys < 512 else ""
-        return f"tree_attn_bf16{short}_kernel<{self.w.d}, {self.plan.query_blocks}, {self.plan.stages}, false>"
+        pairs = self.plan.ordered_by_length and self.plan.key_splits == 1 and self.plan.workgroups <= 512    # long and short ones, two per compute unit
+        ragged = "_ragged" if pairs and self.plan.query_blocks != 4 and (self.w.d, self.plan.query_blocks) != (128, 1) else ""
+        return f"tree_attn_bf16{short}{ragged}_kernel<{self.w.d}, {self.plan.query_blocks}, {self.plan.stages}, false>"
 
     def attention(self, layer):
         ad, w, b = self.layers[layer % len(self.layers)], self.w, self.binding
