@@ -504,10 +504,14 @@ __device__ __forceinline__ void attn_tile(const unsigned char *stage, const Lane
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         if (MODE == 1 || (MODE == 2 && masked)) {
-            const uint32_t own = bits[u] >> (4 * g);            // (tested at constant places)
+            // Bits at constant places, spread over the register and blended: two instructions per score.  (Comparing and selecting
+            // took four, one of them a wait for the condition: 0.1-0.3 us of a call of a tile or two.)
+            const uint32_t own = bits[u] >> (4 * g);
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (!((own >> (8 * (r / 4) + r % 4)) & 1u)) sacc[u][r] = -INFINITY;
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t seen = (uint32_t)__builtin_amdgcn_sbfe((int)own, 8 * (r / 4) + r % 4, 1);       // all ones or zero
+                sacc[u][r] = __uint_as_float((__float_as_uint(sacc[u][r]) & seen) | (0xff800000u & ~seen));
+            }
         }
         mx = fmaxf(fmaxf(mx, sacc[u][0]), sacc[u][1]);
 #pragma unroll
@@ -955,6 +959,13 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
             const int key0 = (kg * C::KPW + u) * 32;        // first key of this block inside the tile
             if (i < 0) {                                    // (a full tile)
                 bits[u] = 0xffffffffu;
+            } else if (RAGGED) {                            // (without branches: with them four registers spill, 102 -> 106 us)
+                const int left = tail_rows - key0;
+                const uint32_t exist = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : ((1u << left) - 1u));
+                const int col = max(i - n_tail, 0) * C::T + key0;
+                const uint64_t word = (col >> 6) ? (p.mask_words > 1 ? mrow[1] : 0) : mrow[0];
+                const uint32_t tree = i < n_tail ? 0u : 0xffffffffu;
+                bits[u] = ((uint32_t)(word >> (col & 63)) & tree) | (exist & ~tree);
             } else if (i < n_tail) {
                 const int left = tail_rows - key0;          // keys of the block that exist
                 bits[u] = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : ((1u << left) - 1u));
@@ -966,7 +977,9 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
     };
     if constexpr (NS == 2) {
         // The tiles that are not full come the same way, a key beyond the last one as that one again (masked out), a value as
-        // zeros: through registers behind the last full tile each of them cost its whole latency once more, 1.7 us.
+        // zeros: through registers behind the last full tile each of them cost its whole latency once more, 1.7 us.  Both halves in
+        // one go, keys first, share their offsets: made anew for the values they cost short calls 0.1-0.2 us.  (For 128 columns only
+        // behind the first two tiles: there, and in the kernel for pairs, which has no registers for it, halves by themselves.)
         auto issue_rest = [&](int i, unsigned char *stage, auto half) __attribute__((always_inline)) {
             constexpr int HALF = decltype(half)::value;
             const bool tail = i < n_tail;
@@ -975,11 +988,17 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
             const int last = (tail ? tail_rows : p.n - (i - n_tail) * C::T) - 1;
             stage += wave * 1024;
             const unsigned char *no_row = zeros + (lane & 3) * 16;
+            uint32_t off[C::NI];
 #pragma unroll
-            for (int j = 0; j < C::NI; ++j) {
-                const uint32_t off = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
-                if (HALF != 1) load_to_lds16<false>(ks, off, stage + j * C::WAVES * 1024);
-                if (HALF != 0) load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off, stage + C::TILE_K + j * C::WAVES * 1024);
+            for (int j = 0; j < C::NI; ++j) off[j] = goff + (uint32_t)((j * STEP - max(row0 + j * STEP - last, 0)) * C::RBP);
+            if (HALF != 1) {
+#pragma unroll
+                for (int j = 0; j < C::NI; ++j) load_to_lds16<false>(ks, off[j], stage + j * C::WAVES * 1024);
+            }
+            if (HALF != 0) {
+#pragma unroll
+                for (int j = 0; j < C::NI; ++j)
+                    load_to_lds16_at(row0 + j * STEP > last ? no_row : vs + off[j], stage + C::TILE_K + j * C::WAVES * 1024);
             }
         };
         // This wavefront's reads of the half tile that is asked for next are done, and what it has waited for has landed; now everyone's.
@@ -995,11 +1014,17 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         // keys alone, with the values and what fits of the second tile already under way behind them.  32 heads of 128 columns:
         // one sequence of 1024 keys 5.5 % of a whole step, of 2000 keys under 120 nodes 17.1 -> 16.8 us; four of 700 under 14
         // nodes 14.8 -> 13.7 (waiting for the whole first tile, with the second behind it: 13.7 too, but 1.5 % of the step).
-        issue(0, ring, KEYS);                                // (behind Q: requested ahead of Q it costs 2 %)
-        issue(0, ring, VALUES);
+        auto issue_first = [&](int i, unsigned char *stage) __attribute__((always_inline)) {         // (one of the first two tiles)
+            if (D == 64 && i >= n_hot) issue_rest(i - n_hot, stage, BOTH);
+            else {
+                issue(i, stage, KEYS);
+                issue(i, stage, VALUES);
+            }
+        };
+        issue_first(0, ring);                                // (behind Q: requested ahead of Q it costs 2 %)
         if (n_all > 1) {
-            if constexpr (C::HALVES_FIRST > 2) issue(1, ring + C::TILE, KEYS);
-            if constexpr (C::HALVES_FIRST > 3) issue(1, ring + C::TILE, VALUES);
+            if constexpr (C::HALVES_FIRST == 3) issue(1, ring + C::TILE, KEYS);
+            if constexpr (C::HALVES_FIRST > 3) issue_first(1, ring + C::TILE);
             MCSD_WAIT_VMCNT((C::HALVES_FIRST - 1) * C::NI);
         } else {
             MCSD_WAIT_VMCNT(C::NI);
@@ -1067,8 +1092,11 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         auto rest = [&](int i, unsigned char *stage, unsigned char *other) __attribute__((always_inline)) {
             arrived();
             if (i + 1 < n_all) {
-                if (!ahead) issue(i + 1, other, KEYS);
-                issue(i + 1, other, VALUES);
+                if constexpr (!RAGGED && !(D == 128 && QBP == 1)) issue(i + 1, other, BOTH);     // (never `ahead`)
+                else {
+                    if (!ahead) issue(i + 1, other, KEYS);
+                    issue(i + 1, other, VALUES);
+                }
             }
             ahead = false;
             uint32_t bits[C::KPW];

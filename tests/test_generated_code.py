@@ -121,6 +121,22 @@ def test_the_loop_of_a_workgroup_alone_waits_for_halves(sweep_asm):
     assert checked == 3                                         # 64 columns x 1, 2 query blocks, 128 x 2
 
 
+def test_masked_scores_cost_two_instructions(sweep_asm):
+    """A bit spread over a register and a blend per score; comparing and selecting takes twice as many."""
+    checked = 0
+    for name, body in _functions(sweep_asm):
+        if "tree_attn_bf16_" not in name or "merge" in name:
+            continue
+        QBP = int(re.search(r"ILi\d+ELi(\d+)E", name).group(1))
+        code = [x.split(";")[0] for x in body]
+        spread = [x for x in code if re.search(r"v_bfe_i32 v\d+, v\d+, \d+, 1\s*$", x)]
+        assert spread and len(spread) % (16 * (2 if QBP == 4 else 1)) == 0, f"{name}: {len(spread)}"
+        assert not any(re.search(r"v_and_b32\w* v\d+, 0x(100|200|400|800|10000|20000|40000|80000), v", x) for x in code), name
+        assert not any("scratch_" in x for x in code), f"{name}: spills"
+        checked += 1
+    assert checked == 12 + 8 + 3
+
+
 def test_the_checked_code_takes_its_leading_arguments_in_registers(sweep_asm):
     """The compile above is the shipped one: its kernels say how many argument registers are preloaded."""
     preloaded = [int(m.group(1)) for l in sweep_asm if (m := re.match(r"\s*\.amdhsa_user_sgpr_kernarg_preload_length\s+(\d+)", l))]
