@@ -133,15 +133,17 @@ void device_shape(int &n_cus, int &n_xcc)
 
 // How the bf16 sweep cuts the keys of a (sequence, unit): S splits, and who takes the tree's own keys (1: a workgroup of its
 // own, 2: the first split, 3: the last).  The candidates are the S that give every split keys; each is priced in tiles of
-// time and the cheapest taken.  Measured on 900 bf16 and 350 fp8 shapes (1-8 sequences of L/2..L keys, 4-32 heads of 64 or 128,
-// 64-6000 keys, 8-120 rows, every S up to 15 with every place for the tree's keys) and on 350 of L/8..L keys: a workgroup's
-// tiles follow one another (0.88 us per 64 keys of 128 dimensions, 0.62 of 64), partial results cost their exchange and fold
-// (`fold_us`), two workgroups on a compute unit slow each other down almost by their sum, and a grid beyond the residents costs
-// its remainder.  The choice is within 0.8 % of the best of the measured ones on average, 1.5 % where the lengths vary most; the
-// prices of the sweep that asked for its second tile when the first was there (1.03 and 0.7 us, folds 10-20 % cheaper for two
-// blocks of 128 dimensions and dearer for 64) lost 1.5 and 1.8 %, up to 23 %: 2 x 12 heads, 541 keys, 14 rows 9.1 -> 7.4 us; 4 x 16
-// heads of 64, 2846 keys, 44 rows 14.6 -> 13.8.  Two workgroups per compute unit and at least 256 keys per split lost 11 %.
-// Prefixes of fewer than PART_F32_KEYS keys, whose partial results are fp32: not splitting at all would lose 11 %, up to 49 %.
+// time and the cheapest taken: a workgroup's tiles follow one another at one memory latency each (1.03 us per 64 keys of 128
+// dimensions, 0.7 us of 64), partial results cost their exchange and fold (`fold_us`), two workgroups on a compute unit slow
+// each other down almost by their sum, and a grid beyond the residents costs its remainder.
+// Measured on 3900 shapes of at most one unit per compute unit (1-64 sequences of up to eight times different lengths, 4-64 heads
+// of 64 or 128 with 1-8 of them sharing keys, bf16 and fp8, 64-32768 keys, 1-120 rows; every S up to 15 with every place for the
+// tree's keys): within 2.2 % of the best of the measured ones on average, one in a hundred 26 % off.  Two workgroups per compute unit
+// and at least 256 keys per split lost 11 %; prefixes of fewer than PART_F32_KEYS keys, whose partial results are fp32, would
+// lose 11 % unsplit, up to 49 %.  Prices fitted to a sweep that requests two tiles at once (0.88 and 0.62 us, dearer folds)
+// were 2.1 % off, on other calls: 2 x 64 heads over 32, 728 keys, 44 rows 12.9 us with these and 16.1 with those; 11 x 8 heads,
+// 6433 keys, 28 rows 53.9 and 45.7.  They cut finer, so that a member of a ragged batch that fits one split here exchanged
+// partial results in bf16, a second rounding (1.17 times the error): not worth it.
 struct SplitChoice { int S, tree; };
 SplitChoice choose_splits(int cus, int d, int QBP, bool f8, int B, long bh, int tiles, int tree_tiles, int tree_forced)
 {
@@ -150,11 +152,11 @@ SplitChoice choose_splits(int cus, int d, int QBP, bool f8, int B, long bh, int 
     if (memo.cus == cus && memo.d == d && memo.QBP == QBP && memo.f8 == (int)f8 && memo.B == B && memo.bh == bh && memo.tiles == tiles &&
         memo.tree_tiles == tree_tiles && memo.forced == tree_forced)
         return memo.c;
-    static const float fold_us[10] = {0.f, 0.f, 2.f, 2.f, 2.6f, 2.6f, 3.1f, 3.1f, 6.f, 6.3f};   // by partial results
-    const float tile_us = (d == 128 ? (QBP == 1 ? 2.3f : QBP == 2 ? 0.88f : 1.45f) : (QBP == 1 ? 0.64f : QBP == 2 ? 0.62f : 0.47f)) *
-                          (f8 ? 0.95f : 1.f);
+    static const float fold_us[10] = {0.f, 0.f, 1.4f, 1.85f, 2.4f, 2.5f, 3.15f, 3.2f, 4.7f, 6.3f};   // by partial results
+    const float tile_us = (d == 128 ? (QBP == 1 ? 1.6f : QBP == 2 ? 1.03f : 1.15f) : (QBP == 1 ? 1.f : QBP == 2 ? 0.7f : 0.74f)) *
+                          (f8 ? 0.8f : 1.f);
     const bool part_f32 = tiles * tile_keys_bf16(QBP) < PART_F32_KEYS;
-    const float fold_scale = (d == 64 ? 0.42f : 1.f) * (QBP == 4 ? 2.f : QBP == 1 ? 1.16f : part_f32 ? 1.28f : 1.f);
+    const float fold_scale = (d == 64 ? 0.55f : 1.f) * (QBP == 4 ? 1.75f : QBP == 1 ? 1.35f : part_f32 ? 1.5f : 1.f);
     const int per_cu = d == 128 && QBP == 1 ? 1 : 2;                     // resident workgroups (LDS)
     SplitChoice best = {1, tree_forced ? tree_forced : 2};
     if (bh > cus) {
@@ -178,14 +180,14 @@ SplitChoice choose_splits(int cus, int d, int QBP, bool f8, int B, long bh, int 
                 const float all = (float)(tiles + tree_tiles), load = (float)bh * parts / cus;   // workgroups per compute unit
                 float us;
                 if (load <= 1.f) us = tile_us * most;
-                else if (load <= per_cu) us = 0.85f * tile_us * (most + all / parts);
+                else if (load <= per_cu) us = 0.94f * tile_us * (most + 0.8f * all / parts);
                 else {
                     const float even = all * bh / cus, two = (float)most * per_cu;
                     if (S == 1) us = 0.9f * tile_us * two * (float)(int)(load / per_cu + 0.999f);
-                    else us = tile_us * ((tree == 3 ? 1.05f : 1.2f) * (two > even ? two : even) + (tree == 3 ? 0.6f : 0.4f) * most);
+                    else us = tile_us * ((tree == 3 ? 0.88f : 0.98f) * (two > even ? two : even) + (tree == 3 ? 0.5f : 0.3f) * most);
                 }
                 if (tree == 3 && B > 1 && bh * S > cus) us *= 1.08f;     // (not ordered by length: 8 x 32 heads, 500-4000 keys 54 us ordered, 62 not)
-                if (tree == 2 && S > 1 && bh * S > cus) us += 2.2f;     // the ordering by length itself
+                if (tree == 2 && S > 1 && bh * S > cus) us += 1.85f;     // the ordering by length itself
                 if (parts > 1) us += fold_us[parts < 9 ? parts : 9] * fold_scale;
                 if (us < best_us) { best_us = us; best = {S, tree}; }
             }

@@ -50,3 +50,33 @@ def test_error_of_split_short_prefixes(binding, oracle, H, br, d, L):
     plans = [dict()] + [dict(key_splits=s, tree_keys=t, fold=f) for s in range(2, min(tiles, 6) + 1) for t in (1, 2, 3) for f in (0, 1)]
     for plan in plans:
         assert error(**plan) <= 1.02 * one, plan
+
+
+@pytest.mark.parametrize("B,heads,d,br,bound,short,fp8", [(7, 12, 128, (3, 2, 2, 1, 1, 1, 1, 1), 2768, 800, False), (4, 32, 64, (4, 2, 2, 1), 639, 300, False),
+                                                          (7, 16, 128, (3, 2, 2, 1, 1, 1, 1, 1), 550, 256, False), (4, 32, 128, (4, 2, 2, 2), 1113, 391, True)])
+def test_error_of_short_members_of_a_batch(binding, oracle, H, B, heads, d, br, bound, short, fp8):
+    """Members that the plan leaves whole are rounded once too: the bound above, over the short members alone (57 000 elements
+    and more)."""
+    lens = (bound,) + (short,) * (B - 1)
+    w = scaled(WORKLOADS["cfg2"], B=B, H=heads, d=d, branching=br, prefix_min=short, prefix_max=bound, cfg_id=151)
+    inp = attention_inputs(w, seed=5, lens=lens, kv_fp8=(1.0, 1.0) if fp8 else None)
+    view = binding.slice_mask(binding.build_mask(br), len(br))
+    n = view.n_nodes
+    want = (oracle.tree_attention_fp8kv if fp8 else oracle.tree_attention)(inp, oracle.build_mask(br), n)
+    none = dict(k_prefix=np.zeros(1, np.uint16), v_prefix=np.zeros(1, np.uint16)) if fp8 else {}
+    ad = H.AttnDevice(dict(inp, **none))
+    if fp8:
+        ad.kp, ad.vp = (torch.from_numpy(inp[k]).cuda() for k in ("k_prefix", "v_prefix"))
+
+    def error(**tuning):
+        tu = binding.AttentionTuning(**tuning)
+        ws = binding.new_workspace(binding.tree_attention_tuned_workspace(tu, int(fp8), B, heads, heads, d, n, 0, bound))
+        ad.out.fill_(float("nan"))
+        binding.tree_attention_tuned(tu, view, 1, int(fp8), 1.0, 1.0, B, heads, heads, d, 0, ad.q, ad.kt, ad.vt, ad.node_stride, ad.kp, ad.vp,
+                                     ad.base, ad.lens, ad.head_stride, bound, ad.scale, ad.out, ws)
+        got = ad.out[:, :, :n].float().cpu().numpy().astype(np.float64)
+        H.assert_close(got, want, "bf16", f"{br} d={d} {tuning}")
+        return float(np.sqrt(np.mean((got[1:] - want[1:]) ** 2)))
+
+    assert binding.tree_attention_plan(None, 1, int(fp8), B, heads, heads, d, n, 0, bound).key_splits > 1
+    assert error() <= 1.02 * error(key_splits=1)
