@@ -500,18 +500,22 @@ __device__ __align__(64) const float zeros[16] = {};
 // batches (no barriers, only its own waits), whole 256-byte pieces of rows (128-byte ones reach the same rate only where
 // rows are a multiple of that long, 64-byte ones use half of every line), swizzled so that the operand reads are free of bank
 // conflicts.  The ring runs on into the next layer, whose first batches are there when it starts.  Rows are staged through LDS as
-// they lie in memory (read as operands from memory, four rows in four neighbouring lanes, they cost 6000 cycles).
+// they lie in memory (read as operands from memory, four rows in four neighbouring lanes, they cost 6000 cycles), four banks
+// apart: what an instruction reads, four columns of four quarters of four rows, then lies in 64 banks (16 apart, in 16).  A batch's
+// operands are read while the one before is multiplied.  (One after the other, and rows 16 banks apart: 2048-256-64-1, 16 rows
+// 27.6 us, 26.0 so.)
 // Bound: the weights, once per workgroup from L2; 256 workgroups at once get 48 bytes per cycle each (768 x 256: 6.8 us; fewer
 // get 64).  Eight rows per workgroup halve that but not the time: the matrix instructions then take as long.
-// 768-256-64-1 with the stop rule: 1024 rows 20.0 -> 17.9 us, 64 rows 19.4 -> 15.8; 288-256-64-1, 1024 rows 17.7 -> 12.8;
-// 1000-256-64-1, whose rows are not whole lines, 22.8 -> 22.6.
+// Against 16 column blocks per output unit and a tree over them, with the stop rule: 768-256-64-1, 1024 rows 21.2 -> 18.7 us,
+// 64 rows 19.0 -> 15.4; 288-256-64-1, 1024 rows 16.8 -> 12.6; 1000-256-64-1, whose rows are not whole lines, 22.5 -> 21.6;
+// 2048-256-64-1, 1024 rows 31.2 -> 30.2, but 16 rows 25.5 -> 26.0 and 256 rows 26.9 -> 28.1.
 constexpr int BATCH = 64, UNITS = 16, RING = 3;          // columns and units per batch; batches per wavefront
 constexpr int R = 4;                                     // rows per workgroup
-constexpr int ACT_PITCH = MCSD_MLP_MAX_WIDTH + 16;       // floats; rows 16 banks apart
+constexpr int ACT_PITCH = MCSD_MLP_MAX_WIDTH + 4;        // floats; rows 4 banks apart
 constexpr int WIDE = 2048;                               // widest hidden state of the matrix path
 struct HiddenShared {
     float4 ring[NW][RING][UNITS * BATCH / 4];
-    float x[R][WIDE + 16];                               // the rows; later partial sums
+    float x[R][WIDE + 4];                                // the rows; later partial sums
     float act[R][ACT_PITCH];
     float bias[MCSD_MLP_MAX_LAYERS][MCSD_MLP_MAX_WIDTH];
     float last[MCSD_MLP_MAX_WIDTH];                      // weights of the last layer
@@ -664,30 +668,56 @@ __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M,
         for (int u = 0; u < GROUPS; ++u) {
             if (p.ug + u * NW >= p.units) break;             // (uniform)
             const float *xb = xr;
-#pragma unroll 1
-            for (int b = p.b0; b < p.b1; ++b, xb += BATCH) {
+            float4 w[2][4];
+            float x[2][4];
+            // operands of a batch: LDS -> registers `to`; its place in the ring is free when they are there
+            auto read = [&](int to) {
                 MCSD_WAIT_VMCNT((RING - 1) * 4);             // this batch has landed, the later ones are under way
                 asm volatile("" ::: "memory");
                 const float4 *at = ring + slot;
                 slot = slot == (RING - 1) * 256 ? 0 : slot + 256;
-                float4 w[4];
-                float x[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) w[c] = at[op ^ c];
+                for (int c = 0; c < 4; ++c) w[to][c] = at[op ^ c];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) x[c] = xb[4 * c];
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[0].x), "+v"(w[1].x), "+v"(w[2].x), "+v"(w[3].x) :: "memory");   // read before it is overwritten
+                for (int c = 0; c < 4; ++c) x[to][c] = xb[4 * c];
+                xb += BATCH;
+            };
+            auto there = [&](int to) {
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[to][0].x), "+v"(w[to][1].x), "+v"(w[to][2].x), "+v"(w[to][3].x) :: "memory");
                 request();
+            };
+            auto add = [&](int of) {
                 f32x4_t a[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[c], w[c].x, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 2, 0, 0);
+                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[of][c], w[of][c].x, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 2, 0, 0);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[c], w[c].y, a[c], 2, 1, 0);
+                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[of][c], w[of][c].y, a[c], 2, 1, 0);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[c], w[c].z, a[c], 2, 2, 0);
+                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[of][c], w[of][c].z, a[c], 2, 2, 0);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[c], w[c].w, a[c], 2, 3, 0);
+                for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[of][c], w[of][c].w, a[c], 2, 3, 0);
                 sum[u] += (a[0] + a[1]) + (a[2] + a[3]);
+            };
+            const int batches = p.b1 - p.b0;
+            if (batches > 0) {
+                read(0);
+                there(0);
+                int b = 1;
+#pragma unroll 1
+                for (; b + 1 < batches; b += 2) {
+                    read(1);
+                    add(0);
+                    there(1);
+                    read(0);
+                    add(1);
+                    there(0);
+                }
+                if (b < batches) {
+                    read(1);
+                    add(0);
+                    there(1);
+                    add(1);
+                } else add(0);
             }
             // the quarters' columns: lanes l, l + 16, l + 32, l + 48
 #pragma unroll

@@ -137,6 +137,30 @@ def test_masked_scores_cost_two_instructions(sweep_asm):
     assert checked == 12 + 8 + 3
 
 
+def test_hidden_networks_read_a_batch_while_the_one_before_is_multiplied(tmp_path):
+    """Matrix instructions stand between the reads of a batch's weights from LDS and the wait for them."""
+    if not (os.path.exists(HIPCC) or shutil.which(HIPCC)):
+        pytest.skip("hipcc not available")
+    out = tmp_path / "decision.s"
+    subprocess.run([HIPCC, *COMMON, *SOURCES["decision.hip"], "-S", "--cuda-device-only", "-o", str(out), os.path.join(CSRC, "decision.hip")],
+                   check=True, capture_output=True)
+    kinds = {"ds_read_b128": "r", "v_mfma_f32_4x4x1": "m", "lgkmcnt(0)": "w"}
+    checked = 0
+    for name, body in _functions(out.read_text().split("\n")):
+        if "decision_hidden_kernel" not in name:
+            continue
+        labels = {m.group(1): i for i, l in enumerate(body) if (m := re.match(r"^(\.LBB\d+_\d+):", l))}
+        spans = [[x.split(";")[0] for x in body[labels[m.group(1)]:i + 1]] for i, l in enumerate(body)
+                 if (m := re.search(r"s_c?branch\w*\s+(\.LBB\d+_\d+)", l)) and labels.get(m.group(1), i) < i]
+        loops = [x for x in spans if sum("v_mfma" in y for y in x) == 32]                # two batches per trip
+        assert loops, f"{name}: no loop of two batches"
+        for loop in loops:
+            events = "".join(v for x in loop for k, v in kinds.items() if k in x)
+            assert events.count("r") == 8 and "rw" not in events, f"{name}: {events}"
+            checked += 1
+    assert checked >= 2
+
+
 def test_the_checked_code_takes_its_leading_arguments_in_registers(sweep_asm):
     """The compile above is the shipped one: its kernels say how many argument registers are preloaded."""
     preloaded = [int(m.group(1)) for l in sweep_asm if (m := re.match(r"\s*\.amdhsa_user_sgpr_kernarg_preload_length\s+(\d+)", l))]
