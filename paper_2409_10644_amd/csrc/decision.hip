@@ -821,7 +821,7 @@ int check_mlp(const mcsd_mlp_t *mlp, int32_t n_in, MlpDesc *out)
 }
 
 constexpr int FEW_ROWS = 256;        // one workgroup per compute unit
-constexpr int SETTLE_HIDDEN = 256;   // (four rows share a workgroup: 64 rows 17.7 us, 16.7 so; 512 rows 17.6 and 17.8)
+constexpr int SETTLE_HIDDEN = 160;   // (four rows share a workgroup: 64 rows 16.2 us with a launch, 15.4 so; 128 rows 16.4 and 16.0; 256 rows 16.3 and 17.0)
 constexpr int SETTLE_ROWS = 64;      // beyond, the flags' and probabilities' cache lines are fought over: 180 rows 15.7 us, 12.8 with a launch
 
 int launch_stop(const float *prob, int32_t B, int32_t W, float beta, int32_t *stop, hipStream_t st)
