@@ -1,5 +1,7 @@
 """Networks on hidden states at the edges of their tiling: groups of 16 output units, batches of 64 columns, column splits of narrow
-layers, four rows per workgroup, stop flags settled in the launch (up to 256 rows) or by a second one."""
+layers, four rows per workgroup, stop flags settled in the launch (up to 160 rows) or by a second one.  The threshold lies
+between the trees' largest probabilities, so that some trees stop and some do not, and the flags are right whatever the
+probabilities were before: all below the threshold, or all above it."""
 import numpy as np
 import pytest
 import torch
@@ -7,6 +9,11 @@ import torch
 from workloads import mlp_weights
 
 pytestmark = pytest.mark.gpu
+
+WIDTHS = [(4, 1), (60, 15, 1), (64, 16, 20, 1), (68, 17, 64, 1), (252, 20, 33, 1), (256, 64, 512, 1), (260, 65, 1), (1000, 129, 16, 1),
+          (2048, 512, 65, 1), (2048, 128, 1), (320, 48, 7, 1), (576, 1, 1, 1)]
+# one tree, a few, as many rows as are settled in the launch, the next ones, 256; trees of four rows per workgroup and across them
+TREES = [(1, 1), (1, 5), (7, 6), (26, 6), (8, 20), (32, 5), (33, 5), (41, 4), (16, 16), (13, 20)]
 
 
 def _reference(ws, bs, x):
@@ -17,23 +24,38 @@ def _reference(ws, bs, x):
     return 1.0 / (1.0 + np.exp(-x[..., 0]))
 
 
-@pytest.mark.parametrize("B,W", [(1, 1), (1, 5), (16, 16), (13, 20)])
-@pytest.mark.parametrize("widths", [(4, 1), (60, 15, 1), (64, 16, 20, 1), (68, 17, 64, 1), (252, 20, 33, 1), (256, 64, 512, 1), (260, 65, 1),
-                                    (1000, 129, 16, 1), (2048, 512, 65, 1), (2048, 128, 1), (320, 48, 7, 1), (576, 1, 1, 1)])
-def test_layer_and_row_edges(widths, B, W):
-    from paper_2409_10644_amd import binding
+def _case(widths, B, W):
+    """Weights, inputs, probabilities, and a threshold in the middle of the widest gap between the trees' largest probabilities;
+    one above and one below them all where there is one tree, or a clipped unit makes them equal."""
     rng = np.random.default_rng(sum(widths) + B)
     ws, bs = mlp_weights(widths, seed=len(widths) + widths[0])
     x = rng.standard_normal((B, W, widths[0])).astype(np.float32)
+    want = _reference(ws, bs, x.astype(np.float64))
+    top = np.sort(want.max(axis=1))
+    if top[-1] - top[0] < 1e-4:
+        betas = [float(top[-1]) + 0.01, float(top[0]) - 0.01]
+    else:
+        k = int(np.argmax(np.diff(top)))
+        betas = [float(top[k] + top[k + 1]) / 2]
+    flags = [(want < beta).all(axis=1) for beta in betas]
+    assert np.any(flags) and not np.all(flags)              # of both kinds, and not where fp32 and binary64 might differ
+    assert min(np.abs(want.max(axis=1) - beta).min() for beta in betas) > 2e-5
+    return ws, bs, x, want, list(zip(betas, flags))
+
+
+@pytest.mark.parametrize("B,W", TREES)
+@pytest.mark.parametrize("widths", WIDTHS)
+def test_layer_and_row_edges(widths, B, W):
+    from paper_2409_10644_amd import binding
+    ws, bs, x, want, thresholds = _case(widths, B, W)
     mlp = binding.make_mlp([torch.from_numpy(w).cuda() for w in ws], [torch.from_numpy(b).cuda() for b in bs])
     d = torch.from_numpy(x).cuda()
-    want = _reference(ws, bs, x.astype(np.float64))
-    beta = float(np.float32(np.median(want)))
-    for _ in range(2):
-        prob = torch.full((B, W), -7.0, device="cuda")
-        stop = torch.full((B,), -7, dtype=torch.int32, device="cuda")
-        binding.early_stop_hidden(mlp, B, W, d, W * widths[0], widths[0], beta, prob, stop)
-        got = prob.cpu().numpy()
-        # a logit of magnitude up to ~10 from at most 2048 + 512 fp32 products in sums of depth < 100: below 1e-5 of a probability
-        assert np.abs(got - want).max() <= 1e-5
-        assert np.array_equal(stop.cpu().numpy(), (got < np.float32(beta)).all(axis=1).astype(np.int32))
+    for beta, flags in thresholds:
+        for before in (-7.0, 2.0):
+            prob = torch.full((B, W), before, device="cuda")
+            stop = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+            binding.early_stop_hidden(mlp, B, W, d, W * widths[0], widths[0], beta, prob, stop)
+            got = prob.cpu().numpy()
+            # a logit of magnitude up to ~10 from at most 2048 + 512 fp32 products in sums of depth < 100: below 1e-5 of a probability
+            assert np.abs(got - want).max() <= 1e-5
+            assert np.array_equal(stop.cpu().numpy(), flags.astype(np.int32)), (beta, before)
