@@ -65,15 +65,18 @@ def test_steady_state_loops_wait_for_memory_once_per_tile(sweep_asm):
         assert loops, f"no streaming loop found in {name}"
         D, QBP, NS, F8 = (int(x) for x in re.search(r"ILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)E", name).groups())
         if NS == 2:
-            # the loop that requests full tiles (nothing else loads non-temporally) with both of its barriers; of the backward
-            # branches that span it the innermost (block placement may put a backward jump inside it: half a loop)
-            both = [x for x in loops if sum("s_barrier" in y.split(";")[0] for y in x) == 2 and any(re.search(r"global_load_lds.*\bnt\b", y) for y in x)]
-            assert both, f"{name}: no two-tile loop found"
-            loop = min(both, key=len)
-            code = [x.split(";")[0] for x in loop]
-            waits = sum("vmcnt" in x for x in code)
-            barriers = sum("s_barrier" in x for x in code)
-            assert barriers == 2 and waits == 2, f"{name}: {waits} vmcnt waits, {barriers} barriers in the two-tile loop"
+            # the loop of two full tiles: all it requests are full tiles (a tile that is not takes an address per lane, "off"), two
+            # of them non-temporally, and block placement may put backward jumps inside it: the innermost that spans all of it
+            alone = D == 128 and QBP == 1 and "short" not in name          # (has the compute unit to itself: waits for halves)
+            keys = {1: 128, 2: 64, 4: 64}[QBP]
+            loads_per_half = keys * D * 2 // 1024 // 4
+            code = [[y.split(";")[0] for y in x] for x in loops]
+            full = [x for x in code if sum(bool(re.search(r"global_load_lds.*\bnt\b", y)) for y in x) == 4 * loads_per_half
+                    and not any(re.search(r"global_load_lds\S* v\[\d+:\d+\], off", y) for y in x) and sum("s_barrier" in y for y in x) == (4 if alone else 2)]
+            assert full, f"{name}: no loop of two full tiles found"
+            code = min(full, key=len)
+            waits = [int(x) for y in code for x in re.findall(r"vmcnt\((\d+)\)", y)]
+            assert waits == ([2 * loads_per_half] * 4 if alone else [0, 0]), f"{name}: {waits}"
         else:
             # four-stage ring, four tiles per trip; a step waits for all loads but those of the two, one or zero tiles
             # requested after its own (three alternative instructions), right before its barrier, and nowhere else
