@@ -141,9 +141,9 @@ void device_shape(int &n_cus, int &n_xcc)
 // tree's keys): within 2.2 % of the best of the measured ones on average, one in a hundred 26 % off.  Two workgroups per compute unit
 // and at least 256 keys per split lost 11 %; prefixes of fewer than PART_F32_KEYS keys, whose partial results are fp32, would
 // lose 11 % unsplit, up to 49 %.  Prices fitted to a sweep that requests two tiles at once (0.88 and 0.62 us, dearer folds)
-// were 2.1 % off, on other calls: 2 x 64 heads over 32, 728 keys, 44 rows 12.9 us with these and 16.1 with those; 11 x 8 heads,
-// 6433 keys, 28 rows 53.9 and 45.7.  They cut finer, so that a member of a ragged batch that fits one split here exchanged
-// partial results in bf16, a second rounding (1.17 times the error): not worth it.
+// were 2.1 % off, on other calls: 2 x 64 heads over 32, 728 keys, 44 rows 12.9 us with these and 16.1 with those; 5 x 4 heads, 552
+// keys, 14 rows 8.0 and 6.5.  They cut finer, so that a member of a ragged batch that fits one split here exchanged partial
+// results in bf16, a second rounding (1.2 times the error): not worth it.
 struct SplitChoice { int S, tree; };
 SplitChoice choose_splits(int cus, int d, int QBP, bool f8, int B, long bh, int tiles, int tree_tiles, int tree_forced)
 {
@@ -173,6 +173,11 @@ SplitChoice choose_splits(int cus, int d, int QBP, bool f8, int B, long bh, int 
                 if (S == 1 && tree != 2) continue;
                 if (tree == 1 && bh * (S + 1) > (long)cus * per_cu) continue;
                 const int parts = S + (tree == 1);
+                // One block of 128 columns fills a compute unit's LDS, and what is beyond the residents waits for one of them to end: where two
+                // splits are resident no more are made (11 x 8 heads, 6433 keys, 10 rows 53.9 -> 45.7 us; unsplit, 5 x 32 heads of 835-6687
+                // keys 73.0 -> 76.1).  Up to nine tiles what is left would give the tree's keys a workgroup, and short members a second
+                // partial result with it.
+                if (per_cu == 1 && 2 * bh <= cus && tiles > 9 && bh * parts > cus) continue;
                 if (S > 1 && part_f32 && (parts > PART_F32_MAX || (long)bh * parts * QBP * 32 * d * 4 > PART_F32_BYTES)) continue;
                 const int most = S == 1 ? tiles + tree_tiles
                                  : tree == 1 ? (tps > tree_tiles ? tps : tree_tiles)
