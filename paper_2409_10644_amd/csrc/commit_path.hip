@@ -26,8 +26,10 @@ __device__ inline int clamp_acc(int a, int gamma) { return a < 0 ? 0 : (a > gamm
 
 // grid (gamma, B, n_layers): cache row L_b + j of layer z <- tree row of node path[b][j], all heads, K and V.
 // A row is a few KB, and the time is the way there: everything a workgroup needs to know is requested at once, and of its rows
-// UNROLL chunks per thread, K and V, before the first is stored (one after the other, and each of the words before only when the
-// one before it was there: 3.1 us for 32 layers of 32 heads of 128; now 2.2).
+// UNROLL chunks per thread, K and V, before the first is stored.  (One after the other, each of the words before only when the
+// one before it was there, and one thread per sequence below: a call of both kernels, 32 layers of 32 heads of 128, replayed in a
+// graph, 5.0 us for four of four nodes and 5.9 for eight of eight; now 4.0 and 4.3.  Alone behind other work, where the way is
+// to memory, the trace shows 4-5 us for this kernel either way.)
 __global__ __launch_bounds__(256) void commit_copy_kernel(const CommitParams P)
 {
     constexpr int UNROLL = 2;
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(256) void commit_copy_kernel(const CommitParams P)
 
 // grid (places of a sequence / 64, B): one thread per place in out_ids, the token id that joins the input there or -1; a
 // sequence's first thread also writes its number of ids and its new length.  (One thread per sequence walked its path in a
-// chain of two loads per node: 2.7 us for 4 levels, now 1.5.)
+// chain of two loads per node.)
 __global__ __launch_bounds__(64) void commit_finish_kernel(const CommitParams P)
 {
     asm("" : : "s"(P.path));

@@ -786,7 +786,7 @@ __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M,
         const int first = m0 / W, last = min(m0 + R, M) - 1;
         for (int tree = first + wave; tree * W <= last; tree += NW) settle_stop(prob, tree, W, beta, stop, lane);
     }
-    MCSD_WAIT_VMCNT(0);                                      // (nothing lands in LDS that is no longer this workgroup's)
+    MCSD_WAIT_VMCNT(0);                                      // (the ring's last requests; the end of the program would wait for them as well)
 }
 
 // ---------------------------------------------------------------------------------------------- stop rule

@@ -723,7 +723,10 @@ __device__ __attribute__((always_inline)) inline void fold_partials(const __amdg
 
 // Whether there is a kernel for grids of long and short workgroups in pairs.  Not for four query blocks, where a second loop
 // does not fit the registers (40 of them spilled), nor for split keys (16 x 16 heads, 851-3407 keys: 53.4 us without, 56.1 with
-// it), nor where a workgroup has the compute unit to itself anyway.
+// it), nor where a workgroup has the compute unit to itself anyway.  What it serves by the plan's own choice: unsplit grids of more
+// units than compute units and at most twice as many, that is twice as many (16 sequences of 32 heads) for prefixes of eight tiles
+// and more, which are halved between, and any number for shorter ones.  16 sequences of 512-4096 keys, 32 heads, 60 nodes, 20
+// draws of the lengths: 7-16 % faster with it for 17, 1-2 % slower for the 3 whose longest pair has two long members.
 template <int D, int QBP, int NS, bool F8>
 constexpr bool has_ragged_kernel() { return NS == 2 && !F8 && QBP != 4 && !(D == 128 && QBP == 1); }
 
@@ -904,7 +907,7 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
     const int t0 = (sep && tree_wg) ? tiles_b : min(s * tps, tiles_b), t1 = min(t0 + tps, tiles_b);
     const int n_tree_tiles = tree_wg ? (p.n + C::T - 1) / C::T : 0;
     const int n_pre = t1 - t0;
-    if (n_pre + n_tree_tiles == 0) return;                  // this split has no keys
+    if (n_pre + n_tree_tiles == 0) return;                  // this split has no keys (the program's end waits for Q and the masks)
     const int n_active = sep ? np + 1 : max(1, np);         // partial results of this sequence: slots 0 .. n_active-1
     const int slot_id = (sep && tree_wg) ? np : s;
     // leading tiles of this split that are full (only the sequence's last tile can be ragged)
@@ -1062,9 +1065,8 @@ __device__ __forceinline__ void sweep(const int32_t *lens, const int64_t *seq_ba
         // other one's loads are under way meanwhile, and where memory is the limit more requests cost 1-2 % (8 x 32 heads of 16384
         // keys: 345 us so, 355 with the loop for one that is alone; 16 x 32 of 2300: 97.7, 98.9).  The one that is alone asks for
         // a half as soon as its place is free, two barriers and waits per tile, and never waits for the last two: 16 sequences of
-        // 1000-4000 keys, 16 heads, one query block 68.9 -> 59.9 us; of 512-4096 keys, 32 heads, 60 nodes 113.7 -> 106; 12 heads
-        // of 64 columns 37.9 -> 32.5.  (A ring of five halves with one barrier per tile: 60.5, 106.7, 35.0, and 355 above, for the
-        // reads' addresses are then made for every tile.)
+        // 1000-4000 keys, 16 heads, one query block 68.9 -> 59.9 us; of 512-4096 keys, 32 heads, 60 nodes 113.7 -> 106.  (A ring of
+        // five halves with one barrier per tile: 60.5, 106.7, and 355 above, for the reads' addresses are then made for every tile.)
         int it = 1;
         auto full = [&](unsigned char *stage, unsigned char *other) __attribute__((always_inline)) {
             MCSD_WAIT_VMCNT(2 * C::NI);
