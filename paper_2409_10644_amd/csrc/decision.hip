@@ -493,9 +493,11 @@ __device__ __align__(64) const float zeros[16] = {};
 // its 16 blocks are four of four output units at one column, and the same units at columns 16, 32 and 48 further; A holds
 // those columns of the four rows, broadcast from the blocks that have them (cbsz, abid).  So a wavefront has 16 units at a time,
 // and what is left is the sum of four quarters of the columns.  Fewer than eight groups of 16 units: the wavefronts split the
-// columns too and add up through LDS.  A sum is four columns in one accumulator, a tree of four of them per batch, the
-// batches one after the other, a tree of the quarters (error against binary64, seven networks of 288 to 2048 columns: 0.95 of that
-// of the 16 column blocks and a tree over them that this replaced, 0.87 to 1.05).
+// columns too and add up through LDS.  A sum is four columns in one accumulator, a tree of four of them per batch, the even
+// batches one after the other and the odd ones, a tree of the quarters.  Error against binary64 over that of the 16 column blocks
+// and a tree over them that this replaced, 36 networks of 288 to 2048 columns, 64 to 256 and 32 or 64 units, 6144 rows each: 0.91
+// (0.80-0.99) for inputs of both signs, 0.98 (0.89-1.03) for inputs behind a ReLU; with all batches one after the other 0.94
+// (0.81-1.00) and 1.00 (0.94-1.04), and 1 % of the time less.
 // Weights go through LDS: batches of 16 units x 64 columns come by direct-to-LDS loads into the wavefront's own ring of RING
 // batches (no barriers, only its own waits), whole 256-byte pieces of rows (128-byte ones reach the same rate only where
 // rows are a multiple of that long, 64-byte ones use half of every line), swizzled so that the operand reads are free of bank
@@ -503,12 +505,12 @@ __device__ __align__(64) const float zeros[16] = {};
 // they lie in memory (read as operands from memory, four rows in four neighbouring lanes, they cost 6000 cycles), four banks
 // apart: what an instruction reads, four columns of four quarters of four rows, then lies in 64 banks (16 apart, in 16).  A batch's
 // operands are read while the one before is multiplied.  (One after the other, and rows 16 banks apart: 2048-256-64-1, 16 rows
-// 27.6 us, 26.0 so.)
+// 27.5 us, 26.4 so.)
 // Bound: the weights, once per workgroup from L2; 256 workgroups at once get 48 bytes per cycle each (768 x 256: 6.8 us; fewer
 // get 64).  Eight rows per workgroup halve that but not the time: the matrix instructions then take as long.
-// Against 16 column blocks per output unit and a tree over them, with the stop rule: 768-256-64-1, 1024 rows 21.2 -> 18.7 us,
-// 64 rows 19.0 -> 15.4; 288-256-64-1, 1024 rows 16.8 -> 12.6; 1000-256-64-1, whose rows are not whole lines, 22.5 -> 21.6;
-// 2048-256-64-1, 1024 rows 31.2 -> 30.2, but 16 rows 25.5 -> 26.0 and 256 rows 26.9 -> 28.1.
+// Against 16 column blocks per output unit and a tree over them, with the stop rule: 768-256-64-1, 1024 rows 20.0 -> 17.7 us,
+// 64 rows 19.0 -> 15.5; 288-256-64-1, 1024 rows 16.9 -> 12.6; 1000-256-64-1, whose rows are not whole lines, 22.2 -> 21.5;
+// 2048-256-64-1, 1024 rows 31.3 -> 30.2, but 16 rows 25.6 -> 26.4 and 256 rows 26.9 -> 28.5.
 constexpr int BATCH = 64, UNITS = 16, RING = 3;          // columns and units per batch; batches per wavefront
 constexpr int R = 4;                                     // rows per workgroup
 constexpr int ACT_PITCH = MCSD_MLP_MAX_WIDTH + 4;        // floats; rows 4 banks apart
@@ -670,6 +672,7 @@ __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M,
             const float *xb = xr;
             float4 w[2][4];
             float x[2][4];
+            f32x4_t odd = {0.f, 0.f, 0.f, 0.f};              // every other batch's sums (behind the generic layer there are few batches)
             // operands of a batch: LDS -> registers `to`; its place in the ring is free when they are there
             auto read = [&](int to) {
                 MCSD_WAIT_VMCNT((RING - 1) * 4);             // this batch has landed, the later ones are under way
@@ -696,7 +699,7 @@ __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M,
                 for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[of][c], w[of][c].z, a[c], 2, 2, 0);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) a[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[of][c], w[of][c].w, a[c], 2, 3, 0);
-                sum[u] += (a[0] + a[1]) + (a[2] + a[3]);
+                (of && !GEN ? odd : sum[u]) += (a[0] + a[1]) + (a[2] + a[3]);
             };
             const int batches = p.b1 - p.b0;
             if (batches > 0) {
@@ -718,6 +721,7 @@ __global__ __launch_bounds__(DT) void decision_hidden_kernel(MlpDesc mlp, int M,
                     there(1);
                     add(1);
                 } else add(0);
+                if (!GEN) sum[u] += odd;
             }
             // the quarters' columns: lanes l, l + 16, l + 32, l + 48
 #pragma unroll
